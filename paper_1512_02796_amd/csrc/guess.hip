@@ -193,16 +193,40 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(Lat L, const uint16_t* __res
     if (lane < 16) P[NCH * 256 + lane] = db;
 }
 
-// grad (canonical [co][ci][27] + [co]) of one layer = sum over wavefronts of the partials
+// The gradient of one layer = the sum over wavefronts of their partials, in two
+// passes of fixed order. One thread per parameter walking all 8192 partials
+// (227 MB, one 28-block launch) had one load in flight per thread: 2539 us a
+// layer at 97^3. Split kSegs ways the read has 3488 blocks: 34 us + 5 us.
+constexpr int kSegs = 32;
+
+// part2[s][p] = sum of partial[w][p] over segment s of the wavefronts
+__global__ __launch_bounds__(kThreads) void k_wgrad_sum(const float* __restrict__ partial, int64_t nw, int stride,
+                                                        float* __restrict__ part2) {
+    __shared__ float sm[kThreads / 64][64];
+    const int lane = threadIdx.x % 64, row = threadIdx.x / 64;
+    const int p = blockIdx.x * 64 + lane;
+    const int64_t per = (nw + kSegs - 1) / kSegs;
+    const int64_t w1 = min(nw, (blockIdx.y + 1) * per);
+    float s = 0.f;
+    if (p < stride) {
+#pragma unroll 8
+        for (int64_t w = blockIdx.y * per + row; w < w1; w += kThreads / 64) s += partial[w * stride + p];
+    }
+    sm[row][lane] = s;
+    __syncthreads();
+    if (row == 0 && p < stride) part2[(int64_t)blockIdx.y * stride + p] = (sm[0][lane] + sm[1][lane]) + (sm[2][lane] + sm[3][lane]);
+}
+
+// grad (canonical [co][ci][27] + [co]) = sum over the segments
 template <int CIN>
-__global__ void k_wgrad_reduce(const float* __restrict__ partial, int64_t nw, int cin, int cout,
-                               float* __restrict__ grad) {
+__global__ void k_wgrad_reduce(const float* __restrict__ part2, int cin, int cout, float* __restrict__ grad) {
     constexpr int NCH = CIN == 16 ? 27 : 7;
     constexpr int STRIDE = NCH * 256 + 16;
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= STRIDE) return;
     float s = 0.f;
-    for (int64_t w = 0; w < nw; ++w) s += partial[w * STRIDE + p];
+#pragma unroll
+    for (int w = 0; w < kSegs; ++w) s += part2[w * STRIDE + p];
     if (p >= NCH * 256) {
         const int co = p - NCH * 256;
         if (co < cout) grad[cout * cin * 27 + co] = s;
@@ -312,10 +336,12 @@ __global__ __launch_bounds__(kThreads) void k_loss(int64_t V, const float* __res
 }
 
 __global__ void k_loss_final(const double* __restrict__ part, int nb, int64_t V, double* __restrict__ out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    // one wavefront: 65 us for 892 blocks at 97^3 while one thread added them, 5 us now
     double s = 0.0;
-    for (int b = 0; b < nb; ++b) s += part[b];
-    *out = s / static_cast<double>(V);
+    for (int b = threadIdx.x; b < nb; b += 64) s += part[b];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+    if (threadIdx.x == 0) *out = s / static_cast<double>(V);
 }
 
 // Adam on the FP32 master parameters (Kingma and Ba's update with bias correction)
@@ -358,6 +384,7 @@ struct GuessNet {
     float* pred = nullptr;       // [V]
     float* target = nullptr;     // [V]
     float* partial = nullptr;    // [waves][27*256+16]
+    float* part2 = nullptr;      // [kSegs][27*256+16]
     double* lossp = nullptr;     // [blocks]
     double* lossv = nullptr;     // [1]
     int step = 0;
@@ -409,12 +436,16 @@ static qpat_status guess_backward(qpat_ctx* c) {
         float* grad = G->grads + param_offset(l);
         if (l == 0) {
             hipLaunchKernelGGL(k_wgrad<4>, g, b, 0, c->stream, G->L, cur, Xin, G->partial);
-            hipLaunchKernelGGL(k_wgrad_reduce<4>, dim3((7 * 256 + 16 + 255) / 256), dim3(256), 0, c->stream,
-                               G->partial, nw, kCin[l], kCout[l], grad);
+            hipLaunchKernelGGL(k_wgrad_sum, dim3((7 * 256 + 16 + 63) / 64, kSegs), b, 0, c->stream, G->partial, nw,
+                               7 * 256 + 16, G->part2);
+            hipLaunchKernelGGL(k_wgrad_reduce<4>, dim3((7 * 256 + 16 + 255) / 256), dim3(256), 0, c->stream, G->part2,
+                               kCin[l], kCout[l], grad);
         } else {
             hipLaunchKernelGGL(k_wgrad<16>, g, b, 0, c->stream, G->L, cur, Xin, G->partial);
-            hipLaunchKernelGGL(k_wgrad_reduce<16>, dim3((27 * 256 + 16 + 255) / 256), dim3(256), 0, c->stream,
-                               G->partial, nw, kCin[l], kCout[l], grad);
+            hipLaunchKernelGGL(k_wgrad_sum, dim3((27 * 256 + 16 + 63) / 64, kSegs), b, 0, c->stream, G->partial, nw,
+                               27 * 256 + 16, G->part2);
+            hipLaunchKernelGGL(k_wgrad_reduce<16>, dim3((27 * 256 + 16 + 255) / 256), dim3(256), 0, c->stream, G->part2,
+                               kCin[l], kCout[l], grad);
             // dZ of layer l-1 = (adjoint convolution of dZ_l) masked by ReLU(Y[l-1]) > 0
             hipLaunchKernelGGL((k_conv<16, 2>), g, b, 0, c->stream, G->L, cur, G->Wb[l], nullptr, G->Y[l - 1],
                                (void*)nxt);
@@ -451,6 +482,7 @@ qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz) {
     QPAT_TRY(dalloc(c, &G->pred, V));
     QPAT_TRY(dalloc(c, &G->target, V));
     QPAT_TRY(dalloc(c, &G->partial, (size_t)kConvBlocks * 4 * (27 * 256 + 16)));
+    QPAT_TRY(dalloc(c, &G->part2, (size_t)kSegs * (27 * 256 + 16)));
     QPAT_TRY(dalloc(c, &G->lossp, 1024));
     QPAT_TRY(dalloc(c, &G->lossv, 1));
     hipLaunchKernelGGL(k_zero_f, dim3((kParams + 255) / 256), dim3(256), 0, c->stream, kParams, G->params);
