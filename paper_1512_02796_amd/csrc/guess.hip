@@ -8,9 +8,8 @@
 // source. Output: the log correction, phi0 = phi_hom,k exp(net). The solve that
 // starts from phi0 stops on the same ||b - K x|| <= rtol ||b|| as a zero start.
 //
-// Convolutions are implicit GEMMs on the 16x16x16 BF16 MFMA: a wavefront owns
-// 16 consecutive lattice points x 16 output channels; the K dimension is one
-// tap x 16 input channels (or four taps x 4 channels for the 3-channel input
+// Convolutions are implicit GEMMs on the 16x16x16 BF16 MFMA over 16 output
+// channels x 16 lattice points; the K dimension is one tap x 16 input channels (or four taps x 4 channels for the 3-channel input
 // layer, padded to 4). Weight gradients are the same product with the voxel
 // index as the K dimension, split over wavefronts and reduced in fixed order.
 #include <cmath>
@@ -43,92 +42,154 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 
 __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(static_cast<uint32_t>(b) << 16); }
 
+// The node lattice and its padded image. Activations live on a padded lattice
+// (stride sx >= nx + 1 along x, sy = ny + 1 rows a plane, guard cells before
+// and after) whose cells outside the lattice hold zeros that nothing
+// overwrites, so a tap is a constant offset from a cell with no test of the
+// lattice's edge: the cell past the end of a row is the zero neighbour of both
+// that row's last node and the next row's first. sx is a multiple of 4, so a
+// group of 4 consecutive cells never straddles two rows.
 struct Lat {
     int nx, ny, nz;
     int64_t V;
+    int sx, sy;
+    int64_t g0;   // cell of node (0, 0, 0)
+    int64_t P;    // cells, guards included
+
+    static Lat of(int nx, int ny, int nz) {
+        Lat L{nx, ny, nz, (int64_t)nx * ny * nz, (nx + 4) / 4 * 4, ny + 1, 0, 0};
+        // the lowest tap is one plane, one row and one cell back; a tile of row
+        // pairs that runs past the last row reads up to two planes, three rows
+        // and 28 cells past the last node
+        const int64_t plane = (int64_t)L.sx * L.sy;
+        L.g0 = (plane + L.sx + 1 + 15) / 16 * 16;
+        L.P = L.g0 + plane * nz + 2 * plane + 4 * L.sx + 128;
+        return L;
+    }
+    __device__ __forceinline__ int64_t cell(int x, int y, int z) const {
+        return g0 + x + (int64_t)sx * (y + (int64_t)sy * z);
+    }
+    __device__ __forceinline__ int64_t cell(int64_t v) const {
+        const int64_t q = v / nx;
+        return cell(static_cast<int>(v % nx), static_cast<int>(q % ny), static_cast<int>(q / ny));
+    }
+    // offset of tap t ((dz, dy, dx) in {-1,0,1}^3, dx fastest)
+    __device__ __forceinline__ int64_t tap(int t) const {
+        return (t % 3 - 1) + (int64_t)sx * ((t / 3) % 3 - 1 + (int64_t)sy * (t / 9 - 1));
+    }
 };
 
-// neighbour of v through tap t ((dz, dy, dx) in {-1,0,1}^3, dx fastest); -1 outside
-__device__ __forceinline__ int64_t neighbour(const Lat& L, int x, int y, int z, int t) {
-    const int dx = t % 3 - 1, dy = (t / 3) % 3 - 1, dz = t / 9 - 1;
-    const int xx = x + dx, yy = y + dy, zz = z + dz;
-    if (xx < 0 || xx >= L.nx || yy < 0 || yy >= L.ny || zz < 0 || zz >= L.nz) return -1;
-    return xx + (int64_t)L.nx * (yy + (int64_t)L.ny * zz);
-}
-
 // ---------------------------------------------------------------- forward / backward-data
-// MODE 0: out bf16 [V][16] = relu(z + bias)
+// MODE 0: out bf16 [P][16] = relu(z + bias)
 // MODE 1: out f32 [V]      = z[:, 0] + bias[0]
-// MODE 2: out bf16 [V][16] = z * (mask[V][16] > 0)          (backward data; no bias)
+// MODE 2: out bf16 [P][16] = z * (mask[P][16] > 0)          (backward data; no bias)
+//
+// A wavefront owns 16 cells x 2 rows x 2 planes: the weights are the MFMA's A
+// operand (rows = output channels) and stay in registers, the cells its B
+// operand (columns), so a lane ends with 4 channels of one cell, one 8-byte
+// store. An input row serves up to four outputs: 48 loads for 108 MFMAs, where
+// a tile of 16 cells alone takes 27 for 27. Taps reach each output in ascending
+// order (planes, rows, cells), one 16x16x16 MFMA each. At 97^3 a 16-channel
+// layer takes 36 us and the input layer 22 us; with the edge tests, the weights
+// in LDS and 2-byte stores they took 85 and 37 us. Load latency bounds it.
 template <int CIN, int MODE>
-__global__ __launch_bounds__(kThreads) void k_conv(Lat L, const uint16_t* __restrict__ X,
-                                                   const uint16_t* __restrict__ Wp, const float* __restrict__ bias,
-                                                   const uint16_t* __restrict__ mask, void* __restrict__ out) {
+__global__ __launch_bounds__(kThreads, 4) void k_conv(Lat L, const uint16_t* __restrict__ X,
+                                                      const uint16_t* __restrict__ Wp, const float* __restrict__ bias,
+                                                      const uint16_t* __restrict__ mask, void* __restrict__ out) {
     constexpr int NCH = CIN == 16 ? 27 : 7;
-    __shared__ s4 wsh[NCH][64];
-    for (int i = threadIdx.x; i < NCH * 64; i += kThreads) {
-        const int m = i / 64, l = i % 64;
-        wsh[m][l] = *reinterpret_cast<const s4*>(Wp + ((int64_t)m * 16 + l % 16) * 16 + 4 * (l / 16));
-    }
-    __syncthreads();
-    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    const int g = lane / 16;
-    const int64_t ntiles = (L.V + 15) / 16;
-    for (int64_t tile = (int64_t)blockIdx.x * 4 + wave; tile < ntiles; tile += (int64_t)gridDim.x * 4) {
-        const int64_t v = tile * 16 + lane % 16;
-        const bool vok = v < L.V;
-        const int x = static_cast<int>(v % L.nx);
-        const int y = static_cast<int>((v / L.nx) % L.ny);
-        const int z = static_cast<int>(v / ((int64_t)L.nx * L.ny));
-        // every tap's A fragment first, then the chain of MFMAs: the loads
-        // are in flight together instead of each waiting for the MFMA before
-        // it. Buffer loads with 32-bit offsets (V CIN 2 < 2^31 bytes, checked
-        // on the host); a tap outside the lattice reads 0 (offset kOut).
-        const auto bx = rsrc(X, static_cast<uint32_t>(L.V * CIN * 2));
-        auto tap = [&](int m) {
-            const int t = CIN == 16 ? m : 4 * m + g;
-            const int ci0 = CIN == 16 ? 4 * g : 0;
-            const int64_t nb = vok && t < 27 ? neighbour(L, x, y, z, t) : -1;
-            const uint32_t off = nb >= 0 ? static_cast<uint32_t>(nb * CIN + ci0) * 2u : kOut;
-            return bload<s4>(bx, off);
-        };
-        f4 acc = {0.f, 0.f, 0.f, 0.f};
-        // taps in groups of one z-plane (9), the loads of the next group issued
-        // before the MFMAs of this one (a two-group pipeline keeps the
-        // registers, and so the waves per SIMD, in bounds)
-        constexpr int G9 = NCH >= 9 ? 9 : NCH;
-        s4 cur[G9], nxt[G9];
+    const int lane = threadIdx.x % 64, g = lane / 16, n = lane % 16;
+    s4 w[NCH];
 #pragma unroll
-        for (int m = 0; m < G9; ++m) cur[m] = tap(m);
+    for (int m = 0; m < NCH; ++m) w[m] = *reinterpret_cast<const s4*>(Wp + (m * 16 + n) * 16 + 4 * g);
+    f4 bs = {0.f, 0.f, 0.f, 0.f};
+    if (MODE == 0)
 #pragma unroll
-        for (int g0 = 0; g0 < NCH; g0 += G9) {
-            __builtin_amdgcn_sched_barrier(0);
-            if (g0 + G9 < NCH) {
+        for (int j = 0; j < 4; ++j) bs[j] = bias[4 * g + j];
+    if (MODE == 1) bs[0] = bias[0];
+    const int64_t plane = (int64_t)L.sx * L.sy;
+    int64_t toff[7];   // the 3-channel layer: group g takes tap 4m + g of product m
+    if (CIN == 4)
 #pragma unroll
-                for (int m = 0; m < G9; ++m) nxt[m] = g0 + G9 + m < NCH ? tap(g0 + G9 + m) : s4{0, 0, 0, 0};
+        for (int m = 0; m < 7; ++m) toff[m] = 4 * m + g < 27 ? L.tap(4 * m + g) * 4 : 0;
+    const int ypairs = (L.ny + 1) / 2, chunks = (ypairs * L.sx + 15) / 16;
+    const int64_t items = (int64_t)chunks * ((L.nz + 1) / 2);
+    for (int64_t it = (int64_t)blockIdx.x * (kThreads / 64) + threadIdx.x / 64; it < items;
+         it += (int64_t)gridDim.x * (kThreads / 64)) {
+        const int z = 2 * static_cast<int>(it / chunks);
+        const int e = static_cast<int>(it % chunks) * 16 + n;
+        const int y = 2 * (e / L.sx), x = e % L.sx;
+        const int64_t p = L.cell(x, y, z);
+        f4 acc[2][2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q / 2][q % 2] = f4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (CIN == 16) {
+            const uint16_t* lp = X + p * 16 + 4 * g;
+#pragma unroll
+            for (int zz = 0; zz < 4; ++zz) {
+                s4 v[4][3];
+#pragma unroll
+                for (int yy = 0; yy < 4; ++yy) {
+                    const uint16_t* row = lp + ((zz - 1) * plane + (int64_t)(yy - 1) * L.sx) * 16;
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) v[yy][d] = *reinterpret_cast<const s4*>(row + (d - 1) * 16);
+                }
+#pragma unroll
+                for (int yy = 0; yy < 4; ++yy)
+#pragma unroll
+                    for (int d = 0; d < 3; ++d)
+#pragma unroll
+                        for (int oz = 0; oz < 2; ++oz)
+#pragma unroll
+                            for (int oy = 0; oy < 2; ++oy) {
+                                const int tz = zz - oz, ty = yy - oy;   // dz + 1, dy + 1
+                                if (tz < 0 || tz > 2 || ty < 0 || ty > 2) continue;
+                                acc[oz][oy] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[tz * 9 + ty * 3 + d], v[yy][d],
+                                                                                        acc[oz][oy], 0, 0, 0);
+                            }
             }
+        } else {
+            s4 v[2][2][NCH];
 #pragma unroll
-            for (int m = 0; m < G9; ++m)
-                if (g0 + m < NCH) acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(cur[m], wsh[g0 + m][lane], acc, 0, 0, 0);
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int m = 0; m < G9; ++m) cur[m] = nxt[m];
+                for (int m = 0; m < NCH; ++m)
+                    v[q / 2][q % 2][m] =
+                        *reinterpret_cast<const s4*>(X + (p + (q / 2) * plane + (q % 2) * L.sx) * 4 + toff[m]);
+#pragma unroll
+            for (int m = 0; m < NCH; ++m)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc[q / 2][q % 2] =
+                        __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[m], v[q / 2][q % 2][m], acc[q / 2][q % 2], 0, 0, 0);
         }
-        const int co = lane % 16;
+        if (x >= L.nx) continue;   // a cell outside the lattice stays zero
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t vo = tile * 16 + 4 * g + j;
-            if (vo >= L.V) continue;
-            float val = acc[j];
-            if (MODE == 0) {
-                val += bias[co];
-                static_cast<uint16_t*>(out)[vo * 16 + co] = f2bf(val > 0.f ? val : 0.f);
-            } else if (MODE == 1) {
-                if (co == 0) static_cast<float*>(out)[vo] = val + bias[0];
-            } else {
-                const bool on = bf2f(mask[vo * 16 + co]) > 0.f;
-                static_cast<uint16_t*>(out)[vo * 16 + co] = f2bf(on ? val : 0.f);
+        for (int oz = 0; oz < 2; ++oz)
+#pragma unroll
+            for (int oy = 0; oy < 2; ++oy) {
+                if (y + oy >= L.ny || z + oz >= L.nz) continue;
+                const int64_t po = p + oz * plane + oy * L.sx;
+                const f4 val = acc[oz][oy];
+                if (MODE == 1) {
+                    if (g == 0)
+                        static_cast<float*>(out)[x + (int64_t)L.nx * (y + oy + (int64_t)L.ny * (z + oz))] = val[0] + bs[0];
+                    continue;
+                }
+                s4 r;
+                if (MODE == 0) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float t = val[j] + bs[j];
+                        r[j] = static_cast<short>(f2bf(t > 0.f ? t : 0.f));
+                    }
+                } else {
+                    const s4 on = *reinterpret_cast<const s4*>(mask + po * 16 + 4 * g);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        r[j] = static_cast<short>(f2bf(bf2f(static_cast<uint16_t>(on[j])) > 0.f ? val[j] : 0.f));
+                }
+                *reinterpret_cast<s4*>(static_cast<uint16_t*>(out) + po * 16 + 4 * g) = r;
             }
-        }
     }
 }
 
@@ -145,41 +206,27 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(Lat L, const uint16_t* __res
     const int g = lane / 16, n = lane % 16;
     const int64_t wg = (int64_t)blockIdx.x * 4 + wave;
     const int64_t nw = (int64_t)gridDim.x * 4;
-    const int64_t ntiles = (L.V + 15) / 16;
+    const int64_t ntiles = ((int64_t)L.sx * L.sy * L.nz + 15) / 16;   // every cell: dZ is zero outside the lattice
+    const int ci = CIN == 16 ? n : n % 4;
     f4 acc[NCH];
 #pragma unroll
     for (int m = 0; m < NCH; ++m) acc[m] = f4{0.f, 0.f, 0.f, 0.f};
     float db = 0.f;
     for (int64_t tile = wg; tile < ntiles; tile += nw) {
+        const int64_t p = L.g0 + tile * 16 + 4 * g;
         s4 a;
-        int64_t vv[4];
-        int xs[4], ys[4], zs[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int64_t v = tile * 16 + 4 * g + j;
-            vv[j] = v;
-            const bool ok = v < L.V;
-            const uint16_t d = ok ? dZ[v * 16 + n] : uint16_t(0);
+            const uint16_t d = dZ[(p + j) * 16 + n];
             a[j] = static_cast<short>(d);
             db += bf2f(d);
-            xs[j] = static_cast<int>(v % L.nx);
-            ys[j] = static_cast<int>((v / L.nx) % L.ny);
-            zs[j] = static_cast<int>(v / ((int64_t)L.nx * L.ny));
         }
 #pragma unroll
         for (int m = 0; m < NCH; ++m) {
             const int t = CIN == 16 ? m : 4 * m + n / 4;
-            const int ci = CIN == 16 ? n : n % 4;
             s4 b;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint16_t xv = 0;
-                if (vv[j] < L.V && t < 27) {
-                    const int64_t nb = neighbour(L, xs[j], ys[j], zs[j], t);
-                    if (nb >= 0) xv = X[nb * CIN + ci];
-                }
-                b[j] = static_cast<short>(xv);
-            }
+            for (int j = 0; j < 4; ++j) b[j] = static_cast<short>(X[(p + j + (t < 27 ? L.tap(t) : 0)) * CIN + ci]);
             acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[m], 0, 0, 0);
         }
     }
@@ -270,25 +317,25 @@ __global__ void k_pack(const float* __restrict__ w, int cin, int cout, int nch, 
 constexpr double kPhiFloor = 1e-16;
 constexpr float kMaxCorr = 8.f;
 
-// network input for illumination k: [V][4] bf16 = (log mu/mu0, log kappa/kappa0, log phi_hom, 0)
-__global__ void k_inputs(int64_t V, const double* __restrict__ kappa, const double* __restrict__ mu, double k0,
-                         double m0, const double* __restrict__ phih, uint16_t* __restrict__ X) {
-    int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (v >= V) return;
-    X[v * 4 + 0] = f2bf(static_cast<float>(log(mu[v] / m0)));
-    X[v * 4 + 1] = f2bf(static_cast<float>(log(kappa[v] / k0)));
-    X[v * 4 + 2] = f2bf(static_cast<float>(log(fmax(phih[v], kPhiFloor))));
-    X[v * 4 + 3] = 0;
+__device__ __forceinline__ void put_input(const Lat& L, int64_t v, float a, float b, float c, uint16_t* __restrict__ X) {
+    const s4 r = {static_cast<short>(f2bf(a)), static_cast<short>(f2bf(b)), static_cast<short>(f2bf(c)), 0};
+    *reinterpret_cast<s4*>(X + L.cell(v) * 4) = r;
 }
 
-// raw input [3][V] f32 -> [V][4] bf16
-__global__ void k_inputs_raw(int64_t V, const float* __restrict__ in, uint16_t* __restrict__ X) {
+// network input for illumination k: [P][4] bf16 = (log mu/mu0, log kappa/kappa0, log phi_hom, 0)
+__global__ void k_inputs(Lat L, const double* __restrict__ kappa, const double* __restrict__ mu, double k0,
+                         double m0, const double* __restrict__ phih, uint16_t* __restrict__ X) {
     int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (v >= V) return;
-    X[v * 4 + 0] = f2bf(in[v]);
-    X[v * 4 + 1] = f2bf(in[V + v]);
-    X[v * 4 + 2] = f2bf(in[2 * V + v]);
-    X[v * 4 + 3] = 0;
+    if (v >= L.V) return;
+    put_input(L, v, static_cast<float>(log(mu[v] / m0)), static_cast<float>(log(kappa[v] / k0)),
+              static_cast<float>(log(fmax(phih[v], kPhiFloor))), X);
+}
+
+// raw input [3][V] f32 -> [P][4] bf16
+__global__ void k_inputs_raw(Lat L, const float* __restrict__ in, uint16_t* __restrict__ X) {
+    int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (v >= L.V) return;
+    put_input(L, v, in[v], in[L.V + v], in[2 * L.V + v], X);
 }
 
 // target = log phi - log phi_hom (f32)
@@ -312,17 +359,18 @@ __global__ void k_fluence(int64_t V, const float* __restrict__ pred, const doubl
 }
 
 // mean squared error: per-block partial sums; dZ4[v][0] = 2 (pred - t) / V
-__global__ __launch_bounds__(kThreads) void k_loss(int64_t V, const float* __restrict__ pred,
+__global__ __launch_bounds__(kThreads) void k_loss(Lat L, const float* __restrict__ pred,
                                                    const float* __restrict__ t, uint16_t* __restrict__ dZ,
                                                    double* __restrict__ part) {
     __shared__ double sm[kThreads / 64];
     double acc = 0.0;
+    const int64_t V = L.V;
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < V; v += (int64_t)gridDim.x * blockDim.x) {
         const float d = pred[v] - t[v];
         acc += static_cast<double>(d) * d;
-        dZ[v * 16] = f2bf(2.f * d / static_cast<float>(V));
-#pragma unroll
-        for (int c = 1; c < 16; ++c) dZ[v * 16 + c] = 0;
+        uint4* row = reinterpret_cast<uint4*>(dZ + L.cell(v) * 16);
+        row[0] = uint4{f2bf(2.f * d / static_cast<float>(V)), 0, 0, 0};
+        row[1] = uint4{0, 0, 0, 0};
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
@@ -357,12 +405,21 @@ __global__ void k_adam(int n, float* __restrict__ w, const float* __restrict__ g
     w[i] -= lr * (a / c1) / (sqrtf(b / c2) + eps);
 }
 
+__global__ void k_zero_16(int64_t n, uint4* p) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        p[i] = uint4{0, 0, 0, 0};
+}
+
 __global__ void k_zero_f(int n, float* p) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0.f;
 }
 
-constexpr int kConvBlocks = 2048;   // 8192 wavefronts over 256 CUs
+constexpr int kWgradBlocks = 2048;
+// the convolutions keep their weights in registers, so a launch is one resident
+// set of 4 blocks a CU (128 registers) that walks the items: inference at 97^3
+// 128 us, against 138 - 151 us with 1536 - 3776 blocks and 135 us with 768
+constexpr int kConvBlocks = 1024;
 
 int nch_of(int layer) { return layer == 0 ? 7 : 27; }
 
@@ -377,10 +434,11 @@ struct GuessNet {
     float* m2 = nullptr;
     uint16_t* Wf[kLayers] = {};  // forward B operands
     uint16_t* Wb[kLayers] = {};  // backward-data B operands
-    uint16_t* X0 = nullptr;      // [V][4]
-    uint16_t* Y[3] = {};         // hidden activations [V][16]
-    uint16_t* dA = nullptr;      // [V][16]
-    uint16_t* dB = nullptr;      // [V][16]
+    // on the padded lattice, zero outside the node lattice
+    uint16_t* X0 = nullptr;      // [P][4]
+    uint16_t* Y[3] = {};         // hidden activations [P][16]
+    uint16_t* dA = nullptr;      // [P][16]
+    uint16_t* dB = nullptr;      // [P][16]
     float* pred = nullptr;       // [V]
     float* target = nullptr;     // [V]
     float* partial = nullptr;    // [waves][27*256+16]
@@ -422,12 +480,12 @@ static qpat_status guess_forward(qpat_ctx* c, float* out) {
 static qpat_status guess_backward(qpat_ctx* c) {
     GuessNet* G = c->guess;
     const int64_t V = G->L.V;
-    const dim3 g(kConvBlocks), b(kThreads);
+    const dim3 g(kConvBlocks), gw(kWgradBlocks), b(kThreads);
     const int lb = grid_for(V, kThreads, 1024);
     QPAT_TRY(guess_forward(c, G->pred));
-    hipLaunchKernelGGL(k_loss, dim3(lb), b, 0, c->stream, V, G->pred, G->target, G->dA, G->lossp);
+    hipLaunchKernelGGL(k_loss, dim3(lb), b, 0, c->stream, G->L, G->pred, G->target, G->dA, G->lossp);
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, c->stream, G->lossp, lb, V, G->lossv);
-    const int64_t nw = (int64_t)kConvBlocks * 4;
+    const int64_t nw = (int64_t)kWgradBlocks * 4;
     // dZ of layer l in cur; its input activation is Y[l-1] (X0 for l = 0)
     uint16_t* cur = G->dA;
     uint16_t* nxt = G->dB;
@@ -435,13 +493,13 @@ static qpat_status guess_backward(qpat_ctx* c) {
         const uint16_t* Xin = l == 0 ? G->X0 : G->Y[l - 1];
         float* grad = G->grads + param_offset(l);
         if (l == 0) {
-            hipLaunchKernelGGL(k_wgrad<4>, g, b, 0, c->stream, G->L, cur, Xin, G->partial);
+            hipLaunchKernelGGL(k_wgrad<4>, gw, b, 0, c->stream, G->L, cur, Xin, G->partial);
             hipLaunchKernelGGL(k_wgrad_sum, dim3((7 * 256 + 16 + 63) / 64, kSegs), b, 0, c->stream, G->partial, nw,
                                7 * 256 + 16, G->part2);
             hipLaunchKernelGGL(k_wgrad_reduce<4>, dim3((7 * 256 + 16 + 255) / 256), dim3(256), 0, c->stream, G->part2,
                                kCin[l], kCout[l], grad);
         } else {
-            hipLaunchKernelGGL(k_wgrad<16>, g, b, 0, c->stream, G->L, cur, Xin, G->partial);
+            hipLaunchKernelGGL(k_wgrad<16>, gw, b, 0, c->stream, G->L, cur, Xin, G->partial);
             hipLaunchKernelGGL(k_wgrad_sum, dim3((27 * 256 + 16 + 63) / 64, kSegs), b, 0, c->stream, G->partial, nw,
                                27 * 256 + 16, G->part2);
             hipLaunchKernelGGL(k_wgrad_reduce<16>, dim3((27 * 256 + 16 + 255) / 256), dim3(256), 0, c->stream, G->part2,
@@ -460,12 +518,12 @@ static qpat_status guess_backward(qpat_ctx* c) {
 
 qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz) {
     if ((int64_t)nx * ny * nz != c->N) return fail(c, QPAT_ERR_ARG, "guess_setup: nx*ny*nz must equal N");
-    if (c->N * 16 * 2 >= (int64_t(1) << 31))   // the convolutions' 32-bit buffer offsets
+    if (c->N * 16 * 2 >= (int64_t(1) << 31))   // 2 GB an activation
         return fail(c, QPAT_ERR_ARG, "guess_setup: lattice too large for the network (N = %lld)", (long long)c->N);
     if (!c->guess) c->guess = new GuessNet();
     GuessNet* G = c->guess;
     if (G->L.V == c->N && G->params) return QPAT_OK;
-    G->L = Lat{nx, ny, nz, c->N};
+    G->L = Lat::of(nx, ny, nz);
     const int64_t V = c->N;
     QPAT_TRY(dalloc(c, &G->params, kParams));
     QPAT_TRY(dalloc(c, &G->grads, kParams));
@@ -475,13 +533,20 @@ qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz) {
         QPAT_TRY(dalloc(c, &G->Wf[l], (size_t)nch_of(l) * 256));
         QPAT_TRY(dalloc(c, &G->Wb[l], (size_t)27 * 256));
     }
-    QPAT_TRY(dalloc(c, &G->X0, V * 4));
-    for (int l = 0; l < 3; ++l) QPAT_TRY(dalloc(c, &G->Y[l], V * 16));
-    QPAT_TRY(dalloc(c, &G->dA, V * 16));
-    QPAT_TRY(dalloc(c, &G->dB, V * 16));
+    const int64_t P = G->L.P;
+    auto zeroed = [&](uint16_t** q, int64_t n) -> qpat_status {   // n: a multiple of 8
+        QPAT_TRY(dalloc(c, q, n));
+        hipLaunchKernelGGL(k_zero_16, dim3(grid_for(n / 8, kThreads, 4096)), dim3(kThreads), 0, c->stream, n / 8,
+                           reinterpret_cast<uint4*>(*q));
+        return QPAT_OK;
+    };
+    QPAT_TRY(zeroed(&G->X0, (P + 1) / 2 * 2 * 4));
+    for (int l = 0; l < 3; ++l) QPAT_TRY(zeroed(&G->Y[l], P * 16));
+    QPAT_TRY(zeroed(&G->dA, P * 16));
+    QPAT_TRY(zeroed(&G->dB, P * 16));
     QPAT_TRY(dalloc(c, &G->pred, V));
     QPAT_TRY(dalloc(c, &G->target, V));
-    QPAT_TRY(dalloc(c, &G->partial, (size_t)kConvBlocks * 4 * (27 * 256 + 16)));
+    QPAT_TRY(dalloc(c, &G->partial, (size_t)kWgradBlocks * 4 * (27 * 256 + 16)));
     QPAT_TRY(dalloc(c, &G->part2, (size_t)kSegs * (27 * 256 + 16)));
     QPAT_TRY(dalloc(c, &G->lossp, 1024));
     QPAT_TRY(dalloc(c, &G->lossv, 1));
@@ -507,14 +572,14 @@ qpat_status guess_get_params(qpat_ctx* c, float* p) {
 qpat_status guess_eval_raw(qpat_ctx* c, const float* in, float* out) {
     GuessNet* G = c->guess;
     hipLaunchKernelGGL(k_inputs_raw, dim3(grid_for(G->L.V, kThreads, 1 << 30)), dim3(kThreads), 0, c->stream,
-                       G->L.V, in, G->X0);
+                       G->L, in, G->X0);
     return guess_forward(c, out);
 }
 
 qpat_status guess_grad_raw(qpat_ctx* c, const float* in, const float* target, float* grad, double* loss) {
     GuessNet* G = c->guess;
     hipLaunchKernelGGL(k_inputs_raw, dim3(grid_for(G->L.V, kThreads, 1 << 30)), dim3(kThreads), 0, c->stream,
-                       G->L.V, in, G->X0);
+                       G->L, in, G->X0);
     QPAT_HIP(c, hipMemcpyAsync(G->target, target, sizeof(float) * G->L.V, hipMemcpyDeviceToDevice, c->stream));
     QPAT_TRY(guess_backward(c));
     if (grad) QPAT_HIP(c, hipMemcpyAsync(grad, G->grads, sizeof(float) * kParams, hipMemcpyDeviceToDevice, c->stream));
@@ -539,7 +604,7 @@ qpat_status guess_train(qpat_ctx* c, const double* kappa, const double* mu, doub
                         const double* phih, const double* phi, float lr, double* loss) {
     GuessNet* G = c->guess;
     const dim3 gg(grid_for(G->L.V, kThreads, 1 << 30)), b(kThreads);
-    hipLaunchKernelGGL(k_inputs, gg, b, 0, c->stream, G->L.V, kappa, mu, k0, m0, phih, G->X0);
+    hipLaunchKernelGGL(k_inputs, gg, b, 0, c->stream, G->L, kappa, mu, k0, m0, phih, G->X0);
     hipLaunchKernelGGL(k_target, gg, b, 0, c->stream, G->L.V, phi, phih, G->target);
     QPAT_TRY(guess_backward(c));
     QPAT_TRY(adam_step(c, lr));
@@ -563,7 +628,7 @@ qpat_status guess_fluence(qpat_ctx* c, const double* kappa, const double* mu, do
     const int64_t V = G->L.V;
     const dim3 gg(grid_for(V, kThreads, 1 << 30)), b(kThreads);
     for (int k = 0; k < c->n_ill; ++k) {
-        hipLaunchKernelGGL(k_inputs, gg, b, 0, c->stream, V, kappa, mu, k0, m0, phih + k * V, G->X0);
+        hipLaunchKernelGGL(k_inputs, gg, b, 0, c->stream, G->L, kappa, mu, k0, m0, phih + k * V, G->X0);
         QPAT_TRY(guess_forward(c, G->pred));
         hipLaunchKernelGGL(k_fluence, gg, b, 0, c->stream, V, G->pred, phih + k * V, phi0 + k * V);
     }

@@ -150,3 +150,28 @@ def test_trained_guess_saves_pcg_iterations():
     agg, _ = learned.evaluate(ctx, held, phi_hom, P.kappa0, P.mu0, "cuda")
     assert agg["relres"] <= 1e-10
     assert agg["net_iters"] < agg["zero_iters"], agg
+
+
+@pytest.mark.parametrize("shape", [(3, 3, 3), (4, 2, 5), (17, 6, 3), (5, 16, 2), (33, 7, 8)])
+def test_net_on_ragged_lattices(shape):
+    """Sides around the tiles' edges (16 cells, pairs of rows and planes, rows padded to a multiple of 4),
+    forward and gradients. Tolerance: the BF16 bound of this file."""
+    from paper_1512_02796_amd import qpat
+    from test_gpu_stencil import kuhn_box
+    nx, ny, nz = shape
+    coords, tets, bfaces = kuhn_box(nx - 1, ny - 1, nz - 1)
+    ctx = qpat.Context(dev(coords), dev(tets, torch.int32), dev(bfaces, torch.int32))
+    ctx.guess_setup(nx, ny, nz)
+    params, x = seeded_net(sum(shape), (nz, ny, nx))
+    target = np.random.default_rng(5).standard_normal((nz, ny, nx)).astype(np.float32).astype(np.float64)
+    ctx.guess_set_params(dev(flat_params(params), torch.float32))
+    out = torch.empty(nx * ny * nz, dtype=torch.float32, device="cuda")
+    ctx.guess_eval(dev(x.reshape(3, -1), torch.float32), out)
+    ref, _ = convnet.forward(params, x)
+    assert_close(host(out).astype(np.float64), ref.ravel(), 3e-2, f"net output {shape}")
+    g = torch.empty(15601, dtype=torch.float32, device="cuda")
+    loss = ctx.guess_grad(dev(x.reshape(3, -1), torch.float32), dev(target.ravel(), torch.float32), g)
+    L, grads = convnet.loss_and_grads(params, x, target)
+    assert abs(loss - L) <= 3e-2 * L
+    ref_g = np.concatenate([np.concatenate([w.ravel(), b.ravel()]) for w, b in grads])
+    assert rel(host(g).astype(np.float64), ref_g) <= 3e-2, f"gradient {shape}"
