@@ -194,9 +194,12 @@ __global__ __launch_bounds__(kThreads, 4) void k_conv(Lat L, const uint16_t* __r
 }
 
 // ---------------------------------------------------------------- weight gradients
-// partial[w][m*256 + co*16 + n] = sum over this wavefront's lattice points of
+// partial[b][m*256 + co*16 + n] = sum over this block's lattice points of
 // dZ[v][co] X[v + tap][ci], with (tap, ci) = (m, n) for CIN = 16 and
-// (4m + n/4, n%4) for CIN = 4; partial[w][NCH*256 + co] = sum dZ[v][co].
+// (4m + n/4, n%4) for CIN = 4; partial[b][NCH*256 + co] = sum dZ[v][co].
+// One resident set of blocks (two waves a SIMD: 108 accumulators), the four
+// wavefronts' sums added in LDS, so that 512 partials leave the kernel and not
+// one a wavefront.
 template <int CIN>
 __global__ __launch_bounds__(kThreads) void k_wgrad(Lat L, const uint16_t* __restrict__ dZ,
                                                     const uint16_t* __restrict__ X, float* __restrict__ partial) {
@@ -230,23 +233,32 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(Lat L, const uint16_t* __res
             acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[m], 0, 0, 0);
         }
     }
-    float* P = partial + wg * STRIDE;
-#pragma unroll
-    for (int m = 0; m < NCH; ++m)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) P[m * 256 + (4 * g + j) * 16 + n] = acc[m][j];
     db += __shfl_xor(db, 16);
     db += __shfl_xor(db, 32);
-    if (lane < 16) P[NCH * 256 + lane] = db;
+    __shared__ float sm[STRIDE];
+    for (int q = 0; q < kThreads / 64; ++q) {   // wavefront by wavefront: a fixed order
+        if (wave == q) {
+#pragma unroll
+            for (int m = 0; m < NCH; ++m)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float* d = sm + m * 256 + (4 * g + j) * 16 + n;
+                    *d = q == 0 ? acc[m][j] : *d + acc[m][j];
+                }
+            if (lane < 16) sm[NCH * 256 + lane] = q == 0 ? db : sm[NCH * 256 + lane] + db;
+        }
+        __syncthreads();
+    }
+    float* P = partial + (int64_t)blockIdx.x * STRIDE;
+    for (int i = threadIdx.x; i < STRIDE; i += kThreads) P[i] = sm[i];
 }
 
-// The gradient of one layer = the sum over wavefronts of their partials, in two
-// passes of fixed order. One thread per parameter walking all 8192 partials
-// (227 MB, one 28-block launch) had one load in flight per thread: 2539 us a
-// layer at 97^3. Split kSegs ways the read has 3488 blocks: 34 us + 5 us.
-constexpr int kSegs = 32;
+// The gradient of one layer = the sum over blocks of their partials, in two
+// passes of fixed order. One thread per parameter walking 8192 partials in one
+// 28-block launch had one load in flight per thread: 2539 us a layer at 97^3.
+constexpr int kSegs = 16;
 
-// part2[s][p] = sum of partial[w][p] over segment s of the wavefronts
+// part2[s][p] = sum of partial[w][p] over segment s of the blocks
 __global__ __launch_bounds__(kThreads) void k_wgrad_sum(const float* __restrict__ partial, int64_t nw, int stride,
                                                         float* __restrict__ part2) {
     __shared__ float sm[kThreads / 64][64];
@@ -415,7 +427,7 @@ __global__ void k_zero_f(int n, float* p) {
     if (i < n) p[i] = 0.f;
 }
 
-constexpr int kWgradBlocks = 2048;
+constexpr int kWgradBlocks = 512;   // two resident blocks a CU
 // the convolutions keep their weights in registers, so a launch is one resident
 // set of 4 blocks a CU (128 registers) that walks the items: inference at 97^3
 // 128 us, against 138 - 151 us with 1536 - 3776 blocks and 135 us with 768
@@ -441,7 +453,7 @@ struct GuessNet {
     uint16_t* dB = nullptr;      // [P][16]
     float* pred = nullptr;       // [V]
     float* target = nullptr;     // [V]
-    float* partial = nullptr;    // [waves][27*256+16]
+    float* partial = nullptr;    // [kWgradBlocks][27*256+16]
     float* part2 = nullptr;      // [kSegs][27*256+16]
     double* lossp = nullptr;     // [blocks]
     double* lossv = nullptr;     // [1]
@@ -485,7 +497,7 @@ static qpat_status guess_backward(qpat_ctx* c) {
     QPAT_TRY(guess_forward(c, G->pred));
     hipLaunchKernelGGL(k_loss, dim3(lb), b, 0, c->stream, G->L, G->pred, G->target, G->dA, G->lossp);
     hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(64), 0, c->stream, G->lossp, lb, V, G->lossv);
-    const int64_t nw = (int64_t)kWgradBlocks * 4;
+    const int64_t nw = kWgradBlocks;
     // dZ of layer l in cur; its input activation is Y[l-1] (X0 for l = 0)
     uint16_t* cur = G->dA;
     uint16_t* nxt = G->dB;
@@ -546,7 +558,7 @@ qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz) {
     QPAT_TRY(zeroed(&G->dB, P * 16));
     QPAT_TRY(dalloc(c, &G->pred, V));
     QPAT_TRY(dalloc(c, &G->target, V));
-    QPAT_TRY(dalloc(c, &G->partial, (size_t)kWgradBlocks * 4 * (27 * 256 + 16)));
+    QPAT_TRY(dalloc(c, &G->partial, (size_t)kWgradBlocks * (27 * 256 + 16)));
     QPAT_TRY(dalloc(c, &G->part2, (size_t)kSegs * (27 * 256 + 16)));
     QPAT_TRY(dalloc(c, &G->lossp, 1024));
     QPAT_TRY(dalloc(c, &G->lossv, 1));
