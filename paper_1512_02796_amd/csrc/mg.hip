@@ -16,8 +16,7 @@
 //     bound: the first-degree Chebyshev weight for the interval [g/4, g] that
 //     the sweep has to damp; 19/(10 g) on the coarse levels (w lambda < 2
 //     keeps the cycle SPD);
-//   * coarsest level: the explicit inverse (dense; on the host up to order
-//     kMgHostDense, on the GPU above).
+//   * coarsest level: the explicit inverse (dense).
 // Vectors hold B right-hand sides interleaved ([sys][N][B]); every lane
 // (system, right-hand side) has its own PCG scalars and stops on its own.
 // With deflation (M_delta: the exact eigenpair (delta, 1) of each block) the
@@ -103,6 +102,9 @@ struct MgState {
     std::vector<MgLevel> lv;
     double* w = nullptr;           // [nsys][levels] Jacobi weights
     double* ainv = nullptr;        // [nsys][Nc][Nc]
+    double* ainv_t = nullptr;      // the other buffer of its steps
+    double* apiv = nullptr;        // [2][nsys][kGj][kGj] their inverted pivot blocks
+    int* bad = nullptr;            // [nsys + 1] set-up checks: a pivot of system s, a diagonal, not positive
     double *pr = nullptr, *pa = nullptr, *pb = nullptr, *pq = nullptr;  // PCG r, p (two), q: [nsys][N][bmax]
     double* pr2 = nullptr;         // the other residual buffer of the fused update (odd iterations write r here)
     double* pring = nullptr;       // [kRing][N][bmax] directions of the tiled iterations (FP32 or FP64 elements)
@@ -131,7 +133,6 @@ namespace {
 
 constexpr int kMgCoarse = 5;      // coarsest lattice: at most this many nodes per axis, or
 constexpr int64_t kMgDenseK = 1000;   // the first coarse level of at most this many nodes
-constexpr int64_t kMgHostDense = 256;   // coarsest inverses up to this order on the host, larger ones on the GPU
 constexpr int kMgNu = 1;          // Jacobi sweeps before and after the coarse correction
 constexpr int kMgBlocks = 2048;   // most blocks of a kernel that writes partial sums (8 per CU)
 constexpr int kMgGrid = 512;      // blocks of the vector kernels of several right-hand sides
@@ -688,58 +689,68 @@ __global__ __launch_bounds__(kMgT) void k_mg_wpack(LvArgs L, double* __restrict_
 // sum over the fine nodes i in the support of I, the fine stencil entries
 // a_ij, and the coarse nodes J whose support holds j, of P(i,I) a_ij P(j,J).
 // W: [nsys][8][N] weights of P, or null (trilinear).
+// 32 lanes share a coarse node, one for each of the 27 fine nodes of its support,
+// and their sums are added in LDS in that order. With one thread a coarse node
+// the few thousand serial loads of a thread bounded every level alike (560 us
+// a level at 65^3, 370 us at 17^3).
+constexpr int kRapLanes = 32;
+constexpr int kRapNodes = kMgT / kRapLanes;   // coarse nodes a block
 __global__ __launch_bounds__(kMgT) void k_mg_rap(LvArgs F, const double* __restrict__ Wall, double* __restrict__ Uc,
                                                  int cx, int cy, int cz) {
-    __shared__ double acc[kMgT][14];
+    __shared__ double acc[14][kMgT];
     const int sys = blockIdx.y;
     const int64_t Nc = (int64_t)cx * cy * cz;
-    const int64_t I = blockIdx.x * (int64_t)kMgT + threadIdx.x;
+    const int64_t I0 = blockIdx.x * (int64_t)kRapNodes, I = I0 + threadIdx.x / kRapLanes;
+    const int di = threadIdx.x % kRapLanes;
     const int Mf = F.m + 1;
     const double* U = F.U + (int64_t)sys * F.N * Mf;
     const double* W = Wall ? Wall + (int64_t)sys * F.N * 8 : nullptr;
-    for (int k = 0; k < 14; ++k) acc[threadIdx.x][k] = 0.0;
-    if (I < Nc) {
-        int Ix, Iy, Iz;
-        coords(static_cast<int32_t>(I), cx, cy, Ix, Iy, Iz);
-        for (int di = 0; di < 27; ++di) {
-            const int ax = di % 3 - 1, ay = (di / 3) % 3 - 1, az = di / 9 - 1;
-            const int fx = 2 * Ix + ax, fy = 2 * Iy + ay, fz = 2 * Iz + az;
-            if (fx < 0 || fx >= F.nx || fy < 0 || fy >= F.ny || fz < 0 || fz >= F.nz) continue;
-            const int32_t i = fx + F.nx * (fy + F.ny * fz);
-            // I = J0(i) + corner, corner 1 exactly along the axes where i sits below 2 I
-            const double wi = pweight(W, F.N, i, fx, fy, fz, (ax < 0 ? 1 : 0) + (ay < 0 ? 2 : 0) + (az < 0 ? 4 : 0));
-            if (wi == 0.0) continue;
-            // the fine row: diagonal, upper and lower entries
-            for (int s = -F.m; s <= F.m; ++s) {
-                int sx = 0, sy = 0, sz = 0, lin = 0;
-                double a;
-                if (s == 0) {
-                    a = U[(int64_t)i * Mf];
-                } else {
-                    const int4 t = F.tab[(s > 0 ? s : -s) - 1];
-                    const int sg = s > 0 ? 1 : -1;
-                    sx = sg * t.x;
-                    sy = sg * t.y;
-                    sz = sg * t.z;
-                    lin = sg * t.w;
-                    const int jx = fx + sx, jy = fy + sy, jz = fz + sz;
-                    if (jx < 0 || jx >= F.nx || jy < 0 || jy >= F.ny || jz < 0 || jz >= F.nz) continue;
-                    a = s > 0 ? U[(int64_t)i * Mf + s] : U[(int64_t)(i + lin) * Mf + (-s)];
-                }
-                const int jx = fx + sx, jy = fy + sy, jz = fz + sz;
-                const int32_t j = i + lin;
-                for (int cj = 0; cj < 8; ++cj) {
-                    const double wj = pweight(W, F.N, j, jx, jy, jz, cj);
-                    if (wj == 0.0) continue;
-                    const int Jx = (jx >> 1) + (cj & 1), Jy = (jy >> 1) + ((cj >> 1) & 1), Jz = (jz >> 1) + (cj >> 2);
-                    const int code = (Jx - Ix + 1) + 3 * (Jy - Iy + 1) + 9 * (Jz - Iz + 1);
-                    if (code < 13) continue;   // lower half: stored at the partner row
-                    acc[threadIdx.x][code - 13] += wi * a * wj;
-                }
+    for (int k = 0; k < 14; ++k) acc[k][threadIdx.x] = 0.0;
+    int Ix, Iy, Iz;
+    coords(static_cast<int32_t>(min(I, Nc - 1)), cx, cy, Ix, Iy, Iz);
+    const int ax = di % 3 - 1, ay = (di / 3) % 3 - 1, az = di / 9 - 1;
+    const int fx = 2 * Ix + ax, fy = 2 * Iy + ay, fz = 2 * Iz + az;
+    const bool in = I < Nc && di < 27 && fx >= 0 && fx < F.nx && fy >= 0 && fy < F.ny && fz >= 0 && fz < F.nz;
+    if (in) {
+        const int32_t i = fx + F.nx * (fy + F.ny * fz);
+        // I = J0(i) + corner, corner 1 exactly along the axes where i sits below 2 I
+        const double wi = pweight(W, F.N, i, fx, fy, fz, (ax < 0 ? 1 : 0) + (ay < 0 ? 2 : 0) + (az < 0 ? 4 : 0));
+        // the fine row: diagonal, upper and lower entries
+        for (int s = -F.m; s <= F.m && wi != 0.0; ++s) {
+            int sx = 0, sy = 0, sz = 0, lin = 0;
+            if (s != 0) {
+                const int4 t = F.tab[(s > 0 ? s : -s) - 1];
+                const int sg = s > 0 ? 1 : -1;
+                sx = sg * t.x;
+                sy = sg * t.y;
+                sz = sg * t.z;
+                lin = sg * t.w;
+            }
+            const int jx = fx + sx, jy = fy + sy, jz = fz + sz;
+            if (jx < 0 || jx >= F.nx || jy < 0 || jy >= F.ny || jz < 0 || jz >= F.nz) continue;
+            const int32_t j = i + lin;
+            const double a = s >= 0 ? U[(int64_t)i * Mf + s] : U[(int64_t)j * Mf - s];
+            // corners that can carry a weight: one step up only along odd axes
+            const int px = jx & 1, py = jy & 1, pz = jz & 1;
+            const int code0 = ((jx >> 1) - Ix) + 3 * ((jy >> 1) - Iy) + 9 * ((jz >> 1) - Iz);
+#pragma unroll
+            for (int cj = 0; cj < 8; ++cj) {
+                const int bx = cj & 1, by = (cj >> 1) & 1, bz = cj >> 2;
+                if (bx > px || by > py || bz > pz) continue;
+                const int code = code0 + bx + 3 * by + 9 * bz;   // the lower half is stored at the partner row
+                if (code < 0) continue;
+                const double wj = W ? W[cj * F.N + j] : (px ? 0.5 : 1.0) * (py ? 0.5 : 1.0) * (pz ? 0.5 : 1.0);
+                acc[code][threadIdx.x] += wi * a * wj;
             }
         }
-        double* out = Uc + ((int64_t)sys * Nc + I) * 14;
-        for (int k = 0; k < 14; ++k) out[k] = acc[threadIdx.x][k];
+    }
+    __syncthreads();
+    const int node = threadIdx.x / 14, k = threadIdx.x % 14;
+    if (node < kRapNodes && I0 + node < Nc) {
+        double t = 0.0;
+#pragma unroll
+        for (int d = 0; d < 27; ++d) t += acc[k][node * kRapLanes + d];
+        Uc[((int64_t)sys * Nc + I0 + node) * 14 + k] = t;
     }
 }
 
@@ -4218,64 +4229,200 @@ static qpat_status region_setup(qpat_ctx* c, MgState& M) {
     return QPAT_OK;
 }
 
-// One step of the symmetric sweep operator (Gauss-Jordan elimination without
-// pivoting) on each system's [n][n] matrix, pivot k, from S to T:
-//   T_kk = -1/d, T_ik = S_ik/d, T_kj = S_kj/d, T_ij = S_ij - S_ik S_kj/d,  d = S_kk.
-// Sweeping every pivot of an SPD matrix turns it into minus its inverse, and
-// each pivot d is then a Schur-complement diagonal, so positive; the last step
-// flips the sign. A pivot that is not positive sets bad[sys].
-__global__ __launch_bounds__(kMgT) void k_sweep(const double* __restrict__ S, double* __restrict__ T, int n, int k,
-                                                int* __restrict__ bad) {
-    const int sys = blockIdx.y;
-    const int64_t nn = (int64_t)n * n;
-    const int64_t e = blockIdx.x * (int64_t)kMgT + threadIdx.x;
-    if (e >= nn) return;
-    const double* s = S + sys * nn;
-    const int i = static_cast<int>(e / n), j = static_cast<int>(e % n);
-    const double d = s[(int64_t)k * n + k];
-    const double sg = k == n - 1 ? -1.0 : 1.0;
-    double v;
-    if (i == k && j == k) {
-        if (!(d > 0.0) || !std::isfinite(d)) bad[sys] = 1;
-        v = -1.0 / d;
-    } else if (i == k) {
-        v = s[e] / d;
-    } else if (j == k) {
-        v = s[e] / d;
-    } else {
-        v = s[e] - s[(int64_t)i * n + k] * s[(int64_t)k * n + j] / d;
-    }
-    T[sys * nn + e] = sg * v;
+// Inverse of the coarsest level's SPD matrix by the sweep operator
+// (Gauss-Jordan elimination without pivoting) taken kGj pivots at a time: with
+// D = S_KK the block of pivots,
+//   T_KK = -D^{-1}, T_IK = S_IK D^{-1}, T_KJ = D^{-1} S_KJ, T_IJ = S_IJ - S_IK D^{-1} S_KJ,
+// and after every block the matrix is minus its inverse. Every pivot is a
+// Schur-complement diagonal, so positive for an SPD matrix; one that is not
+// sets bad[sys].
+// A block owns a kGj x kGj tile and forms it with FP64 MFMAs, one 16 x 16
+// quadrant a wavefront; the block of the next pivots' tile then inverts it, so
+// a step is one launch and one block's inversion (every block inverting D for
+// itself made a step of order 729 18 us, of which 11 were the inversions).
+// Order 729: 24 launches; one launch a pivot (729 of them, 4.1 us each) took 3 ms
+// of every forward solve's set-up.
+constexpr int kGj = 32;
+typedef double mg_d4 __attribute__((ext_vector_type(4)));
+
+// quadrant (qr, qc) of X Y for two kGj x kGj tiles in LDS; the 16x16x4 FP64 MFMA takes
+// A[l % 16][l / 16], B[l / 16][l % 16] from lane l and leaves D[l / 16 + 4 q][l % 16]
+__device__ __forceinline__ mg_d4 gj_product(const double (*X)[kGj + 1], const double (*Y)[kGj + 1], int qr, int qc,
+                                            mg_d4 acc) {
+    const int lane = threadIdx.x & 63, i = lane % 16, k = lane / 16;
+#pragma unroll
+    for (int kk = 0; kk < kGj; kk += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[16 * qr + i][kk + k], Y[kk + k][16 * qc + i], acc, 0, 0, 0);
+    return acc;
 }
 
-// In-place inverse of each system's SPD [n][n] matrix in M.ainv on the GPU by
-// n sweep steps between M.ainv and a scratch copy (no pivoting: the matrix is
-// SPD), with a check of every pivot.
-qpat_status dense_spd_inverse(qpat_ctx* c, MgState& M, int n, const char* what) {
+// D[0] to -D[0]^{-1} by a block, two pivots a step: a step is one chain of LDS
+// reads, a reciprocal and a barrier however many pivots it takes. d: the
+// thread's four elements of D[0]. False where a pivot is not positive.
+__device__ __forceinline__ bool gj_invert(double (&D)[2][kGj][kGj + 1], double (&d)[4]) {
+    const int r0 = threadIdx.x / 8, c0 = threadIdx.x % 8 * 4;
+    bool ok = true;
+    for (int k = 0; k < kGj; k += 2) {
+        const double (*src)[kGj + 1] = D[(k / 2) & 1];
+        const double pa = src[k][k], pb = src[k][k + 1], pc = src[k + 1][k + 1];
+        const double ca = src[r0][k], cb = src[r0][k + 1];
+        const double det = pa * pc - pb * pb, inv = 1.0 / det;
+        ok = ok && pa > 0.0 && det > 0.0 && std::isfinite(inv);
+        const double ia = pc * inv, ib = -pb * inv, ic = pa * inv;   // the pair's inverse
+        const double wa = ca * ia + cb * ib, wb = ca * ib + cb * ic;
+        const bool pr = (r0 & ~1) == k;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int c = c0 + q;
+            const double ra = src[k][c], rb = src[k + 1][c];
+            if (pr && (c & ~1) == k)
+                d[q] = -(r0 != c ? ib : r0 == k ? ia : ic);
+            else if (pr)
+                d[q] = r0 == k ? ia * ra + ib * rb : ib * ra + ic * rb;
+            else if ((c & ~1) == k)
+                d[q] = c == k ? wa : wb;
+            else
+                d[q] -= wa * ra + wb * rb;
+            D[(k / 2 + 1) & 1][r0][c] = d[q];
+        }
+        __syncthreads();
+    }
+    static_assert(kGj % 4 == 0, "the inverse ends in D[0]");
+    return ok;
+}
+
+// P[sys] = -D^{-1} of the first block of pivots (beyond n: an identity block)
+__global__ __launch_bounds__(kMgT) void k_gj_first(const double* __restrict__ Sall, int n, double* __restrict__ P,
+                                                   int* __restrict__ bad) {
+    __shared__ double D[2][kGj][kGj + 1];
+    const int sys = blockIdx.x, r0 = threadIdx.x / 8, c0 = threadIdx.x % 8 * 4;
+    double d[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int c = c0 + q;
+        d[q] = r0 < n && c < n ? Sall[((int64_t)sys * n + r0) * n + c] : (r0 == c ? 1.0 : 0.0);
+        D[0][r0][c] = d[q];
+    }
+    __syncthreads();
+    if (!gj_invert(D, d) && threadIdx.x == 0) bad[sys] = 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) P[(sys * kGj + r0) * kGj + c0 + q] = d[q];
+}
+
+// step K from S to T with P = -D^{-1} of its pivots; leaves the next step's in Pn
+__global__ __launch_bounds__(kMgT) void k_gj(const double* __restrict__ Sall, double* __restrict__ Tall, int n, int K,
+                                             const double* __restrict__ Pall, double* __restrict__ Pn,
+                                             int* __restrict__ bad) {
+    __shared__ double D[2][kGj][kGj + 1], X[kGj][kGj + 1], Y[kGj][kGj + 1];
+    const int I = blockIdx.y, J = blockIdx.x, sys = blockIdx.z;
     const int64_t nn = (int64_t)n * n;
-    double* tmp = nullptr;
-    int* bad = nullptr;
-    QPAT_TRY(dalloc(c, &tmp, M.nsys * nn));
-    QPAT_TRY(dalloc(c, &bad, M.nsys));
-    QPAT_HIP(c, hipMemsetAsync(bad, 0, M.nsys * sizeof(int), c->stream));
-    const dim3 g((unsigned)((nn + kMgT - 1) / kMgT), (unsigned)M.nsys);
-    double* src = M.ainv;
-    double* dst = tmp;
-    for (int k = 0; k < n; ++k) {
-        hipLaunchKernelGGL(k_sweep, g, dim3(kMgT), 0, c->stream, src, dst, n, k, bad);
+    const double* S = Sall + sys * nn;
+    double* T = Tall + sys * nn;
+    auto at = [&](int r, int c) { return r < n && c < n ? S[(int64_t)r * n + c] : 0.0; };
+    const int r0 = threadIdx.x / 8, c0 = threadIdx.x % 8 * 4;
+    const int wave = threadIdx.x >> 6, qr = wave / 2, qc = wave % 2, lane = threadIdx.x & 63;
+    mg_d4 t;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        D[0][r0][c0 + q] = Pall[(sys * kGj + r0) * kGj + c0 + q];
+        X[r0][c0 + q] = at(I * kGj + r0, K * kGj + c0 + q);
+        Y[r0][c0 + q] = at(K * kGj + r0, J * kGj + c0 + q);
+        t[q] = at(I * kGj + 16 * qr + lane / 16 + 4 * q, J * kGj + 16 * qc + lane % 16);
+    }
+    __syncthreads();
+    mg_d4 out;
+    if (I == K && J == K) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) out[q] = D[0][16 * qr + lane / 16 + 4 * q][16 * qc + lane % 16];
+    } else if (I == K) {   // D^{-1} S_KJ
+        out = -gj_product(D[0], Y, qr, qc, mg_d4{0.0, 0.0, 0.0, 0.0});
+    } else {
+        const mg_d4 w = gj_product(X, D[0], qr, qc, mg_d4{0.0, 0.0, 0.0, 0.0});   // -S_IK D^{-1}
+        if (J == K) {
+            out = -w;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) D[1][16 * qr + lane / 16 + 4 * q][16 * qc + lane % 16] = w[q];
+            __syncthreads();   // uniform over the block
+            out = gj_product(D[1], Y, qr, qc, t);
+        }
+    }
+    const bool next = I == K + 1 && J == K + 1;
+    if (next) __syncthreads();   // D is read no more
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int lr = 16 * qr + lane / 16 + 4 * q, lc = 16 * qc + lane % 16, r = I * kGj + lr, c = J * kGj + lc;
+        if (r < n && c < n) T[(int64_t)r * n + c] = out[q];
+        if (next) D[0][lr][lc] = r < n && c < n ? out[q] : (lr == lc ? 1.0 : 0.0);
+    }
+    if (!next) return;
+    __syncthreads();
+    double d[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) d[q] = D[0][r0][c0 + q];
+    if (!gj_invert(D, d) && threadIdx.x == 0) bad[sys] = 1;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) Pn[(sys * kGj + r0) * kGj + c0 + q] = d[q];
+}
+
+// out = -(T + T^T) / 2: the preconditioner must be exactly symmetric
+__global__ __launch_bounds__(kMgT) void k_gj_out(const double* __restrict__ T, double* __restrict__ out, int n) {
+    const int64_t nn = (int64_t)n * n, e = blockIdx.x * (int64_t)kMgT + threadIdx.x;
+    if (e >= nn) return;
+    const double* t = T + blockIdx.y * nn;
+    out[blockIdx.y * nn + e] = -0.5 * (t[e] + t[(e % n) * n + e / n]);
+}
+
+// the coarsest level's 27-point rows as a dense matrix
+__global__ __launch_bounds__(kMgT) void k_dense_fill(LvArgs L, double* __restrict__ A) {
+    const int64_t n = L.N, e = blockIdx.x * (int64_t)kMgT + threadIdx.x;
+    if (e >= n * n) return;
+    const int sys = blockIdx.y;
+    const double* U = L.U + (int64_t)sys * n * 14;
+    const int i = static_cast<int>(e / n), j = static_cast<int>(e % n);
+    int ix, iy, iz, jx, jy, jz;
+    coords(i, L.nx, L.ny, ix, iy, iz);
+    coords(j, L.nx, L.ny, jx, jy, jz);
+    const int dx = jx - ix, dy = jy - iy, dz = jz - iz;
+    double v = 0.0;
+    if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1) {
+        const int code = dx + 3 * dy + 9 * dz;   // > 0: an upper entry of row i, < 0: of row j
+        v = code >= 0 ? U[(int64_t)i * 14 + code] : U[(int64_t)j * 14 - code];
+    }
+    A[sys * n * n + e] = v;
+}
+
+// The Jacobi weights from the Gershgorin bounds g: on the finest level, on the
+// coarse ones. bad[nsys] = 1 where a bound is not positive and finite.
+__global__ void k_mg_weights(const uint64_t* __restrict__ gmax, int nsys, int nl, double fine, double coarse,
+                             double* __restrict__ w, int* __restrict__ bad) {
+    const int i = threadIdx.x;
+    if (i >= nsys * nl) return;
+    const double g = __longlong_as_double(static_cast<long long>(gmax[i]));
+    if (!(g > 0.0) || !std::isfinite(g)) bad[nsys] = 1;
+    w[i] = (i % nl == 0 ? fine : coarse) / g;
+}
+
+__global__ void k_zero_words(uint32_t* p, int n) {
+    if (threadIdx.x < (unsigned)n) p[threadIdx.x] = 0;
+}
+
+// M.ainv = the inverses of the coarsest level's systems (asynchronous; M.bad tells)
+void dense_spd_inverse(const MgState& M, hipStream_t st) {
+    const MgLevel& K = M.lv.back();
+    const int n = static_cast<int>(K.N), steps = (n + kGj - 1) / kGj;
+    const dim3 ge((unsigned)(((int64_t)n * n + kMgT - 1) / kMgT), (unsigned)M.nsys);
+    // the steps alternate between M.ainv and M.ainv_t and end in the latter
+    double* src = steps % 2 ? M.ainv : M.ainv_t;
+    double* dst = steps % 2 ? M.ainv_t : M.ainv;
+    hipLaunchKernelGGL(k_dense_fill, ge, dim3(kMgT), 0, st, lv_args(K), src);
+    double* P[2] = {M.apiv, M.apiv + M.nsys * kGj * kGj};
+    hipLaunchKernelGGL(k_gj_first, dim3(M.nsys), dim3(kMgT), 0, st, src, n, P[0], M.bad);
+    for (int k = 0; k < steps; ++k) {
+        hipLaunchKernelGGL(k_gj, dim3(steps, steps, M.nsys), dim3(kMgT), 0, st, src, dst, n, k, P[k & 1], P[~k & 1], M.bad);
         std::swap(src, dst);
     }
-    QPAT_HIP(c, hipGetLastError());
-    if (src != M.ainv)
-        QPAT_HIP(c, hipMemcpyAsync(M.ainv, src, M.nsys * nn * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-    std::vector<int> bad_h(M.nsys, 0);
-    QPAT_HIP(c, hipMemcpyAsync(bad_h.data(), bad, M.nsys * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    QPAT_HIP(c, hipStreamSynchronize(c->stream));
-    QPAT_TRY(dfree(c, tmp));
-    QPAT_TRY(dfree(c, bad));
-    for (int sys = 0; sys < M.nsys; ++sys)
-        if (bad_h[sys]) return fail(c, QPAT_ERR_ARG, "multigrid: coarsest %s is not positive definite", what);
-    return QPAT_OK;
+    hipLaunchKernelGGL(k_gj_out, ge, dim3(kMgT), 0, st, src, M.ainv, n);
 }
 
 // Hierarchy for the current operator (after its assembly and stencil form).
@@ -4376,6 +4523,9 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
         QPAT_TRY(dalloc(c, &M.w, nsys * nl));
         QPAT_TRY(dalloc(c, &M.gmax, nsys * nl));
         QPAT_TRY(dalloc(c, &M.ainv, nsys * Nc * Nc));
+        QPAT_TRY(dalloc(c, &M.ainv_t, nsys * Nc * Nc));
+        QPAT_TRY(dalloc(c, &M.apiv, 2 * nsys * kGj * kGj));
+        QPAT_TRY(dalloc(c, &M.bad, nsys + 1));
         QPAT_TRY(dalloc(c, &M.pr, V * c->N));
         QPAT_TRY(dalloc(c, &M.pr2, V * c->N));
         QPAT_TRY(dalloc(c, &M.pa, V * c->N));
@@ -4419,7 +4569,7 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
             // below uses the same rounded values, so A_c = P^T A P holds for the P applied
             hipLaunchKernelGGL(k_mg_wpack, g, dim3(kMgT), 0, c->stream, lv_args(F), F.W, F.Wc);
         }
-        hipLaunchKernelGGL(k_mg_rap, dim3((unsigned)((C.N + kMgT - 1) / kMgT), nsys), dim3(kMgT), 0, c->stream,
+        hipLaunchKernelGGL(k_mg_rap, dim3((unsigned)((C.N + kRapNodes - 1) / kRapNodes), nsys), dim3(kMgT), 0, c->stream,
                            lv_args(F), M.opdep ? F.W : nullptr, C.U, C.nx, C.ny, C.nz);
     }
     for (int l = 1; l < nl; ++l)
@@ -4436,57 +4586,25 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
                 hipLaunchKernelGGL(k_to_f32, dim3(grid_for(nsys * M.lv[l].N * 27, kMgT, 4096)), dim3(kMgT), 0,
                                    c->stream, M.lv[l].Uf, M.lv[l].Uf32, nsys * M.lv[l].N * 27);
         }
-    QPAT_HIP(c, hipMemsetAsync(M.gmax, 0, nsys * nl * sizeof(uint64_t), c->stream));
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(kMgT), 0, c->stream, reinterpret_cast<uint32_t*>(M.gmax),
+                       2 * nsys * nl);
+    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(kMgT), 0, c->stream, reinterpret_cast<uint32_t*>(M.bad), nsys + 1);
     for (int l = 0; l < nl; ++l)
         hipLaunchKernelGGL(k_mg_diag, dim3(grid_for(M.lv[l].N, kMgT, kMgBlocks), nsys), dim3(kMgT), 0, c->stream,
                            lv_args(M.lv[l]), M.lv[l].dinv, M.gmax, nl, l);
+    // finest level, coarse levels; M_delta's (strongly varying diffusivity)
+    // take larger weights, still below 2 / g so that the cycle stays SPD
+    hipLaunchKernelGGL(k_mg_weights, dim3(1), dim3(kMgT), 0, c->stream, M.gmax, nsys, nl,
+                       op == Op::Prior ? 7.0 / 4.0 : 8.0 / 5.0, op == Op::Prior ? 39.0 / 20.0 : 19.0 / 10.0, M.w, M.bad);
+    dense_spd_inverse(M, c->stream);
     QPAT_HIP(c, hipGetLastError());
-    std::vector<uint64_t> gm(nsys * nl);
-    QPAT_HIP(c, hipMemcpyAsync(gm.data(), M.gmax, gm.size() * sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream));
-    // coarsest operator to the host for its dense inverse
-    const MgLevel& K = M.lv[nl - 1];
-    std::vector<double> Uk(nsys * K.N * (K.m + 1));
-    QPAT_HIP(c, hipMemcpyAsync(Uk.data(), K.U, Uk.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    int32_t tabk[4 * 13];
-    QPAT_HIP(c, hipMemcpyAsync(tabk, K.tab, sizeof(int32_t) * 4 * K.m, hipMemcpyDeviceToHost, c->stream));
+    int bad_h[3] = {0, 0, 0};
+    QPAT_HIP(c, hipMemcpyAsync(bad_h, M.bad, (nsys + 1) * sizeof(int), hipMemcpyDeviceToHost, c->stream));
     QPAT_HIP(c, hipStreamSynchronize(c->stream));
     const char* what = op == Op::K ? "K" : "M_delta";
-    std::vector<double> w(nsys * nl);
-    for (int i = 0; i < nsys * nl; ++i) {
-        double g;
-        std::memcpy(&g, &gm[i], sizeof g);
-        if (!(g > 0.0) || !std::isfinite(g)) return fail(c, QPAT_ERR_ARG, "multigrid: non-positive diagonal in %s", what);
-        // finest level, coarse levels; M_delta's (strongly varying diffusivity)
-        // take larger weights, still below 2 / g so that the cycle stays SPD
-        if (op == Op::Prior)
-            w[i] = (i % nl == 0 ? 7.0 / 4.0 : 39.0 / 20.0) / g;
-        else
-            w[i] = (i % nl == 0 ? 8.0 / 5.0 : 19.0 / 10.0) / g;
-    }
-    QPAT_HIP(c, hipMemcpyAsync(M.w, w.data(), w.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    const int n = static_cast<int>(K.N), M1 = K.m + 1;
-    const bool on_gpu = n > kMgHostDense;
-    std::vector<double> inv(nsys * (size_t)n * n);
-    for (int sys = 0; sys < nsys; ++sys) {
-        std::vector<double> A((size_t)n * n, 0.0);
-        const double* U = Uk.data() + (size_t)sys * n * M1;
-        for (int i = 0; i < n; ++i) {
-            const int ix = i % K.nx, iy = (i / K.nx) % K.ny, iz = i / (K.nx * K.ny);
-            A[(size_t)i * n + i] = U[(size_t)i * M1];
-            for (int j = 0; j < K.m; ++j) {
-                const int jx = ix + tabk[4 * j], jy = iy + tabk[4 * j + 1], jz = iz + tabk[4 * j + 2];
-                if (jx < 0 || jx >= K.nx || jy < 0 || jy >= K.ny || jz < 0 || jz >= K.nz) continue;
-                const int k = jx + K.nx * (jy + K.ny * jz);
-                A[(size_t)i * n + k] = A[(size_t)k * n + i] = U[(size_t)i * M1 + j + 1];
-            }
-        }
-        if (!on_gpu && !spd_inverse(A, n))
-            return fail(c, QPAT_ERR_ARG, "multigrid: coarsest %s is not positive definite", what);
-        std::copy(A.begin(), A.end(), inv.begin() + (size_t)sys * n * n);
-    }
-    QPAT_HIP(c, hipMemcpyAsync(M.ainv, inv.data(), inv.size() * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    if (on_gpu) QPAT_TRY(dense_spd_inverse(c, M, n, what));
-    QPAT_HIP(c, hipStreamSynchronize(c->stream));
+    if (bad_h[nsys]) return fail(c, QPAT_ERR_ARG, "multigrid: non-positive diagonal in %s", what);
+    for (int sys = 0; sys < nsys; ++sys)
+        if (bad_h[sys]) return fail(c, QPAT_ERR_ARG, "multigrid: coarsest %s is not positive definite", what);
     if (op == Op::Prior) QPAT_TRY(region_setup(c, M));
     if (M.lv[0].Uf && op == Op::Prior) M.lv[0].kind = 3;
     if (M.lv[0].Uf32 && op == Op::Prior) M.lv[0].vkind = 5;   // the V-cycle's sweeps and residuals on FP32 rows

@@ -274,3 +274,30 @@ def test_prior_multigrid_on_phantom_regions(which):
     assert_close(outs[0], outs[1], 1e-7, "M_delta^-1 multigrid vs Jacobi on a phantom")
     assert infos[0]["iters_max"] <= 40, infos
     assert infos[0]["iters_max"] * 10 < infos[1]["iters_max"], infos
+
+
+@pytest.mark.parametrize("nx,ny,nz,order", [(5, 3, 1, 24), (6, 6, 1, 32), (7, 3, 3, 45), (6, 6, 6, 64), (9, 7, 5, 120),
+                                            (16, 16, 16, 729), (17, 17, 17, 1000)])
+def test_coarse_set_up(nx, ny, nz, order):
+    """The coarsest level's blocked inverse (orders below, at and past its 32-pivot blocks) and the Galerkin
+    product: K and M_delta solved in few iterations, K against the oracle. A wrong coarse operator or inverse
+    leaves PCG right but slow, so the iteration count is part of the check: 14 - 16 at 16^3 - 128^3, 20 allowed;
+    M_delta (constant diffusivity) at most as many as at 16^3 plus a few, 30 allowed."""
+    def coarse(n):
+        return n // 2 + 1 if n > 2 else n
+    assert coarse(nx + 1) * coarse(ny + 1) * coarse(nz + 1) == order
+    coords, tets, bfaces, kappa, mu, src = box_problem(nx, ny, nz, 2, 7 * order)
+    ctx, phi, info = solve(coords, tets, bfaces, kappa, mu, src, pcg_rtol=1e-12, prior_rtol=1e-10)
+    g = fem.geometry(coords, tets, bfaces)
+    lin = Linearisation(g, kappa, mu, src)
+    assert_close(phi, lin.phi, 1e-10, f"phi {nx}x{ny}x{nz}")
+    assert info["iters_max"] <= 20, info
+    N = coords.shape[0]
+    z = torch.zeros(N, dtype=torch.float64, device="cuda")
+    ctx.prior_setup(z, z)
+    p = dev(np.random.default_rng(order).standard_normal(2 * N))
+    r, y = torch.empty_like(p), torch.empty_like(p)
+    info = ctx.prior_solve(p, r)
+    assert info["iters_max"] <= 30, info
+    ctx.prior_apply(r, y)
+    assert rel(host(y), host(p)) <= 1e-9
