@@ -80,7 +80,7 @@ struct TileGeo {
     Rst rst[kMgMaxLevels];
     // the fused prolongation + last sweep (16 right-hand sides; even z-chunks)
     bool ps_on = false;
-    int32_t ps_zc = 0, ps_items = 0, ps_blocks = 0;
+    int32_t ps_tx = 0, ps_ty = 0, ps_zc = 0, ps_items = 0, ps_blocks = 0;
     int32_t ps_zc32 = 0, ps_items32 = 0, ps_blocks32 = 0;   // its FP32-staged form
     // the cost model's z-chunk lengths (tiles, prolongation + sweep FP64, FP32) and whether
     // the ones in use were picked by timing them (autotune)
@@ -445,6 +445,12 @@ struct CompSum {
         const double err = (s - (t - bp)) + (-p - bp);   // s - p = t + err exactly
         s = t;
         c += err - e;
+    }
+    __device__ __forceinline__ void add(double b) {
+        const double t = s + b;
+        const double bp = t - s;
+        c += (s - (t - bp)) + (b - bp);   // s + b = t + that exactly
+        s = t;
     }
     __device__ __forceinline__ double value() const { return s + c; }
 };
@@ -1862,27 +1868,66 @@ __global__ __launch_bounds__(kMgT) void k_mgp_ring_flush(int64_t n, int B, doubl
     }
 }
 
+// pairs of adjacent right-hand sides through buffer descriptors
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2v __attribute__((ext_vector_type(2)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ d2v bload2(__amdgpu_buffer_rsrc_t b, uint32_t off) {
+    return __builtin_bit_cast(d2v, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
+}
+// (from FP32 as it is: converted where it is used, so that the load can stay in flight)
+__device__ __forceinline__ f2v bload2f(__amdgpu_buffer_rsrc_t b, uint32_t off) {
+    return __builtin_bit_cast(f2v, __builtin_amdgcn_raw_buffer_load_b64(b, off, 0, 0));
+}
+__device__ __forceinline__ d2v as_d2(f2v v) { return d2v{static_cast<double>(v.x), static_cast<double>(v.y)}; }
+__device__ __forceinline__ d2v as_d2(d2v v) { return v; }
+__device__ __forceinline__ void bstore2_nt(__amdgpu_buffer_rsrc_t b, uint32_t off, d2v v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), b, off, 0, 2);
+}
+template <bool NT>
+__device__ __forceinline__ void bstore2f(__amdgpu_buffer_rsrc_t b, uint32_t off, d2v v) {   // to FP32
+    __builtin_amdgcn_raw_buffer_store_b64(
+        __builtin_bit_cast(u32x2v, f2v{static_cast<float>(v.x), static_cast<float>(v.y)}), b, off, 0, NT ? 2 : 0);
+}
+
 // ------------------------------------------------ LDS-tiled finest-level kernels
 // On the finest level of a Kuhn lattice with B >= 8 right-hand sides (the
 // K solves) the stencil products run 2.5D-tiled: a work item is a tile of
-// (kTHX - 2) x (kTHY - 2) lattice columns over a chunk of planes, and the
-// block sweeps the chunk plane by plane with the input vector of three planes
-// (plus a one-node halo) and the stored operator rows of the same planes in
-// LDS. Every input value then comes from global memory kTHX kTHY /
-// ((kTHX - 2)(kTHY - 2)) times per product (the halo) instead of once per row
-// that uses it, and the gathers are LDS reads with immediate offsets. The
-// work items of one XCD are contiguous bands of tiles. Byte offsets are
-// 32-bit buffer offsets: loads outside the lattice return 0, stores there are
-// dropped.
-constexpr int kTT = 512;                 // threads of the tiled kernels
-constexpr int kTHX = 12, kTHY = 10;      // halo'd tile
-constexpr int kTHN = kTHX * kTHY;
+// kTX x kTY lattice columns over a chunk of planes, and the block sweeps the
+// chunk plane by plane, staging each plane of the input vector (with a one-node
+// halo) and of the stored operator rows in LDS. Every input value then comes
+// from global memory kTHalo / (kTX kTY) times per product (the halo) instead of
+// once per row that uses it, and the gathers are LDS reads with immediate
+// offsets. The work items of one XCD are contiguous bands of tiles. Byte
+// offsets are 32-bit buffer offsets: loads outside the lattice return 0, stores
+// there are dropped.
+//
+// LDS reads are what a plane costs most, so a thread owns two right-hand sides
+// of one node (an operator entry is read once for both), and what it read of
+// plane z + 1 for node z's upper neighbours stays in its registers for plane
+// z + 1 itself and, at the lower neighbours, for plane z + 2: 7 vector values
+// and 15 operator entries a node, plane and pair, where one thread a right-hand
+// side read 30 (45 with w / a_jj) each. With the plane below in registers, three
+// LDS slots need one barrier a plane.
+constexpr int kTX = 8, kTY = 8;          // the tile: a thread for every node and pair of right-hand sides
+constexpr int kTW = kTX + 2, kTHalo = (kTX + 2) * (kTY + 2);
 template <int B>
 struct MgTile {
-    static constexpr int NPF = (kTHN * B + kTT - 1) / kTT;   // input elements per thread and plane
-    static constexpr int NU = (kTHN * 8 + kTT - 1) / kTT;     // operator values per thread and plane
-    static constexpr size_t LDS = (size_t)3 * (NPF + NU) * kTT * sizeof(double) + 3 * kTHN * sizeof(double);
+    static constexpr int P = B / 2;                          // pairs per node
+    static constexpr int T = kTX * kTY * P;                  // threads
+    static constexpr int NS = (kTHalo * P + T - 1) / T;       // staged pairs per thread and plane
+    static constexpr int NU = (kTHalo * 4 + T - 1) / T;       // 16-byte loads of operator rows per thread and plane
+    static constexpr int RS = kTHalo * B, US = kTHalo * 8;    // doubles of a slot
+    static constexpr int OS = kTX * kTY * B;                  // the tile's own nodes
+    static constexpr size_t LDS = (size_t)(3 * (RS + US) + 2 * OS) * sizeof(double);
+    static constexpr int W = B == 16 ? 4 : 3;                // waves per SIMD that the LDS admits (2, 3 blocks a CU)
 };
+// the 16-right-hand-side kernels that stage one right-hand side per thread
+// (fused prolongation + last sweep, 27-point levels)
+constexpr int kTT = 512;                 // their threads, and the restriction's
+constexpr int kTHX = 12, kTHY = 10;      // their halo'd tile
+constexpr int kTHN = kTHX * kTHY;
+constexpr int kNpf16 = (kTHN * 16 + kTT - 1) / kTT;   // input elements per thread and plane
 enum TileMode { kTDirSpmv = 0, kTResidFirst = 1, kTSmoothDots = 2, kTTrue = 3, kTResid = 4, kTApply = 5, kTUpdResid = 6 };
 
 struct TileArgs {
@@ -1900,8 +1945,6 @@ struct TileArgs {
     double* out2;         // kTDirSpmv: the new direction
     double* parts;        // partial sums, [lanes][4][kMgBlocks]
     const MgScal* sc;     // [B]
-    double* x3;           // kTUpdResid: the iterate (updated in place; null: x is formed from the ring)
-    const double* p3;     // kTUpdResid: the direction
     // kTDirSpmv with ring_n > 0: the old and new directions are the ring slots
     // of iterations slot - 1 and slot (ring_stride bytes apart)
     const int32_t* slot;
@@ -1921,21 +1964,20 @@ struct TileArgs {
 // kTApply: out = scale A in for every right-hand side (any Kuhn stencil
 //   form U, e.g. the derivative of K in the Jacobian product).
 // kTUpdResid: the PCG update fused with kTResidFirst: r' = in - alpha in2
-//   (in = r, in2 = q = A p) staged, to out2, x3 += alpha p3, partial r'.r',
+//   (in = r, in2 = q = A p) staged, to out2, partial r'.r',
 //   and out = r' - A x with the first sweep x = w D^{-1} r' (w / a_jj from
 //   LDS per neighbour). r' goes to another buffer than r: neighbouring tiles
 //   still read r's halo.
 // Z32 (kTDirSpmv only): `in` (z, the V-cycle's output) is FP32 [N][B].
-// P32 (kTDirSpmv, kTUpdResid): the PCG direction p is stored in FP32. The
-// direction kernel rounds p before staging it, so q = A p is the FP64 product of
-// exactly the stored p, and the update adds alpha times that same p to the FP64
-// iterate: x and r stay consistent (r = b - A x up to FP64 rounding), and the
-// rounding only perturbs the choice of the next direction.
+// P32 (kTDirSpmv): the PCG direction p is stored in FP32. The direction kernel
+// rounds p before staging it, so q = A p is the FP64 product of exactly the
+// stored p, and x later takes alpha times that same p: x and r stay consistent
+// (r = b - A x up to FP64 rounding), and the rounding only perturbs the choice
+// of the next direction.
 template <int MODE, int B, bool Z32 = false, bool P32 = false>
-__global__ __launch_bounds__(kTT, 4) void k_mg_tile(TileArgs g) {
+__global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs g) {
     using TL = MgTile<B>;
-    constexpr int NPF = TL::NPF, NU = TL::NU, RS = NPF * kTT, US = NU * kTT;
-    constexpr int TX = kTHX - 2, TY = kTHY - 2, M1 = 8;
+    constexpr int P = TL::P, T = TL::T, NS = TL::NS, NU = TL::NU, RS = TL::RS, US = TL::US;
     constexpr uint32_t SZ = sizeof(double);
     constexpr bool UPD = MODE == kTUpdResid;
     // the finest level's residual for the restriction is stored in FP32 (it only
@@ -1943,38 +1985,42 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile(TileArgs g) {
     constexpr bool RES32 = MODE == kTResidFirst || MODE == kTResid || UPD;
     constexpr bool HAS_B = MODE != kTDirSpmv && MODE != kTApply && !UPD;
     constexpr bool CENTER_D = MODE == kTSmoothDots;
-    // the right-hand side's loads go out a plane ahead where the registers allow
-    constexpr bool PRE_B = HAS_B && !CENTER_D;
     extern __shared__ __align__(16) unsigned char mg_smem[];
-    __shared__ double sm[(kTT / 64) * 16];
-    double* ring = reinterpret_cast<double*>(mg_smem);   // [3][RS]: [halo node][B]
-    double* ust = ring + 3 * RS;                          // [3][US]: [halo node][8]
-    double* dring = ust + 3 * US;                         // UPD: [3][kTHN] w / a_ii of the halo nodes
-    const int tid = threadIdx.x, k = tid % B;
+    __shared__ double sm[(T / 64) * B];
+    double* ring = reinterpret_cast<double*>(mg_smem);   // [3][halo node][B]
+    double* ust = ring + 3 * RS;                          // [3][halo node][8]
+    double* own = ust + 3 * US;                           // UPD: [2][own node][B] r' of the tile's nodes
+    const int tid = threadIdx.x, kp = tid % P;
     constexpr bool ALL = MODE == kTTrue || MODE == kTApply;   // every right-hand side, no PCG scalars
     if constexpr (!ALL) {   // every right-hand side stopped: nothing to do
         bool any = false;
         for (int j = 0; j < B; ++j) any = any || g.sc[j].active != 0;
         if (!any) return;
     }
-    bool act = true;
-    double cc_ = 0.0, beta = 0.0, alpha = 0.0;
-    if constexpr (!ALL) {
-        const MgScal scl = g.sc[k];
-        act = scl.active != 0;
-        if constexpr (MODE == kTDirSpmv) {
-            cc_ = scl.c;
-            beta = scl.beta;
+    // A right-hand side that stopped is carried along with p = q = 0, which leaves
+    // its r as it is (the other vectors of it that are written are not read again)
+    // Its scalars wait in LDS for the one use a plane: registers are what is short.
+    __shared__ double lane_c[2][B];   // kTDirSpmv: c, beta; UPD: alpha
+    bool on0 = true, on1 = true;
+    if constexpr (MODE == kTDirSpmv || UPD) {
+        on0 = g.sc[2 * kp].active != 0;
+        on1 = g.sc[2 * kp + 1].active != 0;
+        if (tid < B) {
+            const MgScal& l = g.sc[tid];
+            lane_c[0][tid] = UPD ? (l.active ? l.alpha : 0.0) : l.c;
+            lane_c[1][tid] = l.beta;
         }
-        if constexpr (UPD) alpha = scl.alpha;
     }
     const int32_t nx = g.nx, ny = g.ny, nz = g.nz;
     const uint32_t nxy = static_cast<uint32_t>(nx) * ny;
-    const uint32_t pv = nxy * B * SZ, pu = nxy * M1 * SZ, pd = nxy * SZ, pin = nxy * g.ld * SZ;
+    const uint32_t pv = nxy * B * SZ, pu = nxy * 8 * SZ, pd = nxy * SZ, pin = nxy * g.ld * SZ;
     const double w = (MODE == kTSmoothDots || MODE == kTResidFirst || UPD) ? *g.w : 0.0;
+    // descriptors stay uniform over the wavefront (a per-lane size would turn
+    // every access into a loop over the distinct values)
+    // (the plane clamped and no branch: a step stays one basic block, so its
+    // sections keep their order)
     auto plane = [&](const auto* base, int pl, uint32_t stride, uint32_t bytes) {
-        const bool in = pl >= 0 && pl < nz;
-        return rsrc(base + (in ? (int64_t)pl * stride : 0), in ? bytes : 0u);
+        return rsrc(base + (int64_t)min(max(pl, 0), nz - 1) * stride, pl >= 0 && pl < nz ? bytes : 0u);
     };
     if constexpr (MODE == kTDirSpmv) {
         if (g.ring_n > 0) {   // this iteration's slot and the one before (uniform)
@@ -1984,16 +2030,18 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile(TileArgs g) {
         }
     }
     static_assert(!Z32 || MODE == kTDirSpmv, "FP32 input only for the direction + product");
-    static_assert(!P32 || MODE == kTDirSpmv || MODE == kTUpdResid, "FP32 direction: direction and update only");
-    // LDS node of output slot u (slots past the tile point at an interior node)
-    int32_t oc[NPF];
-#pragma unroll
-    for (int u = 0; u < NPF; ++u) {
-        const int nl = (tid + u * kTT) / B;
-        oc[u] = nl < TX * TY ? (nl / TX + 1) * kTHX + nl % TX + 1 : kTHX + 1;
-    }
-    double fr[NPF], f2[NPF], fu[NU], dd = 0.0;
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+    static_assert(!P32 || MODE == kTDirSpmv, "FP32 direction: the direction + product only");
+    const int hc = (tid / P / kTX + 1) * kTW + tid / P % kTX + 1;   // halo node of the thread's own node
+    // LDS, from the thread's node and pair: vector values, operator row
+    const double* rb = ring + hc * B + 2 * kp;
+    const double* ub = ust + hc * 8;
+    auto val_at = [&](int sl, int d) { return *reinterpret_cast<const d2v*>(rb + sl * RS + d * B); };
+    auto off_of = [](int q) constexpr { return (q >> 1) * kTW + (q & 1); };   // in-plane offset of mask q (x 1, y 2)
+    std::conditional_t<Z32, f2v, d2v> fr[NS];
+    std::conditional_t<P32, f2v, d2v> f2[NS];
+    d2v fu[NU];
+    double f2d[NS];   // kTResidFirst, UPD: 1 / a_ii of the staged nodes
+    d2v a0 = 0.0, a1 = 0.0, a2 = 0.0;
 
     const int32_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per = gridDim.x >> 3;
     const int32_t wx = (g.items + 7) / 8;
@@ -2001,241 +2049,258 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile(TileArgs g) {
     const int32_t tiles = g.tiles_x * g.tiles_y;
     for (int32_t item = xcd * wx + slot; item < it_end; item += per) {
         const int32_t ch = item / tiles, t2 = item % tiles;
-        const int32_t x0 = (t2 % g.tiles_x) * TX, y0 = (t2 / g.tiles_x) * TY;
+        const int32_t x0 = (t2 % g.tiles_x) * kTX, y0 = (t2 / g.tiles_x) * kTY;
         const int32_t zb = ch * g.zc, ze = min(zb + g.zc, nz);
-        uint32_t fo[NPF], oo[NPF], od[NPF], uo[NU];
+        // node of halo node h, or -1 outside the lattice
+        auto node_of = [&](int h) {
+            const int gx = x0 - 1 + h % kTW, gy = y0 - 1 + h / kTW;
+            return h < kTHalo && gx >= 0 && gx < nx && gy >= 0 && gy < ny ? gy * nx + gx : -1;
+        };
+        uint32_t fo[NS], uo[NU], oo;
 #pragma unroll
-        for (int u = 0; u < NPF; ++u) {
-            const int nl = (tid + u * kTT) / B;
-            const int gx = x0 - 1 + nl % kTHX, gy = y0 - 1 + nl / kTHX;
-            const bool fin = nl < kTHN && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-            fo[u] = fin ? (static_cast<uint32_t>(gy * nx + gx) * g.ld + g.col + k) * SZ : kOut;
-            const int ox = x0 + nl % TX, oy = y0 + nl / TX;
-            const bool oin = nl < TX * TY && ox < nx && oy < ny;
-            oo[u] = oin ? (static_cast<uint32_t>(oy * nx + ox) * B + k) * SZ : kOut;
-            od[u] = oin ? static_cast<uint32_t>(oy * nx + ox) * SZ : kOut;
-        }
-        uint32_t dof = kOut;   // UPD: thread tid < kTHN loads 1 / a_ii of halo node tid
-        if (UPD && tid < kTHN) {
-            const int gx = x0 - 1 + tid % kTHX, gy = y0 - 1 + tid / kTHX;
-            if (gx >= 0 && gx < nx && gy >= 0 && gy < ny) dof = static_cast<uint32_t>(gy * nx + gx) * SZ;
+        for (int u = 0; u < NS; ++u) {
+            const int n = node_of((tid + u * T) / P);
+            fo[u] = n >= 0 ? (static_cast<uint32_t>(n) * g.ld + g.col + 2 * kp) * SZ : kOut;
         }
 #pragma unroll
         for (int v = 0; v < NU; ++v) {
-            const int e = tid + v * kTT, nl = e / M1;
-            const int gx = x0 - 1 + nl % kTHX, gy = y0 - 1 + nl / kTHX;
-            uo[v] = (nl < kTHN && gx >= 0 && gx < nx && gy >= 0 && gy < ny)
-                        ? (static_cast<uint32_t>(gy * nx + gx) * M1 + e % M1) * SZ
-                        : kOut;
+            const int e = tid + v * T, n = node_of(e / 4);
+            uo[v] = n >= 0 ? (static_cast<uint32_t>(n) * 8 + 2 * (e % 4)) * SZ : kOut;
         }
+        {
+            const int n = node_of(hc);
+            oo = n >= 0 ? (static_cast<uint32_t>(n) * B + 2 * kp) * SZ : kOut;
+        }
+        const bool in = oo != kOut;
+        // the pair's offset in an FP32 array, its node's in an [N] array (ld = B): kOut
+        // stays past the end of both (kOut / 2 and kOut / B bytes are as many as a
+        // plane of 2^31 bytes of pairs can have there)
+        auto half = [](uint32_t o) { return o / 2; };
+        auto node8 = [](uint32_t o) { return o / (B * 8) * 8; };
         auto fetch = [&](int pl) {
-            const auto bu = plane(g.U, pl, nxy * M1, pu);
             if constexpr (Z32) {
                 const auto bi = plane(reinterpret_cast<const float*>(g.in), pl, nxy * g.ld, pin / 2);
 #pragma unroll
-                for (int u = 0; u < NPF; ++u)
-                    fr[u] = static_cast<double>(bload<float>(bi, fo[u] == kOut ? kOut : fo[u] / 2));
+                for (int u = 0; u < NS; ++u) fr[u] = bload2f(bi, half(fo[u]));
             } else {
                 const auto bi = plane(g.in, pl, nxy * g.ld, pin);
 #pragma unroll
-                for (int u = 0; u < NPF; ++u) fr[u] = bload<double>(bi, fo[u]);
+                for (int u = 0; u < NS; ++u) fr[u] = bload2(bi, fo[u]);
             }
             if constexpr (MODE == kTDirSpmv && P32) {   // the old direction, FP32
                 const auto b2 = plane(reinterpret_cast<const float*>(g.in2), pl, nxy * B, pv / 2);
 #pragma unroll
-                for (int u = 0; u < NPF; ++u)
-                    f2[u] = static_cast<double>(bload<float>(b2, fo[u] == kOut ? kOut : fo[u] / 2));
+                for (int u = 0; u < NS; ++u) f2[u] = bload2f(b2, half(fo[u]));
             } else if constexpr (MODE == kTDirSpmv || UPD) {
                 const auto b2 = plane(g.in2, pl, nxy * B, pv);
 #pragma unroll
-                for (int u = 0; u < NPF; ++u) f2[u] = bload<double>(b2, fo[u]);
+                for (int u = 0; u < NS; ++u) f2[u] = bload2(b2, fo[u]);
             }
-            if constexpr (MODE == kTResidFirst) {
+            if constexpr (MODE == kTResidFirst || UPD) {
                 const auto bd = plane(g.dinv, pl, nxy, pd);
 #pragma unroll
-                for (int u = 0; u < NPF; ++u) f2[u] = bload<double>(bd, fo[u] == kOut ? kOut : (fo[u] / SZ - k) / B * SZ);
+                for (int u = 0; u < NS; ++u) f2d[u] = bload<double>(bd, node8(fo[u]));
             }
-            if constexpr (UPD) {   // one value per halo node, through LDS (dring)
-                const auto bd = plane(g.dinv, pl, nxy, pd);
-                dd = bload<double>(bd, dof);
+            const auto bu = plane(g.U, pl, nxy * 8, pu);
+#pragma unroll
+            for (int v = 0; v < NU; ++v) fu[v] = bload2(bu, uo[v]);
+        };
+        d2v bn = 0.0;   // the right-hand side of the next plane
+        auto loadb = [&](int z) { bn = bload2(plane(g.b, z, nxy * B, pv), oo); };
+        if constexpr (HAS_B) loadb(zb);
+        auto store = [&](int sl, int pl) {
+            d2v lc0 = 0.0, lc1 = 0.0;
+            if constexpr (MODE == kTDirSpmv || UPD) {
+                lc0 = *reinterpret_cast<const d2v*>(&lane_c[0][2 * kp]);
+                lc1 = *reinterpret_cast<const d2v*>(&lane_c[1][2 * kp]);
             }
 #pragma unroll
-            for (int v = 0; v < NU; ++v) fu[v] = bload<double>(bu, uo[v]);
-        };
-        auto loadb = [&](int z, double(&to)[NPF]) {
-            const auto bb = plane(g.b, z, nxy * B, pv);
-#pragma unroll
-            for (int u = 0; u < NPF; ++u) to[u] = bload<double>(bb, oo[u]);
-        };
-        double bn[NPF];   // PRE_B: b of the next plane
-        if constexpr (PRE_B) loadb(zb, bn);
-        auto store = [&](int sl) {
-#pragma unroll
-            for (int u = 0; u < NPF; ++u) {
-                double val = fr[u];
+            for (int u = 0; u < NS; ++u) {
+                const d2v in1 = as_d2(fr[u]), in2 = as_d2(f2[u]);
+                d2v val = in1;
                 // beta = 0 (a run's first direction) never reads the old direction's values
-                if constexpr (MODE == kTDirSpmv)
-                    val = fo[u] != kOut ? (beta != 0.0 ? fr[u] - cc_ + beta * f2[u] : fr[u] - cc_) : 0.0;
-                if constexpr (MODE == kTDirSpmv && P32) val = static_cast<double>(static_cast<float>(val));
-                if constexpr (MODE == kTResidFirst) val = w * f2[u] * fr[u];
-                if constexpr (UPD) val = fr[u] - alpha * f2[u];   // r' itself: the sweep scales it per neighbour
-                ring[sl * RS + tid + u * kTT] = val;
+                if constexpr (MODE == kTDirSpmv) {
+                    const bool st = fo[u] != kOut;
+                    val.x = st && on0 ? (lc1.x != 0.0 ? in1.x - lc0.x + lc1.x * in2.x : in1.x - lc0.x) : 0.0;
+                    val.y = st && on1 ? (lc1.y != 0.0 ? in1.y - lc0.y + lc1.y * in2.y : in1.y - lc0.y) : 0.0;
+                }
+                if constexpr (P32)
+                    val = d2v{static_cast<double>(static_cast<float>(val.x)), static_cast<double>(static_cast<float>(val.y))};
+                if constexpr (MODE == kTResidFirst) val = w * f2d[u] * in1;
+                if constexpr (UPD) {   // w D^{-1} r' for the products, r' of the tile's own nodes beside it
+                    const d2v rn = in1 - lc0 * in2;
+                    const int h = (tid + u * T) / P, hx = h % kTW - 1, hy = h / kTW - 1;
+                    if (hx >= 0 && hx < kTX && hy >= 0 && hy < kTY)
+                        *reinterpret_cast<d2v*>(own + (pl & 1) * TL::OS + (hy * kTX + hx) * B + 2 * kp) = rn;
+                    val = (w * f2d[u]) * rn;
+                }
+                if (tid + u * T < kTHalo * P) *reinterpret_cast<d2v*>(ring + sl * RS + 2 * (tid + u * T)) = val;
             }
 #pragma unroll
-            for (int v = 0; v < NU; ++v) ust[sl * US + tid + v * kTT] = fu[v];
-            // w / a_ii of the same plane, with the plane's other staged values:
-            // slot sl is free only after the barrier that ends the step before
-            if (UPD && tid < kTHN) dring[sl * kTHN + tid] = w * dd;
+            for (int v = 0; v < NU; ++v)
+                if (tid + v * T < kTHalo * 4) *reinterpret_cast<d2v*>(ust + sl * US + 2 * (tid + v * T)) = fu[v];
         };
-        // plane z with slots (z, z+1, z-1) = (SZ0, SP0, SL0)
-        auto step = [&](int z, auto SZ0, auto SP0, auto SL0) {
-            constexpr int sz = decltype(SZ0)::value, sp = decltype(SP0)::value, sl = decltype(SL0)::value;
-            store(sp);
+        // Kept between planes: the current plane's values at the node and its three
+        // upper in-plane neighbours (cur), r' there (rc), and the sum over the four
+        // neighbours in the plane below (part; kTTrue: compensated, part + pcomp)
+        auto own_at = [&](int pl) { return *reinterpret_cast<const d2v*>(own + (pl & 1) * TL::OS + 2 * tid); };
+        d2v cur[4], part = 0.0, pcomp = 0.0, rc = 0.0;
+        // the sum over the lower neighbours of the next plane's node: the values at
+        // this plane's node and its three lower neighbours
+        CompSum b0(0.0), b1(0.0);
+        auto below_start = [&] {
+            part = 0.0;
+            b0 = b1 = CompSum(0.0);
+        };
+        auto below_term = [&](double c, d2v x) {
+            if constexpr (MODE == kTTrue) {
+                b0.sub(c, x.x);
+                b1.sub(c, x.y);
+            } else {
+                part = d2v{fma(c, x.x, part.x), fma(c, x.y, part.y)};
+            }
+        };
+        auto below_end = [&] {
+            part = d2v{b0.s, b1.s};
+            pcomp = d2v{b0.c, b1.c};
+        };
+        // plane z in slot sz, plane z + 1 in slot sp
+        auto step = [&](int z, auto SZ0, auto SP0) {
+            constexpr int sz = decltype(SZ0)::value, sp = decltype(SP0)::value;
+            store(sp, z + 1);
             __syncthreads();
             if (z + 1 < ze) fetch(z + 2);
-            // per-node inputs of plane z: loads in flight during the arithmetic
-            double bc[NPF], dc[NPF];
-            if constexpr (PRE_B) {   // loaded one step earlier
-#pragma unroll
-                for (int u = 0; u < NPF; ++u) bc[u] = bn[u];
-                if (z + 1 < ze) loadb(z + 1, bn);
-            } else if constexpr (HAS_B) {
-                loadb(z, bc);
+            const d2v bc = bn;   // loaded one step earlier
+            if constexpr (HAS_B) {
+                if (z + 1 < ze) loadb(z + 1);
             }
-            if constexpr (CENTER_D) {
-                const auto bd = plane(g.dinv, z, nxy, pd);
-#pragma unroll
-                for (int u = 0; u < NPF; ++u) dc[u] = bload<double>(bd, od[u]);
+            double dc = 0.0;
+            if constexpr (CENTER_D) dc = bload<double>(plane(g.dinv, z, nxy, pd), node8(oo));
+            const d2v xc = cur[0];
+            d2v sum = part;
+            CompSum c0(0.0), c1(0.0);
+            if constexpr (MODE == kTTrue) {
+                c0.s = part.x;
+                c0.c = pcomp.x;
+                c1.s = part.y;
+                c1.c = pcomp.y;
             }
-            constexpr int NO = UPD ? (TX * TY * B + kTT - 1) / kTT : 1;   // output slots in use
-            // descriptors stay uniform over the wavefront (a per-lane size would
-            // turn every access into a loop over the distinct values); the
-            // stores of stopped right-hand sides are skipped by the branch
-            // RES32: float [N][B] planes
-            // kTTrue with out = null: only the partial out.out (every store dropped)
+            auto term = [&](double c, d2v x) {
+                if constexpr (MODE == kTTrue) {
+                    c0.sub(c, x.x);
+                    c1.sub(c, x.y);
+                } else {
+                    sum = d2v{fma(c, x.x, sum.x), fma(c, x.y, sum.y)};
+                }
+            };
+            const auto row = [&](int q) { return *reinterpret_cast<const d2v*>(ub + sz * US + 2 * q); };
+            // The stencil form's entry of offset mask m is m. The sections' operands
+            // are not live together (128 registers).
+            {   // this plane, upper half
+                const d2v u01 = row(0), u23 = row(1);
+                const double um[4] = {u01.x, u01.y, u23.x, u23.y};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) term(um[q], cur[q]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // this plane, lower half, and the next plane's sum over it
+            below_start();
+            below_term(ub[sz * US + 4], xc);
+#pragma unroll
+            for (int q = 1; q < 4; ++q) {
+                const d2v lo = val_at(sz, -off_of(q));
+                term(ub[sz * US - off_of(q) * 8 + q], lo);
+                below_term(ub[sz * US - off_of(q) * 8 + 4 + q], lo);
+            }
+            if constexpr (MODE == kTTrue) below_end();
+            __builtin_amdgcn_sched_barrier(0);
+            const d2v rz = rc;
+            if constexpr (UPD) rc = own_at(z + 1);   // read in the step that staged it: two slots do
+            {   // the plane above
+                const d2v u45 = row(2), u67 = row(3);
+                const double um[4] = {u45.x, u45.y, u67.x, u67.y};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    cur[q] = val_at(sp, off_of(q));
+                    term(um[q], cur[q]);
+                }
+            }
+            d2v rtrue = 0.0;
+            if constexpr (MODE == kTTrue) {
+                c0.add(bc.x);
+                c1.add(bc.y);
+                rtrue = d2v{c0.value(), c1.value()};
+            }
+            // RES32: float [N][B] planes; kTTrue with out = null: only the partial out.out
             const auto bo = RES32 ? rsrc(reinterpret_cast<const float*>(g.out) + (int64_t)z * nxy * B, pv / 2)
                                   : plane(g.out, z, nxy * B, g.out ? pv : 0u);
-            if (act) {
-                const auto bo2 = (MODE == kTDirSpmv && P32)
-                                     ? plane(reinterpret_cast<const float*>(g.out2), z, nxy * B, pv / 2)
-                                     : plane(g.out2, z, nxy * B, MODE == kTDirSpmv || UPD ? pv : 0u);
-#pragma unroll
-                for (int u = 0; u < NPF; ++u) {
-                    if (tid + u * kTT >= TX * TY * B) continue;   // whole waves past the tile skip
-                    // offsets from the tile-corner neighbour of the node are
-                    // non-negative compile-time constants
-                    const double* rb = ring + (oc[u] - kTHX - 1) * B + k;
-                    const double* ub = ust + (oc[u] - kTHX - 1) * M1;
-                    constexpr int cc = kTHX + 1;
-                    const double xc = rb[sz * RS + cc * B];
-                    double sum = 0.0, rtrue = 0.0;
-                    if constexpr (MODE == kTTrue) {   // b - A x, compensated
-                        CompSum rc(bc[u]);
-                        rc.sub(ub[sz * US + cc * M1], xc);
-#pragma unroll
-                        for (int j = 0; j < 7; ++j) {
-                            const int d = kKy[j] * kTHX + kKx[j];
-                            const int up = kKz[j] ? sp : sz, lo = kKz[j] ? sl : sz;
-                            rc.sub(ub[sz * US + cc * M1 + j + 1], rb[up * RS + (cc + d) * B]);
-                            rc.sub(ub[lo * US + (cc - d) * M1 + j + 1], rb[lo * RS + (cc - d) * B]);
-                        }
-                        rtrue = rc.value();
-                    } else if constexpr (UPD) {   // A (w D^{-1} r'): each neighbour scaled by its w / a_jj
-                        const double* db = dring + (oc[u] - kTHX - 1);
-                        sum = ub[sz * US + cc * M1] * (db[sz * kTHN + cc] * xc);
-#pragma unroll
-                        for (int j = 0; j < 7; ++j) {
-                            const int d = kKy[j] * kTHX + kKx[j];
-                            const int up = kKz[j] ? sp : sz, lo = kKz[j] ? sl : sz;
-                            sum += ub[sz * US + cc * M1 + j + 1] * (db[up * kTHN + cc + d] * rb[up * RS + (cc + d) * B]) +
-                                   ub[lo * US + (cc - d) * M1 + j + 1] * (db[lo * kTHN + cc - d] * rb[lo * RS + (cc - d) * B]);
-                        }
-                    } else {
-                        sum = ub[sz * US + cc * M1] * xc;
-#pragma unroll
-                        for (int j = 0; j < 7; ++j) {
-                            const int d = kKy[j] * kTHX + kKx[j];
-                            const int up = kKz[j] ? sp : sz, lo = kKz[j] ? sl : sz;
-                            sum = fma(ub[sz * US + cc * M1 + j + 1], rb[up * RS + (cc + d) * B], sum);
-                            sum = fma(ub[lo * US + (cc - d) * M1 + j + 1], rb[lo * RS + (cc - d) * B], sum);
-                        }
-                    }
-                    const bool in = oo[u] != kOut;
-                    double o;
-                    if constexpr (MODE == kTDirSpmv) {
-                        o = sum;
-                        a0 += in ? xc * sum : 0.0;
-                        if constexpr (P32)   // xc is already an FP32 value
-                            bstore_nt_f32(bo2, oo[u] == kOut ? kOut : oo[u] / 2, static_cast<float>(xc));
-                        else
-                            bstore_nt(bo2, oo[u], xc);   // p: next read by the update pass
-                    } else if constexpr (MODE == kTApply) {
-                        o = g.scale * sum;
-                    } else if constexpr (UPD) {
-                        const double rnew = xc;   // the staged r' of the node
-                        o = rnew - sum;
-                        a1 += in ? rnew * rnew : 0.0;
-                        bstore_nt(bo2, oo[u], rnew);
-                    } else if constexpr (MODE == kTSmoothDots) {
-                        o = xc + w * dc[u] * (bc[u] - sum);
-                        a0 += in ? bc[u] * o : 0.0;
-                        a1 += in ? o : 0.0;
-                        a2 += in ? bc[u] : 0.0;
-                    } else {
-                        o = MODE == kTTrue ? rtrue : bc[u] - sum;
-                        if constexpr (MODE == kTTrue) a1 += in ? o * o : 0.0;
-                    }
-                    if constexpr (RES32)
-                        bstore<float>(bo, oo[u] == kOut ? kOut : oo[u] / 2, static_cast<float>(o));   // read next
-                    else
-                        bstore_nt(bo, oo[u], o);
-                }
-                if (UPD && g.x3) {   // x += alpha p on this plane's nodes, after the stencil work
-                    __builtin_amdgcn_sched_barrier(0);
-                    const auto bx = plane(g.x3, z, nxy * B, pv);
-                    if constexpr (P32) {
-                        const auto bp = plane(reinterpret_cast<const float*>(g.p3), z, nxy * B, pv / 2);
-#pragma unroll
-                        for (int u = 0; u < NO; ++u) {
-                            if (tid + u * kTT >= TX * TY * B) continue;
-                            const double pu = static_cast<double>(bload<float>(bp, oo[u] == kOut ? kOut : oo[u] / 2));
-                            bstore_nt(bx, oo[u], bload_nt(bx, oo[u]) + alpha * pu);
-                        }
-                    } else {
-                        const auto bp = plane(g.p3, z, nxy * B, pv);
-#pragma unroll
-                        for (int u = 0; u < NO; ++u) {
-                            if (tid + u * kTT >= TX * TY * B) continue;
-                            bstore_nt(bx, oo[u], bload_nt(bx, oo[u]) + alpha * bload_nt(bp, oo[u]));
-                        }
-                    }
-                }
+            const d2v zero = 0.0;
+            d2v o;
+            if constexpr (MODE == kTDirSpmv) {
+                o = sum;
+                a0 += in ? xc * sum : zero;
+                if constexpr (P32)   // xc is already an FP32 value
+                    bstore2f<true>(plane(reinterpret_cast<const float*>(g.out2), z, nxy * B, pv / 2), half(oo), xc);
+                else
+                    bstore2_nt(plane(g.out2, z, nxy * B, pv), oo, xc);   // p: next read by the next iteration
+            } else if constexpr (MODE == kTApply) {
+                o = g.scale * sum;
+            } else if constexpr (UPD) {
+                o = rz - sum;
+                a1 += in ? rz * rz : zero;
+                bstore2_nt(plane(g.out2, z, nxy * B, pv), oo, rz);
+            } else if constexpr (MODE == kTSmoothDots) {
+                o = xc + w * dc * (bc - sum);
+                a0 += in ? bc * o : zero;
+                a1 += in ? o : zero;
+                a2 += in ? bc : zero;
+            } else {
+                o = MODE == kTTrue ? rtrue : bc - sum;
+                if constexpr (MODE == kTTrue) a1 += in ? o * o : zero;
             }
-            __syncthreads();
+            if constexpr (RES32)
+                bstore2f<false>(bo, half(oo), o);   // read next
+            else
+                bstore2_nt(bo, oo, o);
         };
+        __syncthreads();   // the last planes of the item before are read
         fetch(zb - 1);
-        store(0);
+        store(0, zb - 1);
         fetch(zb);
-        store(1);
+        store(1, zb);
         fetch(zb + 1);
+        __syncthreads();
+        if constexpr (UPD) rc = own_at(zb);
+        below_start();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            below_term(ub[-off_of(q) * 8 + 4 + q], val_at(0, -off_of(q)));
+            cur[q] = val_at(1, off_of(q));
+        }
+        if constexpr (MODE == kTTrue) below_end();
+        // plane z - zb + 1 lives in slot (z - zb + 1) % 3. A wavefront at most one
+        // barrier ahead writes plane z + 2 over plane z - 1, which no step reads
         using I0 = std::integral_constant<int, 0>;
         using I1 = std::integral_constant<int, 1>;
         using I2 = std::integral_constant<int, 2>;
-        for (int z = zb; z < ze; z += 3) {   // plane z - zb + 1 lives in slot (z - zb + 1) % 3
-            step(z, I1{}, I2{}, I0{});
-            if (z + 1 < ze) step(z + 1, I2{}, I0{}, I1{});
-            if (z + 2 < ze) step(z + 2, I0{}, I1{}, I2{});
+        for (int z = zb; z < ze; z += 3) {
+            step(z, I1{}, I2{});
+            if (z + 1 < ze) step(z + 1, I2{}, I0{});
+            if (z + 2 < ze) step(z + 2, I0{}, I1{});
         }
     }
-    auto out_sum = [&](double v, int slot_) {
+    auto out_sum = [&](d2v v, int slot_) {
 #pragma unroll
-        for (int off = 32; off >= B; off >>= 1) v += __shfl_xor(v, off);
-        const int lane = tid & 63, wave = tid >> 6;
-        if (lane < B) sm[wave * B + lane] = v;
+        for (int c = 0; c < 2; ++c) {
+            double t = comp(v, c);
+#pragma unroll
+            for (int off = 32; off >= P; off >>= 1) t += __shfl_xor(t, off);
+            if ((tid & 63) < P) sm[(tid >> 6) * B + 2 * kp + c] = t;
+        }
         __syncthreads();
         if (tid < B) {
             double t = 0.0;
-            for (int wv = 0; wv < kTT / 64; ++wv) t += sm[wv * B + tid];
+            for (int wv = 0; wv < T / 64; ++wv) t += sm[wv * B + tid];
             put(g.parts, tid, slot_, t);
         }
         __syncthreads();
@@ -2521,7 +2586,7 @@ struct Tile27Args {
 template <int MODE, bool R32 = false, bool V32 = false>
 __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
     constexpr int B = 16;
-    constexpr int NPF = MgTile<B>::NPF, RS = NPF * kTT;
+    constexpr int NPF = kNpf16, RS = NPF * kTT;
     constexpr int TX = kTHX - 2, TY = kTHY - 2;
     constexpr int NO = (TX * TY * B + kTT - 1) / kTT;   // output slots per thread
     constexpr uint32_t SZ = sizeof(double);
@@ -2743,7 +2808,7 @@ template <bool F32, bool C32 = false>
 __global__ __launch_bounds__(kTT, 4) void k_mg_prolong_smooth(PSArgs g) {
     using RT = std::conditional_t<F32, float, double>;   // x0 as staged
     constexpr int B = 16;
-    constexpr int NPF = MgTile<B>::NPF, RS = kTHN * B;   // ring slot: exactly the halo tile
+    constexpr int NPF = kNpf16, RS = kTHN * B;   // ring slot: exactly the halo tile
     constexpr int TX = kTHX - 2, TY = kTHY - 2;
     constexpr int NO = (TX * TY * B + kTT - 1) / kTT;
     constexpr int NC = (kPCN + kTT - 1) / kTT;   // coarse patch values per thread
@@ -3090,8 +3155,7 @@ struct RingArg {
 
 template <int MODE, int B, bool Z32 = false, bool P32 = false>
 void launch_tile(const MgState& M, const TileGeo& t, hipStream_t st, const double* in, const double* in2,
-                 const double* b, double* out, double* out2, double* x3 = nullptr, const double* p3 = nullptr,
-                 RingArg ring = {}) {
+                 const double* b, double* out, double* out2, RingArg ring = {}) {
     if constexpr (B >= 8) {   // tile_setup turns the tiling on only there
         const MgLevel& L = M.lv[0];
         TileArgs g;
@@ -3115,13 +3179,11 @@ void launch_tile(const MgState& M, const TileGeo& t, hipStream_t st, const doubl
         g.out2 = out2;
         g.parts = M.parts;
         g.sc = M.sc;
-        g.x3 = x3;
-        g.p3 = p3;
         g.slot = ring.slot;
         g.ring = ring.base;
         g.ring_stride = ring.stride;
         g.ring_n = ring.n;
-        hipLaunchKernelGGL((k_mg_tile<MODE, B, Z32, P32>), dim3(t.blocks), dim3(kTT), MgTile<B>::LDS, st, g);
+        hipLaunchKernelGGL((k_mg_tile<MODE, B, Z32, P32>), dim3(t.blocks), dim3(MgTile<B>::T), MgTile<B>::LDS, st, g);
     }
 }
 
@@ -3147,7 +3209,7 @@ void launch_tile27(const MgState& M, const TileGeo& t, int l, hipStream_t st, co
     g.w = M.w + l;   // system 0, level l
     g.out = out;
     g.sc = M.sc;
-    const size_t lds = (size_t)3 * MgTile<16>::NPF * kTT * sizeof(double);
+    const size_t lds = (size_t)3 * kNpf16 * kTT * sizeof(double);
     if (L.Uf27p && v32)   // the rows and (v32) the level's vectors in FP32
         hipLaunchKernelGGL((k_mg_tile27<MODE, true, true>), dim3(q.blocks), dim3(kTT), lds, st, g);
     else if (L.Uf27p)   // the rows in FP32 (the V-cycle's coarse operators)
@@ -3169,8 +3231,8 @@ inline void launch_ps(const MgState& M, const TileGeo& t, hipStream_t st, const 
     g.cx = C.nx;
     g.cy = C.ny;
     g.cz = C.nz;
-    g.tiles_x = t.tiles_x;
-    g.tiles_y = t.tiles_y;
+    g.tiles_x = t.ps_tx;
+    g.tiles_y = t.ps_ty;
     g.zc = f32 ? t.ps_zc32 : t.ps_zc;
     g.items = f32 ? t.ps_items32 : t.ps_items;
     g.Uf = L.Ufk32;
@@ -3304,7 +3366,7 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
     if constexpr (B >= 8) {
         if (M.nsys != 1 || L.kind != 1 || L.N * B * (int64_t)sizeof(double) >= (int64_t(1) << 31)) return QPAT_OK;
         static_assert(MgTile<B>::LDS <= 159 * 1024, "tiled multigrid LDS budget");
-        const void* fns[10] = {reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B>),
+        const void* fns[9] = {reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B>),
                               reinterpret_cast<const void*>(&k_mg_tile<kTResidFirst, B>),
                               reinterpret_cast<const void*>(&k_mg_tile<kTSmoothDots, B>),
                               reinterpret_cast<const void*>(&k_mg_tile<kTTrue, B>),
@@ -3312,16 +3374,15 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                               reinterpret_cast<const void*>(&k_mg_tile<kTApply, B>),
                               reinterpret_cast<const void*>(&k_mg_tile<kTUpdResid, B>),
                               reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B, true>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B, true, true>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTUpdResid, B, false, true>)};
+                              reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B, true, true>)};
         for (const void* f : fns)   // dynamic LDS beyond the default limit is allowed per kernel
             QPAT_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MgTile<B>::LDS));
         int occ = 1, cus = 256;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fns[2], kTT, MgTile<B>::LDS) != hipSuccess) occ = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fns[6], MgTile<B>::T, MgTile<B>::LDS) != hipSuccess) occ = 1;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) cus = 256;
-        const int64_t blocks = sgrid<B>(L.N).x;
-        const int64_t conc = std::max<int64_t>(1, std::min<int64_t>((int64_t)std::max(occ, 1) * (cus / 8), blocks / 8));
-        const int64_t tx = (L.nx + kTHX - 3) / (kTHX - 2), ty = (L.ny + kTHY - 3) / (kTHY - 2);
+        // blocks resident per XCD; each leaves one partial sum
+        const int64_t conc = std::min<int64_t>((int64_t)std::max(occ, 1) * std::max(cus / 8, 1), kMgBlocks / 8);
+        const int64_t tx = (L.nx + kTX - 1) / kTX, ty = (L.ny + kTY - 1) / kTY;
         int64_t best = -1, best_zc = L.nz;
         for (int64_t nch = 1; nch <= L.nz; ++nch) {
             const int64_t zc = (L.nz + nch - 1) / nch;
@@ -3395,15 +3456,13 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                     gu.in2 = M.pq;   // q
                     gu.out = M.lv[0].r;
                     gu.out2 = M.pr2;
-                    gu.x3 = M.pa;
-                    gu.p3 = M.pb;
                     const dim3 grid(t.blocks);
                     float ms_d = 0.f, ms_u = 0.f;
                     QPAT_TRY(time_launches(c, [&] {
-                        hipLaunchKernelGGL((k_mg_tile<kTDirSpmv, B>), grid, dim3(kTT), MgTile<B>::LDS, c->stream, gd);
+                        hipLaunchKernelGGL((k_mg_tile<kTDirSpmv, B>), grid, dim3(MgTile<B>::T), MgTile<B>::LDS, c->stream, gd);
                     }, &ms_d));
                     QPAT_TRY(time_launches(c, [&] {
-                        hipLaunchKernelGGL((k_mg_tile<kTUpdResid, B>), grid, dim3(kTT), MgTile<B>::LDS, c->stream, gu);
+                        hipLaunchKernelGGL((k_mg_tile<kTUpdResid, B>), grid, dim3(MgTile<B>::T), MgTile<B>::LDS, c->stream, gu);
                     }, &ms_u));
                     cms[ci] = round == 0 ? ms_d + ms_u : std::min(cms[ci], ms_d + ms_u);
                 }
@@ -3447,8 +3506,11 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
             q.blocks = static_cast<int32_t>(8 * std::min<int64_t>(rconc, (q.items + 7) / 8));
             q.on = true;
         }
-        if constexpr (B == 16) {   // the fused prolongation + last sweep: the same tiles, even chunks
+        if constexpr (B == 16) {   // the fused prolongation + last sweep: even chunks
             if (L.Uf && L.Ufk32) {
+                const int64_t ptx = (L.nx + kTHX - 3) / (kTHX - 2), pty = (L.ny + kTHY - 3) / (kTHY - 2);
+                t.ps_tx = static_cast<int32_t>(ptx);
+                t.ps_ty = static_cast<int32_t>(pty);
                 for (const bool f32 : {false, true}) {
                     const void* fps = f32 ? reinterpret_cast<const void*>(&k_mg_prolong_smooth<true>)
                                           : reinterpret_cast<const void*>(&k_mg_prolong_smooth<false>);
@@ -3464,7 +3526,7 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                     for (int64_t nch = 1; nch <= L.nz; ++nch) {
                         int64_t zc = (L.nz + nch - 1) / nch;
                         zc += zc & 1;
-                        const int64_t items = tx * ty * ((L.nz + zc - 1) / zc);
+                        const int64_t items = ptx * pty * ((L.nz + zc - 1) / zc);
                         const int64_t cost = (((items + 7) / 8 + conc_ps - 1) / conc_ps) * (zc + 2);
                         if (best_ps < 0 || cost < best_ps) {
                             best_ps = cost;
@@ -3472,7 +3534,7 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                         }
                     }
                     auto set_ps = [&](int64_t zc) {
-                        const int32_t items = static_cast<int32_t>(tx * ty * ((L.nz + zc - 1) / zc));
+                        const int32_t items = static_cast<int32_t>(ptx * pty * ((L.nz + zc - 1) / zc));
                         (f32 ? t.ps_zc32 : t.ps_zc) = static_cast<int32_t>(zc);
                         (f32 ? t.ps_items32 : t.ps_items) = items;
                         (f32 ? t.ps_blocks32 : t.ps_blocks) =
@@ -3500,7 +3562,7 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                         QPAT_HIP(c, hipMemcpyAsync(sc_t, hs.data(), B * sizeof(MgScal), hipMemcpyHostToDevice, c->stream));
                         QPAT_HIP(c, hipMemsetAsync(M.pa, 0, L.N * B * sizeof(double), c->stream));
                         QPAT_HIP(c, hipMemsetAsync(C.x, 0, C.N * B * sizeof(double), c->stream));
-                        const std::vector<int64_t> cands = chunk_candidates(L.nz, tx * ty, conc_ps, true);
+                        const std::vector<int64_t> cands = chunk_candidates(L.nz, ptx * pty, conc_ps, true);
                         std::vector<float> cms(cands.size(), 0.f);
                         for (int round = 0; round < kTuneRounds; ++round)
                         for (size_t ci = 0; ci < cands.size(); ++ci) {
@@ -3513,8 +3575,8 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                             g.cx = C.nx;
                             g.cy = C.ny;
                             g.cz = C.nz;
-                            g.tiles_x = static_cast<int32_t>(tx);
-                            g.tiles_y = static_cast<int32_t>(ty);
+                            g.tiles_x = t.ps_tx;
+                            g.tiles_y = t.ps_ty;
                             g.zc = static_cast<int32_t>(zc);
                             g.items = f32 ? t.ps_items32 : t.ps_items;
                             g.Uf = L.Ufk32;
@@ -3552,7 +3614,7 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                                   reinterpret_cast<const void*>(&k_mg_tile27<kT27Smooth, true>),
                                   reinterpret_cast<const void*>(&k_mg_tile27<kT27Resid, true, true>),
                                   reinterpret_cast<const void*>(&k_mg_tile27<kT27Smooth, true, true>)};
-            constexpr size_t lds27 = (size_t)3 * MgTile<16>::NPF * kTT * sizeof(double);
+            constexpr size_t lds27 = (size_t)3 * kNpf16 * kTT * sizeof(double);
             for (const void* f : f27)
                 QPAT_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds27));
             int occ27 = 1;
@@ -3819,13 +3881,12 @@ void iteration(const MgState& M, PcgMg a, const TileGeo& tg, hipStream_t st, int
         ring.stride = a.L.N * B * (p32 ? 4 : 8);
         ring.n = a.ring;
     }
-    double* const xu = a.ring > 0 ? nullptr : a.x;   // with the ring, x is formed later (k_mgp_ring_flush)
     if (tg.on && p32) {
-        launch_tile<kTDirSpmv, B, true, true>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, nullptr, nullptr, ring);
+        launch_tile<kTDirSpmv, B, true, true>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, ring);
     } else if (tg.on && z32_path<B>(M, tg)) {   // z from the fused prolongation + last sweep, FP32
-        launch_tile<kTDirSpmv, B, true>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, nullptr, nullptr, ring);
+        launch_tile<kTDirSpmv, B, true>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, ring);
     } else if (tg.on) {
-        launch_tile<kTDirSpmv, B>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, nullptr, nullptr, ring);
+        launch_tile<kTDirSpmv, B>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, ring);
     } else {
         if (f32v0_path<B>(M, tg))   // z in FP32
             hipLaunchKernelGGL((k_mgp_dir<B, true>), g, dim3(kMgT), 0, st, a);
@@ -3840,10 +3901,7 @@ void iteration(const MgState& M, PcgMg a, const TileGeo& tg, hipStream_t st, int
     if (fused_update(tg)) {   // r, x and the V-cycle's first sweep + residual in one pass; r alternates buffers
         double* r_old = par ? M.pr2 : M.pr;
         double* r_new = par ? M.pr : M.pr2;
-        if (p32)
-            launch_tile<kTUpdResid, B, false, true>(M, tg, st, r_old, a.q, nullptr, M.lv[0].r, r_new, xu, a.pn);
-        else
-            launch_tile<kTUpdResid, B>(M, tg, st, r_old, a.q, nullptr, M.lv[0].r, r_new, xu, a.pn);
+        launch_tile<kTUpdResid, B>(M, tg, st, r_old, a.q, nullptr, M.lv[0].r, r_new);
         a.r = r_new;
     } else if (upd1 && f32v0_path<B>(M, tg)) {   // one right-hand side: update, first sweep (FP32), region sums
         hipLaunchKernelGGL(k_mgp_update_first<float>, sys_rows(vgrid(a.L.N, kMgGrid), B, a.nsys), dim3(kMgT), 0, st,
@@ -3881,6 +3939,7 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
     PcgMg a = pcg_args<B>(c, op);
     QPAT_TRY(tile_setup<B>(c, M));
     const TileGeo tg = M.tiles[B];
+    if (tg.on) a.nb = std::max({a.nb, tg.blocks, tg.ps_blocks, tg.ps_blocks32});   // every kernel that leaves partials
     // The tiled iterations keep their directions and alphas in a ring and form
     // x = x + sum alpha_j p_j (k_mgp_ring_flush) before x is read: the update
     // then neither reads nor writes x nor reads p.
@@ -4645,7 +4704,7 @@ static qpat_status apply_B(qpat_ctx* c, const double* U, const double* in, int l
         g.U = U;
         g.in = in;
         g.out = out;
-        hipLaunchKernelGGL((k_mg_tile<kTApply, B>), dim3(t.blocks), dim3(kTT), MgTile<B>::LDS, c->stream, g);
+        hipLaunchKernelGGL((k_mg_tile<kTApply, B>), dim3(t.blocks), dim3(MgTile<B>::T), MgTile<B>::LDS, c->stream, g);
         QPAT_HIP(c, hipGetLastError());
         *done = true;
     }

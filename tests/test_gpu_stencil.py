@@ -301,3 +301,26 @@ def test_coarse_set_up(nx, ny, nz, order):
     assert info["iters_max"] <= 30, info
     ctx.prior_apply(r, y)
     assert rel(host(y), host(p)) <= 1e-9
+
+
+@pytest.mark.parametrize("nx,ny,nz,n_ill,precision", [(7, 7, 6, 16, 0), (8, 15, 7, 9, 1), (16, 8, 9, 16, 1), (23, 24, 6, 5, 0),
+                                                      (25, 6, 17, 7, 1), (6, 31, 8, 13, 0)])
+def test_tiled_products_at_tile_edges(nx, ny, nz, n_ill, precision):
+    """The tiled finest-level kernels on lattices whose sides end on, just before and just past a tile of
+    8 x 8 nodes, with blocks of 8 and 16 right-hand sides and with pairs of which one is padding (odd n_ill):
+    forward, J s and J^T t against the oracle (solves at 1e-12, element-wise 1e-10 as above)."""
+    coords, tets, bfaces, kappa, mu, src = box_problem(nx, ny, nz, n_ill, nx + 31 * ny)
+    ctx, phi, _ = solve(coords, tets, bfaces, kappa, mu, src, pcg_rtol=1e-12, precision=precision)
+    assert ctx.tile_schedule(16 if n_ill > 8 else 8)["tiled"]
+    g = fem.geometry(coords, tets, bfaces)
+    lin = Linearisation(g, kappa, mu, src)
+    assert_close(phi, lin.phi, 1e-10, "phi")
+    rng = np.random.default_rng(n_ill)
+    N = coords.shape[0]
+    s, t = rng.standard_normal(2 * N), rng.standard_normal((n_ill, N))
+    js = torch.empty(n_ill * N, dtype=torch.float64, device="cuda")
+    jt = torch.empty(2 * N, dtype=torch.float64, device="cuda")
+    ctx.jvp(dev(s), js)
+    ctx.vjp(dev(t), jt)
+    assert_close(host(js).reshape(n_ill, N), lin.jvp(s), 1e-10, "J s")
+    assert_close(host(jt), lin.vjp(t), 1e-10, "J^T t")
