@@ -38,16 +38,6 @@ qpat_status dfree(qpat_ctx* c, void* p) {
 
 namespace {
 
-__global__ void k_from_interleaved(int64_t N, int n_ill, int n_pad, const double* __restrict__ src,
-                                   const double* __restrict__ mu, double* __restrict__ dst) {
-    int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= N * n_ill) return;
-    const int64_t k = t / N, row = t % N;
-    double v = src[row * n_pad + k];
-    if (mu) v *= mu[row];
-    dst[t] = v;
-}
-
 __global__ void k_copy_d(int64_t n, const double* __restrict__ a, double* __restrict__ b) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < n) b[i] = a[i];
@@ -264,21 +254,27 @@ qpat_status qpat_set_sources(qpat_ctx* c, int32_t n_ill, const double* phi_src) 
     return QPAT_OK;
 }
 
+// K and its multigrid hierarchy at c->kappa, c->mu
+static qpat_status build_K(qpat_ctx* c) {
+    bool lattice = false;
+    QPAT_TRY(assemble_K_lattice(c, &lattice));
+    c->K_sell = !lattice;
+    if (!lattice) {
+        QPAT_TRY(assemble_K(c));
+        QPAT_TRY(lattice_convert(c, Op::K));
+    }
+    return mg_setup(c, Op::K);
+}
+
 static qpat_status forward_common(qpat_ctx* c, double* phi_out, double* h_out, qpat_info* info,
                                   const double* x0 = nullptr) {
-    QPAT_TRY(assemble_K(c));
-    QPAT_TRY(lattice_convert(c, Op::K));
-    QPAT_TRY(mg_setup(c, Op::K));
+    QPAT_TRY(build_K(c));
     SolveStats st;
     c->have_forward = false;
     c->lsqr_ready = false;
     if (x0) QPAT_TRY(forward_solve_x0(c, x0, &st));
     else QPAT_TRY(forward_solve(c, &st));
-    const int64_t n = c->N * c->n_ill;
-    const dim3 g(grid_for(n, kThreads, 1 << 30)), b(kThreads);
-    if (phi_out) hipLaunchKernelGGL(k_from_interleaved, g, b, 0, c->stream, c->N, c->n_ill, c->n_pad, c->phi, nullptr, phi_out);
-    if (h_out) hipLaunchKernelGGL(k_from_interleaved, g, b, 0, c->stream, c->N, c->n_ill, c->n_pad, c->phi, c->mu, h_out);
-    QPAT_HIP(c, hipGetLastError());
+    QPAT_TRY(forward_out(c, phi_out, h_out));
     QPAT_HIP(c, hipStreamSynchronize(c->stream));
     qpat_status s = finish(c, st, info);
     if (s == QPAT_OK) c->have_forward = true;
@@ -291,10 +287,9 @@ qpat_status qpat_forward(qpat_ctx* c, const double* kappa, const double* mu, dou
     DeviceGuard g(c->device);
     if (!kappa || !mu) return fail(c, QPAT_ERR_ARG, "forward: null kappa or mu");
     if (c->n_ill == 0) return fail(c, QPAT_ERR_STATE, "forward: call qpat_set_sources first");
-    bool ok1 = false, ok2 = false;
-    QPAT_TRY(check_positive(c, kappa, c->N, &ok1));
-    QPAT_TRY(check_positive(c, mu, c->N, &ok2));
-    if (!ok1 || !ok2) return fail(c, QPAT_ERR_ARG, "forward: kappa and mu must be finite and > 0");
+    bool ok = false;
+    QPAT_TRY(check_positive(c, kappa, mu, c->N, &ok));
+    if (!ok) return fail(c, QPAT_ERR_ARG, "forward: kappa and mu must be finite and > 0");
     const dim3 gr(grid_for(c->N, kThreads, 1 << 30)), b(kThreads);
     hipLaunchKernelGGL(k_copy_d, gr, b, 0, c->stream, c->N, kappa, c->kappa);
     hipLaunchKernelGGL(k_copy_d, gr, b, 0, c->stream, c->N, mu, c->mu);
@@ -307,10 +302,9 @@ qpat_status qpat_forward_x0(qpat_ctx* c, const double* kappa, const double* mu, 
     DeviceGuard g(c->device);
     if (!kappa || !mu || !x0) return fail(c, QPAT_ERR_ARG, "forward_x0: null pointer");
     if (c->n_ill == 0) return fail(c, QPAT_ERR_STATE, "forward_x0: call qpat_set_sources first");
-    bool ok1 = false, ok2 = false;
-    QPAT_TRY(check_positive(c, kappa, c->N, &ok1));
-    QPAT_TRY(check_positive(c, mu, c->N, &ok2));
-    if (!ok1 || !ok2) return fail(c, QPAT_ERR_ARG, "forward_x0: kappa and mu must be finite and > 0");
+    bool ok = false;
+    QPAT_TRY(check_positive(c, kappa, mu, c->N, &ok));
+    if (!ok) return fail(c, QPAT_ERR_ARG, "forward_x0: kappa and mu must be finite and > 0");
     const dim3 gr(grid_for(c->N, kThreads, 1 << 30)), b(kThreads);
     hipLaunchKernelGGL(k_copy_d, gr, b, 0, c->stream, c->N, kappa, c->kappa);
     hipLaunchKernelGGL(k_copy_d, gr, b, 0, c->stream, c->N, mu, c->mu);
@@ -409,10 +403,9 @@ qpat_status qpat_forward_log(qpat_ctx* c, double kappa0, double mu0, const doubl
     if (!beta || !(kappa0 > 0.0) || !(mu0 > 0.0)) return fail(c, QPAT_ERR_ARG, "forward_log: bad arguments");
     if (c->n_ill == 0) return fail(c, QPAT_ERR_STATE, "forward_log: call qpat_set_sources first");
     QPAT_TRY(exp_params(c, kappa0, mu0, beta));
-    bool ok1 = false, ok2 = false;
-    QPAT_TRY(check_positive(c, c->kappa, c->N, &ok1));
-    QPAT_TRY(check_positive(c, c->mu, c->N, &ok2));
-    if (!ok1 || !ok2) return fail(c, QPAT_ERR_ARG, "forward_log: exp(beta) not finite and positive");
+    bool ok = false;
+    QPAT_TRY(check_positive(c, c->kappa, c->mu, c->N, &ok));
+    if (!ok) return fail(c, QPAT_ERR_ARG, "forward_log: exp(beta) not finite and positive");
     return forward_common(c, phi_out, h_out, info);
 }
 
@@ -583,9 +576,7 @@ qpat_status qpat_fit_background(qpat_ctx* c, const double* chi, const double* w,
             return fail(c, QPAT_ERR_BREAKDOWN, "fit_background: the iterate left the positive reals");
         c->have_forward = false;
         QPAT_TRY(exp_params(c, k, m, zero));
-        QPAT_TRY(assemble_K(c));
-        QPAT_TRY(lattice_convert(c, Op::K));
-        QPAT_TRY(mg_setup(c, Op::K));
+        QPAT_TRY(build_K(c));
         QPAT_TRY(forward_solve(c, &st));
         if (st.noconv)
             return fail(c, QPAT_ERR_NOCONV, "fit_background: PCG did not converge (relres %.3e)", st.relres_max);

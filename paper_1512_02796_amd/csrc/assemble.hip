@@ -187,12 +187,18 @@ __global__ void k_exp(int64_t N, double k0, double m0, const double* __restrict_
     mu[i] = m0 * exp(beta[N + i]);
 }
 
-__global__ void k_check_pos(const double* __restrict__ a, int64_t n, int32_t* flag) {
+__global__ void k_clear_flag(int32_t* flag) { *flag = 0; }
+
+// flag |= 16 / 32 where a / b has an entry that is not positive and finite
+__global__ void k_check_pos(const double* __restrict__ a, const double* __restrict__ b, int64_t n, int32_t* flag) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    int32_t bad = 0;
     for (; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        double v = a[i];
-        if (!(v > 0.0) || !(v < INFINITY)) atomicOr(flag, 16);
+        const double va = a[i], vb = b[i];
+        if (!(va > 0.0) || !(va < INFINITY)) bad |= 16;
+        if (!(vb > 0.0) || !(vb < INFINITY)) bad |= 32;
     }
+    if (bad) atomicOr(flag, bad);
 }
 
 }  // namespace
@@ -230,14 +236,14 @@ qpat_status exp_params(qpat_ctx* c, double kappa0, double mu0, const double* bet
     return QPAT_OK;
 }
 
-qpat_status check_positive(qpat_ctx* c, const double* a, int64_t n, bool* ok) {
-    QPAT_HIP(c, hipMemsetAsync(c->dev_flag, 0, sizeof(int32_t), c->stream));
-    hipLaunchKernelGGL(k_check_pos, dim3(grid_for(n, kThreads, 8192)), dim3(kThreads), 0, c->stream, a, n,
+qpat_status check_positive(qpat_ctx* c, const double* a, const double* b, int64_t n, bool* ok) {
+    hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, c->stream, c->dev_flag);
+    hipLaunchKernelGGL(k_check_pos, dim3(grid_for(n, kThreads, 8192)), dim3(kThreads), 0, c->stream, a, b, n,
                        c->dev_flag);
-    int32_t flag = 0;
-    QPAT_HIP(c, hipMemcpyAsync(&flag, c->dev_flag, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
+    int32_t* flag = reinterpret_cast<int32_t*>(c->red_host);   // pinned
+    QPAT_HIP(c, hipMemcpyAsync(flag, c->dev_flag, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
     QPAT_HIP(c, hipStreamSynchronize(c->stream));
-    *ok = flag == 0;
+    *ok = *flag == 0;
     return QPAT_OK;
 }
 

@@ -126,14 +126,14 @@ __global__ __launch_bounds__(kThreads) void k_gfwd(int64_t N, const int32_t* __r
 // more of them are in flight than with one thread per node.
 constexpr int kSplit = 8;
 
-// the coefficients of dK(s) per node: uu[i] = (kappa_i s1_i, mu_i s2_i)
+// the coefficients of dK(s) per node: uu[i] = (kappa_i s1_i, mu_i s2_i) (s null: of K, s = 1)
 __global__ __launch_bounds__(kThreads) void k_dk_coef(int64_t N, const double* __restrict__ kappa,
                                                       const double* __restrict__ mu, const double* __restrict__ s,
                                                       double* __restrict__ uu) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= N) return;
-    uu[2 * i] = kappa[i] * s[i];
-    uu[2 * i + 1] = mu[i] * s[N + i];
+    uu[2 * i] = s ? kappa[i] * s[i] : kappa[i];
+    uu[2 * i + 1] = s ? mu[i] * s[N + i] : mu[i];
 }
 
 // M1: stored entries per row (8 on the Kuhn lattice, else kMaxUpper + 1)
@@ -437,6 +437,32 @@ __global__ __launch_bounds__(kThreads) void k_dk_voxel(int64_t N, Lattice lat, V
     }
 }
 
+// the Robin term of K, B/2 with B_ab = |F| (1 + d_ab) / 12 per boundary triangle, added to the rows
+// (diagonal and upper offsets) of the stencil form U [N][8]
+__global__ __launch_bounds__(kThreads) void k_robin_lattice(int64_t N, Lattice lat, const int32_t* __restrict__ bf,
+                                                            const double* __restrict__ barea,
+                                                            const int32_t* __restrict__ n2f_ptr,
+                                                            const int32_t* __restrict__ n2f, double* __restrict__ U) {
+    const int64_t row = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (row >= N) return;
+    const int32_t q0 = n2f_ptr[row], q1 = n2f_ptr[row + 1];
+    if (q0 == q1) return;
+    const int64_t nx = lat.nx, nxy = nx * lat.ny;
+    const int rx = static_cast<int>(row % nx), ry = static_cast<int>((row / nx) % lat.ny), rz = static_cast<int>(row / nxy);
+    for (int32_t q = q0; q < q1; ++q) {
+        const int32_t f = n2f[q] / 3, a = n2f[q] % 3;
+        const double ar = barea[f];
+        for (int b = 0; b < 3; ++b) {
+            const int64_t v = bf[3 * f + b];
+            const int dx = static_cast<int>(v % nx) - rx, dy = static_cast<int>((v / nx) % lat.ny) - ry,
+                      dz = static_cast<int>(v / nxy) - rz;
+            if (dx < -1 || dx > 1 || dy < -1 || dy > 1 || dz < -1 || dz > 1) continue;
+            const int slot = lat.code[(dx + 1) + 3 * (dy + 1) + 9 * (dz + 1)];   // -1: a lower entry
+            if (slot >= 0) U[row * 8 + slot] += 0.5 * ar * (a == b ? 2.0 : 1.0) * (1.0 / 12.0);
+        }
+    }
+}
+
 // J^T t per voxel and right-hand side k (B lanes per voxel), summed over the
 // lanes: QR[c][v] (+)= sum over the voxel's tetrahedra T at corner c of
 // sum_k |T|/4 grad(phi_k).grad(z_k), and QR[8 + c][v] of sum_k (Mass_T(phi_k) z_k)_c
@@ -637,25 +663,93 @@ __global__ void k_pack_ext(int64_t N, const double* __restrict__ src, int n_ill,
     dst[t] = kk < n_ill ? src[(int64_t)kk * N + t / B] : 0.0;
 }
 
-// adjoint right-hand side b = mu t (tmode 0: external t; 1: t = W u interleaved)
+// The caller's data arrays are [n_ill][N], the library's [N][columns]. The
+// kernels between them transpose kTrN nodes x C columns through LDS, so that
+// both sides move whole segments (reading or writing one of them 8 bytes per
+// N or per column a lane reached 2.2 - 3.5 TB/s). Row stride kTrS: the 16 columns
+// of 4 nodes that a wavefront writes fall on distinct banks.
+constexpr int kTrN = 128, kTrS = kTrN + 4;
+
+// J s for a caller's [n_ill][N] array: y = mu w + phi mu s2
 template <int B>
-__global__ void k_adj_rhs(int64_t N, const double* __restrict__ mu, int n_pad, int n_ill, int col0, int tmode,
-                          const double* __restrict__ t_ext, const double* __restrict__ W,
-                          const double* __restrict__ U, double* __restrict__ b) {
+__global__ __launch_bounds__(kThreads) void k_jvp_out_ext(int64_t N, const double* __restrict__ mu,
+                                                          const double* __restrict__ phi, const double* __restrict__ s,
+                                                          const double* __restrict__ w, int n_pad, int n_ill, int col0,
+                                                          double* __restrict__ out) {
+    __shared__ double t[B * kTrS];
+    const int64_t row0 = blockIdx.x * (int64_t)kTrN;
+#pragma unroll
+    for (int e = threadIdx.x; e < kTrN * B; e += kThreads) {
+        const int n = e / B, c = e % B;
+        const int64_t row = row0 + n;
+        if (row < N) t[c * kTrS + n] = mu[row] * (w[row * B + c] + phi[row * n_pad + col0 + c] * s[N + row]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = threadIdx.x; e < kTrN * B; e += kThreads) {
+        const int n = e % kTrN, c = e / kTrN;
+        if (row0 + n < N && col0 + c < n_ill) out[(int64_t)(col0 + c) * N + row0 + n] = t[c * kTrS + n];
+    }
+}
+
+// adjoint right-hand side b = mu t from a caller's [n_ill][N] array (zero past n_ill)
+template <int B>
+__global__ __launch_bounds__(kThreads) void k_adj_rhs_ext(int64_t N, const double* __restrict__ mu, int n_ill, int col0,
+                                                          const double* __restrict__ t_ext, double* __restrict__ b) {
+    __shared__ double t[B * kTrS];
+    const int64_t row0 = blockIdx.x * (int64_t)kTrN;
+#pragma unroll
+    for (int e = threadIdx.x; e < kTrN * B; e += kThreads) {
+        const int n = e % kTrN, c = e / kTrN;
+        t[c * kTrS + n] = row0 + n < N && col0 + c < n_ill ? t_ext[(int64_t)(col0 + c) * N + row0 + n] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = threadIdx.x; e < kTrN * B; e += kThreads) {
+        const int n = e / B, c = e % B;
+        if (row0 + n < N) b[(row0 + n) * B + c] = mu[row0 + n] * t[c * kTrS + n];
+    }
+}
+
+// fluence and data of the forward solves for a caller's [n_ill][N] arrays (either may
+// be null): phi and mu phi, C columns from col0 of [N][n_pad]
+template <int C>
+__global__ __launch_bounds__(kThreads) void k_forward_out(int64_t N, int n_ill, int n_pad, const double* __restrict__ phi,
+                                                          const double* __restrict__ mu, double* __restrict__ phi_out,
+                                                          double* __restrict__ h_out) {
+    __shared__ double t[C * kTrS];
+    const int64_t row0 = blockIdx.x * (int64_t)kTrN;
+    const int col0 = blockIdx.y * C;
+#pragma unroll
+    for (int e = threadIdx.x; e < kTrN * C; e += kThreads) {
+        const int n = e / C, c = e % C;
+        if (row0 + n < N) t[c * kTrS + n] = phi[(row0 + n) * n_pad + col0 + c];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = threadIdx.x; e < kTrN * C; e += kThreads) {
+        const int n = e % kTrN, c = e / kTrN;
+        if (row0 + n >= N || col0 + c >= n_ill) continue;
+        const int64_t at = (int64_t)(col0 + c) * N + row0 + n;
+        const double v = t[c * kTrS + n];
+        if (phi_out) phi_out[at] = v;
+        if (h_out) h_out[at] = v * mu[row0 + n];
+    }
+}
+
+// adjoint right-hand side b = mu t, t = W u interleaved
+template <int B>
+__global__ void k_adj_rhs(int64_t N, const double* __restrict__ mu, int n_pad, int n_ill, int col0,
+                          const double* __restrict__ W, const double* __restrict__ U, double* __restrict__ b) {
     int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (t >= N * B) return;
     const int64_t row = t / B;
     const int kk = col0 + static_cast<int>(t % B);
-    double tv = 0.0;
-    if (kk < n_ill) {
-        if (tmode == 0) tv = t_ext[(int64_t)kk * N + row];
-        else tv = W[row * n_pad + kk] * U[row * n_pad + kk];
-    }
-    b[t] = mu[row] * tv;
+    b[t] = kk < n_ill ? mu[row] * (W[row * n_pad + kk] * U[row * n_pad + kk]) : 0.0;
 }
 
-// J s output: y = mu w + phi mu s2.
-// mode 0: out [n_ill][N]; mode 1: q = W y - alpha u (interleaved); mode 2: out interleaved y
+// J s output, interleaved: y = mu w + phi mu s2.
+// mode 1: q = W y - alpha u; mode 2: y
 template <int B>
 __global__ void k_jvp_out(int64_t N, const double* __restrict__ mu, const double* __restrict__ phi,
                           const double* __restrict__ s, const double* __restrict__ w, int n_pad, int n_ill, int col0,
@@ -667,9 +761,7 @@ __global__ void k_jvp_out(int64_t N, const double* __restrict__ mu, const double
     const int kk = col0 + static_cast<int>(t % B);
     const int64_t di = row * n_pad + kk;
     const double y = mu[row] * (w[t] + phi[di] * s[N + row]);
-    if (mode == 0) {
-        if (kk < n_ill) out[(int64_t)kk * N + row] = y;
-    } else if (mode == 1) {
+    if (mode == 1) {
         out[di] = (kk < n_ill ? W[di] * y : 0.0) - ls->alpha * U[di];
     } else {
         out[di] = kk < n_ill ? y : 0.0;
@@ -742,27 +834,22 @@ static qpat_status rel_maxdiff(qpat_ctx* c, int64_t n, const double* a, const do
 }
 
 // The voxel form assumes Kuhn elements in equal voxels; the lattice check
-// only saw the node-node pattern. Before its first use it is compared with
-// the element form (any mesh) on pseudo-random coefficients and fields: dK(s)
-// rows and the J^T t node sums must agree to 1e-12 relative, else the
-// element form stays in use.
-static qpat_status vox_check(qpat_ctx* c) {
-    if (c->vox != 0) return QPAT_OK;
-    c->vox = -1;
+// only saw the node-node pattern. Before their first use its kernels are
+// compared with the element form (any mesh) on pseudo-random coefficients and
+// fields: the rows of K and dK(s) here, the J^T t node sums in vox_check, must
+// agree to 1e-12 relative, else the element form stays in use.
+static qpat_status vox_check_rows(qpat_ctx* c) {
+    if (c->vox_rows != 0 || c->vox < 0) return QPAT_OK;
+    c->vox_rows = -1;
     if (!c->lat.on || c->lat.m != 7 || c->opts.operator_format != 1) return QPAT_OK;
     for (int m = 1; m < 8; ++m)   // upper offset with axis mask m in slot m (the Kuhn pattern's order)
         if (c->lat.code[13 + (m & 1) + 3 * ((m >> 1) & 1) + 9 * (m >> 2)] != m) return QPAT_OK;
     const int64_t N = c->N, nx = c->lat.nx, ny = c->lat.ny, nz = c->lat.nz;
     const int64_t Nv = (nx - 1) * (ny - 1) * (nz - 1);
     if (Nv < 1 || 6 * Nv != c->E) return QPAT_OK;
-    // the adjoint kernel's 32-bit byte offsets: phi [N][n_pad], blocks [N][16], sums [16][Nv]
-    const int64_t lim = (int64_t(1) << 31) - 1;
-    if (N * std::max<int64_t>(c->n_pad, 16) * 8 > lim || 16 * Nv * 8 > lim) return QPAT_OK;
     const VoxGeo vg = vox_geo(c);
     const dim3 blk(kThreads);
-    constexpr int BC = 16;   // right-hand sides of the check
-    double *uu = nullptr, *ue = nullptr, *uv = nullptr, *f = nullptr, *z = nullptr, *tq = nullptr, *tr = nullptr,
-           *qr = nullptr, *a = nullptr;
+    double *uu = nullptr, *ue = nullptr, *uv = nullptr;
     QPAT_TRY(dalloc(c, &uu, 2 * N));
     QPAT_TRY(dalloc(c, &ue, 8 * N));
     QPAT_TRY(dalloc(c, &uv, 8 * N));
@@ -777,7 +864,23 @@ static qpat_status vox_check(qpat_ctx* c) {
     QPAT_TRY(dfree(c, uu));
     QPAT_TRY(dfree(c, ue));
     QPAT_TRY(dfree(c, uv));
-    if (!(rel_dk <= 1e-12)) return QPAT_OK;
+    if (rel_dk <= 1e-12) c->vox_rows = 1;
+    return QPAT_OK;
+}
+
+static qpat_status vox_check(qpat_ctx* c) {
+    if (c->vox != 0) return QPAT_OK;
+    QPAT_TRY(vox_check_rows(c));
+    c->vox = -1;
+    if (c->vox_rows != 1) return QPAT_OK;
+    const int64_t N = c->N, Nv = c->E / 6;
+    // the adjoint kernel's 32-bit byte offsets: phi [N][n_pad], blocks [N][16], sums [16][Nv]
+    const int64_t lim = (int64_t(1) << 31) - 1;
+    if (N * std::max<int64_t>(c->n_pad, 16) * 8 > lim || 16 * Nv * 8 > lim) return QPAT_OK;
+    const VoxGeo vg = vox_geo(c);
+    const dim3 blk(kThreads);
+    constexpr int BC = 16;   // right-hand sides of the check
+    double *f = nullptr, *z = nullptr, *tq = nullptr, *tr = nullptr, *qr = nullptr, *a = nullptr;
     QPAT_TRY(dalloc(c, &f, BC * N));
     QPAT_TRY(dalloc(c, &z, BC * N));
     QPAT_TRY(dalloc(c, &tq, c->E));
@@ -800,6 +903,40 @@ static qpat_status vox_check(qpat_ctx* c) {
     QPAT_TRY(rel_maxdiff(c, N, a + 3 * N, a + N, &rel2));
     for (double* p : {f, z, tq, tr, qr, a}) QPAT_TRY(dfree(c, p));
     if (rel1 <= 1e-12 && rel2 <= 1e-12) c->vox = 1;
+    return QPAT_OK;
+}
+
+qpat_status forward_out(qpat_ctx* c, double* phi_out, double* h_out) {
+    if (!phi_out && !h_out) return QPAT_OK;
+    const int C = std::min(c->n_pad, kMaxRhs);   // n_pad: a power of two up to 16, or a multiple of 16
+    const dim3 g(grid_for(c->N, kTrN, 1 << 30), c->n_pad / C), blk(kThreads);
+    QPAT_DISPATCH_B(C, hipLaunchKernelGGL(k_forward_out<BB>, g, blk, 0, c->stream, c->N, c->n_ill, c->n_pad, c->phi,
+                                          c->mu, phi_out, h_out));
+    QPAT_HIP(c, hipGetLastError());
+    return QPAT_OK;
+}
+
+// K in the stencil form straight from the nodal coefficients, where the solves
+// use only that form (multigrid) and the lattice has the voxel form: dK's
+// element sums with coefficients (kappa, mu), then the boundary term. The
+// sliced-ELL form is then assembled only if a Jacobi-PCG solve asks for it
+// (pcg_solve). The element loop reads 24 tetrahedra a row and adds into the
+// row in memory: 1.69 ms at 97^3 and 0.19 ms for its conversion; this: 0.05 ms.
+qpat_status assemble_K_lattice(qpat_ctx* c, bool* done) {
+    *done = false;
+    if (!mg_available(c, Op::K)) return QPAT_OK;
+    QPAT_TRY(vox_check_rows(c));
+    if (c->vox_rows != 1) return QPAT_OK;
+    if (!c->dKc) QPAT_TRY(dalloc(c, &c->dKc, 2 * c->N));
+    const dim3 blk(kThreads);
+    hipLaunchKernelGGL(k_dk_coef, dim3(grid_for(c->N, kThreads, 1 << 30)), blk, 0, c->stream, c->N, c->kappa, c->mu,
+                       static_cast<const double*>(nullptr), c->dKc);
+    hipLaunchKernelGGL(k_dk_voxel, dim3((std::min<int64_t>((c->N + kThreads - 1) / kThreads, 4096) + 7) & ~7), blk, 0,
+                       c->stream, c->N, c->lat, vox_geo(c), c->dKc, c->KU64);
+    hipLaunchKernelGGL(k_robin_lattice, dim3(grid_for(c->N, kThreads, 1 << 30)), blk, 0, c->stream, c->N, c->lat,
+                       c->bfaces, c->barea, c->n2f_ptr, c->n2f, c->KU64);
+    QPAT_HIP(c, hipGetLastError());
+    *done = true;
     return QPAT_OK;
 }
 
@@ -839,21 +976,19 @@ qpat_status forward_solve_x0(qpat_ctx* c, const double* x0, SolveStats* st) {
 
 qpat_status jvp_core(qpat_ctx* c, const double* s, int mode, double* out, SolveStats* st) {
     const int B = block_size(c);
-    const dim3 g(grid_for(c->N * B, kThreads, 1 << 30)), blk(kThreads);
+    const dim3 g(grid_for(c->N * B, kThreads, 1 << 30)), blk(kThreads), gt(grid_for(c->N, kTrN, 1 << 30));
     // lattice meshes: dK(s) once in the stencil form, then one tiled stencil
     // product per block (else the element loop per block)
     const bool lat = c->lat.on && c->opts.operator_format == 1 && B >= 8;
     if (lat) {
-        if (!c->dK) {
-            QPAT_TRY(dalloc(c, &c->dK, (int64_t)(c->lat.m + 1) * c->N));
-            QPAT_TRY(dalloc(c, &c->dKc, 2 * c->N));
-        }
+        if (!c->dK) QPAT_TRY(dalloc(c, &c->dK, (int64_t)(c->lat.m + 1) * c->N));
+        if (!c->dKc) QPAT_TRY(dalloc(c, &c->dKc, 2 * c->N));
         hipLaunchKernelGGL(k_dk_coef, dim3(grid_for(c->N, kThreads, 1 << 30)), blk, 0, c->stream, c->N, c->kappa, c->mu,
                            s, c->dKc);
         // a multiple of 8 blocks (the XCD strips), several per compute unit
         const dim3 gd((std::min<int64_t>((c->N * kSplit + kThreads - 1) / kThreads, 4096) + 7) & ~7);
-        QPAT_TRY(vox_check(c));
-        if (c->vox == 1)
+        QPAT_TRY(vox_check_rows(c));
+        if (c->vox_rows == 1)
             hipLaunchKernelGGL(k_dk_voxel, dim3((std::min<int64_t>((c->N + kThreads - 1) / kThreads, 4096) + 7) & ~7),
                                blk, 0, c->stream, c->N, c->lat, vox_geo(c), c->dKc, c->dK);
         else if (c->lat.m == 7)
@@ -872,8 +1007,13 @@ qpat_status jvp_core(qpat_ctx* c, const double* s, int mode, double* out, SolveS
                                                   c->stream, c->N, c->tets, c->geo, c->n2t_ptr, c->n2t, c->kappa,
                                                   c->mu, s, c->phi, c->n_pad, col0, c->b64));
         QPAT_TRY(k_solve(c, B, st));
-        QPAT_DISPATCH_B(B, hipLaunchKernelGGL(k_jvp_out<BB>, g, blk, 0, c->stream, c->N, c->mu, c->phi, s, c->x64,
-                                              c->n_pad, c->n_ill, col0, mode, out, c->lw, c->lu, c->ls));
+        if (mode == 0) {
+            QPAT_DISPATCH_B(B, hipLaunchKernelGGL(k_jvp_out_ext<BB>, gt, blk, 0, c->stream, c->N, c->mu, c->phi, s, c->x64,
+                                                  c->n_pad, c->n_ill, col0, out));
+        } else {
+            QPAT_DISPATCH_B(B, hipLaunchKernelGGL(k_jvp_out<BB>, g, blk, 0, c->stream, c->N, c->mu, c->phi, s, c->x64,
+                                                  c->n_pad, c->n_ill, col0, mode, out, c->lw, c->lu, c->ls));
+        }
     }
     QPAT_HIP(c, hipGetLastError());
     return QPAT_OK;
@@ -886,7 +1026,7 @@ qpat_status jvp_core(qpat_ctx* c, const double* s, int mode, double* out, SolveS
 // then gathered per node once.
 qpat_status vjp_core(qpat_ctx* c, const double* t, int mode, double* out, SolveStats* st) {
     const int B = block_size(c);
-    const dim3 g(grid_for(c->N * B, kThreads, 1 << 30)), blk(kThreads);
+    const dim3 g(grid_for(c->N * B, kThreads, 1 << 30)), blk(kThreads), gt(grid_for(c->N, kTrN, 1 << 30));
     const int tmode = mode == 0 ? 0 : 1;
     if (!c->tq) {
         QPAT_TRY(dalloc(c, &c->tq, c->E));
@@ -896,8 +1036,13 @@ qpat_status vjp_core(qpat_ctx* c, const double* t, int mode, double* out, SolveS
     const bool vox = c->vox == 1;   // per-voxel sums [Nv][16] in tr (4 E = 24 Nv values)
     const int64_t Nv = vox ? c->E / 6 : 0;
     for (int col0 = 0; col0 < c->n_pad; col0 += B) {
-        QPAT_DISPATCH_B(B, hipLaunchKernelGGL(k_adj_rhs<BB>, g, blk, 0, c->stream, c->N, c->mu, c->n_pad, c->n_ill,
-                                              col0, tmode, t, c->lw, c->lu, c->b64));
+        if (tmode == 0) {
+            QPAT_DISPATCH_B(B, hipLaunchKernelGGL(k_adj_rhs_ext<BB>, gt, blk, 0, c->stream, c->N, c->mu, c->n_ill, col0, t,
+                                                  c->b64));
+        } else {
+            QPAT_DISPATCH_B(B, hipLaunchKernelGGL(k_adj_rhs<BB>, g, blk, 0, c->stream, c->N, c->mu, c->n_pad, c->n_ill,
+                                                  col0, c->lw, c->lu, c->b64));
+        }
         QPAT_TRY(k_solve(c, B, st));
         if (vox) {
             QPAT_DISPATCH_B(B, hipLaunchKernelGGL(k_gadj_vox<BB>, vox_grid(Nv, BB), blk, 0, c->stream, c->lat,

@@ -1373,6 +1373,11 @@ PcgArgs<T> make_args(qpat_ctx* c, Op op, int B) {
 }  // namespace
 
 qpat_status pcg_solve(qpat_ctx* c, Op op, int B, SolveStats* st, bool has_x0) {
+    if (op == Op::K && !c->K_sell) {   // the forward call assembled the stencil form alone
+        QPAT_TRY(assemble_K(c));
+        QPAT_TRY(lattice_convert(c, Op::K));
+        c->K_sell = true;
+    }
     const bool mixed = c->opts.precision == 1 && op == Op::K;
     const bool defl = op == Op::Prior && c->opts.prior_deflate;
     const double rtol = op == Op::K ? c->opts.pcg_rtol : c->opts.prior_rtol;

@@ -180,6 +180,7 @@ struct qpat_ctx {
     float* Kdinv32 = nullptr;
     double* KU64 = nullptr;        // lattice form of K, [N][m+1]
     float* KU32 = nullptr;
+    bool K_sell = false;           // K64, K32, Kdinv and KU32 hold the current K (else only KU64 does)
     bool have_forward = false;
 
     // prior
@@ -219,9 +220,12 @@ struct qpat_ctx {
     double* dKc = nullptr;         // [N][2] its coefficients kappa s1, mu s2
     double* tq = nullptr;          // [E] per-tetrahedron sums of J^T t (stiffness part)
     double* tr = nullptr;          // [E][4] per-tetrahedron sums of J^T t (mass part)
-    // voxel form of the G kernels (Kuhn lattices of equal voxels): 0 not yet
-    // checked against the element form, 1 in use, -1 not applicable
+    // voxel form of the assembly and G kernels (Kuhn lattices of equal voxels): 0
+    // not yet checked against the element form, 1 in use, -1 not applicable. vox:
+    // the kernels of J^T t (-1 at set-up where the lattice rules the form out);
+    // vox_rows: the rows of K and dK(s)
     int32_t vox = -1;
+    int32_t vox_rows = 0;
     double vox_h[3] = {0.0, 0.0, 0.0};   // the lattice spacings along x, y, z
 
     // LSQR
@@ -320,7 +324,8 @@ qpat_status assemble_prior(qpat_ctx* c, const double* kt, const double* mt, int 
                            double q, double b_over_a, double delta);
 qpat_status assemble_load(qpat_ctx* c, const double* phi_src);
 qpat_status exp_params(qpat_ctx* c, double kappa0, double mu0, const double* beta);
-qpat_status check_positive(qpat_ctx* c, const double* a, int64_t n, bool* ok);
+// both arrays finite and > 0 (one pass, one host check)
+qpat_status check_positive(qpat_ctx* c, const double* a, const double* b, int64_t n, bool* ok);
 
 // ---- pcg.hip
 // Which operator a solve uses.
@@ -368,6 +373,10 @@ qpat_status spmv64(qpat_ctx* c, Op op, int B, const double* x, double* y, double
 
 // ---- jacobian.hip
 qpat_status forward_solve(qpat_ctx* c, SolveStats* st);
+// phi and h = mu phi to the caller's [n_ill][N] arrays (or null)
+qpat_status forward_out(qpat_ctx* c, double* phi_out, double* h_out);
+// K's stencil form KU64 alone, without the sliced-ELL form; *done = false where it does not apply
+qpat_status assemble_K_lattice(qpat_ctx* c, bool* done);
 // J s: s [2N]; mode 0 -> out [n_ill][N]; mode 1 (LSQR) -> q = W (J s) - alpha u
 qpat_status jvp_core(qpat_ctx* c, const double* s, int mode, double* out, SolveStats* st);
 // J^T t: mode 0 -> t [n_ill][N]; mode 1 (LSQR) -> t = W u (interleaved), out = J^T t - beta what

@@ -324,3 +324,28 @@ def test_tiled_products_at_tile_edges(nx, ny, nz, n_ill, precision):
     ctx.vjp(dev(t), jt)
     assert_close(host(js).reshape(n_ill, N), lin.jvp(s), 1e-10, "J s")
     assert_close(host(jt), lin.vjp(t), 1e-10, "J^T t")
+
+
+@pytest.mark.parametrize("n_ill", [1, 3, 8, 18])
+def test_data_arrays_and_options_switched_after_forward(n_ill):
+    """phi, h, J s and J^T t in the caller's [n_ill][N] layout for every column count of the transposes (N no
+    multiple of their 128-node tiles), then the same products after switching the context to Jacobi-PCG on the
+    sliced-ELL form, which the forward call did not assemble. Solves at 1e-12, element-wise 1e-10 (mixed
+    Jacobi-PCG stops on the same FP64 residual: 1e-9)."""
+    coords, tets, bfaces, kappa, mu, src = box_problem(9, 6, 12, n_ill, 40 + n_ill)
+    ctx, _, _ = solve(coords, tets, bfaces, kappa, mu, src, pcg_rtol=1e-12)
+    lin = Linearisation(fem.geometry(coords, tets, bfaces), kappa, mu, src)
+    N = coords.shape[0]
+    rng = np.random.default_rng(n_ill)
+    s, t = rng.standard_normal(2 * N), rng.standard_normal((n_ill, N))
+    phi, h, js = (torch.empty(n_ill * N, dtype=torch.float64, device="cuda") for _ in range(3))
+    jt = torch.empty(2 * N, dtype=torch.float64, device="cuda")
+    ctx.forward(dev(kappa), dev(mu), phi, h)
+    assert_close(host(phi).reshape(n_ill, N), lin.phi, 1e-10, "phi")
+    assert_close(host(h).reshape(n_ill, N), lin.h, 1e-10, "h")
+    for kw, tol in (({}, 1e-10), ({"pcg_precond": 0, "operator_format": 0}, 1e-10), ({"precision": 1}, 1e-9)):
+        ctx.set_opts(**kw)
+        ctx.jvp(dev(s), js)
+        ctx.vjp(dev(t), jt)
+        assert_close(host(js).reshape(n_ill, N), lin.jvp(s), tol, f"J s {kw}")
+        assert_close(host(jt), lin.vjp(t), tol, f"J^T t {kw}")
