@@ -319,37 +319,59 @@ __device__ __forceinline__ const double* rows_of(const LvArgs& L, int sys) {
     return L.U + (int64_t)sys * L.N * (L.m + 1);
 }
 
-// (A x)_i for the thread's V right-hand sides; x points at the thread's
-// first right-hand side of node 0 ([N][B] interleaved). Interior rows skip
-// the lattice-edge tests.
-template <int KIND, int B, typename XT = double>
-__device__ __forceinline__ TB<B> apply(const LvArgs& L, const double* __restrict__ U, const XT* __restrict__ x,
-                                       int32_t ix, int32_t iy, int32_t iz, int32_t i) {
+// the thread's V right-hand sides of a node, from memory: x points at its
+// first right-hand side of node 0 ([N][B] interleaved)
+template <int B, typename XT>
+struct VecAt {
+    const XT* x;
+    __device__ __forceinline__ TB<B> operator()(int32_t i) const { return vldx<TB<B>>(x + i * B); }
+};
+
+// which neighbours of a node are on the lattice: six tests a node, whose lane
+// masks the (compile-time) offsets combine on the scalar unit
+struct Edges {
+    bool xp, xm, yp, ym, zp, zm;
+    __device__ __forceinline__ Edges(int32_t nx, int32_t ny, int32_t nz, int32_t ix, int32_t iy, int32_t iz)
+        : xp(ix + 1 < nx), xm(ix > 0), yp(iy + 1 < ny), ym(iy > 0), zp(iz + 1 < nz), zm(iz > 0) {}
+    __device__ __forceinline__ bool has(int dx, int dy, int dz) const {
+        return (dx == 0 || (dx > 0 ? xp : xm)) & (dy == 0 || (dy > 0 ? yp : ym)) & (dz == 0 || (dz > 0 ? zp : zm));
+    }
+};
+
+// (A x)_i for the thread's V right-hand sides; x(j): its values at node j
+// (VecAt, or formed on the fly: DirAt). A row's loads, from clamped indices,
+// are all issued before its sums: a scheduling barrier keeps them together
+// (left to itself the compiler takes them in five or six round trips: the
+// last sweep on 33^3 nodes 19 us instead of 7 with 4 right-hand sides, 18
+// instead of 5 in FP32 with one).
+template <int KIND, int B, typename X>
+__device__ __forceinline__ TB<B> apply(const LvArgs& L, const double* __restrict__ U, const X& x, int32_t ix,
+                                       int32_t iy, int32_t iz, int32_t i) {
     using T = TB<B>;
     if constexpr (KIND == 0) {
         const int32_t M1 = L.m + 1;
-        T s = U[i * M1] * vldx<T>(x + i * B);
+        T s = U[i * M1] * x(i);
         for (int j = 0; j < L.m; ++j) {
             const int4 t = L.tab[j];
             if (ix + t.x >= 0 && ix + t.x < L.nx && iy + t.y >= 0 && iy + t.y < L.ny && iz + t.z < L.nz)
-                s += U[i * M1 + j + 1] * vldx<T>(x + (i + t.w) * B);
+                s += U[i * M1 + j + 1] * x(i + t.w);
             if (ix - t.x >= 0 && ix - t.x < L.nx && iy - t.y >= 0 && iy - t.y < L.ny && iz - t.z >= 0)
-                s += U[(i - t.w) * M1 + j + 1] * vldx<T>(x + (i - t.w) * B);
+                s += U[(i - t.w) * M1 + j + 1] * x(i - t.w);
         }
         return s;
     } else if constexpr (KIND == 4) {   // 27-point whole rows, entry-major ([27][N])
-        const bool inner = ix > 0 && ix < L.nx - 1 && iy > 0 && iy < L.ny - 1 && iz > 0 && iz < L.nz - 1;
-        T s = U[i] * vldx<T>(x + i * B);
+        const Edges in(L.nx, L.ny, L.nz, ix, iy, iz);
+        T s = U[i] * x(i);
 #pragma unroll
         for (int j = 0; j < 13; ++j) {
             const int code = 14 + j;
             const int dx = code % 3 - 1, dy = (code / 3) % 3 - 1, dz = code / 9 - 1;
             const int32_t lin = dx + L.nx * (dy + L.ny * dz);
-            const bool up = inner || (ix + dx >= 0 && ix + dx < L.nx && iy + dy >= 0 && iy + dy < L.ny && iz + dz < L.nz);
-            const bool lo = inner || (ix - dx >= 0 && ix - dx < L.nx && iy - dy >= 0 && iy - dy < L.ny && iz - dz >= 0);
+            const bool up = in.has(dx, dy, dz);
+            const bool lo = in.has(-dx, -dy, -dz);
             // loads from clamped indices and selected sums: no branch per
             // neighbour, so all of a row's loads are in flight together
-            const T xu = vldx<T>(x + (up ? i + lin : i) * B), xl = vldx<T>(x + (lo ? i - lin : i) * B);
+            const T xu = x(up ? i + lin : i), xl = x(lo ? i - lin : i);
             const double cu = U[(1 + j) * L.N + i], cl = U[(14 + j) * L.N + i];
             s = up ? s + cu * xu : s;
             s = lo ? s + cl * xl : s;
@@ -357,16 +379,16 @@ __device__ __forceinline__ TB<B> apply(const LvArgs& L, const double* __restrict
         return s;
     } else if constexpr (KIND == 6) {   // the kind-4 rows in FP32 (a preconditioner's coarse operator)
         const float* Uw = reinterpret_cast<const float*>(U);
-        const bool inner = ix > 0 && ix < L.nx - 1 && iy > 0 && iy < L.ny - 1 && iz > 0 && iz < L.nz - 1;
-        T s = static_cast<double>(Uw[i]) * vldx<T>(x + i * B);
+        const Edges in(L.nx, L.ny, L.nz, ix, iy, iz);
+        T s = static_cast<double>(Uw[i]) * x(i);
 #pragma unroll
         for (int j = 0; j < 13; ++j) {
             const int code = 14 + j;
             const int dx = code % 3 - 1, dy = (code / 3) % 3 - 1, dz = code / 9 - 1;
             const int32_t lin = dx + L.nx * (dy + L.ny * dz);
-            const bool up = inner || (ix + dx >= 0 && ix + dx < L.nx && iy + dy >= 0 && iy + dy < L.ny && iz + dz < L.nz);
-            const bool lo = inner || (ix - dx >= 0 && ix - dx < L.nx && iy - dy >= 0 && iy - dy < L.ny && iz - dz >= 0);
-            const T xu = vldx<T>(x + (up ? i + lin : i) * B), xl = vldx<T>(x + (lo ? i - lin : i) * B);
+            const bool up = in.has(dx, dy, dz);
+            const bool lo = in.has(-dx, -dy, -dz);
+            const T xu = x(up ? i + lin : i), xl = x(lo ? i - lin : i);
             const double cu = static_cast<double>(Uw[(1 + j) * L.N + i]), cl = static_cast<double>(Uw[(14 + j) * L.N + i]);
             s = up ? s + cu * xu : s;
             s = lo ? s + cl * xl : s;
@@ -383,19 +405,25 @@ __device__ __forceinline__ TB<B> apply(const LvArgs& L, const double* __restrict
         double u[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) u[k] = static_cast<double>(Uw[k * L.N + i]);
-        const bool inner = ix > 0 && ix < L.nx - 1 && iy > 0 && iy < L.ny - 1 && iz > 0 && iz < L.nz - 1;
-        T s = u[0] * vldx<T>(x + i * B);
+        const Edges in(L.nx, L.ny, L.nz, ix, iy, iz);
+        T s = u[0] * x(i), xu[7], xl[7];
+        double cl[7];
 #pragma unroll
         for (int j = 0; j < 7; ++j) {
             const int dx = kKx[j], dy = kKy[j], dz = kKz[j];
             const int32_t lin = dx + L.nx * (dy + L.ny * dz);
-            const bool up = inner || (ix + dx < L.nx && iy + dy < L.ny && iz + dz < L.nz);
-            const bool lo = inner || (ix - dx >= 0 && iy - dy >= 0 && iz - dz >= 0);
+            const bool up = in.has(dx, dy, dz);
+            const bool lo = in.has(-dx, -dy, -dz);
             const int32_t il = lo ? i - lin : i;
-            const T xu = vldx<T>(x + (up ? i + lin : i) * B), xl = vldx<T>(x + il * B);
-            const double cl = static_cast<double>(Uw[(1 + j) * L.N + il]);
-            s = up ? s + u[1 + j] * xu : s;
-            s = lo ? s + cl * xl : s;
+            xu[j] = x(up ? i + lin : i);
+            xl[j] = x(il);
+            cl[j] = static_cast<double>(Uw[(1 + j) * L.N + il]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            s = in.has(kKx[j], kKy[j], kKz[j]) ? s + u[1 + j] * xu[j] : s;
+            s = in.has(-kKx[j], -kKy[j], -kKz[j]) ? s + cl[j] * xl[j] : s;
         }
         return s;
     } else {
@@ -409,8 +437,9 @@ __device__ __forceinline__ TB<B> apply(const LvArgs& L, const double* __restrict
             u[2 * k] = t.x;
             u[2 * k + 1] = t.y;
         }
-        const bool inner = ix > 0 && ix < L.nx - 1 && iy > 0 && iy < L.ny - 1 && iz > 0 && iz < L.nz - 1;
-        T s = u[0] * vldx<T>(x + i * B);
+        const Edges in(L.nx, L.ny, L.nz, ix, iy, iz);
+        T s = u[0] * x(i), xu[MM], xl[MM];
+        double cl[MM];
 #pragma unroll
         for (int j = 0; j < MM; ++j) {
             const int code = 14 + j;
@@ -418,13 +447,22 @@ __device__ __forceinline__ TB<B> apply(const LvArgs& L, const double* __restrict
             const int dy = KIND == 1 ? kKy[j] : (code / 3) % 3 - 1;
             const int dz = KIND == 1 ? kKz[j] : code / 9 - 1;
             const int32_t lin = dx + L.nx * (dy + L.ny * dz);
-            const bool up = inner || (ix + dx >= 0 && ix + dx < L.nx && iy + dy >= 0 && iy + dy < L.ny && iz + dz < L.nz);
-            const bool lo = inner || (ix - dx >= 0 && ix - dx < L.nx && iy - dy >= 0 && iy - dy < L.ny && iz - dz >= 0);
+            const bool up = in.has(dx, dy, dz);
+            const bool lo = in.has(-dx, -dy, -dz);
             const int32_t il = lo ? i - lin : i;
-            const T xu = vldx<T>(x + (up ? i + lin : i) * B), xl = vldx<T>(x + il * B);
-            const double cl = U[il * M1 + j + 1];
-            s = up ? s + u[j + 1] * xu : s;
-            s = lo ? s + cl * xl : s;
+            xu[j] = x(up ? i + lin : i);
+            xl[j] = x(il);
+            cl[j] = U[il * M1 + j + 1];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < MM; ++j) {
+            const int code = 14 + j;
+            const int dx = KIND == 1 ? kKx[j] : code % 3 - 1;
+            const int dy = KIND == 1 ? kKy[j] : (code / 3) % 3 - 1;
+            const int dz = KIND == 1 ? kKz[j] : code / 9 - 1;
+            s = in.has(dx, dy, dz) ? s + u[j + 1] * xu[j] : s;
+            s = in.has(-dx, -dy, -dz) ? s + cl[j] * xl[j] : s;
         }
         return s;
     }
@@ -536,21 +574,45 @@ __device__ __forceinline__ bool pair_active(const MgScal* sc, int sys, int v) {
 }
 
 // partial sums of the block: parts[lane][slot][block]
-// a block's partial sum; a grid smaller than kMgBlocks also clears the slots
-// no block of it owns, so that the reductions can read a fixed count
+// a block's partial sum; the reduction that follows is told how many blocks wrote
 __device__ __forceinline__ void put(double* parts, int lane, int slot, double val) {
-    double* p = parts + (lane * 4 + slot) * kMgBlocks;
-    p[blockIdx.x] = val;
-    for (int b = blockIdx.x + gridDim.x; b < kMgBlocks; b += gridDim.x) p[b] = 0.0;
+    parts[(lane * 4 + slot) * kMgBlocks + blockIdx.x] = val;
 }
 
-// per-right-hand-side block sums of a V-wide accumulator, written as partials
-template <int B>
-__device__ __forceinline__ void put_sums(double* parts, int sys, int slot, TB<B> acc, double* sm) {
+// per-right-hand-side block sums of NS V-wide accumulators, written as the
+// partials of their slots: the shuffles of all of them interleave and they
+// share one barrier (one after the other they were 3 us of a small lattice's
+// last sweep). sm: kSumLds doubles.
+constexpr int kSumLds = (kMgT / 64) * 16 * 3;
+template <int B, int... SLOT>
+__device__ __forceinline__ void put_sums(double* parts, int sys, const TB<B> (&acc)[sizeof...(SLOT)], double* sm) {
+    constexpr int V = Pk<B>::V, BV = Pk<B>::BV, NS = sizeof...(SLOT);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double t[NS][V];
 #pragma unroll
-    for (int c = 0; c < Pk<B>::V; ++c) {
-        const double t = group_sum<Pk<B>::BV>(comp(acc, c), sm);
-        if (threadIdx.x < Pk<B>::BV) put(parts, sys * B + threadIdx.x * Pk<B>::V + c, slot, t);
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+        for (int c = 0; c < V; ++c) t[n][c] = comp(acc[n], c);
+#pragma unroll
+    for (int off = 32; off >= BV; off >>= 1)
+#pragma unroll
+        for (int n = 0; n < NS; ++n)
+#pragma unroll
+            for (int c = 0; c < V; ++c) t[n][c] += __shfl_xor(t[n][c], off);
+    __syncthreads();   // sm's last use
+    if (lane < BV)
+#pragma unroll
+        for (int n = 0; n < NS; ++n)
+#pragma unroll
+            for (int c = 0; c < V; ++c) sm[(wave * NS + n) * B + lane * V + c] = t[n][c];
+    __syncthreads();
+    if (threadIdx.x < NS * B) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < kMgT / 64; ++w) v += sm[w * NS * B + threadIdx.x];
+        int n = threadIdx.x / B, at = 0;
+        ((at = n-- == 0 ? SLOT : at), ...);
+        put(parts, sys * B + threadIdx.x % B, at, v);
     }
 }
 
@@ -867,7 +929,7 @@ __global__ __launch_bounds__(kMgT) void k_mg_smooth(SmArgs a, const double* __re
                                                     double* __restrict__ parts) {
     using T = TB<B>;
     constexpr int V = Pk<B>::V;
-    __shared__ double sm[(kMgT / 64) * 16];
+    __shared__ double sm[kSumLds];
     const int v = threadIdx.x % Pk<B>::BV;
     const int32_t M1 = a.L.m + 1;
     for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
@@ -882,7 +944,7 @@ __global__ __launch_bounds__(kMgT) void k_mg_smooth(SmArgs a, const double* __re
         if (pair_active<B>(a.sc, sys, v)) {
             walk<Pk<B>::BV>(a.L.nx, a.L.ny, a.L.nz, [&](int32_t ix, int32_t iy, int32_t iz, int32_t i, int32_t) {
                 const T bi = vld<T>(bs + i * B);
-                const T ax = apply<KIND, B, VT>(a.L, U, xs, ix, iy, iz, i);
+                const T ax = apply<KIND, B>(a.L, U, VecAt<B, VT>{xs}, ix, iy, iz, i);
                 T yi = vldx<T>(xs + i * B) + (w * dinv[i]) * (bi - ax);
                 if constexpr (sizeof(VT) == 4) {
                     static_assert(B == 1, "FP32 sweep output: one right-hand side per thread");
@@ -897,9 +959,7 @@ __global__ __launch_bounds__(kMgT) void k_mg_smooth(SmArgs a, const double* __re
             });
         }
         if constexpr (DOTS) {
-            put_sums<B>(parts, sys, 0, rz, sm);
-            put_sums<B>(parts, sys, 2, z1, sm);
-            put_sums<B>(parts, sys, 3, r1, sm);
+            put_sums<B, 0, 2, 3>(parts, sys, {rz, z1, r1}, sm);
         }
     }
 }
@@ -920,7 +980,7 @@ __global__ __launch_bounds__(kMgT) void k_mg_resid(SmArgs a, const double* __res
         const VT* xs = x + o;
         VT* rs = r + o;
         walk<Pk<B>::BV>(a.L.nx, a.L.ny, a.L.nz, [&](int32_t ix, int32_t iy, int32_t iz, int32_t i, int32_t) {
-            vstx<T>(rs + i * B, vld<T>(bs + i * B) - apply<KIND, B, VT>(a.L, U, xs, ix, iy, iz, i));
+            vstx<T>(rs + i * B, vld<T>(bs + i * B) - apply<KIND, B>(a.L, U, VecAt<B, VT>{xs}, ix, iy, iz, i));
         });
     }
 }
@@ -1017,6 +1077,68 @@ __global__ __launch_bounds__(kMgT) void k_mg_restrict(SmArgs c, int32_t nx, int3
     }
 }
 
+// k_mg_resid on level f and k_mg_restrict into level c in one pass: 32 lanes a
+// coarse node, each of the first 27 forming the residual at one fine node of
+// its support (every fine residual is formed up to 8 times, and never stored)
+// and the weighted sum taken across the lanes. One launch less on the levels
+// where launches are the time (fuse_small): 4.8 us against 4.3 + 3.8 on 17^3
+// nodes with 4 right-hand sides.
+template <int KIND, int B, bool OPW, typename VT = double>
+__global__ __launch_bounds__(kMgT) void k_mg_resid_restrict(SmArgs f, SmArgs c, const double* __restrict__ b,
+                                                            const VT* __restrict__ x, double* __restrict__ bc,
+                                                            double* __restrict__ xc, const float* __restrict__ Wc) {
+    using T = TB<B>;
+    constexpr int V = Pk<B>::V, BV = Pk<B>::BV;
+    const int32_t nx = f.L.nx, ny = f.L.ny, nz = f.L.nz;
+    const int64_t Nf = f.L.N, Nc = c.L.N;
+    const int sub = threadIdx.x & 31;
+    const int64_t item = (blockIdx.x * (int64_t)kMgT + threadIdx.x) >> 5;
+    if (item >= Nc * BV) return;   // whole groups of 32 lanes
+    const int v = static_cast<int>(item % BV);
+    const int32_t I = static_cast<int32_t>(item / BV);
+    const int32_t M1 = f.L.m + 1;
+    const WPack pk{nx, ny, nz};
+    int32_t Ix, Iy, Iz;
+    coords(I, c.L.nx, c.L.ny, Ix, Iy, Iz);
+    const int dx = sub % 3, dy = (sub / 3) % 3, dz = sub / 9;
+    const int32_t gx = 2 * Ix + dx - 1, gy = 2 * Iy + dy - 1, gz = 2 * Iz + dz - 1;
+    const bool in = sub < 27 && gx >= 0 && gx < nx && gy >= 0 && gy < ny && gz >= 0 && gz < nz;
+    for (int sys = blockIdx.y; sys < f.nsys; sys += gridDim.y) {
+        if (!pair_active<B>(c.sc, sys, v)) continue;
+        T s = 0.0;
+        if (in) {
+            const int32_t i = gx + nx * (gy + ny * gz);
+            double wgt;
+            if constexpr (OPW)
+                wgt = static_cast<double>(
+                    (Wc + sys * pk.size())[pk.atc((dx == 0) + 2 * (dy == 0) + 4 * (dz == 0), gx, gy, gz)]);
+            else
+                wgt = (dx == 1 ? 1.0 : 0.5) * (dy == 1 ? 1.0 : 0.5) * (dz == 1 ? 1.0 : 0.5);
+            const int64_t o = sys * Nf * B + v * V;
+            T ri = vld<T>(b + o + i * B) -
+                   apply<KIND, B>(f.L, rows_of<KIND>(f.L, sys), VecAt<B, VT>{x + o}, gx, gy, gz, i);
+            if constexpr (sizeof(VT) == 4) ri = held_as<VT>(ri);   // as the two kernels store it between them
+            s = wgt * ri;
+        }
+        double t[V];
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            t[k] = comp(s, k);
+#pragma unroll
+            for (int off = 16; off >= 1; off >>= 1) t[k] += __shfl_xor(t[k], off);
+        }
+        if (sub == 0) {
+            const double wd = c.w[sys * c.nlev + c.lev] * c.dinv[sys * Nc + I];
+            const int64_t oc = sys * Nc * B + I * (int64_t)B + v * V;
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                bc[oc + k] = t[k];
+                xc[oc + k] = wd * t[k];
+            }
+        }
+    }
+}
+
 // x = base + P xc on fine level f (coarse lattice cx, cy, cz). base = x, or
 // with FIRST the first sweep w D^{-1} b, which is then never stored. P:
 // trilinear, or the packed weights Wc ([nsys][WPack size]).
@@ -1100,16 +1222,33 @@ __global__ __launch_bounds__(kMgT) void k_mg_dense(int64_t Nc, int nsys, const d
     const int sys = blockIdx.z, v = blockIdx.y;
     if (!pair_active<B>(sc, sys, v)) return;   // uniform over the block
     const double* bs = b + sys * Nc * B + v * V;
+    const int lane = threadIdx.x & 63;
+    const int64_t I = blockIdx.x * (int64_t)(kMgT / 64) + (threadIdx.x >> 6);
+    const double* A = ainv + (sys * Nc + min(I, Nc - 1)) * Nc;
+    // a row's first 1024 entries in flight together, and beside the loads of b
+    // (the coarsest solve is a chain of memory round trips)
+    constexpr int NA = 16;
+    double a[NA];
+    const auto row = [&](int64_t J0) {
+#pragma unroll
+        for (int u = 0; u < NA; ++u) {
+            const int64_t J = J0 + u * 64 + lane;
+            a[u] = J < Nc ? A[J] : 0.0;
+        }
+    };
+    row(0);
 #pragma unroll 4
     for (int64_t J = threadIdx.x; J < Nc; J += kMgT) bl[J] = vld<T>(bs + J * B);
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int64_t I = blockIdx.x * (int64_t)(kMgT / 64) + (threadIdx.x >> 6);
     if (I >= Nc) return;   // whole wavefronts, after the barrier
-    const double* A = ainv + (sys * Nc + I) * Nc;
     T s = 0.0;
-#pragma unroll 4   // several rows' loads in flight (the coarsest solve is latency-bound)
-    for (int64_t J = lane; J < Nc; J += 64) s += A[J] * bl[J];
+    for (int64_t J0 = 0;;) {
+#pragma unroll
+        for (int u = 0; u < NA; ++u) s += a[u] * bl[min(J0 + u * 64 + lane, Nc - 1)];
+        J0 += NA * 64;
+        if (J0 >= Nc) break;
+        row(J0);
+    }
     double out[V];
 #pragma unroll
     for (int c = 0; c < V; ++c) {
@@ -1141,10 +1280,8 @@ struct PcgMg {
     MgScal* sc;           // [lanes]
     double rtol2;
     int32_t maxit, deflate, nsys;
-    int32_t nb;           // blocks of the kernels that write partials
     // region coarse space (one right-hand side per system), kreg = 0: off;
-    // nbr: blocks of the kernels that write the region partials (the later
-    // slots hold zeros)
+    // nbr: blocks of the kernels that write the region partials
     int32_t kreg, nbr;
     int32_t p32;          // 1: the direction in FP32 on the tiled 16-right-hand-side path (mixed precision)
     int32_t ring;         // kRing: directions and alphas kept in the ring (x formed later), 0: x updated each iteration
@@ -1216,7 +1353,7 @@ template <int KIND, int B>
 __global__ __launch_bounds__(kMgT) void k_mgp_spmv(PcgMg a) {
     using T = TB<B>;
     constexpr int V = Pk<B>::V;
-    __shared__ double sm[(kMgT / 64) * 16];
+    __shared__ double sm[kSumLds];
     const int v = threadIdx.x % Pk<B>::BV;
     const int32_t M1 = a.L.m + 1;
     for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
@@ -1227,111 +1364,205 @@ __global__ __launch_bounds__(kMgT) void k_mgp_spmv(PcgMg a) {
         T pq = 0.0;
         if (pair_active<B>(a.sc, sys, v)) {
             walk<Pk<B>::BV>(a.L.nx, a.L.ny, a.L.nz, [&](int32_t ix, int32_t iy, int32_t iz, int32_t i, int32_t) {
-                const T qi = apply<KIND, B>(a.L, U, ps, ix, iy, iz, i);
+                const T qi = apply<KIND, B>(a.L, U, VecAt<B, double>{ps}, ix, iy, iz, i);
                 vst<T>(qs + i * B, qi);
                 pq += vld<T>(ps + i * B) * qi;
             });
         }
-        put_sums<B>(a.parts, sys, 0, pq, sm);
+        put_sums<B, 0>(a.parts, sys, {pq}, sm);
+    }
+}
+
+// The new direction z - c + beta po at a node, formed where it is read (ZF: z
+// in FP32). reg, ytab: the region coarse-space part of z (one right-hand
+// side per system), ytab[g + 1] = y_g - ybar with g = -1 for no region.
+template <int B, bool ZF>
+struct DirAt {
+    const double* z;
+    const double* po;
+    TB<B> c, beta;
+    const int32_t* reg;
+    const double* ytab;
+    __device__ __forceinline__ TB<B> operator()(int32_t i) const {
+        using T = TB<B>;
+        T zc = ZF ? vldf<T>(reinterpret_cast<const float*>(z) + i * B) : vld<T>(z + i * B);
+        if constexpr (B == 1)
+            if (reg) zc += ytab[reg[i] + 1];
+        return zc - c + beta * vld<T>(po + i * B);
+    }
+};
+
+// k_mgp_dir and k_mgp_spmv in one pass: pn = z - c + beta po, q = A pn, partial
+// pn.q, every neighbour's direction formed again from z and po. Twice the
+// vector reads of the two kernels, but one launch less: for the lattices
+// where the launches, not the reads, are the time (fuse_small): 5.5 us
+// against 2.9 + 5.3 on 17^3 nodes with 4 right-hand sides.
+template <int KIND, int B, bool ZF = false>
+__global__ __launch_bounds__(kMgT) void k_mgp_dir_spmv(PcgMg a) {
+    using T = TB<B>;
+    constexpr int V = Pk<B>::V;
+    __shared__ double sm[kSumLds], ytab[kRegMax + 1];
+    const int v = threadIdx.x % Pk<B>::BV;
+    const int32_t M1 = a.L.m + 1;
+    for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
+        if (B == 1 && a.kreg > 0) {
+            __syncthreads();
+            if (threadIdx.x <= kRegMax)
+                ytab[threadIdx.x] = (threadIdx.x > 0 ? a.ry[sys * kRegMax + threadIdx.x - 1] : 0.0) - a.rcorr[2 * sys + 1];
+            __syncthreads();
+        }
+        const LaneScal<B> s(a.sc, sys, v);
+        const double* U = rows_of<KIND>(a.L, sys);
+        const int64_t o = sys * a.L.N * B + v * V;
+        double* ps = a.pn + o;
+        double* qs = a.q + o;
+        T pq = 0.0;
+        if (s.on0 || s.on1) {
+            const double* zs = ZF ? reinterpret_cast<const double*>(reinterpret_cast<const float*>(a.z) + o) : a.z + o;
+            const DirAt<B, ZF> p{zs, a.po + o, s.c, s.beta, B == 1 && a.kreg > 0 ? a.reg + sys * a.L.N : nullptr, ytab};
+            walk<Pk<B>::BV>(a.L.nx, a.L.ny, a.L.nz, [&](int32_t ix, int32_t iy, int32_t iz, int32_t i, int32_t) {
+                const T pi = p(i);
+                const T qi = apply<KIND, B>(a.L, U, p, ix, iy, iz, i);
+                vst<T>(ps + i * B, s.on0 && s.on1 ? pi : pick(pi, vld<T>(ps + i * B), s.on0, s.on1));
+                vst<T>(qs + i * B, qi);
+                pq += pi * qi;
+            });
+        }
+        put_sums<B, 0>(a.parts, sys, {pq}, sm);
     }
 }
 
 // x += alpha pn, r -= alpha q (right-hand sides that stopped keep both),
-// partial r.r
+// partial r.r, and the V-cycle's first sweep on the finest level, x0 =
+// w D^{-1} r, from the new r where it is at hand
 template <int B>
-__global__ __launch_bounds__(kMgT) void k_mgp_update(PcgMg a) {
+__global__ __launch_bounds__(kMgT) void k_mgp_update(PcgMg a, SmArgs m, double* __restrict__ x0) {
     using T = TB<B>;
     constexpr int V = Pk<B>::V, BV = Pk<B>::BV;
-    __shared__ double sm[(kMgT / 64) * 16];
+    __shared__ double sm[kSumLds];
     const int v = threadIdx.x % BV;
     for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
         const LaneScal<B> s(a.sc, sys, v);
         const int64_t o = sys * a.L.N * B + v * V;
         T rr = 0.0;
         if (s.on0 || s.on1) {
+            const double w = m.w[sys * m.nlev + m.lev];
+            const double* dinv = m.dinv + sys * a.L.N;
             QPAT_MG_ELEMS(e, a.L.N * BV) {
                 const int64_t at = o + (e / BV) * B;
+                const double wd = w * dinv[e / BV];
                 const T p = vld<T>(a.pn + at), r = vld<T>(a.r + at), x = vld<T>(a.x + at);
                 const T rn = pick(r - s.alpha * vld<T>(a.q + at), r, s.on0, s.on1);
                 vst<T>(a.x + at, pick(x + s.alpha * p, x, s.on0, s.on1));
                 vst<T>(a.r + at, rn);
+                vst<T>(x0 + at, wd * rn);
                 rr += rn * rn;
             }
         }
-        put_sums<B>(a.parts, sys, 1, rr, sm);
+        put_sums<B, 1>(a.parts, sys, {rr}, sm);
     }
 }
 
-// deterministic sum of one lane's partials (one block)
-__device__ double red(const double* parts, int nb, int lane, int slot, double* sm) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) s += parts[(lane * 4 + slot) * kMgBlocks + b];
-    return group_sum<1>(s, sm);
+// Deterministic sums of NS slots of one lane's partials, written by nb blocks
+// (one block of kMgT threads). The constructor issues every load, take() adds:
+// the one-block kernels that use this are a chain of memory round trips and
+// little else, and this way the partials come beside the lane's scalars.
+template <int NS>
+struct Red {
+    static constexpr int NL = kMgBlocks / kMgT;
+    double v[NS][NL];
+    __device__ __forceinline__ Red(const double* parts, int nb, int lane, const int (&slot)[NS]) {
+#pragma unroll
+        for (int c = 0; c < NS; ++c) {
+            const double* p = parts + (lane * 4 + slot[c]) * kMgBlocks;
+#pragma unroll
+            for (int u = 0; u < NL; ++u) {
+                const int b = u * kMgT + static_cast<int>(threadIdx.x);
+                v[c][u] = u * kMgT < nb && b < nb ? p[b] : 0.0;
+            }
+        }
+    }
+    // the sums, valid in thread 0 (sm: NS doubles a wavefront)
+    __device__ __forceinline__ void take(double* sm, double (&out)[NS]) const {
+        const int ln = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        double s[NS];
+#pragma unroll
+        for (int c = 0; c < NS; ++c) {
+            s[c] = 0.0;
+#pragma unroll
+            for (int u = 0; u < NL; ++u) s[c] += v[c][u];
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+            for (int c = 0; c < NS; ++c) s[c] += __shfl_xor(s[c], off);
+        if (ln == 0)
+#pragma unroll
+            for (int c = 0; c < NS; ++c) sm[wave * NS + c] = s[c];
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < NS; ++c) {
+            out[c] = 0.0;
+            if (threadIdx.x == 0)
+                for (int w = 0; w < kMgT / 64; ++w) out[c] += sm[w * NS + c];
+        }
+    }
+};
+
+// phase 1 of k_mgp_scalars for one lane that iterates (thread 0 writes)
+__device__ __forceinline__ void scalars_rr(const PcgMg& a, const Red<1>& part, int lane, double* sm) {
+    MgScal& s = a.sc[lane];
+    const double tol = a.rtol2 * s.bnorm2;
+    const int iters = s.iters + 1;
+    double rr[1];
+    part.take(sm, rr);
+    if (threadIdx.x == 0) {
+        s.rr = rr[0];
+        s.iters = iters;
+        if (rr[0] <= tol) {
+            s.done = 1;
+            s.active = 0;
+        } else if (iters >= a.maxit) {
+            s.active = 0;
+        }
+    }
 }
 
-// the same sums of three slots of one lane in one pass (each in red's order)
-__device__ void red3(const double* parts, int nb, int lane, const int (&slot)[3], double* sm3, double (&out)[3]) {
-    double s[3] = {0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nb; b += blockDim.x)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) s[c] += parts[(lane * 4 + slot[c]) * kMgBlocks + b];
-    const int ln = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) s[c] += __shfl_xor(s[c], off);
-        if (ln == 0) sm3[wave * 3 + c] = s[c];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        double t = 0.0;
-        if (threadIdx.x == 0)
-            for (int w = 0; w < kMgT / 64; ++w) t += sm3[w * 3 + c];
-        out[c] = t;
-    }
-    __syncthreads();
-}
-
-// one block per lane (blockIdx.y). phase 0: alpha = rz / pq; phase 1: rr,
-// convergence, iteration count; phase 2 (after the V-cycle): c, beta, rz;
-// phase 3: start of a run (after its first V-cycle): c, rz, beta = 0
-__global__ __launch_bounds__(kMgT) void k_mgp_scalars(PcgMg a, int phase) {
-    __shared__ double sm[kMgT / 64];
+// one block per lane (blockIdx.y); nb blocks wrote the partials. phase 0:
+// alpha = rz / pq; phase 1: rr, convergence, iteration count; phase 2 (after
+// the V-cycle): c, beta, rz; phase 3: start of a run (after its first
+// V-cycle): c, rz, beta = 0
+__global__ __launch_bounds__(kMgT) void k_mgp_scalars(PcgMg a, int nb, int phase) {
+    __shared__ double sm[(kMgT / 64) * 3];
     const int lane = blockIdx.y;
+    MgScal& s = a.sc[lane];
+    const Red<1> p1(a.parts, phase == 2 || phase == 3 ? 0 : nb, lane, {phase == 1 ? 1 : 0});
+    const Red<3> p3(a.parts, phase == 2 || phase == 3 ? nb : 0, lane, {0, 2, 3});
+    const double rz_old = s.rz;
     // the direction ring: each iteration's alpha per lane (0 where the lane did
     // not iterate), and the iteration counter, advanced once at the end of an
     // iteration (phase 2, lane 0's block)
-    const bool on = a.sc[lane].active != 0;
+    const bool on = s.active != 0;
     if (a.ring > 0 && threadIdx.x == 0) {
         if (phase == 0 && !on) a.ahist[(*a.slot % a.ring) * gridDim.y + lane] = 0.0;
         if (phase == 2 && lane == 0) *a.slot += 1;
     }
     if (!on) return;
-    MgScal& s = a.sc[lane];
     if (phase == 0) {
-        const double pq = red(a.parts, a.nb, lane, 0, sm);
+        const int slot = a.ring > 0 ? *a.slot % a.ring : 0;
+        double pq[1];
+        p1.take(sm, pq);
         if (threadIdx.x == 0) {
-            s.pq = pq;
-            s.alpha = pq != 0.0 ? s.rz / pq : 0.0;
-            if (a.ring > 0) a.ahist[(*a.slot % a.ring) * gridDim.y + lane] = s.alpha;
+            s.pq = pq[0];
+            const double alpha = pq[0] != 0.0 ? rz_old / pq[0] : 0.0;
+            s.alpha = alpha;
+            if (a.ring > 0) a.ahist[slot * gridDim.y + lane] = alpha;
         }
     } else if (phase == 1) {
-        const double rr = red(a.parts, a.nb, lane, 1, sm);
-        if (threadIdx.x == 0) {
-            s.rr = rr;
-            s.iters += 1;
-            if (rr <= a.rtol2 * s.bnorm2) {
-                s.done = 1;
-                s.active = 0;
-            } else if (s.iters >= a.maxit) {
-                s.active = 0;
-            }
-        }
+        scalars_rr(a, p1, lane, sm);
     } else {
-        __shared__ double sm3[(kMgT / 64) * 3];
         double v[3];
-        red3(a.parts, a.nb, lane, {0, 2, 3}, sm3, v);
+        p3.take(sm, v);
         double rz = v[0];
         const double z1 = v[1], r1 = v[2];
         if (threadIdx.x == 0) {
@@ -1346,7 +1577,7 @@ __global__ __launch_bounds__(kMgT) void k_mgp_scalars(PcgMg a, int phase) {
             const double c = a.deflate ? z1 / static_cast<double>(a.L.N) : 0.0;
             rz -= (c + ybar) * r1;     // r.(z - mean z)
             s.c = c;
-            s.beta = (phase == 2 && s.rz != 0.0) ? rz / s.rz : 0.0;
+            s.beta = (phase == 2 && rz_old != 0.0) ? rz / rz_old : 0.0;
             s.rz = rz;
         }
     }
@@ -1389,12 +1620,10 @@ __global__ __launch_bounds__(kMgT) void k_reg_rsum(PcgMg a, double* __restrict__
             if (lane == 0) sm[wave * kRegMax + j] = t;
         }
         __syncthreads();
-        if (threadIdx.x < kRegMax) {   // the slots no block owns read 0 (fewer blocks than kMgBlocks)
+        if (threadIdx.x < kRegMax) {
             double t = 0.0;
             for (int w = 0; w < kMgT / 64; ++w) t += sm[w * kRegMax + threadIdx.x];
-            double* p = rparts + (sys * kRegMax + threadIdx.x) * kMgBlocks;
-            p[blockIdx.x] = t;
-            for (int b = blockIdx.x + gridDim.x; b < kMgBlocks; b += gridDim.x) p[b] = 0.0;
+            rparts[(sys * kRegMax + threadIdx.x) * kMgBlocks + blockIdx.x] = t;
         }
         __syncthreads();
     }
@@ -1407,8 +1636,7 @@ __global__ __launch_bounds__(kMgT) void k_reg_rsum(PcgMg a, double* __restrict__
 // coarse space, the partial sums of Z^T r. Four nodes' loads in flight per trip (buffer loads
 // with 32-bit offsets: N 8 < 2^31; past the end they read 0 and the stores
 // drop); few, full blocks (kMgGrid), so that each block's reduction of its
-// kRegMax region sums is spread over many nodes. Slots of blocks past the
-// grid read as zero.
+// kRegMax region sums is spread over many nodes.
 template <typename XT>
 __global__ __launch_bounds__(kMgT, 4) void k_mgp_update_first(PcgMg a, SmArgs s, XT* __restrict__ x0,
                                                            double* __restrict__ rparts) {
@@ -1470,9 +1698,7 @@ __global__ __launch_bounds__(kMgT, 4) void k_mgp_update_first(PcgMg a, SmArgs s,
             if (threadIdx.x < kRegMax) {
                 double v = 0.0;
                 for (int wv = 0; wv < kMgT / 64; ++wv) v += sm[wv * kRegMax + threadIdx.x];
-                double* pp = rparts + (sys * kRegMax + threadIdx.x) * kMgBlocks;
-                pp[blockIdx.x] = v;
-                for (int b = blockIdx.x + gridDim.x; b < kMgBlocks; b += gridDim.x) pp[b] = 0.0;
+                rparts[(sys * kRegMax + threadIdx.x) * kMgBlocks + blockIdx.x] = v;
             }
             __syncthreads();
         }
@@ -1480,13 +1706,20 @@ __global__ __launch_bounds__(kMgT, 4) void k_mgp_update_first(PcgMg a, SmArgs s,
 }
 
 // y = E^{-1} Z^T r and the corrections r.(Z y), mean(Z y) (deflation) of the
-// dot products and the direction; one block per system (blockIdx.y)
-__global__ __launch_bounds__(kMgT) void k_reg_solve(PcgMg a, const double* __restrict__ rparts,
+// dot products and the direction; one block per system (blockIdx.y).
+// nb > 0: first phase 1 of k_mgp_scalars for the system's one right-hand side,
+// from the nb partials that the update left beside those of Z^T r
+__global__ __launch_bounds__(kMgT) void k_reg_solve(PcgMg a, int nb, const double* __restrict__ rparts,
                                                     const double* __restrict__ einv, const double* __restrict__ rsize,
                                                     double* __restrict__ ry, double* __restrict__ rcorr) {
     __shared__ double zr[kRegMax], yy[kRegMax];
     const int sys = blockIdx.y;
-    if (!a.sc[sys].active) return;
+    if (!a.sc[sys].active) return;   // as it was before this kernel: uniform over the block
+    if (nb > 0) {
+        __syncthreads();             // every thread has read active
+        __shared__ double sm[kMgT / 64];
+        scalars_rr(a, Red<1>(a.parts, nb, sys, {1}), sys, sm);
+    }
     const int t = threadIdx.x;
     {   // fixed-order block sums of the partials, every region in one pass
         // (slots of regions past kreg hold zeros)
@@ -1697,12 +1930,13 @@ __global__ __launch_bounds__(kMgT) void k_mgp_bstats(PcgMg a, const double* __re
     }
 }
 
-__global__ __launch_bounds__(kMgT) void k_mgp_init(PcgMg a, double inv_delta) {
-    __shared__ double sm[kMgT / 64];
+__global__ __launch_bounds__(kMgT) void k_mgp_init(PcgMg a, int nb, double inv_delta) {
+    __shared__ double sm[(kMgT / 64) * 2];
     const int lane = blockIdx.y;
     if (a.ring > 0 && lane == 0 && threadIdx.x == 0) *a.slot = 0;   // a run's first iteration: slot 0
-    const double s1 = red(a.parts, a.nb, lane, 2, sm);
-    const double s2 = red(a.parts, a.nb, lane, 3, sm);
+    double v[2];
+    Red<2>(a.parts, nb, lane, {2, 3}).take(sm, v);
+    const double s1 = v[0], s2 = v[1];
     if (threadIdx.x == 0) {
         MgScal& s = a.sc[lane];
         const double mean = a.deflate ? s1 / static_cast<double>(a.L.N) : 0.0;
@@ -1767,7 +2001,7 @@ template <int KIND, int B>
 __global__ __launch_bounds__(kMgT) void k_mgp_true(PcgMg a, const double* __restrict__ b) {
     using T = TB<B>;
     constexpr int V = Pk<B>::V;
-    __shared__ double sm[(kMgT / 64) * 16];
+    __shared__ double sm[kSumLds];
     const int v = threadIdx.x % Pk<B>::BV;
     const int32_t M1 = a.L.m + 1;
     for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
@@ -1796,14 +2030,16 @@ __global__ __launch_bounds__(kMgT) void k_mgp_true(PcgMg a, const double* __rest
             vst<T>(rs + i * B, ri);
             rr += ri * ri;
         });
-        put_sums<B>(a.parts, sys, 1, rr, sm);
+        put_sums<B, 1>(a.parts, sys, {rr}, sm);
     }
 }
 
-__global__ __launch_bounds__(kMgT) void k_mgp_true_fin(PcgMg a, int reopen) {
+__global__ __launch_bounds__(kMgT) void k_mgp_true_fin(PcgMg a, int nb, int reopen) {
     __shared__ double sm[kMgT / 64];
     const int lane = blockIdx.y;
-    const double rr = red(a.parts, a.nb, lane, 1, sm);
+    double v[1];
+    Red<1>(a.parts, nb, lane, {1}).take(sm, v);
+    const double rr = v[0];
     if (threadIdx.x == 0) {
         MgScal& s = a.sc[lane];
         s.rr = rr;
@@ -3703,8 +3939,58 @@ inline SmArgs level_args(const MgState& M, int l) {
     return a;
 }
 
+// Small levels: the time of a kernel is its launch and its first memory round
+// trips, and two passes in one launch (k_mgp_dir_spmv, k_mg_resid_restrict)
+// beat the two with fewer reads. In threads of the walk kernels; a Jacobian
+// pair (separate -> fused) on 17^3 nodes with 4 right-hand sides 1449 -> 1302
+// us, 33^3 with 4 2250 -> 2210, 41^3 with 1 2578 -> 2498; M_delta's kernels
+// read their transfer weights as well: 17^3 838 -> 793, 25^3 1756 -> 1742,
+// 33^3 1484 -> 1583.
+constexpr int64_t kFuseK = 80000, kFuseM = 32768;
+template <int B>
+inline bool fuse_small(int64_t n, int nsys) {
+    return n * Pk<B>::BV * nsys <= (nsys == 1 ? kFuseK : kFuseM);
+}
+
+// level l's residual to level l + 1's b and first sweep xc, in one launch
+// (f0: level 0's vectors in FP32)
+template <int B>
+void launch_resid_restrict(const MgState& M, int l, hipStream_t st, const double* b, const double* x, double* xc,
+                           bool f0) {
+    const MgLevel& L = M.lv[l];
+    const MgLevel& C = M.lv[l + 1];
+    const SmArgs f = level_args(M, l), c = level_args(M, l + 1);
+    const dim3 g = sys_rows(dim3((unsigned)((C.N * Pk<B>::BV * 32 + kMgT - 1) / kMgT)), B, M.nsys);
+    const auto go = [&](auto kind, auto opw, auto x_) {
+        hipLaunchKernelGGL((k_mg_resid_restrict<decltype(kind)::value, B, decltype(opw)::value,
+                                                std::remove_const_t<std::remove_pointer_t<decltype(x_)>>>),
+                           g, dim3(kMgT), 0, st, f, c, b, x_, C.b, xc, L.Wc);
+    };
+    using std::integral_constant;
+    const auto kinds = [&](auto opw) {
+        switch (vkind(L)) {
+            case 1: go(integral_constant<int, 1>{}, opw, x); break;
+            case 2: go(integral_constant<int, 2>{}, opw, x); break;
+            case 3: go(integral_constant<int, 3>{}, opw, x); break;
+            case 4: if constexpr (B == 1) go(integral_constant<int, 4>{}, opw, x); break;
+            case 5: if constexpr (B == 1) go(integral_constant<int, 5>{}, opw, x); break;
+            case 6: if constexpr (B == 1) go(integral_constant<int, 6>{}, opw, x); break;
+            default: go(integral_constant<int, 0>{}, opw, x); break;
+        }
+    };
+    if constexpr (B == 1) {   // M_delta: operator-dependent weights
+        if (f0)
+            go(integral_constant<int, 5>{}, std::true_type{}, reinterpret_cast<const float*>(x));
+        else if (M.opdep)
+            kinds(std::true_type{});
+        else
+            kinds(std::false_type{});
+    } else {
+        kinds(std::false_type{});
+    }
+}
+
 // first_done: the PCG update already wrote the finest level's first sweep
-// (k_mgp_update_first)
 template <int B>
 void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev = nullptr, const double* b0 = nullptr,
             bool resid_done = false, bool lo32 = false, bool first_done = false) {
@@ -3735,6 +4021,12 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
             std::swap(xl[l], tl[l]);
         }
         if (l == 0 && ev) (void)hipEventRecord(ev[0], st);
+        const bool tiled = (l == 0 && tg.on) || (B == 16 && tiled27(tg, l)) ||
+                           (tg.on && l < kMgMaxLevels && tg.rst[l].on && !M.opdep);
+        if (!tiled && !ev && fuse_small<B>(L.N, M.nsys)) {   // residual and restriction in one launch
+            launch_resid_restrict<B>(M, l, st, bl, xl[l], xl[l + 1], l == 0 && f0);
+            continue;
+        }
         if (l == 0 && fused0 && resid_done)
             ;   // the PCG update produced level 0's residual (kTUpdResid)
         else if (l == 0 && fused0)
@@ -3819,6 +4111,13 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
     }
 }
 
+// blocks of the V-cycle's last finest-level sweep, which leave r.z, sum z, sum r
+template <int B>
+inline int last_blocks(const MgState& M, const TileGeo& tg, bool lo32) {
+    if (z32_path<B>(M, tg)) return lo32 ? tg.ps_blocks32 : tg.ps_blocks;
+    return tg.on ? tg.blocks : static_cast<int>(sgrid<B>(M.lv[0].N).x);
+}
+
 MgState*& state_of(qpat_ctx* c, Op op) { return op == Op::K ? c->mgk : c->mg; }
 
 template <int B>
@@ -3839,7 +4138,6 @@ PcgMg pcg_args(qpat_ctx* c, Op op) {
     a.maxit = c->opts.pcg_maxit;
     a.deflate = op == Op::Prior ? c->opts.prior_deflate : 0;
     a.nsys = M.nsys;
-    a.nb = static_cast<int32_t>(sgrid<B>(c->N).x);
     a.nbr = static_cast<int32_t>(vgrid(c->N, kMgGrid).x);   // k_reg_rsum, k_mgp_update_first
     a.kreg = B == 1 ? M.kreg : 0;
     a.p32 = op == Op::K && c->opts.precision == 1 ? 1 : 0;
@@ -3853,14 +4151,16 @@ PcgMg pcg_args(qpat_ctx* c, Op op) {
 }
 
 // the region coarse-space part of the preconditioner for the current r
-// (sums_done: the PCG update already left the partial sums of Z^T r)
+// (sums_done: the PCG update already left the partial sums of Z^T r and of
+// r.r, and the scalars of the latter are due)
 template <int B>
 void region_solve(const MgState& M, const PcgMg& a, hipStream_t st, bool sums_done = false) {
     if (a.kreg <= 0) return;
     // each block reduces kRegMax sums: fewer, fuller blocks than the walk kernels
     if (!sums_done)
         hipLaunchKernelGGL(k_reg_rsum, sys_rows(vgrid(a.L.N, kMgGrid), B, a.nsys), dim3(kMgT), 0, st, a, M.rparts);
-    hipLaunchKernelGGL(k_reg_solve, dim3(1, a.nsys), dim3(kMgT), 0, st, a, M.rparts, M.einv, M.rsize, M.ry, M.rcorr);
+    hipLaunchKernelGGL(k_reg_solve, dim3(1, a.nsys), dim3(kMgT), 0, st, a, sums_done ? a.nbr : 0, M.rparts, M.einv,
+                       M.rsize, M.ry, M.rcorr);
 }
 
 // one iteration after the first direction: direction and product, alpha,
@@ -3888,16 +4188,28 @@ void iteration(const MgState& M, PcgMg a, const TileGeo& tg, hipStream_t st, int
     } else if (tg.on) {
         launch_tile<kTDirSpmv, B>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, ring);
     } else {
-        if (f32v0_path<B>(M, tg))   // z in FP32
-            hipLaunchKernelGGL((k_mgp_dir<B, true>), g, dim3(kMgT), 0, st, a);
-        else
-            hipLaunchKernelGGL(k_mgp_dir<B>, g, dim3(kMgT), 0, st, a);
-        QPAT_MG_KIND(a.L.kind, B, k_mgp_spmv, g, dim3(kMgT), 0, st, a);
+        const bool zf = f32v0_path<B>(M, tg);   // z in FP32
+        if (fuse_small<B>(a.L.N, a.nsys)) {
+            if constexpr (B == 1) {
+                if (zf && a.L.kind == 3)
+                    hipLaunchKernelGGL((k_mgp_dir_spmv<3, 1, true>), g, dim3(kMgT), 0, st, a);
+                else
+                    QPAT_MG_KIND(a.L.kind, B, k_mgp_dir_spmv, g, dim3(kMgT), 0, st, a);
+            } else {
+                QPAT_MG_KIND(a.L.kind, B, k_mgp_dir_spmv, g, dim3(kMgT), 0, st, a);
+            }
+        } else {
+            if (zf)
+                hipLaunchKernelGGL((k_mgp_dir<B, true>), g, dim3(kMgT), 0, st, a);
+            else
+                hipLaunchKernelGGL(k_mgp_dir<B>, g, dim3(kMgT), 0, st, a);
+            QPAT_MG_KIND(a.L.kind, B, k_mgp_spmv, g, dim3(kMgT), 0, st, a);
+        }
     }
     if (ev) (void)hipEventRecord(ev[1], st);
-    hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, 0);
+    hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, tg.on ? tg.blocks : (int)g.x, 0);
     if (ev) (void)hipEventRecord(ev[2], st);
-    const bool upd1 = B == 1 && !fused_update(tg) && M.lv.size() > 1 && a.L.N * 8 < (int64_t(1) << 31);
+    const bool upd1 = B == 1 && !fused_update(tg) && a.L.N * 8 < (int64_t(1) << 31);
     if (fused_update(tg)) {   // r, x and the V-cycle's first sweep + residual in one pass; r alternates buffers
         double* r_old = par ? M.pr2 : M.pr;
         double* r_new = par ? M.pr : M.pr2;
@@ -3910,13 +4222,15 @@ void iteration(const MgState& M, PcgMg a, const TileGeo& tg, hipStream_t st, int
         hipLaunchKernelGGL(k_mgp_update_first<double>, sys_rows(vgrid(a.L.N, kMgGrid), B, a.nsys), dim3(kMgT), 0, st,
                            a, level_args(M, 0), M.lv[0].x, M.rparts);
     } else {
-        hipLaunchKernelGGL(k_mgp_update<B>, g, dim3(kMgT), 0, st, a);
+        hipLaunchKernelGGL(k_mgp_update<B>, g, dim3(kMgT), 0, st, a, level_args(M, 0), M.lv[0].x);
     }
     if (ev) (void)hipEventRecord(ev[3], st);
-    hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, 1);
+    const int nb1 = fused_update(tg) ? tg.blocks : upd1 ? a.nbr : (int)g.x;
+    const bool reg1 = upd1 && a.kreg > 0;   // k_reg_solve takes the scalars with it
+    if (!reg1) hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, nb1, 1);
     region_solve<B>(M, a, st, upd1);
-    vcycle<B>(M, st, tg, ev ? ev + 4 : nullptr, a.r, fused_update(tg), p32, upd1);
-    hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, 2);
+    vcycle<B>(M, st, tg, ev ? ev + 4 : nullptr, a.r, fused_update(tg), p32, !fused_update(tg));
+    hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, last_blocks<B>(M, tg, p32), 2);
 }
 
 // true residual r = b - A x of every lane, partial r.r (write_r false, tiled path:
@@ -3939,7 +4253,6 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
     PcgMg a = pcg_args<B>(c, op);
     QPAT_TRY(tile_setup<B>(c, M));
     const TileGeo tg = M.tiles[B];
-    if (tg.on) a.nb = std::max({a.nb, tg.blocks, tg.ps_blocks, tg.ps_blocks32});   // every kernel that leaves partials
     // The tiled iterations keep their directions and alphas in a ring and form
     // x = x + sum alpha_j p_j (k_mgp_ring_flush) before x is read: the update
     // then neither reads nor writes x nor reads p.
@@ -3979,15 +4292,15 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
     };
     if (tg.on && !a.deflate && !has_x0) {   // one pass over b
         hipLaunchKernelGGL(k_mgp_start0<B>, g, dim3(kMgT), 0, sm, a, c->b64);
-        hipLaunchKernelGGL(k_mgp_init, lanes, dim3(kMgT), 0, sm, a, c->delta > 0 ? 1.0 / c->delta : 0.0);
+        hipLaunchKernelGGL(k_mgp_init, lanes, dim3(kMgT), 0, sm, a, (int)g.x, c->delta > 0 ? 1.0 / c->delta : 0.0);
     } else {
         hipLaunchKernelGGL(k_mgp_bstats<B>, g, dim3(kMgT), 0, sm, a, c->b64);
-        hipLaunchKernelGGL(k_mgp_init, lanes, dim3(kMgT), 0, sm, a, c->delta > 0 ? 1.0 / c->delta : 0.0);
+        hipLaunchKernelGGL(k_mgp_init, lanes, dim3(kMgT), 0, sm, a, (int)g.x, c->delta > 0 ? 1.0 / c->delta : 0.0);
         hipLaunchKernelGGL(k_mgp_start<B>, g, dim3(kMgT), 0, sm, a, c->b64, has_x0 ? 1 : 0);
     }
     if (has_x0) {   // r = b - A x0; lanes that x0 already solves stop here
         true_residual<B>(M, a, tg, c->b64, sm);
-        hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, 1);
+        hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, tg.on ? tg.blocks : (int)g.x, 1);
     }
     QPAT_HIP(c, hipGetLastError());
     auto fetch = [&]() -> qpat_status {
@@ -4012,7 +4325,8 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         // first direction of a run: z = V(r) (+ Z y), p = z - c
         region_solve<B>(M, a, sm);
         vcycle<B>(M, sm, tg, nullptr, nullptr, false, a.p32 != 0 && z32_path<B>(M, tg));
-        hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, sm, a, 3);
+        hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, sm, a,
+                           last_blocks<B>(M, tg, a.p32 != 0 && z32_path<B>(M, tg)), 3);
         QPAT_HIP(c, hipGetLastError());
         // Iterations run in chunks of even length between host checks. The
         // first is kMgChunk0 long; later ones cover the iterations that the
@@ -4127,7 +4441,7 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         // confirm on the true residual; a failed check restarts from the true residual
         QPAT_TRY(ring_flush());
         true_residual<B>(M, a, tg, c->b64, sm, !tg.on);
-        hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, restart < 3 ? 1 : 0);
+        hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, tg.on ? tg.blocks : (int)g.x, restart < 3 ? 1 : 0);
         QPAT_HIP(c, hipGetLastError());
     }
     QPAT_TRY(ring_flush());   // a run that stopped before iterating still needs its x = 0

@@ -326,6 +326,42 @@ def test_tiled_products_at_tile_edges(nx, ny, nz, n_ill, precision):
     assert_close(host(jt), lin.vjp(t), 1e-10, "J^T t")
 
 
+@pytest.mark.parametrize("nx,ny,nz,block,n_ill", [(42, 42, 42, 1, 1), (43, 42, 42, 1, 2), (42, 42, 42, 2, 2),
+                                                  (43, 42, 42, 2, 1), (33, 33, 33, 4, 3), (33, 34, 33, 4, 4)])
+def test_k_solves_either_side_of_the_fused_sizes(nx, ny, nz, block, n_ill):
+    """Lattices of just under and just over 80000 threads of the untiled kernels, where direction + product and
+    residual + restriction go from one kernel to two, with right-hand sides that are zero from the start:
+    multigrid against Jacobi-PCG (both at 1e-12: 1e-10 as above) in no more iterations than the fused sizes take."""
+    P = box_problem(nx, ny, nz, n_ill, nx + ny + block)
+    _, phi, info = solve(*P, max_rhs_block=block, pcg_rtol=1e-12)
+    _, ref, _ = solve(*P, max_rhs_block=block, pcg_rtol=1e-12, pcg_precond=0)
+    assert_close(phi, ref, 1e-10, "phi")
+    assert info["relres_max"] <= 1e-12 and info["iters_max"] <= 20, info
+
+
+@pytest.mark.parametrize("deflate", [1, 0])
+@pytest.mark.parametrize("nx,ny,nz", [(24, 24, 25), (25, 25, 24)])
+def test_prior_solves_either_side_of_the_fused_sizes(nx, ny, nz, deflate):
+    """The same for M_delta (32768 threads of its two systems), a diffusivity with a jump that takes the region
+    coarse space: M_delta (M_delta^{-1} p) = p to the solver tolerance, 1e-10, times the condition of the scaled
+    operator (a jump of the parameter of 0.5 a voxel: 1e-8 as above without deflation, 1e-9 with it)."""
+    coords, tets, bfaces, _, _, _ = box_problem(nx, ny, nz, 1, 3)
+    from paper_1512_02796_amd import qpat
+    N = coords.shape[0]
+    inside = np.sum((coords - coords.mean(axis=0)) ** 2, axis=1) < (nx / 4) ** 2
+    rng = np.random.default_rng(nx)
+    kt, mt = 0.5 * inside + 0.01 * rng.standard_normal(N), -0.5 * inside + 0.01 * rng.standard_normal(N)
+    ctx = qpat.Context(dev(coords), dev(tets, torch.int32), dev(bfaces, torch.int32),
+                       opts=qpat.default_opts(prior_rtol=1e-10, prior_deflate=deflate))
+    ctx.prior_setup(dev(kt), dev(mt))
+    p = dev(rng.standard_normal(2 * N))
+    r, y = torch.empty_like(p), torch.empty_like(p)
+    info = ctx.prior_solve(p, r)
+    assert info["relres_max"] <= 1e-10 and info["iters_max"] <= 40, info
+    ctx.prior_apply(r, y)
+    assert rel(host(y), host(p)) <= (1e-9 if deflate else 1e-8)
+
+
 @pytest.mark.parametrize("n_ill", [1, 3, 8, 18])
 def test_data_arrays_and_options_switched_after_forward(n_ill):
     """phi, h, J s and J^T t in the caller's [n_ill][N] layout for every column count of the transposes (N no
