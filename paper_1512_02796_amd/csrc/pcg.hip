@@ -6,13 +6,14 @@
 // goes through this engine. Stopping rule: ||b - A x||_2 <= rtol ||b||_2 on
 // the FP64 true residual.
 //
-// One iteration is two kernels:
-//   dir_spmv : p <- D^{-1} r - c + beta p (recomputed on the fly for every
-//              gathered neighbour, p ping-pongs between two buffers),
-//              q = A p, partial p.q; the last block to finish reduces the
-//              partials in fixed order and sets alpha = r.z / p.q.
+// One iteration is two passes, each followed by a one-block kernel that
+// reduces its partial sums in fixed order:
+//   dir_spmv : p <- D^{-1} r - c + beta p (on small systems recomputed on the
+//              fly for every gathered neighbour, else formed first; p
+//              ping-pongs between two buffers), q = A p, partial p.q; then
+//              alpha = r.z / p.q.
 //   update   : x += alpha p, r -= alpha q, partial r.D^{-1}r and r.r (and
-//              the deflation sums); the last block sets beta and flags.
+//              the deflation sums); then beta and the flags.
 // All scalars stay on the device; the host reads them once per chunk of
 // iterations to schedule FP64 true-residual recomputations (reliable updates
 // in mixed precision, confirmation of convergence in both modes).
@@ -27,7 +28,8 @@
 namespace qpat {
 namespace {
 
-constexpr int kUnroll = 16;   // neighbours gathered per row before the arithmetic
+constexpr int kUnroll = 16;   // entries of a row loaded before the arithmetic
+constexpr int kGather = 8;     // of which the fused direction gathers the neighbours together
 constexpr int kMaxBlocks = 2048;  // blocks per system (partial-sum buffer: 5 x kMaxSys x kMaxBlocks)
 
 template <typename T>
@@ -36,7 +38,7 @@ struct PcgArgs {
     int64_t N;
     int32_t nsys;
     int32_t gs;          // blocks per system (multiple of 8)
-    int32_t rpb;         // rows per block (multiple of 64)
+    int32_t rpb;         // rows per block (whole passes of kThreads / B rows)
     const T* vals;       // [nsys][len]
     const T* dinv;       // [nsys][N]
     const double* vals64;
@@ -112,28 +114,74 @@ __device__ __forceinline__ void write_partial(double* partials, int v, int gs, d
     partials[(int64_t)v * gs + local] = val;
 }
 
-__device__ void count_active(PcgScal* sc, PcgShared* sh, int S) {
-    if (threadIdx.x == 0) {
-        int n = 0;
-        for (int i = 0; i < S; ++i) n += sc[i].active;
-        sh->n_active = n;
-    }
+// active: of right-hand side threadIdx.x (0 in threads past the last one, all
+// in the first wavefront: kMaxSys <= 64)
+__device__ void count_active(PcgShared* sh, bool active) {
+    static_assert(kMaxSys <= 64, "one wavefront counts the right-hand sides");
+    const uint64_t on = __ballot(active);
+    if (threadIdx.x == 0) sh->n_active = __popcll(on);
 }
 
 // ---------------------------------------------------------------- iteration
+// p <- D^{-1} r - c + beta p, the direction alone (right-hand sides that
+// stopped carry theirs over to the other buffer)
 template <typename T, int B, bool DEFL>
+__global__ __launch_bounds__(kThreads) void k_dir(PcgArgs<T> a) {
+    int32_t sys;
+    int64_t r0, r1;
+    block_rows(a.gs, a.rpb, a.N, sys, r0, r1);
+    const int k = threadIdx.x % B;
+    const int n_active = a.sh->n_active;
+    const int par = a.sh->parity;
+    const PcgScal scl = a.sc[sys * B + k];
+    if (n_active == 0) return;
+    const bool act = scl.active != 0;
+    const T beta = static_cast<T>(scl.beta);
+    const T cc = DEFL ? static_cast<T>(scl.c) : T(0);
+    const T* __restrict__ dinv = a.dinv + (int64_t)sys * a.N;
+    const T* __restrict__ r = a.r + (int64_t)sys * a.N * B;
+    const T* __restrict__ po = (par ? a.pb : a.pa) + (int64_t)sys * a.N * B;
+    T* __restrict__ pn = (par ? a.pa : a.pb) + (int64_t)sys * a.N * B;
+    constexpr int RS = kThreads / B;
+    for (int64_t row = r0 + threadIdx.x / B; row < r1; row += 4 * RS) {   // four rows' loads in flight
+        T dv[4], rv[4], pv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t at = min(row + u * RS, r1 - 1);
+            dv[u] = dinv[at];
+            rv[u] = r[at * B + k];
+            pv[u] = po[at * B + k];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (row + u * RS < r1) pn[(row + u * RS) * B + k] = act ? dv[u] * rv[u] - cc + beta * pv[u] : pv[u];
+    }
+}
+
+// q = A p and partial p.q on sliced ELL, after k_dir (FUSED = false), or with
+// the direction formed here: p = D^{-1} r - c + beta p_old at the row and at
+// each of its neighbours. A chain of memory round trips: the scalars and the
+// row's place, its columns and values, then the neighbours. The scheduling
+// barriers keep the loads of each together (without them the compiler waited
+// for one neighbour after another: 13.3 us on 15625 shuffled rows with 8
+// right-hand sides, now 8.8 us). FUSED gathers three values a neighbour
+// instead of one and saves a launch: for the sizes where that counts for
+// more (fused_dir), and only there (its offsets are 32-bit).
+template <typename T, int B, bool DEFL, bool FUSED>
 __global__ __launch_bounds__(kThreads) void k_dir_spmv(PcgArgs<T> a) {
     __shared__ double sm[4 * kMaxRhs];
-    if (a.sh->n_active == 0) return;
     int32_t sys;
     int64_t r0, r1;
     block_rows(a.gs, a.rpb, a.N, sys, r0, r1);
     const int k = threadIdx.x % B;
     const int sidx = sys * B + k;
+    const int n_active = a.sh->n_active;
     const int par = a.sh->parity;
+    const PcgScal scl = a.sc[sidx];
+    if (n_active == 0) return;
     const T* __restrict__ pold = par ? a.pb : a.pa;
     T* __restrict__ pnew = par ? a.pa : a.pb;
-    const PcgScal scl = a.sc[sidx];
     const bool act = scl.active != 0;
     const T beta = static_cast<T>(scl.beta);
     const T cc = DEFL ? static_cast<T>(scl.c) : T(0);
@@ -144,38 +192,70 @@ __global__ __launch_bounds__(kThreads) void k_dir_spmv(PcgArgs<T> a) {
     T* __restrict__ pn = pnew + (int64_t)sys * a.N * B;
     T* __restrict__ q = a.q + (int64_t)sys * a.N * B;
     const int32_t* __restrict__ cols = a.s.cols;
+    using Ix = std::conditional_t<FUSED, uint32_t, int64_t>;   // FUSED: N B sizeof(T) < 2^31
+    const auto at = [&](const T* v, Ix i) {
+        return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(v) + i * static_cast<Ix>(sizeof(T)));
+    };
     double acc = 0.0;
     for (int64_t row = r0 + threadIdx.x / B; row < r1; row += kThreads / B) {
         const int64_t idx = row * B + k;
         if (act) {
             const int32_t base = a.s.slice_ptr[row / kSlice] + static_cast<int32_t>(row % kSlice);
             const int32_t n = a.s.rowlen[row];
-            // all column indices and values first, then all gathers: two memory
-            // round trips per row instead of two per neighbour
+            T pi;
+            if constexpr (FUSED) {
+                const T di = dinv[row], ri = r[idx], oi = po[idx];
+                __builtin_amdgcn_sched_barrier(0);
+                pi = di * ri - cc + beta * oi;
+            } else {
+                pi = pn[idx];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // entries past the row's end: its first one again (a row holds at least its diagonal)
             int32_t col[kUnroll];
             T av[kUnroll];
 #pragma unroll
             for (int j = 0; j < kUnroll; ++j) {
-                col[j] = j < n ? cols[base + j * kSlice] : static_cast<int32_t>(row);
-                av[j] = j < n ? vals[base + j * kSlice] : T(0);
+                const int32_t e = base + (j < n ? j * kSlice : 0);
+                col[j] = cols[e];
+                av[j] = vals[e];
             }
-            const T pi = dinv[row] * r[idx] - cc + beta * po[idx];
+            __builtin_amdgcn_sched_barrier(0);
             T sum = T(0);
+            if constexpr (FUSED) {
 #pragma unroll
-            for (int j = 0; j < kUnroll; ++j) {
-                const int64_t jdx = (int64_t)col[j] * B + k;
-                const T pj = dinv[col[j]] * r[jdx] - cc + beta * po[jdx];
-                sum += av[j] * pj;
+                for (int h = 0; h < kUnroll; h += kGather) {
+                    T dj[kGather], rj[kGather], pj[kGather];
+#pragma unroll
+                    for (int j = 0; j < kGather; ++j) {
+                        const Ix jdx = static_cast<Ix>(col[h + j]) * B + k;
+                        dj[j] = at(dinv, static_cast<Ix>(col[h + j]));
+                        rj[j] = at(r, jdx);
+                        pj[j] = at(po, jdx);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int j = 0; j < kGather; ++j)
+                        sum = h + j < n ? sum + av[h + j] * (dj[j] * rj[j] - cc + beta * pj[j]) : sum;
+                }
+            } else {
+                T pj[kUnroll];
+#pragma unroll
+                for (int j = 0; j < kUnroll; ++j) pj[j] = at(pn, static_cast<Ix>(col[j]) * B + k);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < kUnroll; ++j) sum = j < n ? sum + av[j] * pj[j] : sum;
             }
             for (int32_t j = kUnroll; j < n; ++j) {   // rows longer than kUnroll (unstructured meshes)
                 const int32_t cj = cols[base + j * kSlice];
-                const int64_t jdx = (int64_t)cj * B + k;
-                sum += vals[base + j * kSlice] * (dinv[cj] * r[jdx] - cc + beta * po[jdx]);
+                const Ix jdx = static_cast<Ix>(cj) * B + k;
+                const T p = FUSED ? dinv[cj] * at(r, jdx) - cc + beta * at(po, jdx) : at(pn, jdx);
+                sum += vals[base + j * kSlice] * p;
             }
-            pn[idx] = pi;
+            if (FUSED) pn[idx] = pi;
             q[idx] = sum;
             acc += static_cast<double>(pi) * static_cast<double>(sum);
-        } else {
+        } else if (FUSED) {
             pn[idx] = po[idx];
         }
     }
@@ -438,15 +518,16 @@ __global__ __launch_bounds__(kStThreads, 4) void k_dir_stencil(PcgArgs<T> a, StA
 template <typename T, int B, bool DEFL, bool XD>
 __global__ __launch_bounds__(kThreads) void k_update(PcgArgs<T> a) {
     __shared__ double sm[4 * kMaxRhs];
-    if (a.sh->n_active == 0) return;
     int32_t sys;
     int64_t r0, r1;
     block_rows(a.gs, a.rpb, a.N, sys, r0, r1);
     const int k = threadIdx.x % B;
     const int sidx = sys * B + k;
+    const int n_active = a.sh->n_active;
     const int par = a.sh->parity;
-    const T* __restrict__ p = (par ? a.pb : a.pa) + (int64_t)sys * a.N * B;
     const PcgScal scl = a.sc[sidx];
+    if (n_active == 0) return;
+    const T* __restrict__ p = (par ? a.pb : a.pa) + (int64_t)sys * a.N * B;
     const bool act = scl.active != 0;
     const T alpha = static_cast<T>(scl.alpha);
     const T* __restrict__ dinv = a.dinv + (int64_t)sys * a.N;
@@ -664,7 +745,9 @@ struct RedArgs {
     int32_t init;
 };
 
-// out[v] = sum_b partials[v * gs + b] for v < nv, in shared memory
+// out[v] = sum_b partials[v * gs + b] for v < nv, in shared memory. A thread's
+// loads go out eight together (one after another they were most of the 4 us
+// of these one-block kernels).
 __device__ void reduce_rows(const double* partials, int nv, int gs, double* out) {
     int tpv = 64;
     while (tpv * nv > kRedThreads && tpv > 1) tpv >>= 1;
@@ -672,19 +755,18 @@ __device__ void reduce_rows(const double* partials, int nv, int gs, double* out)
     for (int v0 = 0; v0 < nv; v0 += vpp) {
         const int v = v0 + threadIdx.x / tpv;
         const int sub = threadIdx.x % tpv;
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+        double sum = 0.0;
         if (v < nv) {
             const double* P = partials + (int64_t)v * gs;
-            int b = sub;
-            for (; b + 3 * tpv < gs; b += 4 * tpv) {
-                s0 += P[b];
-                s1 += P[b + tpv];
-                s2 += P[b + 2 * tpv];
-                s3 += P[b + 3 * tpv];
+            for (int b = sub; b < gs; b += 8 * tpv) {
+                double t[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) t[u] = P[min(b + u * tpv, gs - 1)];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) sum += b + u * tpv < gs ? t[u] : 0.0;
             }
-            for (; b < gs; b += tpv) s0 += P[b];
         }
-        double sum = (s0 + s1) + (s2 + s3);
         for (int off = tpv >> 1; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
         if (sub == 0 && v < nv) out[v] = sum;
     }
@@ -694,54 +776,59 @@ __device__ void reduce_rows(const double* partials, int nv, int gs, double* out)
 // after direction+SpMV: alpha = r.z / p.q; the new p becomes current
 __global__ __launch_bounds__(kRedThreads) void k_red_alpha(RedArgs a) {
     __shared__ double tot[kMaxSys];
-    if (a.sh->n_active == 0) return;
+    const int n_active = a.sh->n_active, parity = a.sh->parity;
+    PcgScal& c = a.sc[threadIdx.x < a.S ? threadIdx.x : 0];
+    const int active = c.active;
+    const double rz = c.rz;
+    if (n_active == 0) return;
     reduce_rows(a.partials, a.S, a.gs, tot);
     if (threadIdx.x < a.S) {
-        PcgScal& c = a.sc[threadIdx.x];
-        if (c.active) {
-            c.pq = tot[threadIdx.x];
-            c.alpha = c.pq != 0.0 ? c.rz / c.pq : 0.0;
-        } else {
-            c.alpha = 0.0;
+        double alpha = 0.0;
+        if (active) {
+            const double pq = tot[threadIdx.x];
+            c.pq = pq;
+            alpha = pq != 0.0 ? rz / pq : 0.0;
         }
+        c.alpha = alpha;
     }
-    if (threadIdx.x == 0) a.sh->parity ^= 1;
+    if (threadIdx.x == 0) a.sh->parity = parity ^ 1;
 }
 
 // after the update: beta, convergence flags, iteration counts
 template <bool DEFL>
 __global__ __launch_bounds__(kRedThreads) void k_red_beta(RedArgs a) {
     __shared__ double tot[4 * kMaxSys];
-    if (a.sh->n_active == 0) return;
+    const int n_active = a.sh->n_active;
+    PcgScal& c = a.sc[threadIdx.x < a.S ? threadIdx.x : 0];
+    int active = c.active;
+    const double rz = c.rz, bnorm2 = c.bnorm2;
+    const int iters = c.iters + 1;
+    if (n_active == 0) return;
     constexpr int Q = DEFL ? 4 : 2;
     const int S = a.S;
     reduce_rows(a.partials, Q * S, a.gs, tot);
-    if (threadIdx.x < S) {
-        PcgScal& c = a.sc[threadIdx.x];
-        if (c.active) {
-            double rzn = tot[threadIdx.x];
-            const double rrn = tot[S + threadIdx.x];
-            double cn = 0.0;
-            if (DEFL) {
-                cn = tot[2 * S + threadIdx.x] / static_cast<double>(a.N);
-                rzn -= cn * tot[3 * S + threadIdx.x];
-            }
-            c.beta = c.rz != 0.0 ? rzn / c.rz : 0.0;
-            c.rz_prev = c.rz;
-            c.rz = rzn;
-            c.c = cn;
-            c.rr = rrn;
-            c.iters += 1;
-            if (rrn <= a.rtol2 * c.bnorm2 || !(rrn == rrn)) {
-                c.active = 0;
-                c.pending = 1;
-            } else if (c.iters >= a.maxit) {
-                c.active = 0;
-            }
+    if (threadIdx.x < S && active) {
+        double rzn = tot[threadIdx.x];
+        const double rrn = tot[S + threadIdx.x];
+        double cn = 0.0;
+        if (DEFL) {
+            cn = tot[2 * S + threadIdx.x] / static_cast<double>(a.N);
+            rzn -= cn * tot[3 * S + threadIdx.x];
+        }
+        c.beta = rz != 0.0 ? rzn / rz : 0.0;
+        c.rz_prev = rz;
+        c.rz = rzn;
+        c.c = cn;
+        c.rr = rrn;
+        c.iters = iters;
+        if (rrn <= a.rtol2 * bnorm2 || !(rrn == rrn)) {
+            active = c.active = 0;
+            c.pending = 1;
+        } else if (iters >= a.maxit) {
+            active = c.active = 0;
         }
     }
-    __syncthreads();
-    count_active(a.sc, a.sh, S);
+    if (threadIdx.x < 64) count_active(a.sh, threadIdx.x < S && active);
 }
 // after a true-residual recomputation (or the set-up of a run)
 template <bool DEFL>
@@ -750,6 +837,7 @@ __global__ __launch_bounds__(kRedThreads) void k_red_true(RedArgs a) {
     const int S = a.S;
     const int init = a.init;
     reduce_rows(a.partials, 5 * S, a.gs, tot);
+    bool active = threadIdx.x < S && a.sc[threadIdx.x].active;
     if (threadIdx.x < S && ((a.mask >> threadIdx.x) & 1u)) {
         PcgScal& c = a.sc[threadIdx.x];
         const double rrt = tot[threadIdx.x];
@@ -794,9 +882,9 @@ __global__ __launch_bounds__(kRedThreads) void k_red_true(RedArgs a) {
             c.done = 0;
             c.active = 1;
         }
+        active = c.active;
     }
-    __syncthreads();
-    count_active(a.sc, a.sh, S);
+    if (threadIdx.x < 64) count_active(a.sh, active);
     if (threadIdx.x == 0) {
         if (init) a.sh->parity = 0;
     }
@@ -944,6 +1032,16 @@ const void* stencil_kernel() {
     return reinterpret_cast<const void*>(&k_dir_stencil<T, B, DEFL, TL::NPF, TL::NU, KUHN ? TL::HX : 0>);
 }
 
+// Sliced ELL: whether the direction is formed where the product gathers it.
+// On shuffled lattices, a Jacobian pair (separate -> fused): 17^3 with 4
+// right-hand sides 2643 -> 2452 us, 25^3 with 8 4036 -> 3961, 29^3 with 8
+// 5873 -> 5900, 33^3 with 8 7843 -> 8654, 65^3 with 16 75 -> 116 ms; with 2
+// 25^3 3385 -> 3496; in FP32 25^3 with 16 5249 -> 5088, 33^3 8926 -> 9659.
+template <typename T>
+inline bool fused_dir(int64_t N, int B) {
+    return B >= 4 && N * B * (int64_t)sizeof(T) <= (int64_t(1) << 20);
+}
+
 // one PCG iteration: direction+SpMV, alpha, update, beta
 template <typename T, int B, bool DEFL>
 inline void launch_iteration(const PcgArgs<T>& a, const StArgs<T>& g, dim3 grid, dim3 blk, hipStream_t st,
@@ -957,8 +1055,12 @@ inline void launch_iteration(const PcgArgs<T>& a, const StArgs<T>& g, dim3 grid,
     else if (g.on)
         hipLaunchKernelGGL((k_dir_stencil<T, B, DEFL, TL::NPF, TL::NU, 0>), grid, dim3(kStThreads), TL::LDS, st, a,
                            g);
-    else
-        hipLaunchKernelGGL((k_dir_spmv<T, B, DEFL>), grid, blk, 0, st, a);
+    else if (fused_dir<T>(a.N, B))
+        hipLaunchKernelGGL((k_dir_spmv<T, B, DEFL, true>), grid, blk, 0, st, a);
+    else {
+        hipLaunchKernelGGL((k_dir<T, B, DEFL>), grid, blk, 0, st, a);
+        hipLaunchKernelGGL((k_dir_spmv<T, B, DEFL, false>), grid, blk, 0, st, a);
+    }
     if (ev) (void)hipEventRecord(ev[1], st);
     hipLaunchKernelGGL(k_red_alpha, dim3(1), dim3(kRedThreads), 0, st, ra);
     if (ev) (void)hipEventRecord(ev[2], st);
@@ -983,7 +1085,7 @@ inline void launch_true_residual(const PcgArgs<T>& a, dim3 grid, dim3 blk, hipSt
 template <typename T, int B, bool DEFL>
 qpat_status chunk_graph(qpat_ctx* c, const PcgArgs<T>& a, const StArgs<T>& g, int chunk, dim3 grid, dim3 blk,
                         hipGraphExec_t* out) {
-    const void* kfn = !g.on ? reinterpret_cast<const void*>(&k_dir_spmv<T, B, DEFL>)
+    const void* kfn = !g.on ? reinterpret_cast<const void*>(&k_dir_spmv<T, B, DEFL, false>)
                       : g.kuhn ? stencil_kernel<T, B, DEFL, true>() : stencil_kernel<T, B, DEFL, false>();
     char key[256];
     snprintf(key, sizeof key, "%p/%d/%d/%d/%.17g/%d/%d/%p/%d/%d/%d/%d", kfn, chunk, a.gs, a.nsys, a.rtol2, a.maxit,
@@ -1275,62 +1377,26 @@ qpat_status dispatch_B(qpat_ctx* c, Op op, int B, PcgArgs<T>& a, double rtol, So
     }
 }
 
-template <typename T, int B, bool DEFL>
-int occupancy_of() {
-    int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, reinterpret_cast<const void*>(&k_dir_spmv<T, B, DEFL>),
-                                                     kThreads, 0) != hipSuccess)
-        blocks = 4;
-    return blocks;
-}
-
-// resident blocks of the direction+SpMV kernel over the whole device (cached)
-int resident_blocks(qpat_ctx* c, bool defl, bool fp64, int B) {
-    const int key = (defl ? 100 : 0) + (fp64 ? 50 : 0) + B;
-    auto it = c->occupancy.find(key);
-    if (it != c->occupancy.end()) return it->second;
-    int cus = 256;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) cus = 256;
-    int per_cu = 4;
-    if (defl) per_cu = occupancy_of<double, 1, true>();
-    else if (fp64) {
-        switch (B) {
-            case 1: per_cu = occupancy_of<double, 1, false>(); break;
-            case 2: per_cu = occupancy_of<double, 2, false>(); break;
-            case 4: per_cu = occupancy_of<double, 4, false>(); break;
-            case 8: per_cu = occupancy_of<double, 8, false>(); break;
-            default: per_cu = occupancy_of<double, 16, false>(); break;
-        }
-    } else {
-        switch (B) {
-            case 1: per_cu = occupancy_of<float, 1, false>(); break;
-            case 2: per_cu = occupancy_of<float, 2, false>(); break;
-            case 4: per_cu = occupancy_of<float, 4, false>(); break;
-            case 8: per_cu = occupancy_of<float, 8, false>(); break;
-            default: per_cu = occupancy_of<float, 16, false>(); break;
-        }
-    }
-    const int r = std::max(per_cu, 1) * cus;
-    c->occupancy[key] = r;
-    return r;
-}
-
 template <typename T>
 PcgArgs<T> make_args(qpat_ctx* c, Op op, int B) {
     PcgArgs<T> a{};
     a.s = c->sell;
     a.N = c->N;
     a.nsys = op == Op::Prior ? 2 : 1;
-    // one resident wave of blocks: occupancy of the direction+SpMV kernel times
-    // the compute units, split over the systems, a multiple of 8 (XCD mapping)
+    // about as many blocks as the direction + product keeps resident (more only
+    // lengthen the reductions of their partial sums), split over the systems, a
+    // multiple of 8 (XCD mapping), each with the same number of whole passes
     const int64_t rows_per_pass = kThreads / B;
     int64_t want = (c->N + rows_per_pass - 1) / rows_per_pass;
-    int64_t cap = resident_blocks(c, op == Op::Prior, std::is_same<T, double>::value, B) / a.nsys;
-    int64_t gs = std::min(want, std::max<int64_t>(cap, 8));
+    int cus = 256;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) cus = 256;
+    const int64_t cap = std::max<int64_t>((std::is_same<T, double>::value ? 5 : 7) * cus / a.nsys, 8);
+    const int64_t passes = (want + cap - 1) / cap;
+    int64_t gs = (want + passes - 1) / passes;
     gs = ((gs + 7) / 8) * 8;
     gs = std::min<int64_t>(gs, kMaxBlocks);   // size of the partial-sum buffer
     int64_t rpb = (c->N + gs - 1) / gs;
-    rpb = ((rpb + kSlice - 1) / kSlice) * kSlice;
+    rpb = (rpb + rows_per_pass - 1) / rows_per_pass * rows_per_pass;
     a.gs = static_cast<int32_t>(gs);
     a.rpb = static_cast<int32_t>(rpb);
     const bool is64 = std::is_same<T, double>::value;

@@ -270,8 +270,6 @@ struct qpat_ctx {
     qpat::MgState* mg = nullptr;
     qpat::MgState* mgk = nullptr;
 
-    // resident blocks per kernel configuration (occupancy x compute units)
-    std::map<int, int> occupancy;
     std::map<std::string, int> st_occ;   // stencil kernel, keyed by kernel and LDS size
 
     // captured graphs of PCG iteration chunks, keyed by kernel configuration

@@ -385,3 +385,53 @@ def test_data_arrays_and_options_switched_after_forward(n_ill):
         ctx.vjp(dev(t), jt)
         assert_close(host(js).reshape(n_ill, N), lin.jvp(s), tol, f"J s {kw}")
         assert_close(host(jt), lin.vjp(t), tol, f"J^T t {kw}")
+
+
+def cone(n):
+    """The surface of an n^3 box of voxels joined to its centre: one node with every other as neighbour."""
+    coords, _, bfaces = kuhn_box(n, n, n)
+    surface = np.unique(bfaces)
+    new = np.full(coords.shape[0], -1, dtype=np.int64)
+    new[surface] = np.arange(surface.size)
+    faces = new[bfaces]
+    coords = np.concatenate([coords[surface], coords.mean(axis=0, keepdims=True)])
+    tets = np.concatenate([faces, np.full((faces.shape[0], 1), surface.size)], axis=1)
+    return coords, tets.astype(np.int32), faces.astype(np.int32)
+
+
+@pytest.mark.parametrize("mesh,block,n_ill,precision", [
+    ((12, 11, 9), 1, 2, 0), ((12, 11, 9), 2, 3, 0), ((12, 11, 9), 4, 5, 1), ((12, 11, 9), 16, 16, 0),
+    ((19, 19, 19), 16, 16, 0), ((19, 20, 19), 16, 16, 0), ((24, 25, 24), 16, 16, 1), ((25, 25, 24), 16, 16, 1),
+    (None, 1, 2, 0), (None, 2, 3, 1), (None, 8, 7, 0), (None, 16, 16, 1)])
+def test_sell_products_on_shuffled_meshes(mesh, block, n_ill, precision):
+    """Sliced-ELL Jacobi-PCG with the direction formed in the product and before it (either side of 1 MiB a
+    vector: 8192 nodes with 16 right-hand sides, 16384 in FP32), ragged last blocks, blocks with zero right-hand
+    sides, rows of up to 27 entries: forward, J s and J^T t against the oracle (solves at 1e-12, element-wise
+    1e-10 as above; 1e-9 in mixed precision, whose recursion restarts from the FP64 residual)."""
+    seed = block + 3 * n_ill
+    rng = np.random.default_rng(seed)
+    if mesh is None:
+        coords, tets, bfaces = cone(2)
+        N = coords.shape[0]
+        kappa = 0.3 * np.exp(0.3 * rng.standard_normal(N))
+        mu = 0.02 * np.exp(0.3 * rng.standard_normal(N))
+        src = rng.uniform(0.0, 1.0, size=(n_ill, bfaces.shape[0], 3))
+    else:
+        coords, tets, bfaces, kappa, mu, src = box_problem(*mesh, n_ill, seed)
+        N = coords.shape[0]
+        new = rng.permutation(N).astype(np.int32)
+        back = np.argsort(new)
+        coords, kappa, mu, tets, bfaces = coords[back], kappa[back], mu[back], new[tets], new[bfaces]
+    ctx, phi, info = solve(coords, tets, bfaces, kappa, mu, src, max_rhs_block=block, pcg_rtol=1e-12,
+                           precision=precision)
+    assert info["relres_max"] <= 1e-12, info
+    lin = Linearisation(fem.geometry(coords, tets, bfaces), kappa, mu, src)
+    tol = 1e-9 if precision else 1e-10
+    assert_close(phi, lin.phi, tol, "phi")
+    s, t = rng.standard_normal(2 * N), rng.standard_normal((n_ill, N))
+    js = torch.empty(n_ill * N, dtype=torch.float64, device="cuda")
+    jt = torch.empty(2 * N, dtype=torch.float64, device="cuda")
+    ctx.jvp(dev(s), js)
+    ctx.vjp(dev(t), jt)
+    assert_close(host(js).reshape(n_ill, N), lin.jvp(s), tol, "J s")
+    assert_close(host(jt), lin.vjp(t), tol, "J^T t")
