@@ -63,7 +63,7 @@ struct MgLevel {
 };
 
 struct MgScal {
-    double rz, pq, alpha, beta, c, rr, bnorm2, mean;
+    double rz, pq, alpha, beta, c, rr, bnorm2, mean, rr0;   // rr0: rr at the start of the solve
     int32_t active, done, iters, pad;
 };
 
@@ -1944,7 +1944,7 @@ __global__ __launch_bounds__(kMgT) void k_mgp_init(PcgMg a, int nb, double inv_d
         s.mean = mean * inv_delta;
         s.bnorm2 = s2;
         s.rz = s.pq = s.alpha = s.beta = 0.0;
-        s.rr = s2;
+        s.rr = s.rr0 = s2;
         s.iters = 0;
         s.done = s2 == 0.0 ? 1 : 0;       // b = 0: x = 0
         s.active = s2 == 0.0 ? 0 : 1;
@@ -2043,6 +2043,7 @@ __global__ __launch_bounds__(kMgT) void k_mgp_true_fin(PcgMg a, int nb, int reop
     if (threadIdx.x == 0) {
         MgScal& s = a.sc[lane];
         s.rr = rr;
+        if (s.iters == 0) s.rr0 = rr;
         const bool ok = rr <= a.rtol2 * s.bnorm2;
         s.done = ok ? 1 : 0;
         s.active = (!ok && reopen && s.iters < a.maxit) ? 1 : 0;
@@ -4314,11 +4315,20 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         return false;
     };
     std::vector<int> reopened(S, 0);   // per lane: restarts after a failed true-residual check
+    bool fetched = false;              // sc_host holds the lanes' last state
+    // A solve's first V-cycle and chunk go out unseen: a lane with nothing to
+    // do is inactive on the device already, and what the chunk lengths need of
+    // the start (rr0) comes back with the first check. Each host check is a
+    // copy, a wait and an idle device while the next chunk is launched.
     for (int restart = 0; restart < 4; ++restart) {
-        QPAT_TRY(fetch());
-        if (!any_active()) break;
-        if (restart > 0)
+        if (restart > 0) {
+            QPAT_TRY(fetch());
+            if (!any_active()) {
+                fetched = true;
+                break;
+            }
             for (int i = 0; i < S; ++i) reopened[i] += M.sc_host[i].active ? 1 : 0;
+        }
         // the tiled check below stores no r (its lanes almost always stop there):
         // a lane it reopened restarts from the true residual formed here
         if (restart > 0 && tg.on) true_residual<B>(M, a, tg, c->b64, sm);
@@ -4338,12 +4348,18 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         // launched after convergence (each still costs its launches) by that
         // half, at the price of a host check more on runs that long.
         int chunk = kMgChunk0, nchunk = 0;
-        std::vector<int> iters_before(S, -1), iters_start(S, 0);
+        std::vector<int> iters_before(S, 0), iters_start(S, 0);
         std::vector<double> rr_before(S, 0.0);
+        for (int i = 0; restart > 0 && i < S; ++i) {   // from the check above
+            iters_before[i] = iters_start[i] = M.sc_host[i].iters;
+            rr_before[i] = M.sc_host[i].rr;
+        }
         for (;;) {
-            QPAT_TRY(fetch());
-            if (!any_active()) break;
-            if (iters_before[0] >= 0) {
+            if (nchunk > 0) {
+                QPAT_TRY(fetch());
+                if (!any_active()) break;
+                if (nchunk == 1 && restart == 0)
+                    for (int i = 0; i < S; ++i) rr_before[i] = M.sc_host[i].rr0;
                 double need = 0.0;
                 for (int i = 0; i < S; ++i) {
                     const MgScal& h = M.sc_host[i];
@@ -4365,14 +4381,12 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
                     const int half = run_its / 2;
                     chunk = std::min(chunk, std::max(2, half + (half & 1)));
                 }
-            } else {
-                for (int i = 0; i < S; ++i) iters_start[i] = M.sc_host[i].iters;
+                for (int i = 0; i < S; ++i) {
+                    iters_before[i] = M.sc_host[i].iters;
+                    rr_before[i] = M.sc_host[i].rr;
+                }
             }
             ++nchunk;
-            for (int i = 0; i < S; ++i) {
-                iters_before[i] = M.sc_host[i].iters;
-                rr_before[i] = M.sc_host[i].rr;
-            }
             // the chunk writes ring slots ring_s ... ring_s + chunk - 1: those not yet in x must survive
             if (a.ring > 0 && ring_s + chunk - ring_f > kRing) QPAT_TRY(ring_flush());
             ring_s += chunk;
@@ -4444,8 +4458,7 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, tg.on ? tg.blocks : (int)g.x, restart < 3 ? 1 : 0);
         QPAT_HIP(c, hipGetLastError());
     }
-    QPAT_TRY(ring_flush());   // a run that stopped before iterating still needs its x = 0
-    QPAT_TRY(fetch());
+    if (!fetched) QPAT_TRY(fetch());
     for (int i = 0; i < S; ++i) {
         const MgScal& s = M.sc_host[i];
         if (op == Op::Prior)   // the output kernel of the prior solve adds mean(b)/delta

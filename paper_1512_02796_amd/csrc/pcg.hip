@@ -1229,20 +1229,23 @@ struct Runner {
             QPAT_HIP(c, hipStreamSynchronize(sm));
             return QPAT_OK;
         };
-        QPAT_TRY(fetch());
         const bool mixed = !std::is_same<T, double>::value;
         const double ru2 = c->opts.ru_delta * c->opts.ru_delta;
         int chunk = 16;
         std::vector<double> best_true(S, INFINITY);
         std::vector<int> stalls(S, 0);
         std::vector<double> rr_prev(S);
-        for (int i = 0; i < S; ++i) rr_prev[i] = hs[i].rr;
-        std::vector<int> iters_before(S);
-        for (;;) {
-            for (int i = 0; i < S; ++i) iters_before[i] = hs[i].iters;
-            bool any_active = false;
-            for (int i = 0; i < S; ++i) any_active |= hs[i].active != 0;
-            if (!any_active) break;
+        std::vector<int> iters_before(S, 0);
+        // the first chunk goes out unseen: with nothing to do its kernels return at once
+        for (bool first = true;; first = false) {
+            if (!first) {
+                bool any_active = false;
+                for (int i = 0; i < S; ++i) {
+                    iters_before[i] = hs[i].iters;
+                    any_active |= hs[i].active != 0;
+                }
+                if (!any_active) break;
+            }
             const bool prof = c->prof_on;
             if (prof && c->ev_pool.size() < (size_t)5 * chunk) {
                 size_t old = c->ev_pool.size();
@@ -1261,6 +1264,7 @@ struct Runner {
             }
             QPAT_HIP(c, hipGetLastError());
             QPAT_TRY(fetch());
+            for (int i = 0; first && i < S; ++i) rr_prev[i] = hs[i].rlast2;   // ||r||^2 at the start
             if (prof) {
                 // launches after every lane stopped exit at once; count only live ones
                 const int base = op == Op::K ? 0 : 2;
