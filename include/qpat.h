@@ -345,7 +345,7 @@ qpat_status qpat_operator_layout(const qpat_ctx* ctx, int64_t out[6]);
  * level is tiled, out[1] / out[2] = the z-chunk length in use / the cost
  * model's for the direction, update and residual tiles, out[3] / out[4] and
  * out[5] / out[6] = the same for the fused prolongation + last sweep in FP64
- * and FP32 staging (0: not in use), out[7] = 1 if the lengths in use were
+ * and in mixed precision (one form serves both; 0: not in use), out[7] = 1 if the lengths in use were
  * picked by timing (opts.autotune). QPAT_ERR_STATE before that solve. */
 qpat_status qpat_tile_schedule(const qpat_ctx* ctx, int32_t B, int32_t out[8]);
 

@@ -55,9 +55,8 @@ struct MgLevel {
                                    // transfers read these (W holds the same rounded values for the Galerkin set-up:
                                    // one P throughout)
     double* Uf = nullptr;          // kind 3: [nsys][kUpRow][N] Kuhn diagonal + upper entries, entry-major;
-                                   // K level 0: [N][kFullRow] whole Kuhn rows; K levels >= 1: [N][kRow27]
+                                   // K levels >= 1: [N][kRow27]
     float* Uf32 = nullptr;         // kind 5 / 6: the kind-3 / kind-4 rows in FP32 (M_delta's V-cycle)
-    float* Ufk32 = nullptr;        // K level 0: the whole Kuhn rows [N][16] in FP32 (fused prolongation + last sweep)
     float* Uf27p = nullptr;        // K tiled levels >= 1: the 27-point rows in FP32 as [N][16] pairs (entry k, entry k + 16)
     int32_t vkind = -1;            // row kind of the V-cycle's kernels on this level (-1: kind)
 };
@@ -78,13 +77,11 @@ struct TileGeo {
         int32_t tx = 0, ty = 0, zc = 0, items = 0, blocks = 0;
     };
     Rst rst[kMgMaxLevels];
-    // the fused prolongation + last sweep (16 right-hand sides; even z-chunks)
-    bool ps_on = false;
-    int32_t ps_tx = 0, ps_ty = 0, ps_zc = 0, ps_items = 0, ps_blocks = 0;
-    int32_t ps_zc32 = 0, ps_items32 = 0, ps_blocks32 = 0;   // its FP32-staged form
+    // the fused prolongation + last sweep (even z-chunks)
+    int32_t ps_zc = 0, ps_items = 0, ps_blocks = 0;
     // the cost model's z-chunk lengths (tiles, prolongation + sweep FP64, FP32) and whether
     // the ones in use were picked by timing them (autotune)
-    int32_t zc_model = 0, ps_zc_model = 0, ps_zc32_model = 0;
+    int32_t zc_model = 0, ps_zc_model = 0;
     bool tuned = false;
     // the tiled 27-point kernels of the coarse levels (16 right-hand sides)
     struct Lv27 {
@@ -305,9 +302,6 @@ struct LvArgs {
 // one entry for consecutive nodes are contiguous, the lower entries included
 // (each is a partner row's upper entry at a shifted index)
 constexpr int kUpRow = 8;
-// whole Kuhn rows (diagonal, 7 upper, 7 lower entries, pad), node-major, for
-// the 16-lane fused prolongation + sweep
-constexpr int kFullRow = 16;
 
 // first stored row of system sys in the form the row kernel KIND reads
 template <int KIND>
@@ -616,37 +610,21 @@ __device__ __forceinline__ void put_sums(double* parts, int sys, const TB<B> (&a
     }
 }
 
-// Kuhn rows from the stencil form (zero where the partner is off the lattice):
-// ENTRY, the row kind 3, the diagonal and upper entries entry-major
-// [kUpRow][N]; otherwise whole rows node-major [N][kFullRow] (the lower entries
-// gathered from the partner rows) for the 16-lane kernels
-template <bool ENTRY>
+// Kuhn rows from the stencil form (zero where the partner is off the lattice),
+// the row kind 3: the diagonal and upper entries entry-major [kUpRow][N]
 __global__ __launch_bounds__(kMgT) void k_mg_fullrows(LvArgs L, double* __restrict__ Uf) {
     const int sys = blockIdx.y;
     constexpr int M1 = 8;
     const double* U = L.U + (int64_t)sys * L.N * M1;
-    double* F = Uf + (int64_t)sys * L.N * (ENTRY ? kUpRow : kFullRow);
+    double* F = Uf + (int64_t)sys * L.N * kUpRow;
     for (int64_t i = blockIdx.x * (int64_t)kMgT + threadIdx.x; i < L.N; i += (int64_t)gridDim.x * kMgT) {
         int ix, iy, iz;
         coords(static_cast<int32_t>(i), L.nx, L.ny, ix, iy, iz);
-        double u[kFullRow];
-        u[0] = U[i * M1];
+        F[i] = U[i * M1];
 #pragma unroll
         for (int j = 0; j < 7; ++j) {
-            const int dx = kKx[j], dy = kKy[j], dz = kKz[j];
-            const int64_t lin = dx + (int64_t)L.nx * (dy + (int64_t)L.ny * dz);
-            const bool up = ix + dx < L.nx && iy + dy < L.ny && iz + dz < L.nz;
-            const bool lo = ix - dx >= 0 && iy - dy >= 0 && iz - dz >= 0;
-            u[1 + j] = up ? U[i * M1 + 1 + j] : 0.0;
-            u[8 + j] = lo ? U[(i - lin) * M1 + 1 + j] : 0.0;
-        }
-        u[15] = 0.0;
-        if constexpr (ENTRY) {
-#pragma unroll
-            for (int k = 0; k < kUpRow; ++k) F[k * L.N + i] = u[k];
-        } else {
-#pragma unroll
-            for (int k = 0; k < kFullRow; ++k) F[i * kFullRow + k] = u[k];
+            const bool up = ix + kKx[j] < L.nx && iy + kKy[j] < L.ny && iz + kKz[j] < L.nz;
+            F[(1 + j) * L.N + i] = up ? U[i * M1 + 1 + j] : 0.0;
         }
     }
 }
@@ -959,7 +937,10 @@ __global__ __launch_bounds__(kMgT) void k_mg_smooth(SmArgs a, const double* __re
             });
         }
         if constexpr (DOTS) {
-            put_sums<B, 0, 2, 3>(parts, sys, {rz, z1, r1}, sm);
+            if constexpr (B == 1)   // M_delta's deflation
+                put_sums<B, 0, 2, 3>(parts, sys, {rz, z1, r1}, sm);
+            else
+                put_sums<B, 0>(parts, sys, {rz}, sm);
         }
     }
 }
@@ -1096,7 +1077,6 @@ __global__ __launch_bounds__(kMgT) void k_mg_resid_restrict(SmArgs f, SmArgs c, 
     if (item >= Nc * BV) return;   // whole groups of 32 lanes
     const int v = static_cast<int>(item % BV);
     const int32_t I = static_cast<int32_t>(item / BV);
-    const int32_t M1 = f.L.m + 1;
     const WPack pk{nx, ny, nz};
     int32_t Ix, Iy, Iz;
     coords(I, c.L.nx, c.L.ny, Ix, Iy, Iz);
@@ -1139,23 +1119,19 @@ __global__ __launch_bounds__(kMgT) void k_mg_resid_restrict(SmArgs f, SmArgs c, 
     }
 }
 
-// x = base + P xc on fine level f (coarse lattice cx, cy, cz). base = x, or
-// with FIRST the first sweep w D^{-1} b, which is then never stored. P:
-// trilinear, or the packed weights Wc ([nsys][WPack size]).
-template <int B, bool FIRST, bool OPW, bool XF = false>
+// x = x + P xc on fine level f (coarse lattice cx, cy, cz). P: trilinear, or
+// the packed weights Wc ([nsys][WPack size]).
+template <int B, bool OPW, bool XF = false>
 __global__ __launch_bounds__(kMgT) void k_mg_prolong(SmArgs f, int32_t cx, int32_t cy, int32_t cz,
-                                                     const double* __restrict__ xc, const double* __restrict__ b,
-                                                     double* __restrict__ x, const float* __restrict__ Wc) {
+                                                     const double* __restrict__ xc, double* __restrict__ x,
+                                                     const float* __restrict__ Wc) {
     using T = TB<B>;
     constexpr int V = Pk<B>::V;
     const int v = threadIdx.x % Pk<B>::BV;
     const int64_t Nf = f.L.N, Nc = (int64_t)cx * cy * cz;
     for (int sys = blockIdx.y; sys < f.nsys; sys += gridDim.y) {
         if (!pair_active<B>(f.sc, sys, v)) continue;
-        const double w = f.w[sys * f.nlev + f.lev];
-        const double* dinv = f.dinv + sys * Nf;
         const double* xs = xc + sys * Nc * B + v * V;
-        const double* bs = b + sys * Nf * B + v * V;
         double* xf = x + sys * Nf * B + v * V;
         float* xf32 = reinterpret_cast<float*>(x) + sys * Nf * B + v * V;   // XF: the fine x in FP32
         const WPack pk{f.L.nx, f.L.ny, f.L.nz};
@@ -1165,9 +1141,7 @@ __global__ __launch_bounds__(kMgT) void k_mg_prolong(SmArgs f, int32_t cx, int32
             const int32_t jx[2] = {sx.j0, sx.j1}, jy[2] = {sy.j0, sy.j1}, jz[2] = {sz.j0, sz.j1};
             const double wx[2] = {sx.w0, sx.w1}, wy[2] = {sy.w0, sy.w1}, wz[2] = {sz.w0, sz.w1};
             T s;
-            if constexpr (FIRST)
-                s = (w * dinv[i]) * vld<T>(bs + i * B);
-            else if constexpr (XF)
+            if constexpr (XF)
                 s = vldf<T>(xf32 + i * B);
             else
                 s = vld<T>(xf + i * B);
@@ -1403,7 +1377,6 @@ __global__ __launch_bounds__(kMgT) void k_mgp_dir_spmv(PcgMg a) {
     constexpr int V = Pk<B>::V;
     __shared__ double sm[kSumLds], ytab[kRegMax + 1];
     const int v = threadIdx.x % Pk<B>::BV;
-    const int32_t M1 = a.L.m + 1;
     for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
         if (B == 1 && a.kreg > 0) {
             __syncthreads();
@@ -1536,8 +1509,9 @@ __global__ __launch_bounds__(kMgT) void k_mgp_scalars(PcgMg a, int nb, int phase
     __shared__ double sm[(kMgT / 64) * 3];
     const int lane = blockIdx.y;
     MgScal& s = a.sc[lane];
-    const Red<1> p1(a.parts, phase == 2 || phase == 3 ? 0 : nb, lane, {phase == 1 ? 1 : 0});
-    const Red<3> p3(a.parts, phase == 2 || phase == 3 ? nb : 0, lane, {0, 2, 3});
+    const bool mean = phase >= 2 && a.deflate;   // the sums of z and r as well
+    const Red<1> p1(a.parts, mean ? 0 : nb, lane, {phase == 1 ? 1 : 0});
+    const Red<3> p3(a.parts, mean ? nb : 0, lane, {0, 2, 3});
     const double rz_old = s.rz;
     // the direction ring: each iteration's alpha per lane (0 where the lane did
     // not iterate), and the iteration counter, advanced once at the end of an
@@ -1561,8 +1535,14 @@ __global__ __launch_bounds__(kMgT) void k_mgp_scalars(PcgMg a, int nb, int phase
     } else if (phase == 1) {
         scalars_rr(a, p1, lane, sm);
     } else {
-        double v[3];
-        p3.take(sm, v);
+        double v[3] = {0.0, 0.0, 0.0};
+        if (mean) {
+            p3.take(sm, v);
+        } else {
+            double v0[1];
+            p1.take(sm, v0);
+            v[0] = v0[0];
+        }
         double rz = v[0];
         const double z1 = v[1], r1 = v[2];
         if (threadIdx.x == 0) {
@@ -2165,7 +2145,8 @@ constexpr int kTT = 512;                 // their threads, and the restriction's
 constexpr int kTHX = 12, kTHY = 10;      // their halo'd tile
 constexpr int kTHN = kTHX * kTHY;
 constexpr int kNpf16 = (kTHN * 16 + kTT - 1) / kTT;   // input elements per thread and plane
-enum TileMode { kTDirSpmv = 0, kTResidFirst = 1, kTSmoothDots = 2, kTTrue = 3, kTResid = 4, kTApply = 5, kTUpdResid = 6 };
+enum TileMode { kTDirSpmv = 0, kTResidFirst = 1, kTTrue = 3, kTApply = 5, kTUpdResid = 6, kTProlongSmooth = 7 };
+constexpr int kTCW = kTX / 2 + 2, kTC = kTCW * (kTY / 2 + 2);   // coarse columns under the halo'd tile
 
 struct TileArgs {
     int32_t nx, ny, nz;
@@ -2175,9 +2156,11 @@ struct TileArgs {
     const double* U;      // [N][8] the Kuhn stencil form
     const double* in;     // the vector staged in LDS (see the modes), [N][B]
     const double* in2;    // kTDirSpmv: the old direction
-    const double* b;      // right-hand side (kTResid*, kTSmoothDots, kTTrue)
-    const double* dinv;   // [N] (kTResidFirst, kTSmoothDots)
-    const double* w;      // the level's Jacobi weight (kTResidFirst, kTSmoothDots)
+    const double* b;      // right-hand side (kTResidFirst, kTProlongSmooth, kTTrue)
+    const double* dinv;   // [N] (kTResidFirst, kTProlongSmooth, kTUpdResid)
+    const double* w;      // the level's Jacobi weight (the same)
+    const double* xc;     // kTProlongSmooth: level 1's x, on its lattice
+    int32_t cx, cy, cz;
     double* out;
     double* out2;         // kTDirSpmv: the new direction
     double* parts;        // partial sums, [lanes][4][kMgBlocks]
@@ -2194,10 +2177,18 @@ struct TileArgs {
 //   in2 = the old direction) staged, out2 = p, out = A p, partial p.out.
 // kTResidFirst: the V-cycle's first sweep and residual, x = w D^{-1} in
 //   (in = r) staged, out = b - A x with b = r.
-// kTResid: out = b - A in. kTTrue: the same for every right-hand side,
-//   partial out.out (out may be null: the partial only).
-// kTSmoothDots: out = in + w D^{-1} (b - A in), partial b.out, sum out,
-//   sum b (the last finest-level sweep of the V-cycle: b = r, out = z).
+// kTTrue: out = b - A in for every right-hand side, partial out.out (out may
+//   be null: the partial only).
+// kTProlongSmooth: the V-cycle's prolongation into the finest level and its
+//   last sweep, x0 = w D^{-1} in + P xc staged (in = b = r, P trilinear), out =
+//   x0 + w D^{-1} (b - A x0), partial b.out. Chunks of even length: a coarse
+//   plane's values wait in LDS, where each is interpolated once, for the odd
+//   fine plane below it; that bilinear sum stays in registers for the even
+//   plane on it. On 98 x 41 x 62 nodes with 8 right-hand sides 18.3 us (two
+//   kernels: 28), on 97^3 with 16 75 (one right-hand side a thread, its rows by
+//   lane broadcasts: 103), on 129^3 with 16 in mixed precision 166 (that form
+//   with x0 and A x0 in FP32: 185). The sums of out and b that deflation would
+//   need are not taken: K is not deflated.
 // kTApply: out = scale A in for every right-hand side (any Kuhn stencil
 //   form U, e.g. the derivative of K in the Jacobian product).
 // kTUpdResid: the PCG update fused with kTResidFirst: r' = in - alpha in2
@@ -2205,7 +2196,9 @@ struct TileArgs {
 //   and out = r' - A x with the first sweep x = w D^{-1} r' (w / a_jj from
 //   LDS per neighbour). r' goes to another buffer than r: neighbouring tiles
 //   still read r's halo.
-// Z32 (kTDirSpmv only): `in` (z, the V-cycle's output) is FP32 [N][B].
+// Z32: z, the V-cycle's output (kTProlongSmooth) and kTDirSpmv's `in`, is FP32
+// [N][B].
+// P32 (kTProlongSmooth): xc is FP32.
 // P32 (kTDirSpmv): the PCG direction p is stored in FP32. The direction kernel
 // rounds p before staging it, so q = A p is the FP64 product of exactly the
 // stored p, and x later takes alpha times that same p: x and r stay consistent
@@ -2219,14 +2212,16 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
     constexpr bool UPD = MODE == kTUpdResid;
     // the finest level's residual for the restriction is stored in FP32 (it only
     // feeds the coarse levels of the preconditioner)
-    constexpr bool RES32 = MODE == kTResidFirst || MODE == kTResid || UPD;
+    constexpr bool RES32 = MODE == kTResidFirst || UPD;
+    constexpr bool PS = MODE == kTProlongSmooth;
     constexpr bool HAS_B = MODE != kTDirSpmv && MODE != kTApply && !UPD;
-    constexpr bool CENTER_D = MODE == kTSmoothDots;
     extern __shared__ __align__(16) unsigned char mg_smem[];
     __shared__ double sm[(T / 64) * B];
     double* ring = reinterpret_cast<double*>(mg_smem);   // [3][halo node][B]
     double* ust = ring + 3 * RS;                          // [3][halo node][8]
     double* own = ust + 3 * US;                           // UPD: [2][own node][B] r' of the tile's nodes
+    double* cring = own;                                  // PS: [coarse column][B] of one coarse plane
+    static_assert(kTC <= 2 * kTX * kTY && kTC * P <= T, "the coarse plane's place in LDS, its loads");
     const int tid = threadIdx.x, kp = tid % P;
     constexpr bool ALL = MODE == kTTrue || MODE == kTApply;   // every right-hand side, no PCG scalars
     if constexpr (!ALL) {   // every right-hand side stopped: nothing to do
@@ -2251,7 +2246,7 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
     const int32_t nx = g.nx, ny = g.ny, nz = g.nz;
     const uint32_t nxy = static_cast<uint32_t>(nx) * ny;
     const uint32_t pv = nxy * B * SZ, pu = nxy * 8 * SZ, pd = nxy * SZ, pin = nxy * g.ld * SZ;
-    const double w = (MODE == kTSmoothDots || MODE == kTResidFirst || UPD) ? *g.w : 0.0;
+    const double w = (PS || MODE == kTResidFirst || UPD) ? *g.w : 0.0;
     // descriptors stay uniform over the wavefront (a per-lane size would turn
     // every access into a loop over the distinct values)
     // (the plane clamped and no branch: a step stays one basic block, so its
@@ -2266,19 +2261,22 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
             g.out2 = reinterpret_cast<double*>(const_cast<char*>(g.ring + (sl % g.ring_n) * g.ring_stride));
         }
     }
-    static_assert(!Z32 || MODE == kTDirSpmv, "FP32 input only for the direction + product");
-    static_assert(!P32 || MODE == kTDirSpmv, "FP32 direction: the direction + product only");
+    static_assert(!Z32 || MODE == kTDirSpmv || PS, "z: the direction + product and the last sweep");
+    static_assert(!P32 || MODE == kTDirSpmv || PS, "FP32 direction or coarse x");
+    constexpr bool ZIN = Z32 && MODE == kTDirSpmv;
     const int hc = (tid / P / kTX + 1) * kTW + tid / P % kTX + 1;   // halo node of the thread's own node
     // LDS, from the thread's node and pair: vector values, operator row
     const double* rb = ring + hc * B + 2 * kp;
     const double* ub = ust + hc * 8;
     auto val_at = [&](int sl, int d) { return *reinterpret_cast<const d2v*>(rb + sl * RS + d * B); };
     auto off_of = [](int q) constexpr { return (q >> 1) * kTW + (q & 1); };   // in-plane offset of mask q (x 1, y 2)
-    std::conditional_t<Z32, f2v, d2v> fr[NS];
+    std::conditional_t<ZIN, f2v, d2v> fr[NS];
     std::conditional_t<P32, f2v, d2v> f2[NS];
+    std::conditional_t<P32, f2v, d2v> cv;   // PS: the thread's pair of the next coarse plane
+    d2v cy[NS];   // PS: the bilinear sum of the last coarse plane at the staged nodes
     d2v fu[NU];
-    double f2d[NS];   // kTResidFirst, UPD: 1 / a_ii of the staged nodes
-    d2v a0 = 0.0, a1 = 0.0, a2 = 0.0;
+    double f2d[NS];   // kTResidFirst, PS, UPD: 1 / a_ii of the staged nodes
+    d2v a0 = 0.0, a1 = 0.0;
 
     const int32_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per = gridDim.x >> 3;
     const int32_t wx = (g.items + 7) / 8;
@@ -2314,8 +2312,38 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
         // plane of 2^31 bytes of pairs can have there)
         auto half = [](uint32_t o) { return o / 2; };
         auto node8 = [](uint32_t o) { return o / (B * 8) * 8; };
-        auto fetch = [&](int pl) {
-            if constexpr (Z32) {
+        // PS: coarse plane Z; the bilinear sum of the coarse plane in LDS at halo node h
+        uint32_t co = kOut;
+        if constexpr (PS) {
+            const int X = x0 / 2 - 1 + tid / P % kTCW, Y = y0 / 2 - 1 + tid / P / kTCW;
+            if (tid < kTC * P && X >= 0 && X < g.cx && Y >= 0 && Y < g.cy)
+                co = (static_cast<uint32_t>(Y * g.cx + X) * B + 2 * kp) * SZ;
+        }
+        auto load_coarse = [&](int Z) {
+            const uint32_t cxy = static_cast<uint32_t>(g.cx) * g.cy * B;
+            const int64_t at = static_cast<int64_t>(min(max(Z, 0), g.cz - 1)) * cxy;
+            const uint32_t n = Z >= 0 && Z < g.cz ? cxy : 0u;
+            if constexpr (P32)
+                cv = bload2f(rsrc(reinterpret_cast<const float*>(g.xc) + at, n * 4u), half(co));
+            else
+                cv = bload2(rsrc(g.xc + at, n * 8u), co);
+        };
+        auto put_coarse = [&] {
+            if (tid < kTC * P) *reinterpret_cast<d2v*>(cring + 2 * tid) = as_d2(cv);
+        };
+        // x0 and y0 are even: a halo node's place among the coarse columns does not
+        // depend on the tile. The weights are 1 or 1/2 an axis: with the even
+        // neighbour read twice every case is a quarter of four terms.
+        auto bil = [&](int u) {
+            const int h = min((tid + u * T) / P, kTHalo - 1), hx = h % kTW, hy = h / kTW;
+            const double* q = cring + (((hy + 1) >> 1) * kTCW + ((hx + 1) >> 1)) * B + 2 * kp;
+            const int dx = hx & 1 ? 0 : B, dy = hy & 1 ? 0 : kTCW * B;
+            const auto at = [&](int o) { return *reinterpret_cast<const d2v*>(q + o); };
+            return 0.25 * ((at(0) + at(dx)) + (at(dy) + at(dy + dx)));
+        };
+        auto fetch = [&](int pl, auto EVEN) {
+            if constexpr (PS && decltype(EVEN)::value) load_coarse(pl / 2 + 1);
+            if constexpr (ZIN) {
                 const auto bi = plane(reinterpret_cast<const float*>(g.in), pl, nxy * g.ld, pin / 2);
 #pragma unroll
                 for (int u = 0; u < NS; ++u) fr[u] = bload2f(bi, half(fo[u]));
@@ -2333,7 +2361,7 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
 #pragma unroll
                 for (int u = 0; u < NS; ++u) f2[u] = bload2(b2, fo[u]);
             }
-            if constexpr (MODE == kTResidFirst || UPD) {
+            if constexpr (PS || MODE == kTResidFirst || UPD) {
                 const auto bd = plane(g.dinv, pl, nxy, pd);
 #pragma unroll
                 for (int u = 0; u < NS; ++u) f2d[u] = bload<double>(bd, node8(fo[u]));
@@ -2345,7 +2373,9 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
         d2v bn = 0.0;   // the right-hand side of the next plane
         auto loadb = [&](int z) { bn = bload2(plane(g.b, z, nxy * B, pv), oo); };
         if constexpr (HAS_B) loadb(zb);
-        auto store = [&](int sl, int pl) {
+        // PS: an odd plane reads the coarse plane above it in LDS, the even plane after
+        // it puts the next one there
+        auto store = [&](int sl, int pl, auto EVEN) {
             d2v lc0 = 0.0, lc1 = 0.0;
             if constexpr (MODE == kTDirSpmv || UPD) {
                 lc0 = *reinterpret_cast<const d2v*>(&lane_c[0][2 * kp]);
@@ -2353,17 +2383,28 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
             }
 #pragma unroll
             for (int u = 0; u < NS; ++u) {
-                const d2v in1 = as_d2(fr[u]), in2 = as_d2(f2[u]);
-                d2v val = in1;
+                const d2v in1 = as_d2(fr[u]);
+                d2v val = in1, in2 = 0.0;
+                if constexpr (MODE == kTDirSpmv || UPD) in2 = as_d2(f2[u]);
                 // beta = 0 (a run's first direction) never reads the old direction's values
                 if constexpr (MODE == kTDirSpmv) {
                     const bool st = fo[u] != kOut;
                     val.x = st && on0 ? (lc1.x != 0.0 ? in1.x - lc0.x + lc1.x * in2.x : in1.x - lc0.x) : 0.0;
                     val.y = st && on1 ? (lc1.y != 0.0 ? in1.y - lc0.y + lc1.y * in2.y : in1.y - lc0.y) : 0.0;
                 }
-                if constexpr (P32)
+                if constexpr (P32 && MODE == kTDirSpmv)
                     val = d2v{static_cast<double>(static_cast<float>(val.x)), static_cast<double>(static_cast<float>(val.y))};
                 if constexpr (MODE == kTResidFirst) val = w * f2d[u] * in1;
+                if constexpr (PS) {
+                    val = w * f2d[u] * in1;
+                    if constexpr (decltype(EVEN)::value) {
+                        val += cy[u];
+                    } else {
+                        const d2v up = bil(u);
+                        val += 0.5 * (cy[u] + up);
+                        cy[u] = up;
+                    }
+                }
                 if constexpr (UPD) {   // w D^{-1} r' for the products, r' of the tile's own nodes beside it
                     const d2v rn = in1 - lc0 * in2;
                     const int h = (tid + u * T) / P, hx = h % kTW - 1, hy = h / kTW - 1;
@@ -2376,6 +2417,7 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
 #pragma unroll
             for (int v = 0; v < NU; ++v)
                 if (tid + v * T < kTHalo * 4) *reinterpret_cast<d2v*>(ust + sl * US + 2 * (tid + v * T)) = fu[v];
+            if constexpr (PS && decltype(EVEN)::value) put_coarse();
         };
         // Kept between planes: the current plane's values at the node and its three
         // upper in-plane neighbours (cur), r' there (rc), and the sum over the four
@@ -2402,17 +2444,17 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
             pcomp = d2v{b0.c, b1.c};
         };
         // plane z in slot sz, plane z + 1 in slot sp
-        auto step = [&](int z, auto SZ0, auto SP0) {
+        auto step = [&](int z, auto SZ0, auto SP0, auto EVEN) {   // EVEN: z - zb is
             constexpr int sz = decltype(SZ0)::value, sp = decltype(SP0)::value;
-            store(sp, z + 1);
+            store(sp, z + 1, std::integral_constant<bool, !decltype(EVEN)::value>{});
             __syncthreads();
-            if (z + 1 < ze) fetch(z + 2);
+            if (z + 1 < ze) fetch(z + 2, EVEN);
             const d2v bc = bn;   // loaded one step earlier
             if constexpr (HAS_B) {
                 if (z + 1 < ze) loadb(z + 1);
             }
             double dc = 0.0;
-            if constexpr (CENTER_D) dc = bload<double>(plane(g.dinv, z, nxy, pd), node8(oo));
+            if constexpr (PS) dc = bload<double>(plane(g.dinv, z, nxy, pd), node8(oo));
             const d2v xc = cur[0];
             d2v sum = part;
             CompSum c0(0.0), c1(0.0);
@@ -2469,7 +2511,8 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
                 rtrue = d2v{c0.value(), c1.value()};
             }
             // RES32: float [N][B] planes; kTTrue with out = null: only the partial out.out
-            const auto bo = RES32 ? rsrc(reinterpret_cast<const float*>(g.out) + (int64_t)z * nxy * B, pv / 2)
+            const auto bo = RES32 || (PS && Z32)
+                                  ? rsrc(reinterpret_cast<const float*>(g.out) + (int64_t)z * nxy * B, pv / 2)
                                   : plane(g.out, z, nxy * B, g.out ? pv : 0u);
             const d2v zero = 0.0;
             d2v o;
@@ -2486,26 +2529,41 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
                 o = rz - sum;
                 a1 += in ? rz * rz : zero;
                 bstore2_nt(plane(g.out2, z, nxy * B, pv), oo, rz);
-            } else if constexpr (MODE == kTSmoothDots) {
+            } else if constexpr (PS) {
                 o = xc + w * dc * (bc - sum);
+                if constexpr (Z32) o = d2v{held_as<float>(o.x), held_as<float>(o.y)};
                 a0 += in ? bc * o : zero;
-                a1 += in ? o : zero;
-                a2 += in ? bc : zero;
             } else {
                 o = MODE == kTTrue ? rtrue : bc - sum;
                 if constexpr (MODE == kTTrue) a1 += in ? o * o : zero;
             }
             if constexpr (RES32)
                 bstore2f<false>(bo, half(oo), o);   // read next
+            else if constexpr (PS && Z32)
+                bstore2f<true>(bo, half(oo), o);
             else
                 bstore2_nt(bo, oo, o);
         };
+        using Even = std::true_type;
+        using Odd = std::false_type;
         __syncthreads();   // the last planes of the item before are read
-        fetch(zb - 1);
-        store(0, zb - 1);
-        fetch(zb);
-        store(1, zb);
-        fetch(zb + 1);
+        if constexpr (PS) {   // zb is even: plane zb - 1 lies between coarse planes zb / 2 - 1 and zb / 2
+            load_coarse(zb / 2 - 1);
+            put_coarse();
+            load_coarse(zb / 2);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < NS; ++u) cy[u] = bil(u);
+            __syncthreads();
+            put_coarse();
+        }
+        fetch(zb - 1, Odd{});
+        if constexpr (PS) __syncthreads();
+        store(0, zb - 1, Odd{});
+        fetch(zb, Even{});
+        if constexpr (PS) __syncthreads();
+        store(1, zb, Even{});
+        fetch(zb + 1, Odd{});
         __syncthreads();
         if constexpr (UPD) rc = own_at(zb);
         below_start();
@@ -2520,10 +2578,21 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
         using I0 = std::integral_constant<int, 0>;
         using I1 = std::integral_constant<int, 1>;
         using I2 = std::integral_constant<int, 2>;
-        for (int z = zb; z < ze; z += 3) {
-            step(z, I1{}, I2{});
-            if (z + 1 < ze) step(z + 1, I2{}, I0{});
-            if (z + 2 < ze) step(z + 2, I0{}, I1{});
+        if constexpr (PS) {   // six steps: the parities too are known at compile time
+            for (int z = zb; z < ze; z += 6) {
+                step(z, I1{}, I2{}, Even{});
+                if (z + 1 < ze) step(z + 1, I2{}, I0{}, Odd{});
+                if (z + 2 < ze) step(z + 2, I0{}, I1{}, Even{});
+                if (z + 3 < ze) step(z + 3, I1{}, I2{}, Odd{});
+                if (z + 4 < ze) step(z + 4, I2{}, I0{}, Even{});
+                if (z + 5 < ze) step(z + 5, I0{}, I1{}, Odd{});
+            }
+        } else {
+            for (int z = zb; z < ze; z += 3) {
+                step(z, I1{}, I2{}, Even{});
+                if (z + 1 < ze) step(z + 1, I2{}, I0{}, Even{});
+                if (z + 2 < ze) step(z + 2, I0{}, I1{}, Even{});
+            }
         }
     }
     auto out_sum = [&](d2v v, int slot_) {
@@ -2542,13 +2611,8 @@ __global__ __launch_bounds__(MgTile<B>::T, MgTile<B>::W) void k_mg_tile(TileArgs
         }
         __syncthreads();
     };
-    if constexpr (MODE == kTDirSpmv) out_sum(a0, 0);
+    if constexpr (MODE == kTDirSpmv || PS) out_sum(a0, 0);
     if constexpr (MODE == kTTrue || UPD) out_sum(a1, 1);
-    if constexpr (MODE == kTSmoothDots) {
-        out_sum(a0, 0);
-        out_sum(a1, 2);
-        out_sum(a2, 3);
-    }
 }
 
 // ------------------------------------------------ LDS-tiled restriction
@@ -2727,14 +2791,8 @@ __device__ __forceinline__ double row_bcast(double v) {
     return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + J, 0xF, 0xF, true);
 }
 
-// Two FP32 row entries as one 64-bit value, so that one 64-bit DPP row
-// broadcast delivers both: pair = (low: v of this lane, high: v of lane k + 8)
-// (row_pair), or two entries stored side by side and loaded as 8 bytes.
-__device__ __forceinline__ double row_pair(float v) {
-    const int hi = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xF, 0xF, true);   // row_ror:8
-    return __builtin_bit_cast(double, (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) |
-                                          static_cast<uint32_t>(__builtin_bit_cast(int, v)));
-}
+// two FP32 row entries stored side by side, loaded as one 64-bit value, so that
+// one 64-bit DPP row broadcast delivers both
 __device__ __forceinline__ float pair_lo(double p) {
     return __builtin_bit_cast(float, static_cast<uint32_t>(__builtin_bit_cast(uint64_t, p)));
 }
@@ -2974,307 +3032,6 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
     }
 }
 
-// ------------------------------------------------ fused prolongation + last sweep
-// The finest level of the K hierarchy with 16 right-hand sides: the staged
-// vector of the last sweep is the prolonged correction itself,
-// x0 = w D^{-1} r + P x1 (the first sweep recomputed, P trilinear), formed
-// plane by plane in LDS from r, 1/a_ii and the coarse planes of the tile's
-// support (a 7 x 6 patch of level 1, two coarse planes in LDS), so x0 never
-// goes to memory. Then z = x0 + w D^{-1} (r - A x0) with the partial sums
-// r.z, sum z, sum r. The stencil rows come whole ([N][16], lane k holds entry
-// k) and reach the node's lanes by DPP row broadcasts, which keeps the LDS
-// at two blocks per CU. Chunks start on even planes (even zc).
-// The sweep is preconditioner work: its rows are read in FP32 and z is stored
-// in FP32; the dot products use the stored z, the vector the PCG direction is
-// built from. In the FP64 form x0 is staged and A x0 summed in FP64; the FP32
-// form (mixed precision) stages x0 in FP32 and sums A x0 in FP32, and forms
-// r - A x0 and z in FP64. The PCG vectors themselves and the operator of
-// q = A p stay FP64.
-constexpr int kPCX = (kTHX - 2) / 2 + 2, kPCY = (kTHY - 2) / 2 + 2;   // coarse patch of a tile
-constexpr int kPCN = kPCX * kPCY * 16;                                // its values per coarse plane
-struct PSArgs {
-    int32_t nx, ny, nz, cx, cy, cz;
-    int32_t tiles_x, tiles_y, zc, items;
-    const float* Uf;      // [N][16] whole Kuhn rows, FP32
-    const double* r;      // [N][16] the PCG residual (level 0's b)
-    const double* xc;     // [Nc][16] level 1's solution
-    const double* dinv;   // [N]
-    const double* w;      // level 0's Jacobi weight
-    float* z;             // [N][16], FP32
-    double* parts;
-    const MgScal* sc;
-};
-
-template <int J>
-__device__ __forceinline__ double kuhn_pair(double s, double ua, const double* rb, int sz, int sp, int sl) {
-    constexpr int d = (kKy[J] * kTHX + kKx[J]) * 16;
-    const int up = kKz[J] ? sp : sz, lo = kKz[J] ? sl : sz;
-    return fma(row_bcast<8 + J>(ua), rb[lo - d], fma(row_bcast<1 + J>(ua), rb[up + d], s));
-}
-template <int... J>
-__device__ __forceinline__ double apply_kuhn16(double ua, const double* rb, int sz, int sp, int sl,
-                                               std::integer_sequence<int, J...>) {
-    double s = row_bcast<0>(ua) * rb[sz];
-    ((s = kuhn_pair<J>(s, ua, rb, sz, sp, sl)), ...);
-    return s;
-}
-
-// The FP32 form (mixed precision) of the fused prolongation + sweep stages x0
-// in FP32 and sums A x0 in FP32: lane k of a node's 16 holds the row entries k
-// and k + 8 as one 64-bit pair (row_pair), so 8 pair broadcasts deliver the
-// diagonal, the 7 upper and the 7 lower entries (pair i: entry i low, entry
-// i + 8 high).
-template <int... J>
-__device__ __forceinline__ float apply_kuhn16_f32(double pr, const float* rb, int sz, int sp, int sl,
-                                                  std::integer_sequence<int, J...>) {
-    static_assert(sizeof...(J) == 7, "the 7 offset pairs of a Kuhn row");
-    const double bc[8] = {row_bcast<0>(pr), row_bcast<J + 1>(pr)...};   // pairs 0..7
-    float s = pair_lo(bc[0]) * rb[sz];
-    // offset J: upper entry 1 + J (pair J + 1, low), lower entry 8 + J (pair J, high)
-    auto term = [&](auto JJ) {
-        constexpr int j = decltype(JJ)::value;
-        constexpr int d = (kKy[j] * kTHX + kKx[j]) * 16;
-        const int up = kKz[j] ? sp : sz, lo = kKz[j] ? sl : sz;
-        s = fmaf(pair_hi(bc[j]), rb[lo - d], fmaf(pair_lo(bc[j + 1]), rb[up + d], s));
-    };
-    (term(std::integral_constant<int, J>{}), ...);
-    return s;
-}
-
-template <bool F32, bool C32 = false>
-__global__ __launch_bounds__(kTT, 4) void k_mg_prolong_smooth(PSArgs g) {
-    using RT = std::conditional_t<F32, float, double>;   // x0 as staged
-    constexpr int B = 16;
-    constexpr int NPF = kNpf16, RS = kTHN * B;   // ring slot: exactly the halo tile
-    constexpr int TX = kTHX - 2, TY = kTHY - 2;
-    constexpr int NO = (TX * TY * B + kTT - 1) / kTT;
-    constexpr int NC = (kPCN + kTT - 1) / kTT;   // coarse patch values per thread
-    constexpr uint32_t SZ = sizeof(double);
-    extern __shared__ __align__(16) unsigned char mg_smem[];
-    __shared__ double sm[(kTT / 64) * 16];
-    double* dring = reinterpret_cast<double*>(mg_smem);   // [3][kTHN]: 1 / a_ii of the halo nodes
-    double* cring = dring + 3 * kTHN;                      // [2][kPCN]: coarse planes, slot Z & 1
-    double* rint = cring + 2 * kPCN;                       // [2][TX TY B]: r of the tile's own nodes, slot p & 1
-    RT* ring = reinterpret_cast<RT*>(rint + 2 * TX * TY * B);   // [3][RS]: x0 of the halo nodes, [node][16]
-    const int tid = threadIdx.x, k = tid % B;
-    bool any = false;
-    for (int j = 0; j < B; ++j) any = any || g.sc[j].active != 0;
-    if (!any) return;
-    const bool act = g.sc[k].active != 0;
-    const int32_t nx = g.nx, ny = g.ny, nz = g.nz;
-    const uint32_t nxy = static_cast<uint32_t>(nx) * ny, cxy = static_cast<uint32_t>(g.cx) * g.cy;
-    const uint32_t pv = nxy * B * SZ, pd = nxy * SZ, pc = cxy * B * SZ;
-    const double w = *g.w;
-    auto plane = [&](const auto* base, int pl, int n, uint32_t stride, uint32_t bytes) {
-        const bool in = pl >= 0 && pl < n;
-        return rsrc(base + (in ? (int64_t)pl * stride : 0), in ? bytes : 0u);
-    };
-    int32_t oc[NO];
-#pragma unroll
-    for (int u = 0; u < NO; ++u) {
-        const int nl = (tid + u * kTT) / B;
-        oc[u] = nl < TX * TY ? (nl / TX + 1) * kTHX + nl % TX + 1 : kTHX + 1;
-    }
-    double fr[NPF], dd = 0.0, cv[NC], cy[NPF];
-    bool cy_ok = false;   // cy holds coarse plane (pl + 1) / 2 of the last staged plane pl
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    const int32_t xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per = gridDim.x >> 3;
-    const int32_t wx = (g.items + 7) / 8;
-    const int32_t it_end = min(g.items, (xcd + 1) * wx);
-    const int32_t tiles = g.tiles_x * g.tiles_y;
-    for (int32_t item = xcd * wx + slot; item < it_end; item += per) {
-        const int32_t ch = item / tiles, t2 = item % tiles;
-        const int32_t x0 = (t2 % g.tiles_x) * TX, y0 = (t2 / g.tiles_x) * TY;
-        const int32_t zb = ch * g.zc, ze = min(zb + g.zc, nz);   // zb even
-        const int32_t cx0 = x0 / 2 - 1, cy0 = y0 / 2 - 1;        // the patch's first coarse column, row
-        uint32_t fo[NPF], o4[NO], dof = kOut;
-#pragma unroll
-        for (int u = 0; u < NPF; ++u) {
-            const int nl = (tid + u * kTT) / B;
-            const int gx = x0 - 1 + nl % kTHX, gy = y0 - 1 + nl / kTHX;
-            const bool fin = nl < kTHN && gx >= 0 && gx < nx && gy >= 0 && gy < ny;
-            fo[u] = fin ? (static_cast<uint32_t>(gy * nx + gx) * B + k) * SZ : kOut;
-        }
-#pragma unroll
-        for (int u = 0; u < NO; ++u) {
-            const int nl = (tid + u * kTT) / B;
-            const int ox = x0 + nl % TX, oy = y0 + nl / TX;
-            // the element's byte offset in an FP32 [N][16] array
-            o4[u] = nl < TX * TY && ox < nx && oy < ny ? (static_cast<uint32_t>(oy * nx + ox) * B + k) * 4u : kOut;
-        }
-        if (tid < kTHN) {
-            const int gx = x0 - 1 + tid % kTHX, gy = y0 - 1 + tid / kTHX;
-            if (gx >= 0 && gx < nx && gy >= 0 && gy < ny) dof = static_cast<uint32_t>(gy * nx + gx) * SZ;
-        }
-        // the patch's coarse values of this thread (offsets formed at each load)
-        auto coarse_off = [&](int u) {
-            const int e = tid + u * kTT, cn = e / B;
-            const int X = cx0 + cn % kPCX, Y = cy0 + cn / kPCX;
-            return e < kPCN && X >= 0 && X < g.cx && Y >= 0 && Y < g.cy
-                       ? (static_cast<uint32_t>(Y * g.cx + X) * B + (e % B)) * SZ : kOut;
-        };
-        // coarse plane Z of level 1's x (C32: stored in FP32)
-        auto load_coarse = [&](int Z) {
-            if constexpr (C32) {
-                const auto bc = plane(reinterpret_cast<const float*>(g.xc), Z, g.cz, cxy * B, pc / 2);
-#pragma unroll
-                for (int u = 0; u < NC; ++u) {
-                    const uint32_t o = coarse_off(u);
-                    cv[u] = static_cast<double>(bload<float>(bc, o == kOut ? kOut : o / 2));
-                }
-            } else {
-                const auto bc = plane(g.xc, Z, g.cz, cxy * B, pc);
-#pragma unroll
-                for (int u = 0; u < NC; ++u) cv[u] = bload<double>(bc, coarse_off(u));
-            }
-        };
-        // fine plane p: r and 1/a_ii; odd p also the coarse plane (p + 1) / 2
-        auto fetch = [&](int pl) {
-            const auto br = plane(g.r, pl, nz, nxy * B, pv), bd = plane(g.dinv, pl, nz, nxy, pd);
-#pragma unroll
-            for (int u = 0; u < NPF; ++u) fr[u] = bload<double>(br, fo[u]);
-            dd = bload<double>(bd, dof);
-            if (pl & 1) load_coarse((pl + 1) / 2);
-        };
-        auto put_coarse = [&](int Z) {   // coarse plane Z to its slot
-#pragma unroll
-            for (int u = 0; u < NC; ++u)
-                if (tid + u * kTT < kPCN) cring[(Z & 1) * kPCN + tid + u * kTT] = cv[u];
-        };
-        auto put_d = [&](int sl) {
-            if (tid < kTHN) dring[sl * kTHN + tid] = dd;
-        };
-        // x0 of fine plane pl into ring slot sl (its 1/a_ii already in dring[sl]),
-        // with the r of the tile's own nodes (the sweep's b) into rint
-        auto store = [&](int sl, int pl) {
-            const bool pin = pl >= 0 && pl < nz;
-            const int z0 = pl >> 1, z1 = (pl + 1) >> 1;
-            const double wz1 = (pl & 1) ? 0.5 : 0.0, wz0 = 1.0 - wz1;
-            const double* c0 = cring + (z0 & 1) * kPCN + k;
-            const double* c1 = cring + (z1 & 1) * kPCN + k;
-            // the bilinear value of coarse plane (pl + 1) / 2 at each element is
-            // kept in cy: an odd plane's upper coarse plane is the next even
-            // plane's own, so each coarse plane is interpolated once per item
-#pragma unroll
-            for (int u = 0; u < NPF; ++u) {
-                const int e = tid + u * kTT, nl = e / B;
-                if (e >= RS) continue;
-                const int lx = nl % kTHX - 1, ly = nl / kTHX - 1;
-                if (lx >= 0 && lx < TX && ly >= 0 && ly < TY) rint[(pl & 1) * (TX * TY * B) + (ly * TX + lx) * B + k] = fr[u];
-                double v = 0.0;
-                if (pin && fo[u] != kOut) {   // inside the halo tile and the grid
-                    v = w * dring[sl * kTHN + nl] * fr[u];
-                    const int gx = x0 - 1 + nl % kTHX, gy = y0 - 1 + nl / kTHX;
-                    const int o = (((gy >> 1) - cy0) * kPCX + (gx >> 1) - cx0) * B;
-                    const int dx = (gx & 1) ? B : 0, dy = (gy & 1) ? kPCX * B : 0;
-                    // trilinear weights are 1 or 1/2 per axis: with the even-parity
-                    // neighbour read twice, every case is a quarter of a four-term
-                    // sum (scaling by powers of two is exact)
-                    auto bil = [&](const double* cp) {
-                        const double* q = cp + o;
-                        return 0.25 * ((q[0] + q[dx]) + (q[dy] + q[dy + dx]));
-                    };
-                    double b0;
-                    if (cy_ok) b0 = cy[u];
-                    else b0 = bil(c0);
-                    if (pl & 1) {   // odd planes lie halfway between two coarse planes
-                        const double b1 = bil(c1);
-                        v = fma(wz1, b1, fma(wz0, b0, v));
-                        cy[u] = b1;
-                    } else {        // even planes on one (weight 1: fma(1, a, b) = a + b exactly)
-                        v += b0;
-                        cy[u] = b0;
-                    }
-                }
-                ring[sl * RS + e] = static_cast<RT>(v);
-                __builtin_amdgcn_sched_barrier(0);   // one element's coarse reads live at a time
-            }
-            cy_ok = pin;
-        };
-        auto step = [&](int z, auto SZ0, auto SP0, auto SL0) {
-            constexpr int sz = decltype(SZ0)::value, sp = decltype(SP0)::value, sl = decltype(SL0)::value;
-            float ua32[NO];   // the rows of this plane's nodes: in flight during the staging
-            const auto bu = plane(g.Uf, z, nz, nxy * B, pv / 2);
-#pragma unroll
-            for (int u = 0; u < NO; ++u) ua32[u] = bload<float>(bu, o4[u]);
-            store(sp, z + 1);
-            __syncthreads();
-            if (z + 1 < ze) fetch(z + 2);
-            const auto bo = plane(g.z, z, nz, nxy * B, pv / 2);
-#pragma unroll
-            for (int u = 0; u < NO; ++u) {
-                if (tid + u * kTT >= TX * TY * B) continue;   // whole waves past the tile skip
-                const RT* rb = ring + oc[u] * B + k;
-                double ax;
-                if constexpr (F32)
-                    ax = apply_kuhn16_f32(row_pair(ua32[u]), rb, sz * RS, sp * RS, sl * RS,
-                                          std::make_integer_sequence<int, 7>{});
-                else
-                    ax = apply_kuhn16(static_cast<double>(ua32[u]), rb, sz * RS, sp * RS, sl * RS,
-                                      std::make_integer_sequence<int, 7>{});
-                const double xc = rb[sz * RS];
-                const double bcu = rint[(z & 1) * (TX * TY * B) + tid + u * kTT];
-                const float o32 = static_cast<float>(xc + w * dring[sz * kTHN + oc[u]] * (bcu - ax));
-                const double o = static_cast<double>(o32);
-                const bool in = act && o4[u] != kOut;
-                a0 += in ? bcu * o : 0.0;
-                a1 += in ? o : 0.0;
-                a2 += in ? bcu : 0.0;
-                bstore_nt_f32(bo, act ? o4[u] : kOut, o32);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (z + 1 < ze) {   // plane z + 2's 1/a_ii (slot sl) and, odd, coarse plane (z + 3) / 2
-                put_d(sl);
-                if ((z + 2) & 1) put_coarse((z + 3) / 2);
-            }
-            __syncthreads();
-        };
-        cy_ok = false;
-        load_coarse(zb / 2 - 1);   // staging plane zb - 1 needs coarse planes zb/2 - 1 and zb/2
-        put_coarse(zb / 2 - 1);
-        fetch(zb - 1);             // odd: also coarse plane zb / 2
-        put_d(0);
-        put_coarse(zb / 2);
-        __syncthreads();
-        store(0, zb - 1);
-        fetch(zb);
-        put_d(1);
-        __syncthreads();
-        store(1, zb);
-        fetch(zb + 1);             // odd: coarse plane zb / 2 + 1
-        put_d(2);
-        put_coarse(zb / 2 + 1);    // slot of zb/2 - 1, whose last use (plane zb - 1) is staged
-        __syncthreads();
-        using I0 = std::integral_constant<int, 0>;
-        using I1 = std::integral_constant<int, 1>;
-        using I2 = std::integral_constant<int, 2>;
-        for (int z = zb; z < ze; z += 3) {   // plane z - zb + 1 lives in slot (z - zb + 1) % 3
-            step(z, I1{}, I2{}, I0{});
-            if (z + 1 < ze) step(z + 1, I2{}, I0{}, I1{});
-            if (z + 2 < ze) step(z + 2, I0{}, I1{}, I2{});
-        }
-    }
-    auto out_sum = [&](double v, int slot_) {
-#pragma unroll
-        for (int off = 32; off >= B; off >>= 1) v += __shfl_xor(v, off);
-        const int lane = tid & 63, wave = tid >> 6;
-        if (lane < B) sm[wave * B + lane] = v;
-        __syncthreads();
-        if (tid < B) {
-            double t = 0.0;
-            for (int wv = 0; wv < kTT / 64; ++wv) t += sm[wv * B + tid];
-            put(g.parts, tid, slot_, t);
-        }
-        __syncthreads();
-    };
-    out_sum(a0, 0);
-    out_sum(a1, 2);
-    out_sum(a2, 3);
-}
-template <bool F32>
-constexpr size_t kPSLds = (size_t)(3 * kTHN + 2 * kPCN + 2 * (kTHX - 2) * (kTHY - 2) * 16) * sizeof(double) +
-                          (size_t)3 * kTHN * 16 * (F32 ? sizeof(float) : sizeof(double));
-
 inline LvArgs lv_args(const MgLevel& L) {
     LvArgs a;
     a.U = L.U;
@@ -3395,7 +3152,7 @@ void launch_tile(const MgState& M, const TileGeo& t, hipStream_t st, const doubl
                  const double* b, double* out, double* out2, RingArg ring = {}) {
     if constexpr (B >= 8) {   // tile_setup turns the tiling on only there
         const MgLevel& L = M.lv[0];
-        TileArgs g;
+        TileArgs g{};
         g.nx = L.nx;
         g.ny = L.ny;
         g.nz = L.nz;
@@ -3422,6 +3179,34 @@ void launch_tile(const MgState& M, const TileGeo& t, hipStream_t st, const doubl
         g.ring_n = ring.n;
         hipLaunchKernelGGL((k_mg_tile<MODE, B, Z32, P32>), dim3(t.blocks), dim3(MgTile<B>::T), MgTile<B>::LDS, st, g);
     }
+}
+
+template <int B>
+TileArgs ps_args(const MgState& M, const TileGeo& t, const double* r, const double* x1, double* z) {
+    const MgLevel& L = M.lv[0];
+    const MgLevel& C = M.lv[1];
+    TileArgs g{};
+    g.nx = L.nx;
+    g.ny = L.ny;
+    g.nz = L.nz;
+    g.tiles_x = t.tiles_x;
+    g.tiles_y = t.tiles_y;
+    g.zc = t.ps_zc;
+    g.items = t.ps_items;
+    g.ld = B;
+    g.U = L.U;
+    g.in = r;
+    g.b = r;
+    g.dinv = L.dinv;
+    g.w = M.w;   // system 0, level 0
+    g.xc = x1;
+    g.cx = C.nx;
+    g.cy = C.ny;
+    g.cz = C.nz;
+    g.out = z;
+    g.parts = M.parts;
+    g.sc = M.sc;
+    return g;
 }
 
 // coarse level l: out = b - A x (kT27Resid) or x + w D^{-1} (b - A x) (kT27Smooth)
@@ -3456,38 +3241,20 @@ void launch_tile27(const MgState& M, const TileGeo& t, int l, hipStream_t st, co
 }
 inline bool tiled27(const TileGeo& t, int l) { return l >= 1 && l < kMgMaxLevels && t.t27[l].on; }
 
-// level 0: z = x0 + w D^{-1} (r - A x0), x0 = w D^{-1} r + P x1 (fused, 16 right-hand sides)
-inline void launch_ps(const MgState& M, const TileGeo& t, hipStream_t st, const double* r, const double* x1, double* z,
-                      bool f32, bool c32 = false) {
-    const MgLevel& L = M.lv[0];
-    const MgLevel& C = M.lv[1];
-    PSArgs g;
-    g.nx = L.nx;
-    g.ny = L.ny;
-    g.nz = L.nz;
-    g.cx = C.nx;
-    g.cy = C.ny;
-    g.cz = C.nz;
-    g.tiles_x = t.ps_tx;
-    g.tiles_y = t.ps_ty;
-    g.zc = f32 ? t.ps_zc32 : t.ps_zc;
-    g.items = f32 ? t.ps_items32 : t.ps_items;
-    g.Uf = L.Ufk32;
-    g.r = r;
-    g.xc = x1;
-    g.dinv = L.dinv;
-    g.w = M.w;   // system 0, level 0
-    g.z = reinterpret_cast<float*>(z);   // FP32 in the double buffer's first half
-    g.parts = M.parts;
-    g.sc = M.sc;
-    if (f32 && c32)   // c32: level 1's x in FP32
-        hipLaunchKernelGGL((k_mg_prolong_smooth<true, true>), dim3(t.ps_blocks32), dim3(kTT), kPSLds<true>, st, g);
-    else if (f32)
-        hipLaunchKernelGGL(k_mg_prolong_smooth<true>, dim3(t.ps_blocks32), dim3(kTT), kPSLds<true>, st, g);
-    else if (c32)
-        hipLaunchKernelGGL((k_mg_prolong_smooth<false, true>), dim3(t.ps_blocks), dim3(kTT), kPSLds<false>, st, g);
-    else
-        hipLaunchKernelGGL(k_mg_prolong_smooth<false>, dim3(t.ps_blocks), dim3(kTT), kPSLds<false>, st, g);
+// level 0: z = x0 + w D^{-1} (r - A x0), x0 = w D^{-1} r + P x1 (fused). z is
+// FP32, in the first half of its FP64 array, with 16 right-hand sides; c32:
+// level 1's x in FP32
+template <int B>
+void launch_ps(const MgState& M, const TileGeo& t, hipStream_t st, const double* r, const double* x1, double* z,
+               bool c32) {
+    if constexpr (B >= 8) {   // tile_setup turns the tiling on only there
+        const TileArgs g = ps_args<B>(M, t, r, x1, z);
+        const dim3 grid(t.ps_blocks), blk(MgTile<B>::T);
+        if (B == 16 && c32)
+            hipLaunchKernelGGL((k_mg_tile<kTProlongSmooth, B, B == 16, B == 16>), grid, blk, MgTile<B>::LDS, st, g);
+        else
+            hipLaunchKernelGGL((k_mg_tile<kTProlongSmooth, B, B == 16>), grid, blk, MgTile<B>::LDS, st, g);
+    }
 }
 
 // level l's residual to level l + 1's b and first sweep xc (tiled; trilinear)
@@ -3603,19 +3370,19 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
     if constexpr (B >= 8) {
         if (M.nsys != 1 || L.kind != 1 || L.N * B * (int64_t)sizeof(double) >= (int64_t(1) << 31)) return QPAT_OK;
         static_assert(MgTile<B>::LDS <= 159 * 1024, "tiled multigrid LDS budget");
-        const void* fns[9] = {reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTResidFirst, B>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTSmoothDots, B>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTTrue, B>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTResid, B>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTApply, B>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTUpdResid, B>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B, true>),
-                              reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B, true, true>)};
+        const void* fns[] = {reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B>),
+                             reinterpret_cast<const void*>(&k_mg_tile<kTResidFirst, B>),
+                             reinterpret_cast<const void*>(&k_mg_tile<kTTrue, B>),
+                             reinterpret_cast<const void*>(&k_mg_tile<kTApply, B>),
+                             reinterpret_cast<const void*>(&k_mg_tile<kTUpdResid, B>),
+                             reinterpret_cast<const void*>(&k_mg_tile<kTProlongSmooth, B, B == 16>),
+                             reinterpret_cast<const void*>(&k_mg_tile<kTProlongSmooth, B, B == 16, B == 16>),
+                             reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B, true>),
+                             reinterpret_cast<const void*>(&k_mg_tile<kTDirSpmv, B, true, true>)};
         for (const void* f : fns)   // dynamic LDS beyond the default limit is allowed per kernel
             QPAT_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MgTile<B>::LDS));
         int occ = 1, cus = 256;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fns[6], MgTile<B>::T, MgTile<B>::LDS) != hipSuccess) occ = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(&k_mg_tile<kTUpdResid, B>), MgTile<B>::T, MgTile<B>::LDS) != hipSuccess) occ = 1;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) cus = 256;
         // blocks resident per XCD; each leaves one partial sum
         const int64_t conc = std::min<int64_t>((int64_t)std::max(occ, 1) * std::max(cus / 8, 1), kMgBlocks / 8);
@@ -3743,105 +3510,65 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
             q.blocks = static_cast<int32_t>(8 * std::min<int64_t>(rconc, (q.items + 7) / 8));
             q.on = true;
         }
-        if constexpr (B == 16) {   // the fused prolongation + last sweep: even chunks
-            if (L.Uf && L.Ufk32) {
-                const int64_t ptx = (L.nx + kTHX - 3) / (kTHX - 2), pty = (L.ny + kTHY - 3) / (kTHY - 2);
-                t.ps_tx = static_cast<int32_t>(ptx);
-                t.ps_ty = static_cast<int32_t>(pty);
-                for (const bool f32 : {false, true}) {
-                    const void* fps = f32 ? reinterpret_cast<const void*>(&k_mg_prolong_smooth<true>)
-                                          : reinterpret_cast<const void*>(&k_mg_prolong_smooth<false>);
-                    const size_t lds = f32 ? kPSLds<true> : kPSLds<false>;
-                    QPAT_HIP(c, hipFuncSetAttribute(fps, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-                    const void* fps_c = f32 ? reinterpret_cast<const void*>(&k_mg_prolong_smooth<true, true>)
-                                            : reinterpret_cast<const void*>(&k_mg_prolong_smooth<false, true>);
-                    QPAT_HIP(c, hipFuncSetAttribute(fps_c, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-                    int occ_ps = 1;
-                    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_ps, fps, kTT, lds) != hipSuccess) occ_ps = 1;
-                    const int64_t conc_ps = (int64_t)std::max(occ_ps, 1) * (cus / 8);
-                    int64_t best_ps = -1, zc_ps = L.nz + (L.nz & 1);
-                    for (int64_t nch = 1; nch <= L.nz; ++nch) {
-                        int64_t zc = (L.nz + nch - 1) / nch;
-                        zc += zc & 1;
-                        const int64_t items = ptx * pty * ((L.nz + zc - 1) / zc);
-                        const int64_t cost = (((items + 7) / 8 + conc_ps - 1) / conc_ps) * (zc + 2);
-                        if (best_ps < 0 || cost < best_ps) {
-                            best_ps = cost;
-                            zc_ps = zc;
-                        }
-                    }
-                    auto set_ps = [&](int64_t zc) {
-                        const int32_t items = static_cast<int32_t>(ptx * pty * ((L.nz + zc - 1) / zc));
-                        (f32 ? t.ps_zc32 : t.ps_zc) = static_cast<int32_t>(zc);
-                        (f32 ? t.ps_items32 : t.ps_items) = items;
-                        (f32 ? t.ps_blocks32 : t.ps_blocks) =
-                            static_cast<int32_t>(8 * std::min<int64_t>(conc_ps, (items + 7) / 8));
-                    };
-                    set_ps(zc_ps);
-                    (f32 ? t.ps_zc32_model : t.ps_zc_model) = static_cast<int32_t>(zc_ps);
-                    if (!c->opts.autotune) continue;
-                    const TuneKey key{f32 ? 2 : 1, L.nx, L.ny, L.nz, B};
-                    int32_t zc_t = 0;
-                    {
-                        std::lock_guard<std::mutex> lk(g_tune_mu);
-                        auto it = g_tune.find(key);
-                        if (it != g_tune.end()) zc_t = it->second;
-                    }
-                    if (!zc_t) {
-                        // scratch: r in pa, z in pq, lanes all active in a private scalar array
-                        MgScal* sc_t = nullptr;
-                        QPAT_TRY(dalloc(c, &sc_t, B));
-                        std::vector<MgScal> hs(B);
-                        for (auto& h : hs) {
-                            std::memset(&h, 0, sizeof h);
-                            h.active = 1;
-                        }
-                        QPAT_HIP(c, hipMemcpyAsync(sc_t, hs.data(), B * sizeof(MgScal), hipMemcpyHostToDevice, c->stream));
-                        QPAT_HIP(c, hipMemsetAsync(M.pa, 0, L.N * B * sizeof(double), c->stream));
-                        QPAT_HIP(c, hipMemsetAsync(C.x, 0, C.N * B * sizeof(double), c->stream));
-                        const std::vector<int64_t> cands = chunk_candidates(L.nz, ptx * pty, conc_ps, true);
-                        std::vector<float> cms(cands.size(), 0.f);
-                        for (int round = 0; round < kTuneRounds; ++round)
-                        for (size_t ci = 0; ci < cands.size(); ++ci) {
-                            const int64_t zc = cands[ci];
-                            set_ps(zc);
-                            PSArgs g;
-                            g.nx = L.nx;
-                            g.ny = L.ny;
-                            g.nz = L.nz;
-                            g.cx = C.nx;
-                            g.cy = C.ny;
-                            g.cz = C.nz;
-                            g.tiles_x = t.ps_tx;
-                            g.tiles_y = t.ps_ty;
-                            g.zc = static_cast<int32_t>(zc);
-                            g.items = f32 ? t.ps_items32 : t.ps_items;
-                            g.Uf = L.Ufk32;
-                            g.r = M.pa;
-                            g.xc = C.x;
-                            g.dinv = L.dinv;
-                            g.w = M.w;
-                            g.z = reinterpret_cast<float*>(M.pq);
-                            g.parts = M.parts;
-                            g.sc = sc_t;
-                            const dim3 grid(f32 ? t.ps_blocks32 : t.ps_blocks);
-                            float ms = 0.f;
-                            QPAT_TRY(time_launches(c, [&] {
-                                if (f32)
-                                    hipLaunchKernelGGL(k_mg_prolong_smooth<true>, grid, dim3(kTT), kPSLds<true>, c->stream, g);
-                                else
-                                    hipLaunchKernelGGL(k_mg_prolong_smooth<false>, grid, dim3(kTT), kPSLds<false>, c->stream, g);
-                            }, &ms));
-                            cms[ci] = round == 0 ? ms : std::min(cms[ci], ms);
-                        }
-                        zc_t = static_cast<int32_t>(cands[tune_pick(cms)]);
-                        QPAT_TRY(dfree(c, sc_t));
-                        std::lock_guard<std::mutex> lk(g_tune_mu);
-                        g_tune.emplace(key, zc_t);
-                    }
-                    set_ps(zc_t);
+        {   // the fused prolongation + last sweep: the same tiles, even chunks
+            int64_t best_ps = -1, zc_ps = L.nz + (L.nz & 1);
+            for (int64_t nch = 1; nch <= L.nz; ++nch) {
+                int64_t zc = (L.nz + nch - 1) / nch;
+                zc += zc & 1;
+                const int64_t items = tx * ty * ((L.nz + zc - 1) / zc);
+                const int64_t cost = (((items + 7) / 8 + conc - 1) / conc) * (zc + 2);
+                if (best_ps < 0 || cost < best_ps) {
+                    best_ps = cost;
+                    zc_ps = zc;
                 }
-                t.ps_on = true;
+            }
+            auto set_ps = [&](int64_t zc) {
+                t.ps_zc = static_cast<int32_t>(zc);
+                t.ps_items = static_cast<int32_t>(tx * ty * ((L.nz + zc - 1) / zc));
+                t.ps_blocks = static_cast<int32_t>(8 * std::min<int64_t>(conc, (t.ps_items + 7) / 8));
+            };
+            set_ps(zc_ps);
+            t.ps_zc_model = t.ps_zc;
+            if (c->opts.autotune) {
+                const TuneKey key{1, L.nx, L.ny, L.nz, B};
+                int32_t zc_t = 0;
+                {
+                    std::lock_guard<std::mutex> lk(g_tune_mu);
+                    auto it = g_tune.find(key);
+                    if (it != g_tune.end()) zc_t = it->second;
+                }
+                if (!zc_t) {
+                    // scratch: r in pa, z in pq, lanes all active in a private scalar array
+                    MgScal* sc_t = nullptr;
+                    QPAT_TRY(dalloc(c, &sc_t, B));
+                    std::vector<MgScal> hs(B);
+                    for (auto& h : hs) {
+                        std::memset(&h, 0, sizeof h);
+                        h.active = 1;
+                    }
+                    QPAT_HIP(c, hipMemcpyAsync(sc_t, hs.data(), B * sizeof(MgScal), hipMemcpyHostToDevice, c->stream));
+                    QPAT_HIP(c, hipMemsetAsync(M.pa, 0, L.N * B * sizeof(double), c->stream));
+                    QPAT_HIP(c, hipMemsetAsync(C.x, 0, C.N * B * sizeof(double), c->stream));
+                    const std::vector<int64_t> cands = chunk_candidates(L.nz, tx * ty, conc, true);
+                    std::vector<float> cms(cands.size(), 0.f);
+                    for (int round = 0; round < kTuneRounds; ++round)
+                    for (size_t ci = 0; ci < cands.size(); ++ci) {
+                        set_ps(cands[ci]);
+                        TileArgs g = ps_args<B>(M, t, M.pa, C.x, M.pq);
+                        g.sc = sc_t;
+                        float ms = 0.f;
+                        QPAT_TRY(time_launches(c, [&] {
+                            hipLaunchKernelGGL((k_mg_tile<kTProlongSmooth, B, B == 16>), dim3(t.ps_blocks),
+                                               dim3(MgTile<B>::T), MgTile<B>::LDS, c->stream, g);
+                        }, &ms));
+                        cms[ci] = round == 0 ? ms : std::min(cms[ci], ms);
+                    }
+                    zc_t = static_cast<int32_t>(cands[tune_pick(cms)]);
+                    QPAT_TRY(dfree(c, sc_t));
+                    std::lock_guard<std::mutex> lk(g_tune_mu);
+                    g_tune.emplace(key, zc_t);
+                }
+                set_ps(zc_t);
             }
         }
         if constexpr (B == 16) {   // the coarse levels' 27-point kernels
@@ -3887,14 +3614,13 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
 // row kind of the V-cycle's kernels on a level
 inline int vkind(const MgLevel& L) { return L.vkind >= 0 ? L.vkind : L.kind; }
 
-// the tiled path fuses the PCG update with the V-cycle's first residual
-inline bool fused_update(const TileGeo& tg) { return tg.on && kMgNu == 1; }
-
-// the V-cycle's last finest-level sweep is the fused prolongation + sweep,
-// which leaves z in FP32 (16 right-hand sides, trilinear transfer: K)
+// The tiled path (K) fuses the PCG update with the V-cycle's first residual and
+// the prolongation with its last finest-level sweep. That leaves z in FP32
+// with 16 right-hand sides.
+static_assert(kMgNu == 1, "the tiled kernels take one sweep each way");
 template <int B>
-inline bool z32_path(const MgState& M, const TileGeo& tg) {
-    return B == 16 && fused_update(tg) && tg.ps_on && !M.opdep;
+inline bool z32_path(const TileGeo& tg) {
+    return B == 16 && tg.on;
 }
 
 // One right-hand side per system (M_delta), walk kernels with the FP32 Kuhn
@@ -3906,7 +3632,7 @@ inline bool z32_path(const MgState& M, const TileGeo& tg) {
 // direction. The PCG's own vectors (x, r, p, q) stay FP64.
 template <int B>
 inline bool f32v0_path(const MgState& M, const TileGeo& tg) {
-    return B == 1 && M.opdep && !tg.on && kMgNu == 1 && M.lv.size() > 1 && M.lv[0].vkind == 5 &&
+    return B == 1 && M.opdep && !tg.on && M.lv.size() > 1 && M.lv[0].vkind == 5 &&
            M.lv[0].N * 8 < (int64_t(1) << 31);
 }
 
@@ -3917,7 +3643,7 @@ inline bool f32v0_path(const MgState& M, const TileGeo& tg) {
 // the fused prolongation + last sweep above it (preconditioner work only).
 template <int B>
 inline bool v32_path(const MgState& M, const TileGeo& tg) {
-    return z32_path<B>(M, tg) && M.lv.size() > 2 && tiled27(tg, 1) && M.lv[1].Uf27p != nullptr && tg.rst[0].on &&
+    return z32_path<B>(tg) && M.lv.size() > 2 && tiled27(tg, 1) && M.lv[1].Uf27p != nullptr && tg.rst[0].on &&
            tg.rst[1].on;
 }
 
@@ -3926,7 +3652,6 @@ inline bool v32_path(const MgState& M, const TileGeo& tg) {
 // sweep each way the first sweep w D^{-1} r is never stored: the residual
 // kernel stages it and the prolongation recomputes it. Level 0 takes
 // 2 kMgNu - 1 ping-pong sweeps (an odd number), so z ends in level 0's t.
-// lo32 (mixed precision) stages the fused last sweep's x0 in FP32.
 // the smoother arguments of level l
 inline SmArgs level_args(const MgState& M, int l) {
     SmArgs a;
@@ -3994,9 +3719,8 @@ void launch_resid_restrict(const MgState& M, int l, hipStream_t st, const double
 // first_done: the PCG update already wrote the finest level's first sweep
 template <int B>
 void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev = nullptr, const double* b0 = nullptr,
-            bool resid_done = false, bool lo32 = false, bool first_done = false) {
+            bool resid_done = false, bool first_done = false) {
     const int nl = static_cast<int>(M.lv.size());
-    const bool fused0 = tg.on && kMgNu == 1;
     const bool v1 = v32_path<B>(M, tg);   // level 1's vectors in FP32
     const bool f0 = f32v0_path<B>(M, tg);  // level 0's vectors in FP32 (one right-hand side)
     const double* r0 = b0 ? b0 : M.lv[0].b;   // level 0's right-hand side (the PCG residual)
@@ -4012,15 +3736,11 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
         const SmArgs a = sm(l);
         const dim3 g = sgrid<B>(L.N, M.nsys);
         const double* bl = l == 0 ? r0 : L.b;
-        if (l == 0 && !fused0 && !first_done && f0)
+        if (l == 0 && !tg.on && !first_done && f0)
             hipLaunchKernelGGL((k_mg_first<B, float>), sys_rows(vgrid(L.N * B), B, M.nsys), dim3(kMgT), 0, st, a, r0,
                                reinterpret_cast<float*>(xl[0]));
-        else if (l == 0 && !fused0 && !first_done)
+        else if (l == 0 && !tg.on && !first_done)
             hipLaunchKernelGGL(k_mg_first<B>, sys_rows(vgrid(L.N * B), B, M.nsys), dim3(kMgT), 0, st, a, r0, xl[0]);
-        for (int k = 1; k < kMgNu; ++k) {
-            launch_smooth<B, false>(vkind(L), g, st, a, bl, xl[l], tl[l], nullptr);
-            std::swap(xl[l], tl[l]);
-        }
         if (l == 0 && ev) (void)hipEventRecord(ev[0], st);
         const bool tiled = (l == 0 && tg.on) || (B == 16 && tiled27(tg, l)) ||
                            (tg.on && l < kMgMaxLevels && tg.rst[l].on && !M.opdep);
@@ -4028,12 +3748,10 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
             launch_resid_restrict<B>(M, l, st, bl, xl[l], xl[l + 1], l == 0 && f0);
             continue;
         }
-        if (l == 0 && fused0 && resid_done)
+        if (l == 0 && tg.on && resid_done)
             ;   // the PCG update produced level 0's residual (kTUpdResid)
-        else if (l == 0 && fused0)
-            launch_tile<kTResidFirst, B>(M, tg, st, r0, nullptr, r0, L.r, nullptr);
         else if (l == 0 && tg.on)
-            launch_tile<kTResid, B>(M, tg, st, xl[0], nullptr, r0, L.r, nullptr);
+            launch_tile<kTResidFirst, B>(M, tg, st, r0, nullptr, r0, L.r, nullptr);
         else if (B == 16 && tiled27(tg, l))
             launch_tile27<kT27Resid>(M, tg, l, st, xl[l], L.b, L.r, v1 && l == 1);
         else if (l == 0 && f0) {
@@ -4065,37 +3783,29 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
         const SmArgs a = sm(l);
         const dim3 g = sgrid<B>(L.N, M.nsys);
         const double* bl = l == 0 ? r0 : L.b;
-        if (l == 0 && z32_path<B>(M, tg)) {   // prolongation fused into the last sweep (z in FP32)
+        if (l == 0 && tg.on) {   // prolongation fused into the last sweep
             if (ev) (void)hipEventRecord(ev[2], st);
-            launch_ps(M, tg, st, r0, xl[1], tl[0], lo32, v1);
+            launch_ps<B>(M, tg, st, r0, xl[1], tl[0], v1);
             if (ev) (void)hipEventRecord(ev[3], st);
             std::swap(xl[0], tl[0]);
             continue;
         }
-        if (l == 0 && fused0 && M.opdep)
-            hipLaunchKernelGGL((k_mg_prolong<B, true, true>), g, dim3(kMgT), 0, st, a, C.nx, C.ny, C.nz, xl[1],
-                               r0, xl[0], L.Wc);
-        else if (l == 0 && fused0)
-            hipLaunchKernelGGL((k_mg_prolong<B, true, false>), g, dim3(kMgT), 0, st, a, C.nx, C.ny, C.nz, xl[1], r0,
-                               xl[0], static_cast<const float*>(nullptr));
-        else if (M.opdep && l == 0 && f0)   // into level 0's FP32 x0
-            hipLaunchKernelGGL((k_mg_prolong<B, false, true, true>), g, dim3(kMgT), 0, st, a, C.nx, C.ny, C.nz,
-                               xl[l + 1], bl, xl[l], L.Wc);
+        if (M.opdep && l == 0 && f0)   // into level 0's FP32 x0
+            hipLaunchKernelGGL((k_mg_prolong<B, true, true>), g, dim3(kMgT), 0, st, a, C.nx, C.ny, C.nz,
+                               xl[l + 1], xl[l], L.Wc);
         else if (M.opdep)
-            hipLaunchKernelGGL((k_mg_prolong<B, false, true>), g, dim3(kMgT), 0, st, a, C.nx, C.ny, C.nz,
-                               xl[l + 1], bl, xl[l], L.Wc);
+            hipLaunchKernelGGL((k_mg_prolong<B, true>), g, dim3(kMgT), 0, st, a, C.nx, C.ny, C.nz,
+                               xl[l + 1], xl[l], L.Wc);
         else if (l == 1 && v1)   // into level 1's FP32 x
-            hipLaunchKernelGGL((k_mg_prolong<B, false, false, true>), g, dim3(kMgT), 0, st, a, C.nx, C.ny,
-                               C.nz, xl[l + 1], bl, xl[l], static_cast<const float*>(nullptr));
+            hipLaunchKernelGGL((k_mg_prolong<B, false, true>), g, dim3(kMgT), 0, st, a, C.nx, C.ny,
+                               C.nz, xl[l + 1], xl[l], static_cast<const float*>(nullptr));
         else
-            hipLaunchKernelGGL((k_mg_prolong<B, false, false>), g, dim3(kMgT), 0, st, a, C.nx, C.ny, C.nz, xl[l + 1],
-                               bl, xl[l], static_cast<const float*>(nullptr));
+            hipLaunchKernelGGL((k_mg_prolong<B, false>), g, dim3(kMgT), 0, st, a, C.nx, C.ny, C.nz, xl[l + 1],
+                               xl[l], static_cast<const float*>(nullptr));
         for (int k = 0; k < kMgNu; ++k) {
             const bool last = l == 0 && k == kMgNu - 1;
             if (last && ev) (void)hipEventRecord(ev[2], st);
-            if (last && tg.on)
-                launch_tile<kTSmoothDots, B>(M, tg, st, xl[0], nullptr, r0, tl[0], nullptr);
-            else if (last && f0) {
+            if (last && f0) {
                 if constexpr (B == 1)
                     hipLaunchKernelGGL((k_mg_smooth<5, 1, true, float>), g, dim3(kMgT), 0, st, a, bl,
                                        reinterpret_cast<const float*>(xl[0]), reinterpret_cast<float*>(tl[0]),
@@ -4114,9 +3824,9 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
 
 // blocks of the V-cycle's last finest-level sweep, which leave r.z, sum z, sum r
 template <int B>
-inline int last_blocks(const MgState& M, const TileGeo& tg, bool lo32) {
-    if (z32_path<B>(M, tg)) return lo32 ? tg.ps_blocks32 : tg.ps_blocks;
-    return tg.on ? tg.blocks : static_cast<int>(sgrid<B>(M.lv[0].N).x);
+inline int last_blocks(const MgState& M, const TileGeo& tg) {
+    if (tg.on) return tg.ps_blocks;
+    return static_cast<int>(sgrid<B>(M.lv[0].N).x);
 }
 
 MgState*& state_of(qpat_ctx* c, Op op) { return op == Op::K ? c->mgk : c->mg; }
@@ -4174,7 +3884,7 @@ void iteration(const MgState& M, PcgMg a, const TileGeo& tg, hipStream_t st, int
     if (par) std::swap(a.po, a.pn);
     const dim3 g = sgrid<B>(a.L.N, a.nsys), lanes(1, a.nsys * B);
     if (ev) (void)hipEventRecord(ev[0], st);
-    const bool p32 = a.p32 && z32_path<B>(M, tg);   // mixed precision: the direction in FP32
+    const bool p32 = a.p32 && z32_path<B>(tg);   // mixed precision: the direction in FP32
     RingArg ring;   // the direction ring: the slots of this iteration and the one before
     if (a.ring > 0) {
         ring.slot = a.slot;
@@ -4184,7 +3894,7 @@ void iteration(const MgState& M, PcgMg a, const TileGeo& tg, hipStream_t st, int
     }
     if (tg.on && p32) {
         launch_tile<kTDirSpmv, B, true, true>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, ring);
-    } else if (tg.on && z32_path<B>(M, tg)) {   // z from the fused prolongation + last sweep, FP32
+    } else if (tg.on && z32_path<B>(tg)) {   // z from the fused prolongation + last sweep, FP32
         launch_tile<kTDirSpmv, B, true>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, ring);
     } else if (tg.on) {
         launch_tile<kTDirSpmv, B>(M, tg, st, a.z, a.po, nullptr, a.q, a.pn, ring);
@@ -4210,8 +3920,8 @@ void iteration(const MgState& M, PcgMg a, const TileGeo& tg, hipStream_t st, int
     if (ev) (void)hipEventRecord(ev[1], st);
     hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, tg.on ? tg.blocks : (int)g.x, 0);
     if (ev) (void)hipEventRecord(ev[2], st);
-    const bool upd1 = B == 1 && !fused_update(tg) && a.L.N * 8 < (int64_t(1) << 31);
-    if (fused_update(tg)) {   // r, x and the V-cycle's first sweep + residual in one pass; r alternates buffers
+    const bool upd1 = B == 1 && !tg.on && a.L.N * 8 < (int64_t(1) << 31);
+    if (tg.on) {   // r, x and the V-cycle's first sweep + residual in one pass; r alternates buffers
         double* r_old = par ? M.pr2 : M.pr;
         double* r_new = par ? M.pr : M.pr2;
         launch_tile<kTUpdResid, B>(M, tg, st, r_old, a.q, nullptr, M.lv[0].r, r_new);
@@ -4226,12 +3936,12 @@ void iteration(const MgState& M, PcgMg a, const TileGeo& tg, hipStream_t st, int
         hipLaunchKernelGGL(k_mgp_update<B>, g, dim3(kMgT), 0, st, a, level_args(M, 0), M.lv[0].x);
     }
     if (ev) (void)hipEventRecord(ev[3], st);
-    const int nb1 = fused_update(tg) ? tg.blocks : upd1 ? a.nbr : (int)g.x;
+    const int nb1 = tg.on ? tg.blocks : upd1 ? a.nbr : (int)g.x;
     const bool reg1 = upd1 && a.kreg > 0;   // k_reg_solve takes the scalars with it
     if (!reg1) hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, nb1, 1);
     region_solve<B>(M, a, st, upd1);
-    vcycle<B>(M, st, tg, ev ? ev + 4 : nullptr, a.r, fused_update(tg), p32, !fused_update(tg));
-    hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, last_blocks<B>(M, tg, p32), 2);
+    vcycle<B>(M, st, tg, ev ? ev + 4 : nullptr, a.r, tg.on, !tg.on);
+    hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, st, a, last_blocks<B>(M, tg), 2);
 }
 
 // true residual r = b - A x of every lane, partial r.r (write_r false, tiled path:
@@ -4257,7 +3967,7 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
     // The tiled iterations keep their directions and alphas in a ring and form
     // x = x + sum alpha_j p_j (k_mgp_ring_flush) before x is read: the update
     // then neither reads nor writes x nor reads p.
-    if (fused_update(tg)) {
+    if (tg.on) {
         if (!M.pring) {
             const size_t n = (size_t)kRing * c->N * M.bmax;   // FP64-sized slots
             QPAT_TRY(dalloc(c, &M.pring, n));
@@ -4276,7 +3986,7 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
     auto ring_flush = [&]() -> qpat_status {
         if (a.ring == 0 || (ring_s == ring_f && !x_zero)) return QPAT_OK;
         const int64_t n = c->N * (int64_t)B;
-        const bool p32r = a.p32 && z32_path<B>(M, tg);
+        const bool p32r = a.p32 && z32_path<B>(tg);
         const int64_t stride = n * (p32r ? 4 : 8);
         const char* base = reinterpret_cast<const char*>(M.pring);
         if (B % (p32r ? 4 : 2) != 0) return fail(c, QPAT_ERR_STATE, "multigrid: direction ring with %d right-hand sides", B);
@@ -4334,9 +4044,9 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         if (restart > 0 && tg.on) true_residual<B>(M, a, tg, c->b64, sm);
         // first direction of a run: z = V(r) (+ Z y), p = z - c
         region_solve<B>(M, a, sm);
-        vcycle<B>(M, sm, tg, nullptr, nullptr, false, a.p32 != 0 && z32_path<B>(M, tg));
+        vcycle<B>(M, sm, tg);
         hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, sm, a,
-                           last_blocks<B>(M, tg, a.p32 != 0 && z32_path<B>(M, tg)), 3);
+                           last_blocks<B>(M, tg), 3);
         QPAT_HIP(c, hipGetLastError());
         // Iterations run in chunks of even length between host checks. The
         // first is kMgChunk0 long; later ones cover the iterations that the
@@ -4407,7 +4117,7 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
                     for (int l = 0; l < S; ++l) lanes_on += (M.sc_host[l].iters - iters_before[l]) > i;
                     if (lanes_on == 0) break;
                     for (int kk = 0; kk < 4; ++kk) {
-                        if (kk == 2 && fused_update(tg)) continue;   // the update's kernel did it
+                        if (kk == 2 && tg.on) continue;   // the update's kernel did it
                         float t = 0.f;
                         QPAT_HIP(c, hipEventElapsedTime(&t, M.ev[8 * i + 2 * kk], M.ev[8 * i + 2 * kk + 1]));
                         qpat_kstat& ks = c->prof[base + kk];
@@ -4891,11 +4601,6 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
                 QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * kUpRow));
                 QPAT_TRY(dalloc(c, &L.Uf32, nsys * L.N * kUpRow));
             }
-            if (op == Op::K && l == 0 && L.kind == 1 && M.bmax == 16 && nl > 1 &&
-                L.N * kFullRow * (int64_t)sizeof(double) < (int64_t(1) << 31)) {   // node-major, for k_mg_prolong_smooth
-                QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * kFullRow));
-                QPAT_TRY(dalloc(c, &L.Ufk32, nsys * L.N * kFullRow));
-            }
             if (op == Op::K && l >= 1 && l < kMgMaxLevels && M.bmax == 16 && M.lv[0].kind == 1 &&
                 L.N >= kTile27Min && L.N * kRow27 * (int64_t)sizeof(double) < (int64_t(1) << 31)) {
                 QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * kRow27));
@@ -4927,20 +4632,13 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
     const int nl = static_cast<int>(M.lv.size());
     M.lv[0].U = op == Op::K ? c->KU64 : c->MU64;
     M.opdep = op == Op::Prior;
-    if (M.lv[0].Uf) {   // M_delta's walk kernels (upper rows), K's fused prolongation + sweep (whole rows)
+    if (M.lv[0].Uf) {   // M_delta's walk kernels
         M.lv[0].kind = 1;
-        if (op == Op::K)
-            hipLaunchKernelGGL(k_mg_fullrows<false>, dim3(grid_for(M.lv[0].N, kMgT, 4096), nsys), dim3(kMgT), 0,
-                               c->stream, lv_args(M.lv[0]), M.lv[0].Uf);
-        else
-            hipLaunchKernelGGL(k_mg_fullrows<true>, dim3(grid_for(M.lv[0].N, kMgT, 4096), nsys), dim3(kMgT), 0,
-                               c->stream, lv_args(M.lv[0]), M.lv[0].Uf);
+        hipLaunchKernelGGL(k_mg_fullrows, dim3(grid_for(M.lv[0].N, kMgT, 4096), nsys), dim3(kMgT), 0, c->stream,
+                           lv_args(M.lv[0]), M.lv[0].Uf);
         if (M.lv[0].Uf32)
             hipLaunchKernelGGL(k_to_f32, dim3(grid_for(nsys * M.lv[0].N * kUpRow, kMgT, 4096)), dim3(kMgT), 0,
                                c->stream, M.lv[0].Uf, M.lv[0].Uf32, nsys * M.lv[0].N * kUpRow);
-        if (M.lv[0].Ufk32)
-            hipLaunchKernelGGL(k_to_f32, dim3(grid_for(nsys * M.lv[0].N * kFullRow, kMgT, 4096)), dim3(kMgT), 0,
-                               c->stream, M.lv[0].Uf, M.lv[0].Ufk32, nsys * M.lv[0].N * kFullRow);
     }
     for (int l = 0; l + 1 < nl; ++l) {
         const MgLevel& F = M.lv[l];
@@ -5047,10 +4745,10 @@ qpat_status mg_tile_schedule(const qpat_ctx* c, int B, int32_t out[8]) {
     out[0] = t.on ? 1 : 0;
     out[1] = t.on ? t.zc : 0;
     out[2] = t.on ? t.zc_model : 0;
-    out[3] = t.ps_on ? t.ps_zc : 0;
-    out[4] = t.ps_on ? t.ps_zc_model : 0;
-    out[5] = t.ps_on ? t.ps_zc32 : 0;
-    out[6] = t.ps_on ? t.ps_zc32_model : 0;
+    out[3] = t.on ? t.ps_zc : 0;
+    out[4] = t.on ? t.ps_zc_model : 0;
+    out[5] = out[3];   // one form for both precisions
+    out[6] = out[4];
     out[7] = t.tuned ? 1 : 0;
     return QPAT_OK;
 }

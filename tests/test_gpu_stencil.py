@@ -362,6 +362,19 @@ def test_prior_solves_either_side_of_the_fused_sizes(nx, ny, nz, deflate):
     assert rel(host(y), host(p)) <= (1e-9 if deflate else 1e-8)
 
 
+@pytest.mark.parametrize("nx,ny,nz", [(7, 8, 1), (8, 7, 2), (9, 16, 3), (16, 9, 12), (17, 15, 31), (6, 24, 64)])
+@pytest.mark.parametrize("n_ill,precision", [(7, 0), (8, 1), (15, 0), (16, 1)])
+def test_tiled_last_sweep_at_chunk_and_parity_edges(nx, ny, nz, n_ill, precision):
+    """The prolongation fused into the tiled last sweep: lattices of 2 to 65 planes, of odd and even sides (whose
+    last coarse column lies on or past the fine edge) in tiles of 8 x 8, with 8 and 16 right-hand sides. PCG is
+    right whatever z is, so the iteration count is part of the check (14 - 16 at 16^3 - 128^3, 20 allowed)."""
+    P = box_problem(nx, ny, nz, n_ill, nx + 64 * nz)
+    _, phi, info = solve(*P, pcg_rtol=1e-12, precision=precision)
+    lin = Linearisation(fem.geometry(*P[:3]), *P[3:])
+    assert_close(phi, lin.phi, 1e-10, "phi")
+    assert info["iters_max"] <= 20, info
+
+
 @pytest.mark.parametrize("n_ill", [1, 3, 8, 18])
 def test_data_arrays_and_options_switched_after_forward(n_ill):
     """phi, h, J s and J^T t in the caller's [n_ill][N] layout for every column count of the transposes (N no
