@@ -353,39 +353,30 @@ __device__ __forceinline__ TB<B> apply(const LvArgs& L, const double* __restrict
                 s += U[(i - t.w) * M1 + j + 1] * x(i - t.w);
         }
         return s;
-    } else if constexpr (KIND == 4) {   // 27-point whole rows, entry-major ([27][N])
+    } else if constexpr (KIND == 4 || KIND == 6) {
+        // 27-point whole rows, entry-major ([27][N]; 4: FP64, 6: FP32)
+        using W = std::conditional_t<KIND == 6, float, double>;
+        const W* Uw = reinterpret_cast<const W*>(U);
         const Edges in(L.nx, L.ny, L.nz, ix, iy, iz);
-        T s = U[i] * x(i);
+        T s = static_cast<double>(Uw[i]) * x(i), xu[13], xl[13];
+        W cu[13], cl[13];
 #pragma unroll
         for (int j = 0; j < 13; ++j) {
             const int code = 14 + j;
             const int dx = code % 3 - 1, dy = (code / 3) % 3 - 1, dz = code / 9 - 1;
             const int32_t lin = dx + L.nx * (dy + L.ny * dz);
-            const bool up = in.has(dx, dy, dz);
-            const bool lo = in.has(-dx, -dy, -dz);
-            // loads from clamped indices and selected sums: no branch per
-            // neighbour, so all of a row's loads are in flight together
-            const T xu = x(up ? i + lin : i), xl = x(lo ? i - lin : i);
-            const double cu = U[(1 + j) * L.N + i], cl = U[(14 + j) * L.N + i];
-            s = up ? s + cu * xu : s;
-            s = lo ? s + cl * xl : s;
+            xu[j] = x(in.has(dx, dy, dz) ? i + lin : i);
+            xl[j] = x(in.has(-dx, -dy, -dz) ? i - lin : i);
+            cu[j] = Uw[(1 + j) * L.N + i];
+            cl[j] = Uw[(14 + j) * L.N + i];
         }
-        return s;
-    } else if constexpr (KIND == 6) {   // the kind-4 rows in FP32 (a preconditioner's coarse operator)
-        const float* Uw = reinterpret_cast<const float*>(U);
-        const Edges in(L.nx, L.ny, L.nz, ix, iy, iz);
-        T s = static_cast<double>(Uw[i]) * x(i);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int j = 0; j < 13; ++j) {
             const int code = 14 + j;
             const int dx = code % 3 - 1, dy = (code / 3) % 3 - 1, dz = code / 9 - 1;
-            const int32_t lin = dx + L.nx * (dy + L.ny * dz);
-            const bool up = in.has(dx, dy, dz);
-            const bool lo = in.has(-dx, -dy, -dz);
-            const T xu = x(up ? i + lin : i), xl = x(lo ? i - lin : i);
-            const double cu = static_cast<double>(Uw[(1 + j) * L.N + i]), cl = static_cast<double>(Uw[(14 + j) * L.N + i]);
-            s = up ? s + cu * xu : s;
-            s = lo ? s + cl * xl : s;
+            s = in.has(dx, dy, dz) ? s + static_cast<double>(cu[j]) * xu[j] : s;
+            s = in.has(-dx, -dy, -dz) ? s + static_cast<double>(cl[j]) * xl[j] : s;
         }
         return s;
     } else if constexpr (KIND == 3 || KIND == 5) {
@@ -3671,11 +3662,14 @@ inline SmArgs level_args(const MgState& M, int l) {
 // pair (separate -> fused) on 17^3 nodes with 4 right-hand sides 1449 -> 1302
 // us, 33^3 with 4 2250 -> 2210, 41^3 with 1 2578 -> 2498; M_delta's kernels
 // read their transfer weights as well: 17^3 838 -> 793, 25^3 1756 -> 1742,
-// 33^3 1484 -> 1583.
-constexpr int64_t kFuseK = 80000, kFuseM = 32768;
+// 33^3 1484 -> 1583. The coarse levels' 27-point rows are formed up to 8 times
+// over at more cost: six solves side by side, 25^3 - 61^3, never 11.15 ms, up
+// to 20000 threads 11.02, up to 80000 11.62 (17^3 with 16 right-hand sides,
+// 39000 threads, 16.7 us against 5.9 + 5.6).
+constexpr int64_t kFuseK = 80000, kFuseM = 32768, kFuseCoarse = 20000;
 template <int B>
-inline bool fuse_small(int64_t n, int nsys) {
-    return n * Pk<B>::BV * nsys <= (nsys == 1 ? kFuseK : kFuseM);
+inline bool fuse_small(int64_t n, int nsys, int lev = 0) {
+    return n * Pk<B>::BV * nsys <= (lev > 0 ? kFuseCoarse : nsys == 1 ? kFuseK : kFuseM);
 }
 
 // level l's residual to level l + 1's b and first sweep xc, in one launch
@@ -3744,7 +3738,7 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
         if (l == 0 && ev) (void)hipEventRecord(ev[0], st);
         const bool tiled = (l == 0 && tg.on) || (B == 16 && tiled27(tg, l)) ||
                            (tg.on && l < kMgMaxLevels && tg.rst[l].on && !M.opdep);
-        if (!tiled && !ev && fuse_small<B>(L.N, M.nsys)) {   // residual and restriction in one launch
+        if (!tiled && !ev && fuse_small<B>(L.N, M.nsys, l)) {   // residual and restriction in one launch
             launch_resid_restrict<B>(M, l, st, bl, xl[l], xl[l + 1], l == 0 && f0);
             continue;
         }
