@@ -54,6 +54,12 @@ __device__ __forceinline__ void load_geo4(const GeoRef& r, int32_t e, Geo4& G) {
         load_geo4(r.geo, e, G);
 }
 
+// kSplit consecutive threads share a node's element list (one element in
+// kSplit each) and sum by shuffles: the list's loads are independent, so
+// more of them are in flight than with one thread per node (k_gfwd on 15625
+// shuffled nodes with 8 right-hand sides: 112 -> 24 us).
+constexpr int kSplit = 8;
+
 // right-hand sides handled by one thread of the G kernels: the per-tetrahedron
 // geometry and coefficients are loaded once for all of them
 template <int B>
@@ -72,13 +78,16 @@ __global__ __launch_bounds__(kThreads) void k_gfwd(int64_t N, const int32_t* __r
                                                   double* __restrict__ b) {
     constexpr int KG = kGroup<B>, G = B / KG;
     int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (t >= N * G) return;
+    const int sub = static_cast<int>(t % kSplit);
+    t /= kSplit;
+    const bool valid = t < N * G;   // whole groups of kSplit lanes
     const int64_t row = t / G;
     const int k0 = static_cast<int>(t % G) * KG;
     double acc[KG];
 #pragma unroll
     for (int i = 0; i < KG; ++i) acc[i] = 0.0;
-    for (int32_t q = n2t_ptr[row]; q < n2t_ptr[row + 1]; ++q) {
+    const int32_t q1 = valid ? n2t_ptr[row + 1] : 0;
+    for (int32_t q = valid ? n2t_ptr[row] + sub : 0; q < q1; q += kSplit) {
         const int32_t e = n2t[q] >> 2, a = n2t[q] & 3;
         Geo4 G4;
         load_geo4(geo, e, G4);
@@ -113,7 +122,12 @@ __global__ __launch_bounds__(kThreads) void k_gfwd(int64_t N, const int32_t* __r
         }
     }
 #pragma unroll
-    for (int i = 0; i < KG; ++i) b[row * B + k0 + i] = acc[i];
+    for (int off = kSplit / 2; off >= 1; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < KG; ++i) acc[i] += __shfl_xor(acc[i], off);
+    if (valid && sub == 0)
+#pragma unroll
+        for (int i = 0; i < KG; ++i) b[row * B + k0 + i] = acc[i];
 }
 
 // ---- lattice meshes: the same products through the stencil form
@@ -121,10 +135,6 @@ __global__ __launch_bounds__(kThreads) void k_gfwd(int64_t N, const int32_t* __r
 // (diagonal and upper offsets, [N][m+1]): the element sums of the assembly of
 // K without the boundary term, so G(1) diag(kappa) s1 + G(2) diag(mu) s2 =
 // -dK(s) phi for every illumination, one stencil product per block.
-// kSplit consecutive threads share a node's element list (one element in
-// kSplit each) and sum by shuffles: the list's loads are independent, so
-// more of them are in flight than with one thread per node.
-constexpr int kSplit = 8;
 
 // the coefficients of dK(s) per node: uu[i] = (kappa_i s1_i, mu_i s2_i) (s null: of K, s = 1)
 __global__ __launch_bounds__(kThreads) void k_dk_coef(int64_t N, const double* __restrict__ kappa,
@@ -977,9 +987,10 @@ qpat_status forward_solve_x0(qpat_ctx* c, const double* x0, SolveStats* st) {
 qpat_status jvp_core(qpat_ctx* c, const double* s, int mode, double* out, SolveStats* st) {
     const int B = block_size(c);
     const dim3 g(grid_for(c->N * B, kThreads, 1 << 30)), blk(kThreads), gt(grid_for(c->N, kTrN, 1 << 30));
-    // lattice meshes: dK(s) once in the stencil form, then one tiled stencil
-    // product per block (else the element loop per block)
-    const bool lat = c->lat.on && c->opts.operator_format == 1 && B >= 8;
+    // lattice meshes: dK(s) once in the stencil form, then one stencil product per
+    // block (else the element loop per block: with 4 right-hand sides 17^3 nodes
+    // 42 -> 13 us, 33^3 58 -> 16)
+    const bool lat = c->lat.on && c->opts.operator_format == 1 && (B >= 8 || mg_stencil_ready(c));
     if (lat) {
         if (!c->dK) QPAT_TRY(dalloc(c, &c->dK, (int64_t)(c->lat.m + 1) * c->N));
         if (!c->dKc) QPAT_TRY(dalloc(c, &c->dKc, 2 * c->N));
@@ -1003,7 +1014,7 @@ qpat_status jvp_core(qpat_ctx* c, const double* s, int mode, double* out, SolveS
         if (lat) QPAT_TRY(mg_stencil_apply(c, B, c->dK, c->phi, c->n_pad, col0, c->b64, -1.0, &done));
         if (!done)
             QPAT_DISPATCH_B(B, hipLaunchKernelGGL(k_gfwd<BB>,
-                                                  dim3(grid_for(c->N * (BB / kGroup<BB>), kThreads, 1 << 30)), blk, 0,
+                                                  dim3(grid_for(c->N * (BB / kGroup<BB>) * kSplit, kThreads, 1 << 30)), blk, 0,
                                                   c->stream, c->N, c->tets, c->geo, c->n2t_ptr, c->n2t, c->kappa,
                                                   c->mu, s, c->phi, c->n_pad, col0, c->b64));
         QPAT_TRY(k_solve(c, B, st));

@@ -4694,16 +4694,43 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
     return QPAT_OK;
 }
 
+namespace {
+// columns col ... of a vector [N][ld], its right-hand sides
+template <int B>
+struct ColAt {
+    const double* x;
+    int64_t ld;
+    __device__ __forceinline__ TB<B> operator()(int32_t i) const { return vld<TB<B>>(x + i * ld); }
+};
+template <int B>
+__global__ __launch_bounds__(kMgT) void k_mg_apply(LvArgs L, const double* __restrict__ in, int ld,
+                                                   double* __restrict__ out, double scale) {
+    using T = TB<B>;
+    const int v = threadIdx.x % Pk<B>::BV * Pk<B>::V;
+    walk<Pk<B>::BV>(L.nx, L.ny, L.nz, [&](int32_t ix, int32_t iy, int32_t iz, int32_t i, int32_t) {
+        vst<T>(out + (int64_t)i * B + v, scale * apply<1, B>(L, L.U, ColAt<B>{in + v, ld}, ix, iy, iz, i));
+    });
+}
+}  // namespace
+
 // out [N][B] = scale U in, U a Kuhn stencil form [N][8] of the lattice, in
-// [N][ld] (columns col ... col + B - 1), with the LDS-tiled kernel of the K
-// hierarchy's finest level. false: that tiling is not available for B.
+// [N][ld] (columns col ... col + B - 1; both multiples of B), with the
+// LDS-tiled kernel of the K hierarchy's finest level, below 8 right-hand sides
+// with the walk kernels' rows. done = false: not available for B.
 template <int B>
 static qpat_status apply_B(qpat_ctx* c, const double* U, const double* in, int ld, int col, double* out,
                            double scale, bool* done) {
     *done = false;
-    if constexpr (B >= 8) {
-        MgState* M = state_of(c, Op::K);
-        if (!M || !mg_ready(c, Op::K)) return QPAT_OK;
+    MgState* M = state_of(c, Op::K);
+    if (!M || !mg_ready(c, Op::K)) return QPAT_OK;
+    if constexpr (B < 8) {
+        if (M->lv[0].kind != 1) return QPAT_OK;
+        LvArgs L = lv_args(M->lv[0]);
+        L.U = U;
+        hipLaunchKernelGGL(k_mg_apply<B>, sgrid<B>(c->N), dim3(kMgT), 0, c->stream, L, in + col, ld, out, scale);
+        QPAT_HIP(c, hipGetLastError());
+        *done = true;
+    } else {
         QPAT_TRY(tile_setup<B>(c, *M));
         const TileGeo& t = M->tiles[B];
         if (!t.on) return QPAT_OK;
@@ -4747,9 +4774,15 @@ qpat_status mg_tile_schedule(const qpat_ctx* c, int B, int32_t out[8]) {
     return QPAT_OK;
 }
 
+// whether mg_stencil_apply has the form for fewer than 8 right-hand sides
+bool mg_stencil_ready(qpat_ctx* c) { return mg_ready(c, Op::K) && state_of(c, Op::K)->lv[0].kind == 1; }
+
 qpat_status mg_stencil_apply(qpat_ctx* c, int B, const double* U, const double* in, int ld, int col, double* out,
                              double scale, bool* done) {
     switch (B) {
+        case 1: return apply_B<1>(c, U, in, ld, col, out, scale, done);
+        case 2: return apply_B<2>(c, U, in, ld, col, out, scale, done);
+        case 4: return apply_B<4>(c, U, in, ld, col, out, scale, done);
         case 8: return apply_B<8>(c, U, in, ld, col, out, scale, done);
         case 16: return apply_B<16>(c, U, in, ld, col, out, scale, done);
         default: *done = false; return QPAT_OK;

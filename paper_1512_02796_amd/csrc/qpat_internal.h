@@ -407,6 +407,7 @@ void mg_destroy(qpat_ctx* c);
 // not available (no current K hierarchy, B < 8, offsets past 32 bits).
 // the tile schedule of the K hierarchy for blocks of B (qpat_tile_schedule)
 qpat_status mg_tile_schedule(const qpat_ctx* c, int B, int32_t out[8]);
+bool mg_stencil_ready(qpat_ctx* c);
 qpat_status mg_stencil_apply(qpat_ctx* c, int B, const double* U, const double* in, int ld, int col, double* out,
                              double scale, bool* done);
 

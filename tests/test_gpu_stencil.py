@@ -375,6 +375,22 @@ def test_tiled_last_sweep_at_chunk_and_parity_edges(nx, ny, nz, n_ill, precision
     assert info["iters_max"] <= 20, info
 
 
+@pytest.mark.parametrize("dims", [(9, 6, 12), (5, 11, 17), (1, 2, 9)])
+@pytest.mark.parametrize("block,n_ill,precond", [(1, 2, 1), (2, 5, 1), (4, 7, 1), (4, 7, 0)])
+def test_jacobian_product_in_small_blocks(dims, block, n_ill, precond):
+    """J s with fewer than 8 right-hand sides a block, several blocks and a ragged last one: the stencil product
+    of the multigrid hierarchy (or, on Jacobi-PCG and where a lattice has no hierarchy, the element loop) against
+    the oracle, element-wise 1e-10 as above."""
+    coords, tets, bfaces, kappa, mu, src = box_problem(*dims, n_ill, block + sum(dims))
+    ctx, _, _ = solve(coords, tets, bfaces, kappa, mu, src, max_rhs_block=block, pcg_rtol=1e-12, pcg_precond=precond)
+    lin = Linearisation(fem.geometry(coords, tets, bfaces), kappa, mu, src)
+    N = coords.shape[0]
+    s = np.random.default_rng(block).standard_normal(2 * N)
+    js = torch.empty(n_ill * N, dtype=torch.float64, device="cuda")
+    ctx.jvp(dev(s), js)
+    assert_close(host(js).reshape(n_ill, N), lin.jvp(s), 1e-10, "J s")
+
+
 @pytest.mark.parametrize("n_ill", [1, 3, 8, 18])
 def test_data_arrays_and_options_switched_after_forward(n_ill):
     """phi, h, J s and J^T t in the caller's [n_ill][N] layout for every column count of the transposes (N no
