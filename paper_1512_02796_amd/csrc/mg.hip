@@ -55,7 +55,7 @@ struct MgLevel {
                                    // transfers read these (W holds the same rounded values for the Galerkin set-up:
                                    // one P throughout)
     double* Uf = nullptr;          // kind 3: [nsys][kUpRow][N] Kuhn diagonal + upper entries, entry-major;
-                                   // K levels >= 1: [N][kRow27]
+                                   // kind 4: [nsys][27][N]
     float* Uf32 = nullptr;         // kind 5 / 6: the kind-3 / kind-4 rows in FP32 (M_delta's V-cycle)
     float* Uf27p = nullptr;        // K tiled levels >= 1: the 27-point rows in FP32 as [N][16] pairs (entry k, entry k + 16)
     int32_t vkind = -1;            // row kind of the V-cycle's kernels on this level (-1: kind)
@@ -155,28 +155,6 @@ __device__ __forceinline__ void coords(int32_t i, int nx, int ny, int& ix, int& 
     iz = q / ny;
 }
 
-// (A x)_i of lane k (x interleaved [N][B]), and sum_j |a_ij| when ABS
-template <bool ABS, int B>
-__device__ __forceinline__ double st_row(const double* __restrict__ U, int M1, const int4* __restrict__ tab, int m,
-                                         int nx, int ny, int nz, const double* __restrict__ x, int32_t i, int k) {
-    int ix, iy, iz;
-    coords(i, nx, ny, ix, iy, iz);
-    double s = ABS ? fabs(U[(int64_t)i * M1]) : U[(int64_t)i * M1] * x[(int64_t)i * B + k];
-    for (int j = 0; j < m; ++j) {
-        const int4 t = tab[j];
-        const int ux = ix + t.x, uy = iy + t.y, uz = iz + t.z;
-        if (ux >= 0 && ux < nx && uy >= 0 && uy < ny && uz < nz) {
-            const double a = U[(int64_t)i * M1 + j + 1];
-            s += ABS ? fabs(a) : a * x[(int64_t)(i + t.w) * B + k];
-        }
-        const int lx = ix - t.x, ly = iy - t.y, lz = iz - t.z;
-        if (lx >= 0 && lx < nx && ly >= 0 && ly < ny && lz >= 0) {
-            const double a = U[(int64_t)(i - t.w) * M1 + j + 1];
-            s += ABS ? fabs(a) : a * x[(int64_t)(i - t.w) * B + k];
-        }
-    }
-    return s;
-}
 // The rows with compile-time offsets: KIND 1 the Kuhn split (7 upper offsets,
 // the fine level of a Kuhn mesh), KIND 2 the full 27-point stencil (13 upper
 // offsets in code order, the Galerkin levels); KIND 0 the generic table.
@@ -626,6 +604,9 @@ __global__ __launch_bounds__(kMgT) void k_to_f32(const double* __restrict__ a, f
 }
 
 // 1 / a_ii and the Gershgorin bound max_i sum_j |a_ij| / a_ii
+// (M: room for the stored upper offsets, at least L.m; a row's loads go out
+// together: the five levels of 97^3 136 -> 75 us)
+template <int M>
 __global__ __launch_bounds__(kMgT) void k_mg_diag(LvArgs L, double* __restrict__ dinv, uint64_t* __restrict__ gmax,
                                                   int nlev, int lev) {
     __shared__ double sm[kMgT / 64];
@@ -636,7 +617,25 @@ __global__ __launch_bounds__(kMgT) void k_mg_diag(LvArgs L, double* __restrict__
     for (int64_t i = blockIdx.x * (int64_t)kMgT + threadIdx.x; i < L.N; i += (int64_t)gridDim.x * kMgT) {
         const double d = U[i * M1];
         dinv[sys * L.N + i] = 1.0 / d;
-        const double row = st_row<true, 1>(U, M1, L.tab, L.m, L.nx, L.ny, L.nz, nullptr, static_cast<int32_t>(i), 0);
+        int ix, iy, iz;
+        coords(static_cast<int32_t>(i), L.nx, L.ny, ix, iy, iz);
+        double up[M], lo[M];
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            const int4 t = L.tab[j < L.m ? j : 0];
+            const bool u = j < L.m && ix + t.x >= 0 && ix + t.x < L.nx && iy + t.y >= 0 && iy + t.y < L.ny && iz + t.z < L.nz;
+            const bool l = j < L.m && ix - t.x >= 0 && ix - t.x < L.nx && iy - t.y >= 0 && iy - t.y < L.ny && iz - t.z >= 0;
+            const double a = U[i * M1 + (u ? j + 1 : 0)], b = U[(l ? i - t.w : i) * M1 + (l ? j + 1 : 0)];
+            up[j] = u ? a : 0.0;
+            lo[j] = l ? b : 0.0;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        double row = fabs(d);
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            row += fabs(up[j]);
+            row += fabs(lo[j]);
+        }
         g = fmax(g, row / d);
     }
 #pragma unroll
@@ -729,9 +728,12 @@ __global__ __launch_bounds__(kMgT) void k_mg_wpack(LvArgs L, double* __restrict_
 // 32 lanes share a coarse node, one for each of the 27 fine nodes of its support,
 // and their sums are added in LDS in that order. With one thread a coarse node
 // the few thousand serial loads of a thread bounded every level alike (560 us
-// a level at 65^3, 370 us at 17^3).
+// a level at 65^3, 370 us at 17^3). A fine row's loads go out together (M: room
+// for its stored upper offsets), and the sums go to LDS as adds nobody waits
+// for, each thread its own column (the four levels of 97^3: 382 -> 319 us).
 constexpr int kRapLanes = 32;
 constexpr int kRapNodes = kMgT / kRapLanes;   // coarse nodes a block
+template <int M>
 __global__ __launch_bounds__(kMgT) void k_mg_rap(LvArgs F, const double* __restrict__ Wall, double* __restrict__ Uc,
                                                  int cx, int cy, int cz) {
     __shared__ double acc[14][kMgT];
@@ -752,21 +754,30 @@ __global__ __launch_bounds__(kMgT) void k_mg_rap(LvArgs F, const double* __restr
         const int32_t i = fx + F.nx * (fy + F.ny * fz);
         // I = J0(i) + corner, corner 1 exactly along the axes where i sits below 2 I
         const double wi = pweight(W, F.N, i, fx, fy, fz, (ax < 0 ? 1 : 0) + (ay < 0 ? 2 : 0) + (az < 0 ? 4 : 0));
-        // the fine row: diagonal, upper and lower entries
-        for (int s = -F.m; s <= F.m && wi != 0.0; ++s) {
-            int sx = 0, sy = 0, sz = 0, lin = 0;
-            if (s != 0) {
-                const int4 t = F.tab[(s > 0 ? s : -s) - 1];
-                const int sg = s > 0 ? 1 : -1;
-                sx = sg * t.x;
-                sy = sg * t.y;
-                sz = sg * t.z;
-                lin = sg * t.w;
-            }
-            const int jx = fx + sx, jy = fy + sy, jz = fz + sz;
-            if (jx < 0 || jx >= F.nx || jy < 0 || jy >= F.ny || jz < 0 || jz >= F.nz) continue;
-            const int32_t j = i + lin;
-            const double a = s >= 0 ? U[(int64_t)i * Mf + s] : U[(int64_t)j * Mf - s];
+        // the fine row: lower entries, diagonal, upper entries
+        double a[2 * M + 1];
+        const auto off = [&](int s) {   // dx, dy, dz, linear
+            const int4 t = F.tab[abs(s) <= F.m ? abs(s) - 1 : 0];
+            return s > 0 ? t : make_int4(-t.x, -t.y, -t.z, -t.w);
+        };
+        const auto at = [&](int s, const int4& t) {   // on the lattice
+            const int jx = fx + t.x, jy = fy + t.y, jz = fz + t.z;
+            return abs(s) <= F.m && jx >= 0 && jx < F.nx && jy >= 0 && jy < F.ny && jz >= 0 && jz < F.nz;
+        };
+#pragma unroll
+        for (int s = -M; s <= M; ++s) {
+            const int4 t = s ? off(s) : make_int4(0, 0, 0, 0);
+            const bool on = s == 0 || at(s, t);
+            a[s + M] = U[(int64_t)(on && s < 0 ? i + t.w : i) * Mf + (on ? abs(s) : 0)];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = -M; s <= M; ++s) {
+            const int4 t = s ? off(s) : make_int4(0, 0, 0, 0);
+            if ((s != 0 && !at(s, t)) || wi == 0.0) continue;
+            const int jx = fx + t.x, jy = fy + t.y, jz = fz + t.z;
+            const int32_t j = i + t.w;
+            const double wa = wi * a[s + M];
             // corners that can carry a weight: one step up only along odd axes
             const int px = jx & 1, py = jy & 1, pz = jz & 1;
             const int code0 = ((jx >> 1) - Ix) + 3 * ((jy >> 1) - Iy) + 9 * ((jz >> 1) - Iz);
@@ -777,7 +788,7 @@ __global__ __launch_bounds__(kMgT) void k_mg_rap(LvArgs F, const double* __restr
                 const int code = code0 + bx + 3 * by + 9 * bz;   // the lower half is stored at the partner row
                 if (code < 0) continue;
                 const double wj = W ? W[cj * F.N + j] : (px ? 0.5 : 1.0) * (py ? 0.5 : 1.0) * (pz ? 0.5 : 1.0);
-                acc[code][threadIdx.x] += wi * a * wj;
+                (void)__hip_atomic_fetch_add(&acc[code][threadIdx.x], wa * wj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
     }
@@ -2736,41 +2747,52 @@ __global__ __launch_bounds__(kTT) void k_mg_restrict_tile(RstArgs g) {
 // ------------------------------------------------ LDS-tiled 27-point kernels
 // The first coarse level of the K hierarchy with 16 right-hand sides: the
 // same 2.5D tiling as the finest level (the input vector's planes in LDS),
-// with the Galerkin operator's 27-point rows stored whole ([N][kRow27]:
+// with the Galerkin operator's 27-point rows stored whole (FP32, 32 a node:
 // diagonal, 13 upper, 13 lower entries, zero where the partner is off the
 // lattice, padding). The 16 lanes of a node load its row as two 128-byte
 // lines, lane k holding entries k and 16 + k, and every entry reaches the
 // row's lanes by a DPP row broadcast, so the operator never passes through
 // LDS and the partner rows are never gathered.
-constexpr int kRow27 = 32;
 constexpr int64_t kTile27Min = 16384;   // smaller levels keep the walk kernels (launch-bound anyway)
 constexpr int64_t kRow27Min = 131072;   // M_delta: whole 27-point rows pay off from about this size on
 enum Tile27Mode { kT27Resid = 0, kT27Smooth = 1 };
 
-// ENTRY: entry-major [27][N] per system (the one-right-hand-side walk
-// kernels, row kind 4) instead of node-major [N][kRow27]
-template <bool ENTRY>
+// whole 27-point rows from the stored half (diagonal, 13 upper, 13 lower
+// entries; zero where the partner is off the lattice), entry e of node i
+__device__ __forceinline__ double row27(const LvArgs& L, const double* __restrict__ U, int64_t i, int ix, int iy, int iz,
+                                        int e) {
+    if (e == 0) return U[i * 14];
+    if (e > 26) return 0.0;
+    const int j = e < 14 ? e - 1 : e - 14, sg = e < 14 ? 1 : -1, code = 14 + j;
+    const int dx = sg * (code % 3 - 1), dy = sg * ((code / 3) % 3 - 1), dz = sg * (code / 9 - 1);
+    const bool in = ix + dx >= 0 && ix + dx < L.nx && iy + dy >= 0 && iy + dy < L.ny && iz + dz >= 0 && iz + dz < L.nz;
+    const int64_t r = e < 14 ? i : i + dx + (int64_t)L.nx * (dy + (int64_t)L.ny * dz);
+    return in ? U[r * 14 + 1 + j] : 0.0;
+}
+
+// entry-major [27][N] per system (the one-right-hand-side walk kernels, row kind 4)
 __global__ __launch_bounds__(kMgT) void k_mg_fullrows27(LvArgs L, double* __restrict__ Uf) {
     const int sys = blockIdx.y;
-    constexpr int M1 = 14;
-    const double* U = L.U + (int64_t)sys * L.N * M1;
-    double* F = Uf + (int64_t)sys * L.N * (ENTRY ? 27 : kRow27);
+    const double* U = L.U + (int64_t)sys * L.N * 14;
+    double* F = Uf + (int64_t)sys * L.N * 27;
     for (int64_t i = blockIdx.x * (int64_t)kMgT + threadIdx.x; i < L.N; i += (int64_t)gridDim.x * kMgT) {
         int ix, iy, iz;
         coords(static_cast<int32_t>(i), L.nx, L.ny, ix, iy, iz);
-        auto o = [&](int e) -> double& { return ENTRY ? F[e * L.N + i] : F[i * kRow27 + e]; };
-        o(0) = U[i * M1];
-        for (int j = 0; j < 13; ++j) {
-            const int code = 14 + j;
-            const int dx = code % 3 - 1, dy = (code / 3) % 3 - 1, dz = code / 9 - 1;
-            const int64_t lin = dx + (int64_t)L.nx * (dy + (int64_t)L.ny * dz);
-            const bool up = ix + dx >= 0 && ix + dx < L.nx && iy + dy >= 0 && iy + dy < L.ny && iz + dz < L.nz;
-            const bool lo = ix - dx >= 0 && ix - dx < L.nx && iy - dy >= 0 && iy - dy < L.ny && iz - dz >= 0;
-            o(1 + j) = up ? U[i * M1 + 1 + j] : 0.0;
-            o(14 + j) = lo ? U[(i - lin) * M1 + 1 + j] : 0.0;
-        }
-        if constexpr (!ENTRY)
-            for (int j = 27; j < kRow27; ++j) o(j) = 0.0;
+#pragma unroll
+        for (int e = 0; e < 27; ++e) F[e * L.N + i] = row27(L, U, i, ix, iy, iz, e);
+    }
+}
+
+// node-major [N][16] FP32 pairs (entry k, entry k + 16): the tiled kernels; 16
+// threads a node (49^3 nodes 13 us; by way of FP64 rows, a thread a node, 75)
+__global__ __launch_bounds__(kMgT) void k_mg_pairs27(LvArgs L, float* __restrict__ P) {
+    for (int64_t t = blockIdx.x * (int64_t)kMgT + threadIdx.x; t < L.N * 16; t += (int64_t)gridDim.x * kMgT) {
+        const int64_t i = t / 16;
+        const int k = static_cast<int>(t % 16);
+        int ix, iy, iz;
+        coords(static_cast<int32_t>(i), L.nx, L.ny, ix, iy, iz);
+        *reinterpret_cast<float2*>(P + 2 * t) = make_float2(static_cast<float>(row27(L, L.U, i, ix, iy, iz, k)),
+                                                            static_cast<float>(row27(L, L.U, i, ix, iy, iz, k + 16)));
     }
 }
 
@@ -2791,32 +2813,7 @@ __device__ __forceinline__ float pair_hi(double p) {
     return __builtin_bit_cast(float, static_cast<uint32_t>(__builtin_bit_cast(uint64_t, p) >> 32));
 }
 
-// sum over the 13 offset pairs: entry 1 + j (upper) and 14 + j (lower) of
-// the row held as (ua: entries 0-15, ub: 16-31) times the LDS neighbours
-template <int J>
-__device__ __forceinline__ double pair27(double s, double ua, double ub, const double* rb, int sz, int sp,
-                                         int sl) {
-    constexpr int code = 14 + J;
-    constexpr int dx = code % 3 - 1, dy = (code / 3) % 3 - 1, dz = code / 9 - 1;
-    constexpr int d = (dy * kTHX + dx) * 16;
-    const int up = dz ? sp : sz, lo = dz ? sl : sz;
-    const double cu = row_bcast<1 + J>(ua);
-    double cl;
-    if constexpr (14 + J < 16)
-        cl = row_bcast<14 + J>(ua);
-    else
-        cl = row_bcast<J - 2>(ub);
-    return fma(cl, rb[lo - d], fma(cu, rb[up + d], s));
-}
-template <int... J>
-__device__ __forceinline__ double apply27(double ua, double ub, const double* rb, int sz, int sp, int sl,
-                                          std::integer_sequence<int, J...>) {
-    double s = row_bcast<0>(ua) * rb[sz];
-    ((s = pair27<J>(s, ua, ub, rb, sz, sp, sl)), ...);
-    return s;
-}
-
-// the same sum with the row in FP32 pairs: pair k = (entry k, entry k + 16),
+// sum over the row's entries held as FP32 pairs: pair k = (entry k, entry k + 16),
 // 16 broadcasts for the 27 entries, the products in FP64
 template <int... K>
 __device__ __forceinline__ void bcast16(double pr, double (&bc)[16], std::integer_sequence<int, K...>) {
@@ -2846,21 +2843,10 @@ __device__ __forceinline__ double apply27p(double pr, const double* rb, int sz, 
     return s;
 }
 
-// [n][16][2] FP32 pairs (entry k, entry k + 16) from the [n][kRow27] FP64 rows
-__global__ void k_pairs27(int64_t n, const double* __restrict__ U, float* __restrict__ P) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n * 16;
-         i += (int64_t)gridDim.x * blockDim.x) {   // (node, k)
-        const int64_t node = i / 16, k = i % 16;
-        P[2 * i] = static_cast<float>(U[node * kRow27 + k]);
-        P[2 * i + 1] = static_cast<float>(U[node * kRow27 + 16 + k]);
-    }
-}
-
 struct Tile27Args {
     int32_t nx, ny, nz;
     int32_t tiles_x, tiles_y, zc, items;
-    const double* Uf;     // [N][kRow27]
-    const float* Uf27p;   // R32: the rows as [N][16] FP32 pairs
+    const float* Uf27p;   // the rows as [N][16] FP32 pairs
     const double* x;      // staged vector [N][16]
     const double* b;      // [N][16]
     const double* dinv;   // [N] (kT27Smooth)
@@ -2869,7 +2855,7 @@ struct Tile27Args {
     const MgScal* sc;     // [16]
 };
 
-template <int MODE, bool R32 = false, bool V32 = false>
+template <int MODE, bool V32 = false>
 __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
     constexpr int B = 16;
     constexpr int NPF = kNpf16, RS = NPF * kTT;
@@ -2885,7 +2871,7 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
     const bool act = g.sc[k].active != 0;
     const int32_t nx = g.nx, ny = g.ny, nz = g.nz;
     const uint32_t nxy = static_cast<uint32_t>(nx) * ny;
-    const uint32_t pv = nxy * B * SZ, pr = nxy * kRow27 * SZ, pd = nxy * SZ;
+    const uint32_t pv = nxy * B * SZ, pd = nxy * SZ;
     const double w = MODE == kT27Smooth ? *g.w : 0.0;
     auto plane = [&](const double* base, int pl, uint32_t stride, uint32_t bytes) {
         const bool in = pl >= 0 && pl < nz;
@@ -2921,7 +2907,7 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
         const int32_t ch = item / tiles, t2 = item % tiles;
         const int32_t x0 = (t2 % g.tiles_x) * TX, y0 = (t2 / g.tiles_x) * TY;
         const int32_t zb = ch * g.zc, ze = min(zb + g.zc, nz);
-        uint32_t fo[NPF], oo[NO], od[NO], ro[NO];
+        uint32_t fo[NPF], oo[NO], od[NO];
 #pragma unroll
         for (int u = 0; u < NPF; ++u) {
             const int nl = (tid + u * kTT) / B;
@@ -2936,7 +2922,6 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
             const bool oin = nl < TX * TY && ox < nx && oy < ny;
             oo[u] = oin ? (static_cast<uint32_t>(oy * nx + ox) * B + k) * SZ : kOut;
             od[u] = oin ? static_cast<uint32_t>(oy * nx + ox) * SZ : kOut;
-            ro[u] = oin ? (static_cast<uint32_t>(oy * nx + ox) * kRow27 + k) * SZ : kOut;
         }
         auto fetch = [&](int pl) {
             const auto bx = vplane(g.x, pl);
@@ -2948,25 +2933,15 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
             for (int u = 0; u < NPF; ++u) ring[sl * RS + tid + u * kTT] = fr[u];
         };
         // the operator rows and b of plane z, loaded a plane ahead
-        double ua[NO], ub[NO], bn[NO];
+        double ua[NO], bn[NO];
         auto load_node = [&](int z) {
             const auto bb = vplane(g.b, z);
-            if constexpr (R32) {   // the pair (entry k, entry k + 16) as 8 bytes: the layout of a [N][16] vector
-                const auto bq = plane(reinterpret_cast<const double*>(g.Uf27p), z, nxy * B, pv);
+            // the pair (entry k, entry k + 16) as 8 bytes: the layout of a [N][16] vector
+            const auto bq = plane(reinterpret_cast<const double*>(g.Uf27p), z, nxy * B, pv);
 #pragma unroll
-                for (int u = 0; u < NO; ++u) {
-                    ua[u] = bload<double>(bq, oo[u]);
-                    ub[u] = 0.0;
-                    bn[u] = vload(bb, oo[u]);
-                }
-            } else {
-                const auto bu = plane(g.Uf, z, nxy * kRow27, pr);
-#pragma unroll
-                for (int u = 0; u < NO; ++u) {
-                    ua[u] = bload<double>(bu, ro[u]);
-                    ub[u] = bload<double>(bu, ro[u] == kOut ? kOut : ro[u] + 16 * SZ);
-                    bn[u] = vload(bb, oo[u]);
-                }
+            for (int u = 0; u < NO; ++u) {
+                ua[u] = bload<double>(bq, oo[u]);
+                bn[u] = vload(bb, oo[u]);
             }
         };
         load_node(zb);
@@ -2975,11 +2950,10 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
             store(sp);
             __syncthreads();
             if (z + 1 < ze) fetch(z + 2);
-            double ca[NO], cb[NO], bc[NO], dc[NO];
+            double ca[NO], bc[NO], dc[NO];
 #pragma unroll
             for (int u = 0; u < NO; ++u) {
                 ca[u] = ua[u];
-                cb[u] = ub[u];
                 bc[u] = bn[u];
             }
             if (z + 1 < ze) load_node(z + 1);
@@ -2993,11 +2967,7 @@ __global__ __launch_bounds__(kTT, 4) void k_mg_tile27(Tile27Args g) {
             for (int u = 0; u < NO; ++u) {
                 if (tid + u * kTT >= TX * TY * B) continue;   // whole waves past the tile skip
                 const double* rb = ring + oc[u] * B + k;
-                double ax;
-                if constexpr (R32)
-                    ax = apply27p(ca[u], rb, sz * RS, sp * RS, sl * RS, std::make_integer_sequence<int, 13>{});
-                else
-                    ax = apply27(ca[u], cb[u], rb, sz * RS, sp * RS, sl * RS, std::make_integer_sequence<int, 13>{});
+                const double ax = apply27p(ca[u], rb, sz * RS, sp * RS, sl * RS, std::make_integer_sequence<int, 13>{});
                 double o = bc[u] - ax;
                 if constexpr (MODE == kT27Smooth) o = rb[sz * RS] + w * dc[u] * o;
                 if constexpr (V32)
@@ -3214,7 +3184,6 @@ void launch_tile27(const MgState& M, const TileGeo& t, int l, hipStream_t st, co
     g.tiles_y = q.ty;
     g.zc = q.zc;
     g.items = q.items;
-    g.Uf = L.Uf;
     g.Uf27p = L.Uf27p;
     g.x = x;
     g.b = b;
@@ -3223,9 +3192,7 @@ void launch_tile27(const MgState& M, const TileGeo& t, int l, hipStream_t st, co
     g.out = out;
     g.sc = M.sc;
     const size_t lds = (size_t)3 * kNpf16 * kTT * sizeof(double);
-    if (L.Uf27p && v32)   // the rows and (v32) the level's vectors in FP32
-        hipLaunchKernelGGL((k_mg_tile27<MODE, true, true>), dim3(q.blocks), dim3(kTT), lds, st, g);
-    else if (L.Uf27p)   // the rows in FP32 (the V-cycle's coarse operators)
+    if (v32)   // the level's vectors in FP32, as its rows
         hipLaunchKernelGGL((k_mg_tile27<MODE, true>), dim3(q.blocks), dim3(kTT), lds, st, g);
     else
         hipLaunchKernelGGL((k_mg_tile27<MODE, false>), dim3(q.blocks), dim3(kTT), lds, st, g);
@@ -3563,12 +3530,10 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
             }
         }
         if constexpr (B == 16) {   // the coarse levels' 27-point kernels
-            const void* f27[6] = {reinterpret_cast<const void*>(&k_mg_tile27<kT27Resid>),
+            const void* f27[4] = {reinterpret_cast<const void*>(&k_mg_tile27<kT27Resid>),
                                   reinterpret_cast<const void*>(&k_mg_tile27<kT27Smooth>),
                                   reinterpret_cast<const void*>(&k_mg_tile27<kT27Resid, true>),
-                                  reinterpret_cast<const void*>(&k_mg_tile27<kT27Smooth, true>),
-                                  reinterpret_cast<const void*>(&k_mg_tile27<kT27Resid, true, true>),
-                                  reinterpret_cast<const void*>(&k_mg_tile27<kT27Smooth, true, true>)};
+                                  reinterpret_cast<const void*>(&k_mg_tile27<kT27Smooth, true>)};
             constexpr size_t lds27 = (size_t)3 * kNpf16 * kTT * sizeof(double);
             for (const void* f : f27)
                 QPAT_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds27));
@@ -3577,7 +3542,7 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
             const int64_t conc27 = (int64_t)std::max(occ27, 1) * (cus / 8);
             for (int l = 1; l < (int)M.lv.size() && l < kMgMaxLevels; ++l) {
                 const MgLevel& Q = M.lv[l];
-                if (!Q.Uf) continue;
+                if (!Q.Uf27p) continue;
                 const int64_t tx27 = (Q.nx + kTHX - 3) / (kTHX - 2), ty27 = (Q.ny + kTHY - 3) / (kTHY - 2);
                 int64_t best27 = -1, zc27 = Q.nz;
                 for (int64_t nch = 1; nch <= Q.nz; ++nch) {
@@ -3634,7 +3599,7 @@ inline bool f32v0_path(const MgState& M, const TileGeo& tg) {
 // the fused prolongation + last sweep above it (preconditioner work only).
 template <int B>
 inline bool v32_path(const MgState& M, const TileGeo& tg) {
-    return z32_path<B>(tg) && M.lv.size() > 2 && tiled27(tg, 1) && M.lv[1].Uf27p != nullptr && tg.rst[0].on &&
+    return z32_path<B>(tg) && M.lv.size() > 2 && tiled27(tg, 1) && tg.rst[0].on &&
            tg.rst[1].on;
 }
 
@@ -4596,10 +4561,8 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
                 QPAT_TRY(dalloc(c, &L.Uf32, nsys * L.N * kUpRow));
             }
             if (op == Op::K && l >= 1 && l < kMgMaxLevels && M.bmax == 16 && M.lv[0].kind == 1 &&
-                L.N >= kTile27Min && L.N * kRow27 * (int64_t)sizeof(double) < (int64_t(1) << 31)) {
-                QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * kRow27));
-                QPAT_TRY(dalloc(c, &L.Uf27p, nsys * L.N * kRow27));
-            }
+                L.N >= kTile27Min && L.N * 32 * (int64_t)sizeof(double) < (int64_t(1) << 31))
+                QPAT_TRY(dalloc(c, &L.Uf27p, L.N * 32));
             if (op == Op::Prior && l >= 1 && l + 1 < nl && L.N >= kRow27Min) {   // entry-major rows (kind 4)
                 QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * 27));
                 QPAT_TRY(dalloc(c, &L.Uf32, nsys * L.N * 27));   // and in FP32 for the V-cycle (kind 6)
@@ -4647,19 +4610,21 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
             // below uses the same rounded values, so A_c = P^T A P holds for the P applied
             hipLaunchKernelGGL(k_mg_wpack, g, dim3(kMgT), 0, c->stream, lv_args(F), F.W, F.Wc);
         }
-        hipLaunchKernelGGL(k_mg_rap, dim3((unsigned)((C.N + kRapNodes - 1) / kRapNodes), nsys), dim3(kMgT), 0, c->stream,
-                           lv_args(F), M.opdep ? F.W : nullptr, C.U, C.nx, C.ny, C.nz);
+        const dim3 gr((unsigned)((C.N + kRapNodes - 1) / kRapNodes), nsys);
+        if (F.m <= 7)
+            hipLaunchKernelGGL(k_mg_rap<7>, gr, dim3(kMgT), 0, c->stream, lv_args(F), M.opdep ? F.W : nullptr, C.U, C.nx,
+                               C.ny, C.nz);
+        else
+            hipLaunchKernelGGL(k_mg_rap<13>, gr, dim3(kMgT), 0, c->stream, lv_args(F), M.opdep ? F.W : nullptr, C.U, C.nx,
+                               C.ny, C.nz);
     }
     for (int l = 1; l < nl; ++l)
-        if (M.lv[l].Uf && op == Op::K) {
-            hipLaunchKernelGGL(k_mg_fullrows27<false>, dim3(grid_for(M.lv[l].N, kMgT, 4096), nsys), dim3(kMgT), 0,
-                               c->stream, lv_args(M.lv[l]), M.lv[l].Uf);
-            if (M.lv[l].Uf27p)
-                hipLaunchKernelGGL(k_pairs27, dim3(grid_for(nsys * M.lv[l].N * 16, kMgT, 4096)), dim3(kMgT), 0,
-                                   c->stream, nsys * M.lv[l].N, M.lv[l].Uf, M.lv[l].Uf27p);
+        if (M.lv[l].Uf27p) {
+            hipLaunchKernelGGL(k_mg_pairs27, dim3(grid_for(M.lv[l].N * 16, kMgT, 4096)), dim3(kMgT), 0, c->stream,
+                               lv_args(M.lv[l]), M.lv[l].Uf27p);
         } else if (M.lv[l].Uf) {
-            hipLaunchKernelGGL(k_mg_fullrows27<true>, dim3(grid_for(M.lv[l].N, kMgT, 4096), nsys), dim3(kMgT), 0,
-                               c->stream, lv_args(M.lv[l]), M.lv[l].Uf);
+            hipLaunchKernelGGL(k_mg_fullrows27, dim3(grid_for(M.lv[l].N, kMgT, 4096), nsys), dim3(kMgT), 0, c->stream,
+                               lv_args(M.lv[l]), M.lv[l].Uf);
             if (M.lv[l].Uf32)
                 hipLaunchKernelGGL(k_to_f32, dim3(grid_for(nsys * M.lv[l].N * 27, kMgT, 4096)), dim3(kMgT), 0,
                                    c->stream, M.lv[l].Uf, M.lv[l].Uf32, nsys * M.lv[l].N * 27);
@@ -4668,8 +4633,12 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
                        2 * nsys * nl);
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(kMgT), 0, c->stream, reinterpret_cast<uint32_t*>(M.bad), nsys + 1);
     for (int l = 0; l < nl; ++l)
-        hipLaunchKernelGGL(k_mg_diag, dim3(grid_for(M.lv[l].N, kMgT, kMgBlocks), nsys), dim3(kMgT), 0, c->stream,
-                           lv_args(M.lv[l]), M.lv[l].dinv, M.gmax, nl, l);
+        if (M.lv[l].m <= 7)
+            hipLaunchKernelGGL(k_mg_diag<7>, dim3(grid_for(M.lv[l].N, kMgT, kMgBlocks), nsys), dim3(kMgT), 0, c->stream,
+                               lv_args(M.lv[l]), M.lv[l].dinv, M.gmax, nl, l);
+        else
+            hipLaunchKernelGGL(k_mg_diag<13>, dim3(grid_for(M.lv[l].N, kMgT, kMgBlocks), nsys), dim3(kMgT), 0, c->stream,
+                               lv_args(M.lv[l]), M.lv[l].dinv, M.gmax, nl, l);
     // finest level, coarse levels; M_delta's (strongly varying diffusivity)
     // take larger weights, still below 2 / g so that the cycle stays SPD
     hipLaunchKernelGGL(k_mg_weights, dim3(1), dim3(kMgT), 0, c->stream, M.gmax, nsys, nl,
