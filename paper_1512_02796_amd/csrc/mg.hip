@@ -4311,38 +4311,96 @@ __device__ __forceinline__ mg_d4 gj_product(const double (*X)[kGj + 1], const do
     return acc;
 }
 
-// D[0] to -D[0]^{-1} by a block, two pivots a step: a step is one chain of LDS
-// reads, a reciprocal and a barrier however many pivots it takes. d: the
-// thread's four elements of D[0]. False where a pivot is not positive.
+// A 16 x 16 symmetric positive definite tile to its inverse by one wavefront,
+// in the registers a MFMA leaves it in (lane l: rows l / 16 + 4 q of column
+// l % 16): Gauss-Jordan elimination, the pivot's column by row broadcasts, its
+// row by one permute. False where a pivot is not positive.
+template <int K>
+__device__ __forceinline__ void gj16_pivot(double (&a)[4], bool& ok) {
+    constexpr int gk = K % 4, qk = K / 4;   // row K: lanes 16 gk ..., element qk
+    const int g = (threadIdx.x & 63) >> 4, c = threadIdx.x & 15;
+    const double rk = __shfl(a[qk], gk * 16 + c);
+    const uint64_t bits = __builtin_bit_cast(uint64_t, a[qk]);
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(bits), gk * 16 + K);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(bits >> 32), gk * 16 + K);
+    const double p = __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
+    const double inv = 1.0 / p, r = rk * inv;
+    ok = ok && p > 0.0 && std::isfinite(inv);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double ck = row_bcast<K>(a[q]);
+        const double other = c == K ? -ck * inv : a[q] - ck * r;
+        a[q] = q == qk && g == gk ? (c == K ? inv : r) : other;
+    }
+}
+template <int... K>
+__device__ __forceinline__ bool gj16(double (&a)[4], std::integer_sequence<int, K...>) {
+    bool ok = true;
+    (gj16_pivot<K>(a, ok), ...);
+    return ok;
+}
+
+// D[0] to -D[0]^{-1} by a block, d the thread's four elements of it. One
+// wavefront does it with nobody to wait for: the inverse of the upper left
+// 16 x 16 tile, the Schur complement's, and the products between them by MFMA,
+// the tiles passing through LDS (32 pivots with a block barrier for every two
+// were most of a step's 14.6 us; 11.5 now).
 __device__ __forceinline__ bool gj_invert(double (&D)[2][kGj][kGj + 1], double (&d)[4]) {
     const int r0 = threadIdx.x / 8, c0 = threadIdx.x % 8 * 4;
     bool ok = true;
-    for (int k = 0; k < kGj; k += 2) {
-        const double (*src)[kGj + 1] = D[(k / 2) & 1];
-        const double pa = src[k][k], pb = src[k][k + 1], pc = src[k + 1][k + 1];
-        const double ca = src[r0][k], cb = src[r0][k + 1];
-        const double det = pa * pc - pb * pb, inv = 1.0 / det;
-        ok = ok && pa > 0.0 && det > 0.0 && std::isfinite(inv);
-        const double ia = pc * inv, ib = -pb * inv, ic = pa * inv;   // the pair's inverse
-        const double wa = ca * ia + cb * ib, wb = ca * ib + cb * ic;
-        const bool pr = (r0 & ~1) == k;
+    if (threadIdx.x < 64) {
+        const int g = threadIdx.x >> 4, c = threadIdx.x & 15;
+        const auto pass = [] {   // the wavefront's LDS writes are seen by its other lanes
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+        using Pivots = std::make_integer_sequence<int, 16>;
+        double i11[4], i22[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) i11[q] = D[0][g + 4 * q][c];
+        ok = gj16(i11, Pivots{});
+#pragma unroll
+        for (int q = 0; q < 4; ++q) D[1][g + 4 * q][c] = i11[q];
+        pass();
+        mg_d4 w = {0.0, 0.0, 0.0, 0.0}, s, z = {0.0, 0.0, 0.0, 0.0}, t;   // W = A_21 A_11^{-1}
+#pragma unroll
+        for (int k = 0; k < 16; k += 4) w = __builtin_amdgcn_mfma_f64_16x16x4f64(D[0][16 + c][k + g], D[1][k + g][c], w, 0, 0, 0);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int c = c0 + q;
-            const double ra = src[k][c], rb = src[k + 1][c];
-            if (pr && (c & ~1) == k)
-                d[q] = -(r0 != c ? ib : r0 == k ? ia : ic);
-            else if (pr)
-                d[q] = r0 == k ? ia * ra + ib * rb : ib * ra + ic * rb;
-            else if ((c & ~1) == k)
-                d[q] = c == k ? wa : wb;
-            else
-                d[q] -= wa * ra + wb * rb;
-            D[(k / 2 + 1) & 1][r0][c] = d[q];
+            D[1][16 + g + 4 * q][c] = w[q];
+            s[q] = D[0][16 + g + 4 * q][16 + c];
         }
-        __syncthreads();
+        pass();
+#pragma unroll
+        for (int k = 0; k < 16; k += 4)   // the Schur complement A_22 - W A_12
+            s = __builtin_amdgcn_mfma_f64_16x16x4f64(-D[1][16 + c][k + g], D[0][k + g][16 + c], s, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) i22[q] = s[q];
+        ok = gj16(i22, Pivots{}) && ok;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) D[1][16 + g + 4 * q][16 + c] = i22[q];
+        pass();
+#pragma unroll
+        for (int k = 0; k < 16; k += 4)   // Z = (Schur complement)^{-1} W
+            z = __builtin_amdgcn_mfma_f64_16x16x4f64(D[1][16 + c][16 + k + g], D[1][16 + k + g][c], z, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            D[0][16 + g + 4 * q][c] = z[q];
+            D[0][c][16 + g + 4 * q] = z[q];
+            D[0][16 + g + 4 * q][16 + c] = -i22[q];
+            t[q] = -i11[q];
+        }
+        pass();
+#pragma unroll
+        for (int k = 0; k < 16; k += 4)   // -A_11^{-1} - W^T Z
+            t = __builtin_amdgcn_mfma_f64_16x16x4f64(-D[1][16 + k + g][c], D[0][16 + k + g][c], t, 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) D[0][g + 4 * q][c] = t[q];
     }
-    static_assert(kGj % 4 == 0, "the inverse ends in D[0]");
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) d[q] = D[0][r0][c0 + q];
+    static_assert(kGj == 32, "two tiles of 16");
     return ok;
 }
 
@@ -4355,8 +4413,7 @@ __global__ __launch_bounds__(kMgT) void k_gj_first(const double* __restrict__ Sa
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int c = c0 + q;
-        d[q] = r0 < n && c < n ? Sall[((int64_t)sys * n + r0) * n + c] : (r0 == c ? 1.0 : 0.0);
-        D[0][r0][c] = d[q];
+        D[0][r0][c] = r0 < n && c < n ? Sall[((int64_t)sys * n + r0) * n + c] : (r0 == c ? 1.0 : 0.0);
     }
     __syncthreads();
     if (!gj_invert(D, d) && threadIdx.x == 0) bad[sys] = 1;
@@ -4413,8 +4470,6 @@ __global__ __launch_bounds__(kMgT) void k_gj(const double* __restrict__ Sall, do
     if (!next) return;
     __syncthreads();
     double d[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) d[q] = D[0][r0][c0 + q];
     if (!gj_invert(D, d) && threadIdx.x == 0) bad[sys] = 1;
 #pragma unroll
     for (int q = 0; q < 4; ++q) Pn[(sys * kGj + r0) * kGj + c0 + q] = d[q];
