@@ -62,20 +62,20 @@ def algorithmic_bytes(kind, N, layout, V, stat):
 # N B doubles per active right-hand side and the stencil rows (m + 1 doubles
 # per node) and 1/a_ii once per launch
 MG_KERNELS = {
-    "K_mg_dir_spmv": ("k_mg_tile<0,16>", 3.5, True, False),  # read z (FP32), p_old; write p, q
-    "K_mg_update": ("k_mgp_update<16>", 6, False, False),    # read x, p, r, q; write x, r
-    "K_mg_resid0": ("k_mg_tile<1,16>", 2, True, True),       # read r; write r - A (w D^-1 r)
-    "K_mg_smooth0": ("k_mg_tile<2,16>", 3, True, True),      # read x, r; write z
+    "K_mg_dir_spmv": ("k_mg_tile<0,16,true,false>", 3.5, True, False),  # read z (FP32), p_old; write p, q
+    "K_mg_update": ("k_mgp_update<16>", 7, False, True),     # read x, p, r, q; write x, r, w D^-1 r
+    "K_mg_resid0": ("k_mg_resid<1,16,double>", 3, True, False),       # read x, r; write r - A x
+    "K_mg_smooth0": ("k_mg_smooth<1,16,true,double>", 3, True, True), # read x, r; write z
 }
 # on the tiled path counter 5 times the update fused with the finest-level
 # residual (counter 6 then stays empty): read r, q; write r' and
 # r' - A (w D^-1 r') in FP32 (half a vector); x is not touched there (the
 # iterations keep their directions, and x is formed once per solve from them),
 # and counter 7 the prolongation fused with the last sweep: read r, level 1's x
-# (1/8 of the nodes, in FP32: 1/16 vector), the whole stencil rows (16 FP32
-# values a node: the bytes of the stored form); write z in FP32 (half a vector)
-MG_FUSED_UPDATE = ("k_mg_tile<6,16>", 3.5, 1, True)
-MG_FUSED_SMOOTH = ("k_mg_prolong_smooth<false,true>", 1.5625, 1, True)
+# (1/8 of the nodes, in FP32: 1/16 vector), the stencil rows; write z in FP32
+# (half a vector). Both are the same in mixed precision.
+MG_FUSED_UPDATE = ("k_mg_tile<6,16,false,false>", 3.5, 1, True)
+MG_FUSED_SMOOTH = ("k_mg_tile<7,16,true,true>", 1.5625, 1, True)
 
 
 def mg_kernel(key, kst, p32=False):
@@ -85,11 +85,9 @@ def mg_kernel(key, kst, p32=False):
     p."""
     fused = kst["K_mg_resid0"]["launches"] == 0
     if key == "K_mg_update" and fused:
-        n, v, o, d = MG_FUSED_UPDATE
-        return ("k_mg_tile<6,16,false,true>", v, o, d) if p32 else (n, v, o, d)
-    if key == "K_mg_smooth0" and fused:   # mixed precision stages its x0 in FP32 (same HBM bytes)
-        n, v, o, d = MG_FUSED_SMOOTH
-        return ("k_mg_prolong_smooth<true,true>", v, o, d) if p32 else (n, v, o, d)
+        return MG_FUSED_UPDATE
+    if key == "K_mg_smooth0" and fused:
+        return MG_FUSED_SMOOTH
     n, v, o, d = MG_KERNELS[key]
     if p32 and key == "K_mg_dir_spmv":
         return ("k_mg_tile<0,16,true,true>", v - 1.0, o, d)
@@ -119,12 +117,12 @@ def pair_algorithmic_bytes(N, E, levels, B, blocks, iters_tan, iters_adj, tiled2
                            voxel=True):
     """Algorithmic HBM bytes of one J s + J^T t pair on the multigrid path: every
     kernel's reads and writes counted once (FP64 vectors of N B values; in
-    FP32 the finest level's residual for the restriction, the V-cycle's output
-    z and the last sweep's whole rows), with the measured PCG iteration counts.
+    FP32 the finest level's residual for the restriction and the V-cycle's
+    output z), with the measured PCG iteration counts.
     Per multigrid-PCG iteration (levels N_0 > N_1 > ...):
       finest level: direction + product 3.5 V_0 + rows, update + first residual
         3.5 V_0 + rows + 1/a_ii, restriction 0.5 V_0 + 2 V_1, prolongation +
-        last sweep 1.5 V_0 + V_1 + whole FP32 rows (16 a node) + 1/a_ii;
+        last sweep 1.5 V_0 + V_1 + rows + 1/a_ii;
       coarse level l: residual 3 V_l + rows, restriction V_l + 2 V_l+1,
         prolongation 2 V_l + V_l+1, sweep 3 V_l + rows (27-point rows: 32
         doubles a node on tiled levels, 27 elsewhere); coarsest: its dense
@@ -149,7 +147,7 @@ def pair_algorithmic_bytes(N, E, levels, B, blocks, iters_tan, iters_adj, tiled2
     V = [n * vb for n in levels]
     if B == 16 and len(levels) > 2 and levels[1] >= tiled27_min:
         V[1] //= 2   # level 1's vectors in FP32
-    rows0, whole0, d0 = 64 * N, 64 * N, 8 * N
+    rows0, d0 = 64 * N, 8 * N
     L = len(levels)
 
     def coarse_rows(l):
@@ -160,7 +158,7 @@ def pair_algorithmic_bytes(N, E, levels, B, blocks, iters_tan, iters_adj, tiled2
         vc += 3 * V[l] + coarse_rows(l) + V[l] + 2 * V[l + 1] + 8 * levels[l + 1]      # down
         vc += 2 * V[l] + V[l + 1] + 3 * V[l] + coarse_rows(l) + 8 * levels[l]         # up
     vc += 8 * levels[-1] ** 2 + 2 * V[-1]
-    vc += 1.5 * V[0] + V[1] + whole0 + d0                                             # prolongation + last sweep
+    vc += 1.5 * V[0] + V[1] + rows0 + d0                                              # prolongation + last sweep
     pcg_it = 3.5 * V[0] + rows0 + 3.5 * V[0] + rows0 + d0 - (1.0 * V[0] if p32 else 0.0)
 
     def solve(it):

@@ -901,8 +901,8 @@ __global__ __launch_bounds__(kMgT) void k_mg_first(SmArgs a, const double* __res
 
 // y = x + w D^{-1} (b - A x). The systems are swept one after the other by
 // the same blocks. DOTS (the last sweep on the finest level, where b = r and
-// y = z): also the partial sums r.z, sum z and sum r of every right-hand side,
-// of y as stored. x and y in FP64 or FP32 (VT).
+// y = z): also the partial sums r.z of every right-hand side and, for one (M_delta's
+// deflation), sum z and sum r, of y as stored. x and y in FP64 or FP32 (VT).
 template <int KIND, int B, bool DOTS, typename VT = double>
 __global__ __launch_bounds__(kMgT) void k_mg_smooth(SmArgs a, const double* __restrict__ b,
                                                     const VT* __restrict__ x, VT* __restrict__ y,
@@ -2152,7 +2152,7 @@ struct MgTile {
     static constexpr int W = B == 16 ? 4 : 3;                // waves per SIMD that the LDS admits (2, 3 blocks a CU)
 };
 // the 16-right-hand-side kernels that stage one right-hand side per thread
-// (fused prolongation + last sweep, 27-point levels)
+// (27-point levels)
 constexpr int kTT = 512;                 // their threads, and the restriction's
 constexpr int kTHX = 12, kTHY = 10;      // their halo'd tile
 constexpr int kTHN = kTHX * kTHY;
@@ -3613,11 +3613,6 @@ inline bool v32_path(const MgState& M, const TileGeo& tg) {
            tg.rst[1].on;
 }
 
-// One V-cycle on every lane: z = V(r), r = level 0's b. The last sweep also
-// leaves the partial sums r.z, sum z, sum r. On a tiled finest level with one
-// sweep each way the first sweep w D^{-1} r is never stored: the residual
-// kernel stages it and the prolongation recomputes it. Level 0 takes
-// 2 kMgNu - 1 ping-pong sweeps (an odd number), so z ends in level 0's t.
 // the smoother arguments of level l
 inline SmArgs level_args(const MgState& M, int l) {
     SmArgs a;
@@ -3685,6 +3680,11 @@ void launch_resid_restrict(const MgState& M, int l, hipStream_t st, const double
     }
 }
 
+// One V-cycle on every lane: z = V(r), r = level 0's b. The last sweep also
+// leaves the partial sum r.z (M_delta: and sum z, sum r). On a tiled finest
+// level the first sweep w D^{-1} r is never stored: the residual kernel stages
+// it and the prolongation recomputes it. Level 0 takes 2 kMgNu - 1 ping-pong
+// sweeps (an odd number), so z ends in level 0's t.
 // first_done: the PCG update already wrote the finest level's first sweep
 template <int B>
 void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev = nullptr, const double* b0 = nullptr,
@@ -3791,7 +3791,7 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
     }
 }
 
-// blocks of the V-cycle's last finest-level sweep, which leave r.z, sum z, sum r
+// blocks of the V-cycle's last finest-level sweep, which leave r.z
 template <int B>
 inline int last_blocks(const MgState& M, const TileGeo& tg) {
     if (tg.on) return tg.ps_blocks;
@@ -3844,7 +3844,7 @@ void region_solve(const MgState& M, const PcgMg& a, hipStream_t st, bool sums_do
 }
 
 // one iteration after the first direction: direction and product, alpha,
-// update, rr, V-cycle (with r.z, sum z, sum r), beta. Iterations alternate
+// update, rr, V-cycle (with r.z), beta. Iterations alternate
 // the two direction buffers (par); chunks of iterations have even length.
 // ev (profiling): 8 events, recorded around the direction + product, the
 // update, and the finest-level residual and last sweep of the V-cycle.
