@@ -473,32 +473,54 @@ __global__ __launch_bounds__(kThreads) void k_robin_lattice(int64_t N, Lattice l
     }
 }
 
-// J^T t per voxel and right-hand side k (B lanes per voxel), summed over the
-// lanes: QR[c][v] (+)= sum over the voxel's tetrahedra T at corner c of
-// sum_k |T|/4 grad(phi_k).grad(z_k), and QR[8 + c][v] of sum_k (Mass_T(phi_k) z_k)_c
-// (entry-major, so that the node gather reads consecutive voxels).
-template <int T>
-__device__ __forceinline__ void gadj_tet_terms(double (&Q)[8], double (&R)[8], const double (&f)[8],
-                                               const double (&g)[8], const VoxGeo& vg) {
-    constexpr int s0 = kPerm[T][0], s1 = kPerm[T][1], s2 = kPerm[T][2];
-    constexpr int P0 = 0, P1 = 1 << s0, P2 = (1 << s0) | (1 << s1), P3 = 7;
-    // grad f . grad g (the factor |T| / 4 is applied once per corner at the end)
-    const double q = vg.w[s0] * (f[P1] - f[P0]) * (g[P1] - g[P0]) + vg.w[s1] * (f[P2] - f[P1]) * (g[P2] - g[P1]) +
-                     vg.w[s2] * (f[P3] - f[P2]) * (g[P3] - g[P2]);
-    const double sp = f[P0] + f[P1] + f[P2] + f[P3];
-    const double sz = g[P0] + g[P1] + g[P2] + g[P3];
-    const double cc = sp * sz + (f[P0] * g[P0] + f[P1] * g[P1] + f[P2] * g[P2] + f[P3] * g[P3]);
-    // sum_c (1 + d_ac)(sp + f_a + f_c) z_c = (sp + f_a) sz + pz + (sp + 2 f_a) z_a
-    //   = cc + f_a (sz + 2 z_a) + sp z_a  (the factor |T| / 120 at the end)
-    auto add = [&](auto AA) {
-        constexpr int A = decltype(AA)::value;
-        Q[A] += q;
-        R[A] += cc + f[A] * (sz + 2.0 * g[A]) + sp * g[A];
+// J^T t per voxel and right-hand side k, summed over them: QR[c][v] (+)= sum
+// over the voxel's tetrahedra T at corner c of sum_k |T|/4 grad(phi_k).grad(z_k),
+// and QR[8 + c][v] of sum_k (Mass_T(phi_k) z_k)_c (entry-major, so that the
+// node gather reads consecutive voxels). B / 2 lanes share a voxel, two
+// right-hand sides each.
+// The two corner sums of one right-hand side, f = phi and g = z at the voxel's
+// corners, without their factors. With sp, sz a tetrahedron's sums of f and g
+// and cc = sp sz + sum f g, the mass term at its corner a is
+//   sum_c (1 + d_ac)(sp + f_a + f_c) z_c = cc + f_a sz + g_a sp + 2 f_a g_a,
+// so a corner needs only the sums of cc, sz and sp over its tetrahedra: all six
+// at corners 0 and 7, two elsewhere. 180 FP64 operations; the tetrahedra one by
+// one took 260, and issuing them is what bounds the kernel (341 us on 128^3
+// voxels with 16 right-hand sides, two a lane; 460 before).
+__device__ __forceinline__ void gadj_voxel(double (&Q)[8], double (&R)[8], const double (&f)[8], const double (&g)[8],
+                                           const VoxGeo& vg) {
+    const auto edge = [&](int a, int b) { return (f[b] - f[a]) * (g[b] - g[a]); };
+    double fg[8], D[6], C[6], F[6], G[6];   // a tetrahedron's grad f . grad g, cc, sp, sz
+#pragma unroll
+    for (int c = 0; c < 8; ++c) fg[c] = f[c] * g[c];
+    const double f07 = f[0] + f[7], g07 = g[0] + g[7], fg07 = fg[0] + fg[7];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+        const int s0 = kPerm[t][0], s1 = kPerm[t][1], s2 = kPerm[t][2], a = 1 << s0, b = a | 1 << s1;
+        D[t] = vg.w[s0] * edge(0, a) + vg.w[s1] * edge(a, b) + vg.w[s2] * edge(b, 7);
+        F[t] = f07 + (f[a] + f[b]);
+        G[t] = g07 + (g[a] + g[b]);
+        C[t] = fma(F[t], G[t], fg07 + (fg[a] + fg[b]));
+    }
+    // sums over the tetrahedra at corner c
+    const auto at = [](const double (&X)[6], double (&S)[8]) {
+        S[1] = X[0] + X[1];   // those that leave 0 along x
+        S[2] = X[2] + X[3];
+        S[4] = X[4] + X[5];
+        S[3] = X[0] + X[2];   // those that reach 7 along z
+        S[5] = X[1] + X[4];
+        S[6] = X[3] + X[5];
+        S[0] = S[7] = S[1] + S[2] + S[4];
     };
-    add(std::integral_constant<int, P0>{});
-    add(std::integral_constant<int, P1>{});
-    add(std::integral_constant<int, P2>{});
-    add(std::integral_constant<int, P3>{});
+    double SD[8], SC[8], SF[8], SG[8];
+    at(D, SD);
+    at(C, SC);
+    at(F, SF);
+    at(G, SG);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        Q[c] += SD[c];
+        R[c] += fma(f[c], SG[c], fma(g[c], SF[c], fma(c == 0 || c == 7 ? 12.0 : 4.0, fg[c], SC[c])));
+    }
 }
 
 // one halving step of the lane sum: offset O, H values kept of 2 H
@@ -520,7 +542,7 @@ __device__ __forceinline__ void halve_all(double (&e)[16], int k) {
 }
 
 template <int B>
-__global__ __launch_bounds__(kThreads) void k_gadj_vox(Lattice lat, VoxGeo vg, const double* __restrict__ phi,
+__global__ __launch_bounds__(kThreads, 4) void k_gadj_vox(Lattice lat, VoxGeo vg, const double* __restrict__ phi,
                                                        int n_pad, int col0, const double* __restrict__ z, int first,
                                                        double* __restrict__ QR) {
     // 32-bit offsets throughout (the set-up admits this form only where every
@@ -530,11 +552,12 @@ __global__ __launch_bounds__(kThreads) void k_gadj_vox(Lattice lat, VoxGeo vg, c
     const uint32_t vxn = nx - 1, vyn = ny - 1, vxyn = vxn * vyn, Nv = vxyn * (lat.nz - 1);
     // block b runs on XCD b mod 8: each XCD takes a contiguous eighth of the
     // voxels, so the corner values shared along y and z stay in its L2
+    constexpr int V = B >= 2 ? 2 : 1, BL = B / V;   // right-hand sides a lane, lanes a voxel
     const uint32_t per_xcd = (Nv + 7) / 8;
-    const uint32_t loc = (blockIdx.x >> 3) * (kThreads / B) + threadIdx.x / B;
+    const uint32_t loc = (blockIdx.x >> 3) * (kThreads / BL) + threadIdx.x / BL;
     const uint32_t v = (blockIdx.x & 7) * per_xcd + loc;
-    const int k = static_cast<int>(threadIdx.x % B);
-    const bool valid = loc < per_xcd && v < Nv;   // whole groups of B lanes
+    const int k = static_cast<int>(threadIdx.x % BL);
+    const bool valid = loc < per_xcd && v < Nv;   // whole groups of BL lanes
     double Q[8], R[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) Q[c] = R[c] = 0.0;
@@ -544,44 +567,48 @@ __global__ __launch_bounds__(kThreads) void k_gadj_vox(Lattice lat, VoxGeo vg, c
         const uint32_t N = nxy * lat.nz;
         const auto bp = rsrc(phi, N * static_cast<uint32_t>(n_pad) * 8u);
         const auto bz = rsrc(z, N * static_cast<uint32_t>(B) * 8u);
-        const uint32_t p0 = (n0 * static_cast<uint32_t>(n_pad) + static_cast<uint32_t>(col0 + k)) * 8u;
-        const uint32_t z0 = (n0 * B + k) * 8u;
-        double f[8], g[8];
+        const uint32_t p0 = (n0 * static_cast<uint32_t>(n_pad) + static_cast<uint32_t>(col0 + k * V)) * 8u;
+        const uint32_t z0 = (n0 * B + k * V) * 8u;
+        double f[V][8], g[V][8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
             const uint32_t cn = (c & 1) + nx * ((c >> 1) & 1) + nxy * (c >> 2);   // uniform
-            f[c] = bload<double>(bp, p0 + cn * static_cast<uint32_t>(n_pad) * 8u);
-            g[c] = bload<double>(bz, z0 + cn * (B * 8u));
+            const uint32_t pc = p0 + cn * static_cast<uint32_t>(n_pad) * 8u, zc = z0 + cn * (B * 8u);
+            if constexpr (V == 2) {   // n_pad and col0 are multiples of B: 16-byte aligned
+                typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+                typedef double d2 __attribute__((ext_vector_type(2)));
+                const d2 fc = __builtin_bit_cast(d2, static_cast<u4>(__builtin_amdgcn_raw_buffer_load_b128(bp, pc, 0, 0)));
+                const d2 gc = __builtin_bit_cast(d2, static_cast<u4>(__builtin_amdgcn_raw_buffer_load_b128(bz, zc, 0, 0)));
+                f[0][c] = fc.x;
+                f[V - 1][c] = fc.y;
+                g[0][c] = gc.x;
+                g[V - 1][c] = gc.y;
+            } else {
+                f[0][c] = bload<double>(bp, pc);
+                g[0][c] = bload<double>(bz, zc);
+            }
         }
-        gadj_tet_terms<0>(Q, R, f, g, vg);
-        gadj_tet_terms<1>(Q, R, f, g, vg);
-        gadj_tet_terms<2>(Q, R, f, g, vg);
-        gadj_tet_terms<3>(Q, R, f, g, vg);
-        gadj_tet_terms<4>(Q, R, f, g, vg);
-        gadj_tet_terms<5>(Q, R, f, g, vg);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            Q[c] *= 0.25 * vg.vol;
-            R[c] *= vg.vol * (1.0 / 120.0);
-        }
+        for (int i = 0; i < V; ++i) gadj_voxel(Q, R, f[i], g[i], vg);
     }
-    // sum over the B lanes by halving: at offset o each lane keeps the half
+    // sum over the BL lanes by halving: at offset o each lane keeps the half
     // of its values its bit o selects and adds the partner's copy of it, so
-    // lane k ends with the totals of entries k L, ..., k L + L - 1 (L = 16 / B)
+    // lane k ends with the totals of entries k L, ..., k L + L - 1 (L = 16 / BL)
     double e[16];
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         e[c] = Q[c];
         e[8 + c] = R[c];
     }
-    halve_all<B, B / 2>(e, k);
+    halve_all<BL, BL / 2>(e, k);
     if (!valid) return;
-    constexpr int L = 16 / B;
+    constexpr int L = 16 / BL;
     const auto bq = rsrc(QR, 16u * Nv * 8u);
 #pragma unroll
     for (int i = 0; i < L; ++i) {
         const uint32_t o = ((k * L + i) * Nv + v) * 8u;   // entry-major [16][Nv]
-        bstore<double>(bq, o, first ? e[i] : bload<double>(bq, o) + e[i]);
+        const double t = e[i] * (k * L + i < 8 ? 0.25 * vg.vol : vg.vol * (1.0 / 120.0));
+        bstore<double>(bq, o, first ? t : bload<double>(bq, o) + t);
     }
 }
 
@@ -821,9 +848,9 @@ static VoxGeo vox_geo(const qpat_ctx* c) {
 }
 
 // k_gadj_vox: 8 equal parts of the voxels (one per XCD), B lanes per voxel
-inline dim3 vox_grid(int64_t Nv, int B) {
-    const int64_t per_xcd = (Nv + 7) / 8;
-    return dim3(static_cast<unsigned>(8 * ((per_xcd * B + kThreads - 1) / kThreads)));
+inline dim3 vox_grid(int64_t Nv, int B) {   // k_gadj_vox: a lane for two right-hand sides
+    const int64_t per_xcd = (Nv + 7) / 8, lanes = B >= 2 ? B / 2 : 1;
+    return dim3(static_cast<unsigned>(8 * ((per_xcd * lanes + kThreads - 1) / kThreads)));
 }
 
 // max |a - b| / max |b| over n values (host-synchronous; set-up only)

@@ -391,6 +391,22 @@ def test_jacobian_product_in_small_blocks(dims, block, n_ill, precond):
     assert_close(host(js).reshape(n_ill, N), lin.jvp(s), 1e-10, "J s")
 
 
+@pytest.mark.parametrize("dims", [(7, 6, 5), (1, 3, 11), (17, 2, 9)])
+@pytest.mark.parametrize("block,n_ill", [(1, 2), (2, 5), (4, 6), (8, 11), (16, 17)])
+def test_adjoint_voxel_sums_per_block(dims, block, n_ill):
+    """J^T t by the voxel sums for every block width (one lane a voxel to eight, two right-hand sides a lane),
+    several blocks added up and a ragged last one, voxel counts that leave lanes idle, against the oracle
+    (element-wise 1e-10 as above)."""
+    coords, tets, bfaces, kappa, mu, src = box_problem(*dims, n_ill, 5 * block + sum(dims))
+    ctx, _, _ = solve(coords, tets, bfaces, kappa, mu, src, max_rhs_block=block, pcg_rtol=1e-12)
+    lin = Linearisation(fem.geometry(coords, tets, bfaces), kappa, mu, src)
+    N = coords.shape[0]
+    t = np.random.default_rng(block).standard_normal((n_ill, N))
+    jt = torch.empty(2 * N, dtype=torch.float64, device="cuda")
+    ctx.vjp(dev(t), jt)
+    assert_close(host(jt), lin.vjp(t), 1e-10, "J^T t")
+
+
 @pytest.mark.parametrize("n_ill", [1, 3, 8, 18])
 def test_data_arrays_and_options_switched_after_forward(n_ill):
     """phi, h, J s and J^T t in the caller's [n_ill][N] layout for every column count of the transposes (N no
