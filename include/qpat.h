@@ -358,6 +358,7 @@ qpat_status qpat_tile_schedule(const qpat_ctx* ctx, int32_t B, int32_t out[8]);
  * b[c_out]. For illumination k the inputs are log(mu/mu0), log(kappa/kappa0)
  * and log(phi_hom_k), phi_hom_k the fluence of the homogeneous (kappa0, mu0)
  * medium; the output is the log correction, phi0_k = phi_hom_k exp(net). */
+/* (again with other sides of the same product: the network moves to them, its parameters stay) */
 qpat_status qpat_guess_setup(qpat_ctx* ctx, int32_t nx, int32_t ny, int32_t nz);
 qpat_status qpat_guess_set_params(qpat_ctx* ctx, const float* params);   /* also resets Adam */
 qpat_status qpat_guess_get_params(qpat_ctx* ctx, float* params);

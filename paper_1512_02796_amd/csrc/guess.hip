@@ -534,19 +534,25 @@ qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz) {
         return fail(c, QPAT_ERR_ARG, "guess_setup: lattice too large for the network (N = %lld)", (long long)c->N);
     if (!c->guess) c->guess = new GuessNet();
     GuessNet* G = c->guess;
-    if (G->L.V == c->N && G->params) return QPAT_OK;
+    const bool first = !G->params;
+    if (!first && G->L.nx == nx && G->L.ny == ny && G->L.nz == nz) return QPAT_OK;
     G->L = Lat::of(nx, ny, nz);
     const int64_t V = c->N;
-    QPAT_TRY(dalloc(c, &G->params, kParams));
-    QPAT_TRY(dalloc(c, &G->grads, kParams));
-    QPAT_TRY(dalloc(c, &G->m1, kParams));
-    QPAT_TRY(dalloc(c, &G->m2, kParams));
-    for (int l = 0; l < kLayers; ++l) {
-        QPAT_TRY(dalloc(c, &G->Wf[l], (size_t)nch_of(l) * 256));
-        QPAT_TRY(dalloc(c, &G->Wb[l], (size_t)27 * 256));
+    if (first) {
+        QPAT_TRY(dalloc(c, &G->params, kParams));
+        QPAT_TRY(dalloc(c, &G->grads, kParams));
+        QPAT_TRY(dalloc(c, &G->m1, kParams));
+        QPAT_TRY(dalloc(c, &G->m2, kParams));
+        for (int l = 0; l < kLayers; ++l) {
+            QPAT_TRY(dalloc(c, &G->Wf[l], (size_t)nch_of(l) * 256));
+            QPAT_TRY(dalloc(c, &G->Wb[l], (size_t)27 * 256));
+        }
     }
+    // the padded lattice follows the sides; on other sides than before its arrays
+    // are made anew (their padding must be zero), the parameters stay
     const int64_t P = G->L.P;
     auto zeroed = [&](uint16_t** q, int64_t n) -> qpat_status {   // n: a multiple of 8
+        QPAT_TRY(dfree(c, *q));
         QPAT_TRY(dalloc(c, q, n));
         hipLaunchKernelGGL(k_zero_16, dim3(grid_for(n / 8, kThreads, 4096)), dim3(kThreads), 0, c->stream, n / 8,
                            reinterpret_cast<uint4*>(*q));
@@ -556,6 +562,10 @@ qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz) {
     for (int l = 0; l < 3; ++l) QPAT_TRY(zeroed(&G->Y[l], P * 16));
     QPAT_TRY(zeroed(&G->dA, P * 16));
     QPAT_TRY(zeroed(&G->dB, P * 16));
+    if (!first) {
+        QPAT_HIP(c, hipGetLastError());
+        return QPAT_OK;
+    }
     QPAT_TRY(dalloc(c, &G->pred, V));
     QPAT_TRY(dalloc(c, &G->target, V));
     QPAT_TRY(dalloc(c, &G->partial, (size_t)kWgradBlocks * (27 * 256 + 16)));

@@ -1,0 +1,209 @@
+// Calls into libqpat's host code on the CPU: this program defines the HIP
+// runtime functions that the library uses, so allocations come from (and fail
+// at) a place the case names, launches are recorded and not run, and what the
+// host reads back from the device is zero unless the case wrote it there.
+// Contexts are filled in by hand. host_calls CASE prints what went wrong and
+// exits with 1, or exits with 0.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+#include <string>
+#include <utility>
+#include <vector>
+
+#include "../paper_1512_02796_amd/csrc/qpat_internal.h"
+
+namespace {
+constexpr size_t kHeld = 1 << 16;   // bytes behind every allocation, whatever its size
+int g_fail_at = -1;                 // allocations that still succeed (-1: all)
+int g_allocs = 0;
+std::map<const void*, std::string>& kernel_names() {
+    static std::map<const void*, std::string> m;
+    return m;
+}
+std::vector<std::string> g_launched;
+std::function<void(const std::string&, void**)> g_on_launch;
+struct Config {
+    dim3 grid, block;
+    size_t lds;
+    hipStream_t stream;
+} g_config;
+
+hipError_t alloc(void** p) {
+    if (g_fail_at == 0) {
+        *p = nullptr;
+        return hipErrorOutOfMemory;
+    }
+    if (g_fail_at > 0) --g_fail_at;
+    ++g_allocs;
+    *p = std::calloc(1, kHeld);
+    return hipSuccess;
+}
+
+int launches(const char* part) {
+    int n = 0;
+    for (const std::string& k : g_launched) n += k.find(part) != std::string::npos;
+    return n;
+}
+}  // namespace
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) {
+    static void* h;
+    return &h;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, uint3*, uint3*, dim3*, dim3*, int*) {
+    kernel_names()[host] = name;
+}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t l, hipStream_t s) {
+    g_config = {g, b, l, s};
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* l, hipStream_t* s) {
+    *g = g_config.grid;
+    *b = g_config.block;
+    *l = g_config.lds;
+    *s = g_config.stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
+    const std::string& name = kernel_names()[f];
+    g_launched.push_back(name);
+    if (g_on_launch) g_on_launch(name, args);
+    return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t) { return alloc(p); }
+hipError_t hipHostMalloc(void** p, size_t, unsigned) { return alloc(p); }
+hipError_t hipFree(void* p) {
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t) {
+    if (k != hipMemcpyDeviceToDevice && n <= kHeld) std::memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t) {
+    std::memset(d, v, n < kHeld ? n : kHeld);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
+    *v = 256;
+    return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
+    *n = 2;
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) {
+    *e = reinterpret_cast<hipEvent_t>(&g_config);
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+    *ms = 1.f;
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "error"; }
+}
+
+using namespace qpat;
+
+namespace {
+#define EXPECT(cond)                                                  \
+    do {                                                              \
+        if (!(cond)) {                                                \
+            std::printf("line %d: not so: %s\n", __LINE__, #cond);    \
+            return 1;                                                 \
+        }                                                             \
+    } while (0)
+
+// a context on an nx x ny x nz node Kuhn lattice with n_ill illuminations, solves without graphs or autotuning
+qpat_ctx* box(int nx, int ny, int nz, int n_ill) {
+    qpat_ctx* c = new qpat_ctx();
+    qpat_default_opts(&c->opts);
+    c->opts.use_graphs = 0;
+    c->opts.autotune = 0;
+    c->N = (int64_t)nx * ny * nz;
+    c->E = (int64_t)6 * (nx - 1) * (ny - 1) * (nz - 1);
+    c->n_ill = n_ill;
+    c->n_pad = n_ill <= 16 ? 16 : (n_ill + 15) / 16 * 16;
+    c->sell.N = c->N;
+    c->lat.on = true;
+    c->lat.nx = nx;
+    c->lat.ny = ny;
+    c->lat.nz = nz;
+    c->lat.m = 7;
+    for (int8_t& k : c->lat.code) k = -1;
+    for (int m = 0; m < 8; ++m) c->lat.code[13 + (m & 1) + 3 * ((m >> 1) & 1) + 9 * (m >> 2)] = static_cast<int8_t>(m);
+    for (int m = 1; m < 8; ++m) {
+        c->lat.dx[m - 1] = m & 1;
+        c->lat.dy[m - 1] = (m >> 1) & 1;
+        c->lat.dz[m - 1] = static_cast<int8_t>(m >> 2);
+    }
+    c->vox = 0;
+    for (double& h : c->vox_h) h = 1.0;
+    for (double** p : {&c->geo, &c->barea, &c->kappa, &c->mu, &c->K64, &c->Kdinv64, &c->KU64, &c->M64, &c->Mdinv64, &c->MU64,
+                       &c->f, &c->phi, &c->x64, &c->b64, &c->partials, &c->acc1, &c->acc2, &c->dvec, &c->lu, &c->lq, &c->lw,
+                       &c->lv, &c->lwh, &c->red_partials, &c->red_out, &c->red_host})
+        (void)dalloc(c, p, 1);
+    for (void** p : {&c->xl, &c->rl, &c->pa, &c->pb, &c->ql}) (void)dalloc(c, reinterpret_cast<char**>(p), 1);
+    for (int32_t** p : {&c->tets, &c->bfaces, &c->n2t_ptr, &c->n2t, &c->n2f_ptr, &c->n2f, &c->lat_tab, &c->dev_flag})
+        (void)dalloc(c, p, 1);
+    (void)dalloc(c, &c->scal, 1);
+    (void)dalloc(c, &c->shared, 1);
+    (void)dalloc(c, &c->scal_host, 1);
+    (void)dalloc(c, &c->ls, 1);
+    (void)dalloc(c, &c->ls_host, 1);
+    return c;
+}
+
+const double kSome[4] = {};   // stands for a caller's device array: never read here
+double g_out[4];
+// A second set-up of the guess network with other sides of the same product works on those sides.
+int guess_sides() {
+    qpat_ctx* c = box(5, 16, 2, 1);
+    int sides[3] = {};
+    g_on_launch = [&](const std::string& name, void** args) {
+        if (name.find("k_inputs_raw") != std::string::npos) std::memcpy(sides, args[0], sizeof sides);   // Lat: nx, ny, nz first
+    };
+    float in[4] = {}, out[4] = {};
+    const int want[3][3] = {{5, 16, 2}, {16, 5, 2}, {16, 5, 2}};
+    for (const auto& w : want) {
+        EXPECT(qpat_guess_setup(c, w[0], w[1], w[2]) == QPAT_OK);
+        EXPECT(qpat_guess_eval(c, in, out) == QPAT_OK);
+        EXPECT(std::memcmp(sides, w, sizeof sides) == 0);
+    }
+    const size_t held = c->allocs.size();   // set up again with the same sides: nothing is allocated
+    EXPECT(qpat_guess_setup(c, 16, 5, 2) == QPAT_OK && c->allocs.size() == held);
+    return 0;
+}
+}  // namespace
+
+int main(int argc, char** argv) {
+    const std::pair<const char*, int (*)()> cases[] = {
+        {"guess_sides", guess_sides},
+    };
+    for (const auto& k : cases)
+        if (argc == 2 && std::string(argv[1]) == k.first) return k.second();
+    std::printf("no such case\n");
+    return 2;
+}

@@ -175,3 +175,24 @@ def test_net_on_ragged_lattices(shape):
     assert abs(loss - L) <= 3e-2 * L
     ref_g = np.concatenate([np.concatenate([w.ravel(), b.ravel()]) for w, b in grads])
     assert rel(host(g).astype(np.float64), ref_g) <= 3e-2, f"gradient {shape}"
+
+
+def test_net_set_up_again_with_other_sides():
+    """A second set-up with other sides of the same node count moves the network to them and keeps its parameters;
+    back again, the first output returns bit for bit. Tolerance: the BF16 bound of this file."""
+    from paper_1512_02796_amd import qpat
+    from test_gpu_stencil import kuhn_box
+    coords, tets, bfaces = kuhn_box(4, 15, 1)
+    ctx = qpat.Context(dev(coords), dev(tets, torch.int32), dev(bfaces, torch.int32))
+    outs = []
+    for i, (nx, ny, nz) in enumerate([(5, 16, 2), (16, 5, 2), (2, 4, 20), (5, 16, 2)]):
+        ctx.guess_setup(nx, ny, nz)
+        params, x = seeded_net(7, (nz, ny, nx))
+        if i == 0:
+            ctx.guess_set_params(dev(flat_params(params), torch.float32))
+        out = torch.empty(nx * ny * nz, dtype=torch.float32, device="cuda")
+        ctx.guess_eval(dev(x.reshape(3, -1), torch.float32), out)
+        ref, _ = convnet.forward(params, x)
+        assert_close(host(out).astype(np.float64), ref.ravel(), 3e-2, f"net output {(nx, ny, nz)}")
+        outs.append(out)
+    assert torch.equal(outs[0], outs[-1])
