@@ -320,9 +320,9 @@ qpat_status qpat_guess_setup(qpat_ctx* c, int32_t nx, int32_t ny, int32_t nz) {
     return QPAT_OK;
 }
 
-#define QPAT_NEED_GUESS(c)                                                                 \
-    do {                                                                                   \
-        if (!(c)->guess) return fail((c), QPAT_ERR_STATE, "call qpat_guess_setup first"); \
+#define QPAT_NEED_GUESS(c)                                                                     \
+    do {                                                                                       \
+        if (!guess_ready(c)) return fail((c), QPAT_ERR_STATE, "call qpat_guess_setup first"); \
     } while (0)
 
 qpat_status qpat_guess_set_params(qpat_ctx* c, const float* params) {

@@ -458,6 +458,8 @@ struct GuessNet {
     double* lossp = nullptr;     // [blocks]
     double* lossv = nullptr;     // [1]
     int step = 0;
+    bool have_params = false;    // zeroed at the first set-up, or the caller's
+    bool ready = false;          // every array is there, for the sides of L
 };
 
 static qpat_status guess_pack(qpat_ctx* c) {
@@ -534,23 +536,26 @@ qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz) {
         return fail(c, QPAT_ERR_ARG, "guess_setup: lattice too large for the network (N = %lld)", (long long)c->N);
     if (!c->guess) c->guess = new GuessNet();
     GuessNet* G = c->guess;
-    const bool first = !G->params;
-    if (!first && G->L.nx == nx && G->L.ny == ny && G->L.nz == nz) return QPAT_OK;
+    if (G->ready && G->L.nx == nx && G->L.ny == ny && G->L.nz == nz) return QPAT_OK;
+    G->ready = false;   // until the last allocation has succeeded
     G->L = Lat::of(nx, ny, nz);
-    const int64_t V = c->N;
-    if (first) {
-        QPAT_TRY(dalloc(c, &G->params, kParams));
-        QPAT_TRY(dalloc(c, &G->grads, kParams));
-        QPAT_TRY(dalloc(c, &G->m1, kParams));
-        QPAT_TRY(dalloc(c, &G->m2, kParams));
-        for (int l = 0; l < kLayers; ++l) {
-            QPAT_TRY(dalloc(c, &G->Wf[l], (size_t)nch_of(l) * 256));
-            QPAT_TRY(dalloc(c, &G->Wb[l], (size_t)27 * 256));
-        }
+    const int64_t V = c->N, P = G->L.P;
+    QPAT_TRY(dalloc_once(c, &G->params, kParams));
+    QPAT_TRY(dalloc_once(c, &G->grads, kParams));
+    QPAT_TRY(dalloc_once(c, &G->m1, kParams));
+    QPAT_TRY(dalloc_once(c, &G->m2, kParams));
+    for (int l = 0; l < kLayers; ++l) {
+        QPAT_TRY(dalloc_once(c, &G->Wf[l], (size_t)nch_of(l) * 256));
+        QPAT_TRY(dalloc_once(c, &G->Wb[l], (size_t)27 * 256));
     }
+    QPAT_TRY(dalloc_once(c, &G->pred, V));
+    QPAT_TRY(dalloc_once(c, &G->target, V));
+    QPAT_TRY(dalloc_once(c, &G->partial, (size_t)kWgradBlocks * (27 * 256 + 16)));
+    QPAT_TRY(dalloc_once(c, &G->part2, (size_t)kSegs * (27 * 256 + 16)));
+    QPAT_TRY(dalloc_once(c, &G->lossp, 1024));
+    QPAT_TRY(dalloc_once(c, &G->lossv, 1));
     // the padded lattice follows the sides; on other sides than before its arrays
     // are made anew (their padding must be zero), the parameters stay
-    const int64_t P = G->L.P;
     auto zeroed = [&](uint16_t** q, int64_t n) -> qpat_status {   // n: a multiple of 8
         QPAT_TRY(dfree(c, *q));
         QPAT_TRY(dalloc(c, q, n));
@@ -562,20 +567,17 @@ qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz) {
     for (int l = 0; l < 3; ++l) QPAT_TRY(zeroed(&G->Y[l], P * 16));
     QPAT_TRY(zeroed(&G->dA, P * 16));
     QPAT_TRY(zeroed(&G->dB, P * 16));
-    if (!first) {
-        QPAT_HIP(c, hipGetLastError());
-        return QPAT_OK;
+    if (!G->have_params) {
+        hipLaunchKernelGGL(k_zero_f, dim3((kParams + 255) / 256), dim3(256), 0, c->stream, kParams, G->params);
+        QPAT_TRY(guess_pack(c));
+        G->have_params = true;
     }
-    QPAT_TRY(dalloc(c, &G->pred, V));
-    QPAT_TRY(dalloc(c, &G->target, V));
-    QPAT_TRY(dalloc(c, &G->partial, (size_t)kWgradBlocks * (27 * 256 + 16)));
-    QPAT_TRY(dalloc(c, &G->part2, (size_t)kSegs * (27 * 256 + 16)));
-    QPAT_TRY(dalloc(c, &G->lossp, 1024));
-    QPAT_TRY(dalloc(c, &G->lossv, 1));
-    hipLaunchKernelGGL(k_zero_f, dim3((kParams + 255) / 256), dim3(256), 0, c->stream, kParams, G->params);
-    QPAT_TRY(guess_pack(c));
+    QPAT_HIP(c, hipGetLastError());
+    G->ready = true;
     return QPAT_OK;
 }
+
+bool guess_ready(const qpat_ctx* c) { return c->guess && c->guess->ready; }
 
 qpat_status guess_set_params(qpat_ctx* c, const float* p) {
     GuessNet* G = c->guess;

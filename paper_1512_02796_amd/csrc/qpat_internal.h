@@ -293,6 +293,11 @@ qpat_status dalloc(qpat_ctx* c, T** p, size_t n) {
     *p = static_cast<T*>(q);
     return QPAT_OK;
 }
+// an array made on first use: kept if a call before this one made it
+template <typename T>
+qpat_status dalloc_once(qpat_ctx* c, T** p, size_t n) {
+    return *p ? QPAT_OK : dalloc(c, p, n);
+}
 qpat_status dfree(qpat_ctx* c, void* p);
 
 #define QPAT_TRY(expr)                    \
@@ -379,6 +384,7 @@ qpat_status vjp_core(qpat_ctx* c, const double* t, int mode, double* out, SolveS
 
 // ---- guess.hip
 qpat_status guess_setup(qpat_ctx* c, int nx, int ny, int nz);
+bool guess_ready(const qpat_ctx* c);   // set up, completely
 qpat_status guess_set_params(qpat_ctx* c, const float* p);
 qpat_status guess_get_params(qpat_ctx* c, float* p);
 qpat_status guess_eval_raw(qpat_ctx* c, const float* in, float* out);

@@ -196,11 +196,41 @@ int guess_sides() {
     EXPECT(qpat_guess_setup(c, 16, 5, 2) == QPAT_OK && c->allocs.size() == held);
     return 0;
 }
+
+// A set-up of the guess network that failed at any of its allocations is not taken for a finished one.
+int guess_alloc_failures() {
+    qpat_ctx* c = box(5, 16, 2, 1);
+    float some[4] = {};
+    for (int k = 0;; ++k) {
+        g_fail_at = k;
+        const qpat_status s = qpat_guess_setup(c, 5, 16, 2);
+        const bool reached = g_fail_at == 0;
+        g_fail_at = -1;
+        if (!reached) {
+            EXPECT(s == QPAT_OK);
+            break;
+        }
+        EXPECT(s == QPAT_ERR_OOM);
+        EXPECT(qpat_guess_eval(c, some, some) == QPAT_ERR_STATE);
+    }
+    EXPECT(qpat_guess_eval(c, some, some) == QPAT_OK);
+    // the same for a change of sides: every buffer is there again after a later, successful call
+    for (int k = 0; k < 3; ++k) {
+        g_fail_at = k;
+        EXPECT(qpat_guess_setup(c, 2, 16, 5) == QPAT_ERR_OOM);
+        g_fail_at = -1;
+        EXPECT(qpat_guess_eval(c, some, some) == QPAT_ERR_STATE);
+    }
+    EXPECT(qpat_guess_setup(c, 2, 16, 5) == QPAT_OK);
+    EXPECT(qpat_guess_eval(c, some, some) == QPAT_OK);
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::pair<const char*, int (*)()> cases[] = {
         {"guess_sides", guess_sides},
+        {"guess_alloc_failures", guess_alloc_failures},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();
