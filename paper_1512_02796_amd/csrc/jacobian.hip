@@ -545,7 +545,7 @@ template <int B>
 __global__ __launch_bounds__(kThreads, 4) void k_gadj_vox(Lattice lat, VoxGeo vg, const double* __restrict__ phi,
                                                        int n_pad, int col0, const double* __restrict__ z, int first,
                                                        double* __restrict__ QR) {
-    // 32-bit offsets throughout (the set-up admits this form only where every
+    // 32-bit offsets throughout (vjp_core takes this form only where every
     // array fits them): voxel coordinates by 32-bit divisions, corner offsets
     // uniform over the block
     const uint32_t nx = lat.nx, ny = lat.ny, nxy = nx * ny;
@@ -905,15 +905,20 @@ static qpat_status vox_check_rows(qpat_ctx* c) {
     return QPAT_OK;
 }
 
+// the adjoint kernel's 32-bit byte offsets: phi [N][columns], blocks [N][16], sums
+// [16][Nv] (asked for each call's columns: they follow the illuminations)
+static bool vox_fits(const qpat_ctx* c, int columns) {
+    const int64_t lim = (int64_t(1) << 31) - 1;
+    return c->N * std::max(columns, 16) * 8 <= lim && 16 * (c->E / 6) * 8 <= lim;
+}
+
 static qpat_status vox_check(qpat_ctx* c) {
     if (c->vox != 0) return QPAT_OK;
     QPAT_TRY(vox_check_rows(c));
     c->vox = -1;
     if (c->vox_rows != 1) return QPAT_OK;
     const int64_t N = c->N, Nv = c->E / 6;
-    // the adjoint kernel's 32-bit byte offsets: phi [N][n_pad], blocks [N][16], sums [16][Nv]
-    const int64_t lim = (int64_t(1) << 31) - 1;
-    if (N * std::max<int64_t>(c->n_pad, 16) * 8 > lim || 16 * Nv * 8 > lim) return QPAT_OK;
+    if (!vox_fits(c, 16)) return QPAT_OK;
     const VoxGeo vg = vox_geo(c);
     const dim3 blk(kThreads);
     constexpr int BC = 16;   // right-hand sides of the check
@@ -1070,8 +1075,9 @@ qpat_status vjp_core(qpat_ctx* c, const double* t, int mode, double* out, SolveS
         QPAT_TRY(dalloc(c, &c->tq, c->E));
         QPAT_TRY(dalloc(c, &c->tr, 4 * c->E));
     }
-    QPAT_TRY(vox_check(c));
-    const bool vox = c->vox == 1;   // per-voxel sums [Nv][16] in tr (4 E = 24 Nv values)
+    const bool fits = vox_fits(c, c->n_pad);
+    if (fits) QPAT_TRY(vox_check(c));
+    const bool vox = fits && c->vox == 1;   // per-voxel sums [16][Nv] in tr (4 E = 24 Nv values)
     const int64_t Nv = vox ? c->E / 6 : 0;
     for (int col0 = 0; col0 < c->n_pad; col0 += B) {
         if (tmode == 0) {

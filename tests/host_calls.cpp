@@ -225,12 +225,29 @@ int guess_alloc_failures() {
     EXPECT(qpat_guess_eval(c, some, some) == QPAT_OK);
     return 0;
 }
+
+// The voxel kernel of J^T t takes 32-bit offsets into phi [N][n_pad]: the limit is looked at for the n_pad of each
+// call, however many illuminations the context had when the form was first checked.
+int voxel_limit_per_call() {
+    qpat_ctx* c = box(205, 205, 203, 16);   // 8.5 million nodes: 16 columns fit, 64 do not, 16 fit again
+    for (const int n_ill : {16, 64, 16}) {
+        c->n_ill = c->n_pad = n_ill;
+        SolveStats st;
+        g_launched.clear();
+        EXPECT(vjp_core(c, kSome, 0, g_out, &st) == QPAT_OK);
+        const bool fits = c->N * n_ill * 8 < (int64_t(1) << 31);
+        EXPECT(launches("k_gadj_vgather") == (fits ? 1 : 0));
+        EXPECT(launches("k_gadj_gather") >= (fits ? 0 : 1));
+    }
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
     const std::pair<const char*, int (*)()> cases[] = {
         {"guess_sides", guess_sides},
         {"guess_alloc_failures", guess_alloc_failures},
+        {"voxel_limit_per_call", voxel_limit_per_call},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();

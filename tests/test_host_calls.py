@@ -24,7 +24,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["guess_sides", "guess_alloc_failures"])
+@pytest.mark.parametrize("case", ["guess_sides", "guess_alloc_failures", "voxel_limit_per_call"])
 def test_host_call(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
