@@ -236,7 +236,7 @@ int voxel_limit_per_call() {
         g_launched.clear();
         EXPECT(vjp_core(c, kSome, 0, g_out, &st) == QPAT_OK);
         const bool fits = c->N * n_ill * 8 < (int64_t(1) << 31);
-        EXPECT(launches("k_gadj_vgather") == (fits ? 1 : 0));
+        EXPECT((launches("k_gadj_vgather") > 0) == fits);
         EXPECT(launches("k_gadj_gather") >= (fits ? 0 : 1));
     }
     return 0;
