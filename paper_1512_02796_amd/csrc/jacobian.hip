@@ -877,8 +877,9 @@ static qpat_status rel_maxdiff(qpat_ctx* c, int64_t n, const double* a, const do
 // agree to 1e-12 relative, else the element form stays in use.
 static qpat_status vox_check_rows(qpat_ctx* c) {
     if (c->vox_rows != 0 || c->vox < 0) return QPAT_OK;
+    if (c->opts.operator_format != 1) return QPAT_OK;   // an option, which may change: no verdict
     c->vox_rows = -1;
-    if (!c->lat.on || c->lat.m != 7 || c->opts.operator_format != 1) return QPAT_OK;
+    if (!c->lat.on || c->lat.m != 7) return QPAT_OK;
     for (int m = 1; m < 8; ++m)   // upper offset with axis mask m in slot m (the Kuhn pattern's order)
         if (c->lat.code[13 + (m & 1) + 3 * ((m >> 1) & 1) + 9 * (m >> 2)] != m) return QPAT_OK;
     const int64_t N = c->N, nx = c->lat.nx, ny = c->lat.ny, nz = c->lat.nz;
@@ -915,6 +916,7 @@ static bool vox_fits(const qpat_ctx* c, int columns) {
 static qpat_status vox_check(qpat_ctx* c) {
     if (c->vox != 0) return QPAT_OK;
     QPAT_TRY(vox_check_rows(c));
+    if (c->vox_rows == 0) return QPAT_OK;
     c->vox = -1;
     if (c->vox_rows != 1) return QPAT_OK;
     const int64_t N = c->N, Nv = c->E / 6;

@@ -241,6 +241,22 @@ int voxel_limit_per_call() {
     }
     return 0;
 }
+
+// A product taken while the sliced-ELL form was asked for leaves no verdict on the voxel form behind.
+int voxel_form_after_format_0() {
+    qpat_ctx* c = box(9, 10, 11, 16);
+    c->opts.operator_format = 0;
+    SolveStats st;
+    EXPECT(vjp_core(c, kSome, 0, g_out, &st) == QPAT_OK);
+    bool done = true;
+    EXPECT(assemble_K_lattice(c, &done) == QPAT_OK && !done);
+    c->opts.operator_format = 1;
+    EXPECT(assemble_K_lattice(c, &done) == QPAT_OK && done);
+    g_launched.clear();
+    EXPECT(vjp_core(c, kSome, 0, g_out, &st) == QPAT_OK);
+    EXPECT(launches("k_gadj_vgather") > 0);
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -248,6 +264,7 @@ int main(int argc, char** argv) {
         {"guess_sides", guess_sides},
         {"guess_alloc_failures", guess_alloc_failures},
         {"voxel_limit_per_call", voxel_limit_per_call},
+        {"voxel_form_after_format_0", voxel_form_after_format_0},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();

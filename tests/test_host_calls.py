@@ -24,7 +24,8 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["guess_sides", "guess_alloc_failures", "voxel_limit_per_call"])
+@pytest.mark.parametrize("case", ["guess_sides", "guess_alloc_failures", "voxel_limit_per_call",
+                                  "voxel_form_after_format_0"])
 def test_host_call(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
