@@ -165,7 +165,10 @@ qpat_status qpat_set_sources(qpat_ctx* ctx, int32_t n_ill, const double* phi_src
  * Mass(mu) + B/2 with kappa, mu entering as P1 interpolants, solves
  * K phi_k = f_k for every illumination and keeps phi inside the context.
  * phi_out, h_out: [n_ill][N] (device) or NULL; h = mu * phi (nodal product).
- * info: host struct or NULL. */
+ * info: host struct or NULL. A forward call that fails (this one once its
+ * input was accepted, qpat_forward_log also where exp(beta) is not finite and
+ * positive) leaves no linearisation point: the calls that need one return
+ * QPAT_ERR_STATE until the next that succeeds. */
 qpat_status qpat_forward(qpat_ctx* ctx, const double* kappa, const double* mu,
                          double* phi_out, double* h_out, qpat_info* info);
 

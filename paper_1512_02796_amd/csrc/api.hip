@@ -254,6 +254,13 @@ qpat_status qpat_set_sources(qpat_ctx* c, int32_t n_ill, const double* phi_src) 
     return QPAT_OK;
 }
 
+// The linearisation point and the LSQR run from it end: before c->kappa or c->mu
+// is written, so that a call that fails after that leaves neither
+static void drop_point(qpat_ctx* c) {
+    c->have_forward = false;
+    c->lsqr_ready = false;
+}
+
 // K and its multigrid hierarchy at c->kappa, c->mu
 static qpat_status build_K(qpat_ctx* c) {
     bool lattice = false;
@@ -270,8 +277,6 @@ static qpat_status forward_common(qpat_ctx* c, double* phi_out, double* h_out, q
                                   const double* x0 = nullptr) {
     QPAT_TRY(build_K(c));
     SolveStats st;
-    c->have_forward = false;
-    c->lsqr_ready = false;
     if (x0) QPAT_TRY(forward_solve_x0(c, x0, &st));
     else QPAT_TRY(forward_solve(c, &st));
     QPAT_TRY(forward_out(c, phi_out, h_out));
@@ -290,6 +295,7 @@ qpat_status qpat_forward(qpat_ctx* c, const double* kappa, const double* mu, dou
     bool ok = false;
     QPAT_TRY(check_positive(c, kappa, mu, c->N, &ok));
     if (!ok) return fail(c, QPAT_ERR_ARG, "forward: kappa and mu must be finite and > 0");
+    drop_point(c);
     const dim3 gr(grid_for(c->N, kThreads, 1 << 30)), b(kThreads);
     hipLaunchKernelGGL(k_copy_d, gr, b, 0, c->stream, c->N, kappa, c->kappa);
     hipLaunchKernelGGL(k_copy_d, gr, b, 0, c->stream, c->N, mu, c->mu);
@@ -305,6 +311,7 @@ qpat_status qpat_forward_x0(qpat_ctx* c, const double* kappa, const double* mu, 
     bool ok = false;
     QPAT_TRY(check_positive(c, kappa, mu, c->N, &ok));
     if (!ok) return fail(c, QPAT_ERR_ARG, "forward_x0: kappa and mu must be finite and > 0");
+    drop_point(c);
     const dim3 gr(grid_for(c->N, kThreads, 1 << 30)), b(kThreads);
     hipLaunchKernelGGL(k_copy_d, gr, b, 0, c->stream, c->N, kappa, c->kappa);
     hipLaunchKernelGGL(k_copy_d, gr, b, 0, c->stream, c->N, mu, c->mu);
@@ -402,6 +409,7 @@ qpat_status qpat_forward_log(qpat_ctx* c, double kappa0, double mu0, const doubl
     DeviceGuard g(c->device);
     if (!beta || !(kappa0 > 0.0) || !(mu0 > 0.0)) return fail(c, QPAT_ERR_ARG, "forward_log: bad arguments");
     if (c->n_ill == 0) return fail(c, QPAT_ERR_STATE, "forward_log: call qpat_set_sources first");
+    drop_point(c);
     QPAT_TRY(exp_params(c, kappa0, mu0, beta));
     bool ok = false;
     QPAT_TRY(check_positive(c, c->kappa, c->mu, c->N, &ok));
@@ -563,12 +571,11 @@ qpat_status qpat_fit_background(qpat_ctx* c, const double* chi, const double* w,
     QPAT_TRY(zero_fill(c, zero, 2 * N));
     QPAT_TRY(zero_fill(c, s1 + N, N));
     QPAT_TRY(zero_fill(c, s2, N));
+    drop_point(c);
     QPAT_TRY(exp_params(c, 1.0, 1.0, zero));   // kappa = mu = 1: the all-ones halves of s1, s2
     QPAT_HIP(c, hipMemcpyAsync(s1, c->kappa, N * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     QPAT_HIP(c, hipMemcpyAsync(s2 + N, c->mu, N * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
     SolveStats st;
-    c->have_forward = false;
-    c->lsqr_ready = false;
     // misfit^2 at the homogeneous point (exp a, exp b); leaves the forward state there
     auto evaluate = [&](double a, double b, double* F) -> qpat_status {
         const double k = std::exp(a), m = std::exp(b);

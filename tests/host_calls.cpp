@@ -257,6 +257,35 @@ int voxel_form_after_format_0() {
     EXPECT(launches("k_gadj_vgather") > 0);
     return 0;
 }
+
+// A forward call that fails once it has written the coefficients leaves no linearisation point (the products and
+// LSQR steps would mix the old fluence with the new coefficients); one refused before that leaves the old one.
+int failed_forward_state() {
+    double k0 = 1.0, m0 = 1.0;
+    const std::function<qpat_status(qpat_ctx*)> calls[] = {
+        [](qpat_ctx* c) { return qpat_forward(c, kSome, kSome, nullptr, nullptr, nullptr); },
+        [](qpat_ctx* c) { return qpat_forward_x0(c, kSome, kSome, kSome, nullptr, nullptr, nullptr); },
+        [](qpat_ctx* c) { return qpat_forward_log(c, 1.0, 1.0, kSome, nullptr, nullptr, nullptr); },
+        [&](qpat_ctx* c) { return qpat_fit_background(c, kSome, kSome, &k0, &m0, 1, 0.0, nullptr, nullptr); }};
+    for (int i = 0; i < 4; ++i) {
+        qpat_ctx* c = box(9, 10, 11, 4);
+        if (i < 3) {   // the check of the input finds a value that is not positive and finite
+            c->have_forward = c->lsqr_ready = true;
+            *c->dev_flag = 16;
+            EXPECT(calls[i](c) == QPAT_ERR_ARG);
+            EXPECT(c->have_forward == (i < 2) && c->lsqr_ready == (i < 2));   // forward_log has written exp(beta)
+            *c->dev_flag = 0;
+        }
+        c->have_forward = c->lsqr_ready = true;
+        g_fail_at = i < 3 ? 0 : 6;   // the assembly's first array (past the fit's own six)
+        EXPECT(calls[i](c) == QPAT_ERR_OOM);
+        g_fail_at = -1;
+        EXPECT(qpat_jvp(c, kSome, g_out, nullptr) == QPAT_ERR_STATE);
+        EXPECT(qpat_vjp(c, kSome, g_out, nullptr) == QPAT_ERR_STATE);
+        EXPECT(qpat_lsqr_step(c, nullptr, nullptr) == QPAT_ERR_STATE);
+    }
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -265,6 +294,7 @@ int main(int argc, char** argv) {
         {"guess_alloc_failures", guess_alloc_failures},
         {"voxel_limit_per_call", voxel_limit_per_call},
         {"voxel_form_after_format_0", voxel_form_after_format_0},
+        {"failed_forward_state", failed_forward_state},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();
