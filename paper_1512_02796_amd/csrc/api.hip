@@ -454,13 +454,14 @@ qpat_status qpat_prior_setup_r(qpat_ctx* c, const double* kt, const double* mt, 
         return fail(c, QPAT_ERR_ARG, "prior_setup: unknown prior kind %d", (int)kind);
     if (kind == QPAT_PRIOR_TVQ && !(q > 0.0 && q <= 2.0))
         return fail(c, QPAT_ERR_ARG, "prior_setup: TV^q needs 0 < q <= 2");
+    c->have_prior = false;   // until the matrices and their hierarchy are complete
+    c->lsqr_ready = false;
     QPAT_TRY(assemble_prior(c, kt, mt, kind, T, q, b_over_a, delta));
     QPAT_TRY(lattice_convert(c, Op::Prior));
     c->delta = delta;
     QPAT_TRY(mg_setup(c, Op::Prior));
-    c->have_prior = true;
-    c->lsqr_ready = false;
     QPAT_HIP(c, hipStreamSynchronize(c->stream));
+    c->have_prior = true;
     return QPAT_OK;
 }
 

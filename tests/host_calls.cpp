@@ -286,6 +286,20 @@ int failed_forward_state() {
     }
     return 0;
 }
+
+// A prior set-up that fails once it has written the matrices leaves no prior.
+int failed_prior_state() {
+    qpat_ctx* c = box(9, 10, 11, 4);
+    c->have_prior = c->lsqr_ready = true;
+    EXPECT(qpat_prior_setup(c, kSome, kSome, -1.0, 1.0, 1.0) == QPAT_ERR_ARG && c->have_prior);
+    g_fail_at = 0;
+    EXPECT(qpat_prior_setup(c, kSome, kSome, 1.0, 1.0, 1.0) == QPAT_ERR_OOM);
+    g_fail_at = -1;
+    EXPECT(qpat_prior_solve(c, kSome, g_out, nullptr) == QPAT_ERR_STATE);
+    EXPECT(qpat_prior_apply(c, kSome, g_out) == QPAT_ERR_STATE);
+    EXPECT(qpat_lsqr_step(c, nullptr, nullptr) == QPAT_ERR_STATE);
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -295,6 +309,7 @@ int main(int argc, char** argv) {
         {"voxel_limit_per_call", voxel_limit_per_call},
         {"voxel_form_after_format_0", voxel_form_after_format_0},
         {"failed_forward_state", failed_forward_state},
+        {"failed_prior_state", failed_prior_state},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();
