@@ -36,6 +36,15 @@ qpat_status dfree(qpat_ctx* c, void* p) {
     return QPAT_OK;
 }
 
+qpat_status dfree_from(qpat_ctx* c, size_t mark) {
+    while (c->allocs.size() > mark) {
+        void* p = c->allocs.back();
+        c->allocs.pop_back();
+        QPAT_HIP(c, hipFree(p));
+    }
+    return QPAT_OK;
+}
+
 namespace {
 
 __global__ void k_copy_d(int64_t n, const double* __restrict__ a, double* __restrict__ b) {

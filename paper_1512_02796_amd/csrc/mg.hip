@@ -4188,14 +4188,13 @@ static qpat_status region_setup(qpat_ctx* c, MgState& M) {
     const MgLevel& F = M.lv[0];
     const int64_t N = F.N;
     const int M1 = F.m + 1;
-    if (!M.reg) {
-        QPAT_TRY(dalloc(c, &M.reg, M.nsys * N));
-        QPAT_TRY(dalloc(c, &M.einv, M.nsys * kRegMax * kRegMax));
-        QPAT_TRY(dalloc(c, &M.rsize, M.nsys * kRegMax));
-        QPAT_TRY(dalloc(c, &M.rparts, (int64_t)M.nsys * kRegMax * kMgBlocks));
-        QPAT_TRY(dalloc(c, &M.ry, M.nsys * kRegMax));
-        QPAT_TRY(dalloc(c, &M.rcorr, 2 * M.nsys));
-    }
+    QPAT_TRY(dalloc_once(c, &M.reg, M.nsys * N));
+    QPAT_TRY(dalloc_once(c, &M.einv, M.nsys * kRegMax * kRegMax));
+    QPAT_TRY(dalloc_once(c, &M.rsize, M.nsys * kRegMax));
+    QPAT_TRY(dalloc_once(c, &M.rparts, (int64_t)M.nsys * kRegMax * kMgBlocks));
+    QPAT_TRY(dalloc_once(c, &M.ry, M.nsys * kRegMax));
+    QPAT_TRY(dalloc_once(c, &M.rcorr, 2 * M.nsys));
+    const ScopedArrays scratch(c);
     int32_t *lab = nullptr, *cnt = nullptr, *flag = nullptr, *list = nullptr, *roots = nullptr;
     unsigned long long *eint = nullptr, *amax = nullptr;
     QPAT_TRY(dalloc(c, &lab, N));
@@ -4290,8 +4289,6 @@ static qpat_status region_setup(qpat_ctx* c, MgState& M) {
     QPAT_HIP(c, hipMemcpyAsync(M.rsize, size_h.data(), size_h.size() * sizeof(double), hipMemcpyHostToDevice, st));
     QPAT_HIP(c, hipGetLastError());
     QPAT_HIP(c, hipStreamSynchronize(st));
-    for (void* p : {(void*)lab, (void*)cnt, (void*)flag, (void*)list, (void*)roots, (void*)eint, (void*)amax})
-        QPAT_TRY(dfree(c, p));
     return QPAT_OK;
 }
 
@@ -4546,6 +4543,105 @@ void dense_spd_inverse(const MgState& M, hipStream_t st) {
     hipLaunchKernelGGL(k_gj_out, ge, dim3(kMgT), 0, st, src, M.ainv, n);
 }
 
+// The levels of op's hierarchy and their arrays; *useful = false where the lattice has none
+static qpat_status mg_alloc(qpat_ctx* c, Op op, int nsys, MgState& M, bool* useful) {
+    *useful = true;
+    M.nsys = nsys;
+    M.bmax = op == Op::K ? kMaxRhs : 1;
+    MgLevel L0;
+    L0.nx = c->lat.nx;
+    L0.ny = c->lat.ny;
+    L0.nz = c->lat.nz;
+    L0.N = c->N;
+    L0.m = c->lat.m;
+    L0.tab = reinterpret_cast<const int4*>(c->lat_tab);
+    bool kuhn = c->lat.m == 7;
+    for (int j = 0; kuhn && j < 7; ++j)
+        kuhn = c->lat.dx[j] == kKx[j] && c->lat.dy[j] == kKy[j] && c->lat.dz[j] == kKz[j];
+    L0.kind = kuhn ? 1 : 0;
+    M.lv.push_back(L0);
+    // stop at the first coarse level small enough for a dense inverse (the
+    // levels below it cost a launch each for almost no work)
+    while (std::max(M.lv.back().nx, std::max(M.lv.back().ny, M.lv.back().nz)) > kMgCoarse &&
+           !(M.lv.size() >= 2 && M.lv.back().N <= kMgDenseK)) {
+        const MgLevel& F = M.lv.back();
+        MgLevel C;
+        C.nx = F.nx > 2 ? F.nx / 2 + 1 : F.nx;
+        C.ny = F.ny > 2 ? F.ny / 2 + 1 : F.ny;
+        C.nz = F.nz > 2 ? F.nz / 2 + 1 : F.nz;
+        if (C.nx == F.nx && C.ny == F.ny && C.nz == F.nz) break;
+        C.N = (int64_t)C.nx * C.ny * C.nz;
+        C.m = 13;
+        C.kind = 2;
+        M.lv.push_back(C);
+    }
+    const int nl = static_cast<int>(M.lv.size());
+    const int64_t Nc = M.lv.back().N;
+    if (Nc > (op == Op::K ? kMgDenseK : 4096) || nl < 2) {   // no useful hierarchy: keep Jacobi-PCG
+        *useful = false;
+        return QPAT_OK;
+    }
+    const int64_t V = (int64_t)nsys * M.bmax;
+    for (int l = 0; l < nl; ++l) {
+        MgLevel& L = M.lv[l];
+        if (l > 0) {
+            int32_t tab[4 * 13];
+            for (int j = 0; j < 13; ++j) {
+                const int code = 14 + j;
+                const int dx = code % 3 - 1, dy = (code / 3) % 3 - 1, dz = code / 9 - 1;
+                tab[4 * j] = dx;
+                tab[4 * j + 1] = dy;
+                tab[4 * j + 2] = dz;
+                tab[4 * j + 3] = dx + L.nx * (dy + L.ny * dz);
+            }
+            QPAT_TRY(dalloc(c, &L.tab_own, 13));
+            QPAT_HIP(c, hipMemcpyAsync(L.tab_own, tab, sizeof tab, hipMemcpyHostToDevice, c->stream));
+            L.tab = L.tab_own;
+            QPAT_TRY(dalloc(c, &L.U, nsys * L.N * 14));
+            QPAT_TRY(dalloc(c, &L.b, V * L.N));
+        }
+        QPAT_TRY(dalloc(c, &L.dinv, nsys * L.N));
+        QPAT_TRY(dalloc(c, &L.x, V * L.N));
+        QPAT_TRY(dalloc(c, &L.t, V * L.N));
+        QPAT_TRY(dalloc(c, &L.r, V * L.N));
+        if (op == Op::Prior && l + 1 < nl) {
+            if (WPack{L.nx, L.ny, L.nz}.size() >= (int64_t(1) << 31))
+                return fail(c, QPAT_ERR_ARG, "multigrid: lattice %d x %d x %d too large for the prior's transfers",
+                            L.nx, L.ny, L.nz);
+            QPAT_TRY(dalloc(c, &L.W, nsys * L.N * 8));
+            QPAT_TRY(dalloc(c, &L.Wc, nsys * WPack{L.nx, L.ny, L.nz}.size()));
+        }
+        if (op == Op::Prior && l == 0 && L.kind == 1) {   // entry-major upper rows (kind 3) and in FP32 (kind 5)
+            QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * kUpRow));
+            QPAT_TRY(dalloc(c, &L.Uf32, nsys * L.N * kUpRow));
+        }
+        if (op == Op::K && l >= 1 && l < kMgMaxLevels && M.bmax == 16 && M.lv[0].kind == 1 &&
+            L.N >= kTile27Min && L.N * 32 * (int64_t)sizeof(double) < (int64_t(1) << 31))
+            QPAT_TRY(dalloc(c, &L.Uf27p, L.N * 32));
+        if (op == Op::Prior && l >= 1 && l + 1 < nl && L.N >= kRow27Min) {   // entry-major rows (kind 4)
+            QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * 27));
+            QPAT_TRY(dalloc(c, &L.Uf32, nsys * L.N * 27));   // and in FP32 for the V-cycle (kind 6)
+        }
+    }
+    QPAT_TRY(dalloc(c, &M.w, nsys * nl));
+    QPAT_TRY(dalloc(c, &M.gmax, nsys * nl));
+    QPAT_TRY(dalloc(c, &M.ainv, nsys * Nc * Nc));
+    QPAT_TRY(dalloc(c, &M.ainv_t, nsys * Nc * Nc));
+    QPAT_TRY(dalloc(c, &M.apiv, 2 * nsys * kGj * kGj));
+    QPAT_TRY(dalloc(c, &M.bad, nsys + 1));
+    QPAT_TRY(dalloc(c, &M.pr, V * c->N));
+    QPAT_TRY(dalloc(c, &M.pr2, V * c->N));
+    QPAT_TRY(dalloc(c, &M.pa, V * c->N));
+    QPAT_TRY(dalloc(c, &M.pb, V * c->N));
+    QPAT_TRY(dalloc(c, &M.pq, V * c->N));
+    QPAT_TRY(dalloc(c, &M.parts, (int64_t)kMgLanes * 4 * kMgBlocks));
+    QPAT_TRY(dalloc(c, &M.sc, kMgLanes));
+    QPAT_HIP(c, hipMemsetAsync(M.sc, 0, kMgLanes * sizeof(MgScal), c->stream));
+    QPAT_HIP(c, hipHostMalloc((void**)&M.sc_host, kMgLanes * sizeof(MgScal), hipHostMallocDefault));
+    M.lv[0].b = M.pr;   // the V-cycle acts on the PCG residual
+    return QPAT_OK;
+}
+
 // Hierarchy for the current operator (after its assembly and stencil form).
 // Called after every assembly: when the options turn multigrid off, an older
 // hierarchy is marked stale so that turning it on again cannot pick it up.
@@ -4555,101 +4651,15 @@ qpat_status mg_setup(qpat_ctx* c, Op op) {
     if (!mg_available(c, op)) return QPAT_OK;
     const int nsys = op == Op::K ? 1 : 2;
     if (!Mp) {
+        const size_t mark = c->allocs.size();
         Mp = new MgState();
-        MgState& M = *Mp;
-        M.nsys = nsys;
-        M.bmax = op == Op::K ? kMaxRhs : 1;
-        MgLevel L0;
-        L0.nx = c->lat.nx;
-        L0.ny = c->lat.ny;
-        L0.nz = c->lat.nz;
-        L0.N = c->N;
-        L0.m = c->lat.m;
-        L0.tab = reinterpret_cast<const int4*>(c->lat_tab);
-        bool kuhn = c->lat.m == 7;
-        for (int j = 0; kuhn && j < 7; ++j)
-            kuhn = c->lat.dx[j] == kKx[j] && c->lat.dy[j] == kKy[j] && c->lat.dz[j] == kKz[j];
-        L0.kind = kuhn ? 1 : 0;
-        M.lv.push_back(L0);
-        // stop at the first coarse level small enough for a dense inverse (the
-        // levels below it cost a launch each for almost no work)
-        while (std::max(M.lv.back().nx, std::max(M.lv.back().ny, M.lv.back().nz)) > kMgCoarse &&
-               !(M.lv.size() >= 2 && M.lv.back().N <= kMgDenseK)) {
-            const MgLevel& F = M.lv.back();
-            MgLevel C;
-            C.nx = F.nx > 2 ? F.nx / 2 + 1 : F.nx;
-            C.ny = F.ny > 2 ? F.ny / 2 + 1 : F.ny;
-            C.nz = F.nz > 2 ? F.nz / 2 + 1 : F.nz;
-            if (C.nx == F.nx && C.ny == F.ny && C.nz == F.nz) break;
-            C.N = (int64_t)C.nx * C.ny * C.nz;
-            C.m = 13;
-            C.kind = 2;
-            M.lv.push_back(C);
-        }
-        const int nl = static_cast<int>(M.lv.size());
-        const int64_t Nc = M.lv.back().N;
-        if (Nc > (op == Op::K ? kMgDenseK : 4096) || nl < 2) {   // no useful hierarchy: keep Jacobi-PCG
+        bool useful = false;
+        const qpat_status st = mg_alloc(c, op, nsys, *Mp, &useful);
+        if (st != QPAT_OK || !useful) {   // a whole hierarchy or none (none: Jacobi-PCG)
             mg_drop(c, op);
-            return QPAT_OK;
+            QPAT_TRY(dfree_from(c, mark));
+            return st;
         }
-        const int64_t V = (int64_t)nsys * M.bmax;
-        for (int l = 0; l < nl; ++l) {
-            MgLevel& L = M.lv[l];
-            if (l > 0) {
-                int32_t tab[4 * 13];
-                for (int j = 0; j < 13; ++j) {
-                    const int code = 14 + j;
-                    const int dx = code % 3 - 1, dy = (code / 3) % 3 - 1, dz = code / 9 - 1;
-                    tab[4 * j] = dx;
-                    tab[4 * j + 1] = dy;
-                    tab[4 * j + 2] = dz;
-                    tab[4 * j + 3] = dx + L.nx * (dy + L.ny * dz);
-                }
-                QPAT_TRY(dalloc(c, &L.tab_own, 13));
-                QPAT_HIP(c, hipMemcpyAsync(L.tab_own, tab, sizeof tab, hipMemcpyHostToDevice, c->stream));
-                L.tab = L.tab_own;
-                QPAT_TRY(dalloc(c, &L.U, nsys * L.N * 14));
-                QPAT_TRY(dalloc(c, &L.b, V * L.N));
-            }
-            QPAT_TRY(dalloc(c, &L.dinv, nsys * L.N));
-            QPAT_TRY(dalloc(c, &L.x, V * L.N));
-            QPAT_TRY(dalloc(c, &L.t, V * L.N));
-            QPAT_TRY(dalloc(c, &L.r, V * L.N));
-            if (op == Op::Prior && l + 1 < nl) {
-                if (WPack{L.nx, L.ny, L.nz}.size() >= (int64_t(1) << 31))
-                    return fail(c, QPAT_ERR_ARG, "multigrid: lattice %d x %d x %d too large for the prior's transfers",
-                                L.nx, L.ny, L.nz);
-                QPAT_TRY(dalloc(c, &L.W, nsys * L.N * 8));
-                QPAT_TRY(dalloc(c, &L.Wc, nsys * WPack{L.nx, L.ny, L.nz}.size()));
-            }
-            if (op == Op::Prior && l == 0 && L.kind == 1) {   // entry-major upper rows (kind 3) and in FP32 (kind 5)
-                QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * kUpRow));
-                QPAT_TRY(dalloc(c, &L.Uf32, nsys * L.N * kUpRow));
-            }
-            if (op == Op::K && l >= 1 && l < kMgMaxLevels && M.bmax == 16 && M.lv[0].kind == 1 &&
-                L.N >= kTile27Min && L.N * 32 * (int64_t)sizeof(double) < (int64_t(1) << 31))
-                QPAT_TRY(dalloc(c, &L.Uf27p, L.N * 32));
-            if (op == Op::Prior && l >= 1 && l + 1 < nl && L.N >= kRow27Min) {   // entry-major rows (kind 4)
-                QPAT_TRY(dalloc(c, &L.Uf, nsys * L.N * 27));
-                QPAT_TRY(dalloc(c, &L.Uf32, nsys * L.N * 27));   // and in FP32 for the V-cycle (kind 6)
-            }
-        }
-        QPAT_TRY(dalloc(c, &M.w, nsys * nl));
-        QPAT_TRY(dalloc(c, &M.gmax, nsys * nl));
-        QPAT_TRY(dalloc(c, &M.ainv, nsys * Nc * Nc));
-        QPAT_TRY(dalloc(c, &M.ainv_t, nsys * Nc * Nc));
-        QPAT_TRY(dalloc(c, &M.apiv, 2 * nsys * kGj * kGj));
-        QPAT_TRY(dalloc(c, &M.bad, nsys + 1));
-        QPAT_TRY(dalloc(c, &M.pr, V * c->N));
-        QPAT_TRY(dalloc(c, &M.pr2, V * c->N));
-        QPAT_TRY(dalloc(c, &M.pa, V * c->N));
-        QPAT_TRY(dalloc(c, &M.pb, V * c->N));
-        QPAT_TRY(dalloc(c, &M.pq, V * c->N));
-        QPAT_TRY(dalloc(c, &M.parts, (int64_t)kMgLanes * 4 * kMgBlocks));
-        QPAT_TRY(dalloc(c, &M.sc, kMgLanes));
-        QPAT_HIP(c, hipMemsetAsync(M.sc, 0, kMgLanes * sizeof(MgScal), c->stream));
-        QPAT_HIP(c, hipHostMalloc((void**)&M.sc_host, kMgLanes * sizeof(MgScal), hipHostMallocDefault));
-        M.lv[0].b = M.pr;   // the V-cycle acts on the PCG residual
     }
     MgState& M = *Mp;
     const int nl = static_cast<int>(M.lv.size());

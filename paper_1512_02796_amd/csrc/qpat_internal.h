@@ -299,6 +299,16 @@ qpat_status dalloc_once(qpat_ctx* c, T** p, size_t n) {
     return *p ? QPAT_OK : dalloc(c, p, n);
 }
 qpat_status dfree(qpat_ctx* c, void* p);
+// every array made since the context held `mark` of them
+qpat_status dfree_from(qpat_ctx* c, size_t mark);
+// gives back the arrays made in its scope, however the scope ends
+struct ScopedArrays {
+    qpat_ctx* c;
+    size_t mark;
+    explicit ScopedArrays(qpat_ctx* ctx) : c(ctx), mark(ctx->allocs.size()) {}
+    ~ScopedArrays() { (void)dfree_from(c, mark); }
+    ScopedArrays(const ScopedArrays&) = delete;
+};
 
 #define QPAT_TRY(expr)                    \
     do {                                  \

@@ -17,7 +17,7 @@
 namespace {
 constexpr size_t kHeld = 1 << 16;   // bytes behind every allocation, whatever its size
 int g_fail_at = -1;                 // allocations that still succeed (-1: all)
-int g_allocs = 0;
+bool g_failed = false;              // one did not, since fail_at
 std::map<const void*, std::string>& kernel_names() {
     static std::map<const void*, std::string> m;
     return m;
@@ -33,12 +33,17 @@ struct Config {
 hipError_t alloc(void** p) {
     if (g_fail_at == 0) {
         *p = nullptr;
+        g_failed = true;
         return hipErrorOutOfMemory;
     }
     if (g_fail_at > 0) --g_fail_at;
-    ++g_allocs;
     *p = std::calloc(1, kHeld);
     return hipSuccess;
+}
+
+void fail_at(int n) {
+    g_fail_at = n;
+    g_failed = false;
 }
 
 int launches(const char* part) {
@@ -202,10 +207,10 @@ int guess_alloc_failures() {
     qpat_ctx* c = box(5, 16, 2, 1);
     float some[4] = {};
     for (int k = 0;; ++k) {
-        g_fail_at = k;
+        fail_at(k);
         const qpat_status s = qpat_guess_setup(c, 5, 16, 2);
-        const bool reached = g_fail_at == 0;
-        g_fail_at = -1;
+        const bool reached = g_failed;
+        fail_at(-1);
         if (!reached) {
             EXPECT(s == QPAT_OK);
             break;
@@ -216,9 +221,9 @@ int guess_alloc_failures() {
     EXPECT(qpat_guess_eval(c, some, some) == QPAT_OK);
     // the same for a change of sides: every buffer is there again after a later, successful call
     for (int k = 0; k < 3; ++k) {
-        g_fail_at = k;
+        fail_at(k);
         EXPECT(qpat_guess_setup(c, 2, 16, 5) == QPAT_ERR_OOM);
-        g_fail_at = -1;
+        fail_at(-1);
         EXPECT(qpat_guess_eval(c, some, some) == QPAT_ERR_STATE);
     }
     EXPECT(qpat_guess_setup(c, 2, 16, 5) == QPAT_OK);
@@ -277,9 +282,9 @@ int failed_forward_state() {
             *c->dev_flag = 0;
         }
         c->have_forward = c->lsqr_ready = true;
-        g_fail_at = i < 3 ? 0 : 6;   // the assembly's first array (past the fit's own six)
+        fail_at(i < 3 ? 0 : 6);   // the assembly's first array (past the fit's own six)
         EXPECT(calls[i](c) == QPAT_ERR_OOM);
-        g_fail_at = -1;
+        fail_at(-1);
         EXPECT(qpat_jvp(c, kSome, g_out, nullptr) == QPAT_ERR_STATE);
         EXPECT(qpat_vjp(c, kSome, g_out, nullptr) == QPAT_ERR_STATE);
         EXPECT(qpat_lsqr_step(c, nullptr, nullptr) == QPAT_ERR_STATE);
@@ -292,12 +297,37 @@ int failed_prior_state() {
     qpat_ctx* c = box(9, 10, 11, 4);
     c->have_prior = c->lsqr_ready = true;
     EXPECT(qpat_prior_setup(c, kSome, kSome, -1.0, 1.0, 1.0) == QPAT_ERR_ARG && c->have_prior);
-    g_fail_at = 0;
+    fail_at(0);
     EXPECT(qpat_prior_setup(c, kSome, kSome, 1.0, 1.0, 1.0) == QPAT_ERR_OOM);
-    g_fail_at = -1;
+    fail_at(-1);
     EXPECT(qpat_prior_solve(c, kSome, g_out, nullptr) == QPAT_ERR_STATE);
     EXPECT(qpat_prior_apply(c, kSome, g_out) == QPAT_ERR_STATE);
     EXPECT(qpat_lsqr_step(c, nullptr, nullptr) == QPAT_ERR_STATE);
+    return 0;
+}
+
+// A multigrid set-up that fails at any of its allocations leaves no half-built hierarchy and gives back what it made;
+// the next one builds it whole.
+int hierarchy_alloc_failures() {
+    for (const Op op : {Op::K, Op::Prior}) {
+        qpat_ctx* c = box(33, 34, 35, 16);
+        const size_t held = c->allocs.size();
+        for (int k = 0;; ++k) {
+            fail_at(k);
+            const qpat_status s = mg_setup(c, op);
+            const bool failed = g_failed;
+            fail_at(-1);
+            EXPECT(s == (failed ? QPAT_ERR_OOM : QPAT_OK));
+            EXPECT(mg_ready(c, op) == !failed);
+            if (!failed) break;
+            const MgState* M = op == Op::K ? c->mgk : c->mg;
+            EXPECT(M == nullptr ? c->allocs.size() == held : op == Op::Prior);   // M_delta: past its hierarchy, the regions'
+        }
+        const size_t whole = c->allocs.size();
+        EXPECT(mg_setup(c, op) == QPAT_OK && c->allocs.size() == whole);
+        qpat_ctx* d = box(33, 34, 35, 16);   // one that never failed holds as many arrays
+        EXPECT(mg_setup(d, op) == QPAT_OK && d->allocs.size() == whole);
+    }
     return 0;
 }
 }  // namespace
@@ -310,6 +340,7 @@ int main(int argc, char** argv) {
         {"voxel_form_after_format_0", voxel_form_after_format_0},
         {"failed_forward_state", failed_forward_state},
         {"failed_prior_state", failed_prior_state},
+        {"hierarchy_alloc_failures", hierarchy_alloc_failures},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();
