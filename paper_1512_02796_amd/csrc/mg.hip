@@ -3329,11 +3329,7 @@ qpat_status time_launches(qpat_ctx* c, F&& launch, float* ms) {
 }
 
 template <int B>
-qpat_status tile_setup(qpat_ctx* c, MgState& M) {
-    TileGeo& t = M.tiles[B];
-    if (t.ready) return QPAT_OK;
-    t.ready = true;
-    t.on = false;
+qpat_status tile_geometry(qpat_ctx* c, MgState& M, TileGeo& t) {
     const MgLevel& L = M.lv[0];
     if constexpr (B >= 8) {
         if (M.nsys != 1 || L.kind != 1 || L.N * B * (int64_t)sizeof(double) >= (int64_t(1) << 31)) return QPAT_OK;
@@ -3439,7 +3435,6 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                     cms[ci] = round == 0 ? ms_d + ms_u : std::min(cms[ci], ms_d + ms_u);
                 }
                 zc_t = static_cast<int32_t>(cands[tune_pick(cms)]);
-                QPAT_TRY(dfree(c, sc_t));
                 std::lock_guard<std::mutex> lk(g_tune_mu);
                 g_tune.emplace(key, zc_t);
             }
@@ -3532,7 +3527,6 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
                         cms[ci] = round == 0 ? ms : std::min(cms[ci], ms);
                     }
                     zc_t = static_cast<int32_t>(cands[tune_pick(cms)]);
-                    QPAT_TRY(dfree(c, sc_t));
                     std::lock_guard<std::mutex> lk(g_tune_mu);
                     g_tune.emplace(key, zc_t);
                 }
@@ -3574,6 +3568,18 @@ qpat_status tile_setup(qpat_ctx* c, MgState& M) {
             }
         }
     }
+    return QPAT_OK;
+}
+
+// M.tiles[B], on the first call that succeeds
+template <int B>
+qpat_status tile_setup(qpat_ctx* c, MgState& M) {
+    if (M.tiles[B].ready) return QPAT_OK;
+    const ScopedArrays scratch(c);
+    TileGeo t;
+    QPAT_TRY(tile_geometry<B>(c, M, t));
+    t.ready = true;
+    M.tiles[B] = t;
     return QPAT_OK;
 }
 
@@ -3937,12 +3943,11 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
     // x = x + sum alpha_j p_j (k_mgp_ring_flush) before x is read: the update
     // then neither reads nor writes x nor reads p.
     if (tg.on) {
-        if (!M.pring) {
-            const size_t n = (size_t)kRing * c->N * M.bmax;   // FP64-sized slots
+        const size_t n = (size_t)kRing * c->N * M.bmax;   // FP64-sized slots
+        QPAT_TRY(dalloc_once(c, &M.ahist, (size_t)kRing * kMgLanes));
+        QPAT_TRY(dalloc_once(c, &M.pslot, 1));
+        if (!M.pring) {   // finite values in the slots of lanes that stopped (their alpha is 0)
             QPAT_TRY(dalloc(c, &M.pring, n));
-            QPAT_TRY(dalloc(c, &M.ahist, (size_t)kRing * kMgLanes));
-            QPAT_TRY(dalloc(c, &M.pslot, 1));
-            // finite values in the slots of lanes that stopped (their alpha is 0)
             QPAT_HIP(c, hipMemsetAsync(M.pring, 0, n * sizeof(double), sm));
         }
         a.ring = kRing;

@@ -330,6 +330,37 @@ int hierarchy_alloc_failures() {
     }
     return 0;
 }
+
+// The same for what a first solve sets up: the direction ring and the tile schedule.
+int solve_alloc_failures() {
+    const auto ready = [] {
+        qpat_ctx* c = box(33, 34, 35, 16);
+        c->opts.autotune = 1;
+        (void)mg_setup(c, Op::K);
+        return c;
+    };
+    qpat_ctx* d = ready();   // one that never fails
+    SolveStats st;
+    EXPECT(mg_solve(d, Op::K, 16, &st) == QPAT_OK);
+    int32_t want[8], got[8];
+    EXPECT(mg_tile_schedule(d, 16, want) == QPAT_OK && want[0] == 1 && want[7] == 1);
+    // (the times of the tuned schedule are kept for the process: another lattice of the same size reuses them, so the
+    // failures of the tuning itself are met on lattices of other sizes)
+    for (int k = 0, failed = 1; failed; ++k) {
+        qpat_ctx* c = box(33, 34, 37 + 2 * k, 16);
+        c->opts.autotune = 1;
+        EXPECT(mg_setup(c, Op::K) == QPAT_OK);
+        fail_at(k);
+        const qpat_status s = mg_solve(c, Op::K, 16, &st);
+        failed = g_failed;
+        fail_at(-1);
+        EXPECT(failed ? s != QPAT_OK : s == QPAT_OK);
+        EXPECT(mg_solve(c, Op::K, 16, &st) == QPAT_OK);
+        EXPECT(c->allocs.size() >= d->allocs.size());
+        EXPECT(mg_tile_schedule(c, 16, got) == QPAT_OK && got[0] == 1 && got[7] == 1);
+    }
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -341,6 +372,7 @@ int main(int argc, char** argv) {
         {"failed_forward_state", failed_forward_state},
         {"failed_prior_state", failed_prior_state},
         {"hierarchy_alloc_failures", hierarchy_alloc_failures},
+        {"solve_alloc_failures", solve_alloc_failures},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();
