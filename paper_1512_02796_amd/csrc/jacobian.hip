@@ -878,13 +878,17 @@ static qpat_status rel_maxdiff(qpat_ctx* c, int64_t n, const double* a, const do
 static qpat_status vox_check_rows(qpat_ctx* c) {
     if (c->vox_rows != 0 || c->vox < 0) return QPAT_OK;
     if (c->opts.operator_format != 1) return QPAT_OK;   // an option, which may change: no verdict
-    c->vox_rows = -1;
-    if (!c->lat.on || c->lat.m != 7) return QPAT_OK;
+    const ScopedArrays scratch(c);
+    const auto verdict = [c](bool same) {   // none where the check fails for want of memory
+        c->vox_rows = same ? 1 : -1;
+        return QPAT_OK;
+    };
+    if (!c->lat.on || c->lat.m != 7) return verdict(false);
     for (int m = 1; m < 8; ++m)   // upper offset with axis mask m in slot m (the Kuhn pattern's order)
-        if (c->lat.code[13 + (m & 1) + 3 * ((m >> 1) & 1) + 9 * (m >> 2)] != m) return QPAT_OK;
+        if (c->lat.code[13 + (m & 1) + 3 * ((m >> 1) & 1) + 9 * (m >> 2)] != m) return verdict(false);
     const int64_t N = c->N, nx = c->lat.nx, ny = c->lat.ny, nz = c->lat.nz;
     const int64_t Nv = (nx - 1) * (ny - 1) * (nz - 1);
-    if (Nv < 1 || 6 * Nv != c->E) return QPAT_OK;
+    if (Nv < 1 || 6 * Nv != c->E) return verdict(false);
     const VoxGeo vg = vox_geo(c);
     const dim3 blk(kThreads);
     double *uu = nullptr, *ue = nullptr, *uv = nullptr;
@@ -899,11 +903,7 @@ static qpat_status vox_check_rows(qpat_ctx* c) {
     hipLaunchKernelGGL(k_dk_voxel, gv, blk, 0, c->stream, N, c->lat, vg, uu, uv);
     double rel_dk = 0.0;
     QPAT_TRY(rel_maxdiff(c, 8 * N, uv, ue, &rel_dk));
-    QPAT_TRY(dfree(c, uu));
-    QPAT_TRY(dfree(c, ue));
-    QPAT_TRY(dfree(c, uv));
-    if (rel_dk <= 1e-12) c->vox_rows = 1;
-    return QPAT_OK;
+    return verdict(rel_dk <= 1e-12);
 }
 
 // the adjoint kernel's 32-bit byte offsets: phi [N][columns], blocks [N][16], sums
@@ -917,10 +917,14 @@ static qpat_status vox_check(qpat_ctx* c) {
     if (c->vox != 0) return QPAT_OK;
     QPAT_TRY(vox_check_rows(c));
     if (c->vox_rows == 0) return QPAT_OK;
-    c->vox = -1;
-    if (c->vox_rows != 1) return QPAT_OK;
+    const ScopedArrays scratch(c);
+    const auto verdict = [c](bool same) {
+        c->vox = same ? 1 : -1;
+        return QPAT_OK;
+    };
+    if (c->vox_rows != 1) return verdict(false);
     const int64_t N = c->N, Nv = c->E / 6;
-    if (!vox_fits(c, 16)) return QPAT_OK;
+    if (!vox_fits(c, 16)) return verdict(false);
     const VoxGeo vg = vox_geo(c);
     const dim3 blk(kThreads);
     constexpr int BC = 16;   // right-hand sides of the check
@@ -945,9 +949,7 @@ static qpat_status vox_check(qpat_ctx* c) {
     double rel1 = 0.0, rel2 = 0.0;
     QPAT_TRY(rel_maxdiff(c, N, a + 2 * N, a, &rel1));
     QPAT_TRY(rel_maxdiff(c, N, a + 3 * N, a + N, &rel2));
-    for (double* p : {f, z, tq, tr, qr, a}) QPAT_TRY(dfree(c, p));
-    if (rel1 <= 1e-12 && rel2 <= 1e-12) c->vox = 1;
-    return QPAT_OK;
+    return verdict(rel1 <= 1e-12 && rel2 <= 1e-12);
 }
 
 qpat_status forward_out(qpat_ctx* c, double* phi_out, double* h_out) {
@@ -971,7 +973,7 @@ qpat_status assemble_K_lattice(qpat_ctx* c, bool* done) {
     if (!mg_available(c, Op::K)) return QPAT_OK;
     QPAT_TRY(vox_check_rows(c));
     if (c->vox_rows != 1) return QPAT_OK;
-    if (!c->dKc) QPAT_TRY(dalloc(c, &c->dKc, 2 * c->N));
+    QPAT_TRY(dalloc_once(c, &c->dKc, 2 * c->N));
     const dim3 blk(kThreads);
     hipLaunchKernelGGL(k_dk_coef, dim3(grid_for(c->N, kThreads, 1 << 30)), blk, 0, c->stream, c->N, c->kappa, c->mu,
                        static_cast<const double*>(nullptr), c->dKc);
@@ -1026,8 +1028,8 @@ qpat_status jvp_core(qpat_ctx* c, const double* s, int mode, double* out, SolveS
     // 42 -> 13 us, 33^3 58 -> 16)
     const bool lat = c->lat.on && c->opts.operator_format == 1 && (B >= 8 || mg_stencil_ready(c));
     if (lat) {
-        if (!c->dK) QPAT_TRY(dalloc(c, &c->dK, (int64_t)(c->lat.m + 1) * c->N));
-        if (!c->dKc) QPAT_TRY(dalloc(c, &c->dKc, 2 * c->N));
+        QPAT_TRY(dalloc_once(c, &c->dK, (int64_t)(c->lat.m + 1) * c->N));
+        QPAT_TRY(dalloc_once(c, &c->dKc, 2 * c->N));
         hipLaunchKernelGGL(k_dk_coef, dim3(grid_for(c->N, kThreads, 1 << 30)), blk, 0, c->stream, c->N, c->kappa, c->mu,
                            s, c->dKc);
         // a multiple of 8 blocks (the XCD strips), several per compute unit
@@ -1073,10 +1075,8 @@ qpat_status vjp_core(qpat_ctx* c, const double* t, int mode, double* out, SolveS
     const int B = block_size(c);
     const dim3 g(grid_for(c->N * B, kThreads, 1 << 30)), blk(kThreads), gt(grid_for(c->N, kTrN, 1 << 30));
     const int tmode = mode == 0 ? 0 : 1;
-    if (!c->tq) {
-        QPAT_TRY(dalloc(c, &c->tq, c->E));
-        QPAT_TRY(dalloc(c, &c->tr, 4 * c->E));
-    }
+    QPAT_TRY(dalloc_once(c, &c->tq, c->E));
+    QPAT_TRY(dalloc_once(c, &c->tr, 4 * c->E));
     const bool fits = vox_fits(c, c->n_pad);
     if (fits) QPAT_TRY(vox_check(c));
     const bool vox = fits && c->vox == 1;   // per-voxel sums [16][Nv] in tr (4 E = 24 Nv values)

@@ -361,6 +361,28 @@ int solve_alloc_failures() {
     }
     return 0;
 }
+
+// The same for the arrays of the Jacobian's products and the check of the voxel form, which leaves no verdict when it
+// could not be made and gives back its own arrays.
+int product_alloc_failures() {
+    size_t whole = 0;
+    for (int k = -1, failed = 1; failed; ++k) {   // -1: never
+        qpat_ctx* c = box(9, 10, 11, 16);
+        EXPECT(mg_setup(c, Op::K) == QPAT_OK);
+        SolveStats st;
+        fail_at(k);
+        qpat_status s = jvp_core(c, kSome, 0, g_out, &st);
+        if (s == QPAT_OK) s = vjp_core(c, kSome, 0, g_out, &st);
+        failed = k < 0 || g_failed;
+        fail_at(-1);
+        EXPECT(k < 0 || !failed ? s == QPAT_OK : s != QPAT_OK);
+        EXPECT(jvp_core(c, kSome, 0, g_out, &st) == QPAT_OK && vjp_core(c, kSome, 0, g_out, &st) == QPAT_OK);
+        EXPECT(c->vox == 1 && c->vox_rows == 1);
+        if (k < 0) whole = c->allocs.size();
+        EXPECT(c->allocs.size() == whole);
+    }
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -373,6 +395,7 @@ int main(int argc, char** argv) {
         {"failed_prior_state", failed_prior_state},
         {"hierarchy_alloc_failures", hierarchy_alloc_failures},
         {"solve_alloc_failures", solve_alloc_failures},
+        {"product_alloc_failures", product_alloc_failures},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();
