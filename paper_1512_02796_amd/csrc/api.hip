@@ -240,7 +240,11 @@ qpat_status qpat_set_sources(qpat_ctx* c, int32_t n_ill, const double* phi_src) 
     int n_pad = 1;
     while (n_pad < n_ill && n_pad < kMaxRhs) n_pad <<= 1;
     if (n_ill > kMaxRhs) n_pad = ((n_ill + kMaxRhs - 1) / kMaxRhs) * kMaxRhs;
+    c->have_forward = false;
+    c->lsqr_ready = false;
+    c->n_ill = 0;   // none until the arrays are there
     if (n_pad != c->n_pad) {
+        c->n_pad = 0;
         for (double** p : {&c->f, &c->phi, &c->dvec, &c->lu, &c->lq, &c->lw}) {
             QPAT_TRY(dfree(c, *p));
             *p = nullptr;
@@ -256,8 +260,6 @@ qpat_status qpat_set_sources(qpat_ctx* c, int32_t n_ill, const double* phi_src) 
     }
     c->n_ill = n_ill;
     c->n_pad = n_pad;
-    c->have_forward = false;
-    c->lsqr_ready = false;
     QPAT_TRY(assemble_load(c, phi_src));
     QPAT_HIP(c, hipStreamSynchronize(c->stream));
     return QPAT_OK;

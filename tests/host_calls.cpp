@@ -383,6 +383,23 @@ int product_alloc_failures() {
     }
     return 0;
 }
+
+// Sources whose arrays could not be made leave none: forward calls and products are refused until others are set.
+int failed_sources_state() {
+    for (int k = 0; k < 6; ++k) {
+        qpat_ctx* c = box(9, 10, 11, 4);
+        c->have_forward = c->lsqr_ready = true;
+        fail_at(k);
+        EXPECT(qpat_set_sources(c, 20, kSome) == QPAT_ERR_OOM);
+        fail_at(-1);
+        EXPECT(qpat_forward(c, kSome, kSome, nullptr, nullptr, nullptr) == QPAT_ERR_STATE);
+        EXPECT(qpat_jvp(c, kSome, g_out, nullptr) == QPAT_ERR_STATE);
+        EXPECT(qpat_lsqr_step(c, nullptr, nullptr) == QPAT_ERR_STATE);
+        EXPECT(qpat_set_sources(c, 20, kSome) == QPAT_OK && c->n_ill == 20 && c->n_pad == 32);
+        EXPECT(c->f && c->phi && c->dvec && c->lu && c->lq && c->lw);
+    }
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -396,6 +413,7 @@ int main(int argc, char** argv) {
         {"hierarchy_alloc_failures", hierarchy_alloc_failures},
         {"solve_alloc_failures", solve_alloc_failures},
         {"product_alloc_failures", product_alloc_failures},
+        {"failed_sources_state", failed_sources_state},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();
