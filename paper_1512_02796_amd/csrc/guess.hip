@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_conv(Lat L, const uint16_t* __r
         for (int j = 0; j < 4; ++j) bs[j] = bias[4 * g + j];
     if (MODE == 1) bs[0] = bias[0];
     const int64_t plane = (int64_t)L.sx * L.sy;
-    int64_t toff[7];   // the 3-channel layer: group g takes tap 4m + g of product m
+    int64_t toff[7];   // the 3-channel layer: group g takes tap 4m + g of product m (the last one has none)
     if (CIN == 4)
 #pragma unroll
         for (int m = 0; m < 7; ++m) toff[m] = 4 * m + g < 27 ? L.tap(4 * m + g) * 4 : 0;
@@ -155,6 +155,9 @@ __global__ __launch_bounds__(kThreads, 4) void k_conv(Lat L, const uint16_t* __r
                 for (int m = 0; m < NCH; ++m)
                     v[q / 2][q % 2][m] =
                         *reinterpret_cast<const s4*>(X + (p + (q / 2) * plane + (q % 2) * L.sx) * 4 + toff[m]);
+            if (4 * (NCH - 1) + g >= 27)   // no 28th tap: 0, not the cell itself (its weight is 0, but 0 inf is no 0)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q / 2][q % 2][NCH - 1] = s4{0, 0, 0, 0};
 #pragma unroll
             for (int m = 0; m < NCH; ++m)
 #pragma unroll
@@ -217,6 +220,15 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(Lat L, const uint16_t* __res
     float db = 0.f;
     for (int64_t tile = wg; tile < ntiles; tile += nw) {
         const int64_t p = L.g0 + tile * 16 + 4 * g;
+        // a cell outside the lattice has dZ = 0, but its taps may reach an infinite
+        // activation, and 0 inf is no 0: their values are masked (sx is a multiple
+        // of 4, so the four cells share a row)
+        const uint32_t q0 = static_cast<uint32_t>(tile * 16 + 4 * g), row = q0 / L.sx;
+        const int in = row % L.sy < static_cast<uint32_t>(L.ny) && row < static_cast<uint32_t>(L.sy) * L.nz
+                           ? L.nx - static_cast<int>(q0 % L.sx) : 0;   // of them inside, from the first
+        s4 on;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) on[j] = j < in ? -1 : 0;
         s4 a;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -230,6 +242,7 @@ __global__ __launch_bounds__(kThreads) void k_wgrad(Lat L, const uint16_t* __res
             s4 b;
 #pragma unroll
             for (int j = 0; j < 4; ++j) b[j] = static_cast<short>(X[(p + j + (t < 27 ? L.tap(t) : 0)) * CIN + ci]);
+            b &= on;
             acc[m] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[m], 0, 0, 0);
         }
     }

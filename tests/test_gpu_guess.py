@@ -196,3 +196,47 @@ def test_net_set_up_again_with_other_sides():
         assert_close(host(out).astype(np.float64), ref.ravel(), 3e-2, f"net output {(nx, ny, nz)}")
         outs.append(out)
     assert torch.equal(outs[0], outs[-1])
+
+
+def test_net_with_an_infinite_input():
+    """An infinite input reaches exactly the outputs its taps lead to. First layer: +1 at the centre and -1 at every
+    other tap of channel 0, so only the cell itself stays infinite after the ReLU; positive weights above it spread
+    that over a box of 3 cells to each side. The gradient of a first-layer weight whose tap reaches an infinite cell
+    only from outside the lattice stays finite (negative weights of channel 0: the ReLU cuts the infinity off).
+    Tolerance: the BF16 bound of this file."""
+    from paper_1512_02796_amd import qpat
+    from test_gpu_stencil import kuhn_box
+    nx, ny, nz = 9, 10, 11
+    coords, tets, bfaces = kuhn_box(nx - 1, ny - 1, nz - 1)
+    ctx = qpat.Context(dev(coords), dev(tets, torch.int32), dev(bfaces, torch.int32))
+    ctx.guess_setup(nx, ny, nz)
+    params, x = seeded_net(3, (nz, ny, nx))
+    params = [[np.abs(w), b] for w, b in params]
+    w0 = params[0][0].reshape(16, 3, 27)
+    w0[:, 0] = -1.0
+    w0[:, 0, 13] = 1.0
+    x[0] = 0.0
+    x[0, 5, 4, 3] = np.inf
+    ctx.guess_set_params(dev(flat_params(params), torch.float32))
+    out = torch.empty(nx * ny * nz, dtype=torch.float32, device="cuda")
+    ctx.guess_eval(dev(x.reshape(3, -1), torch.float32), out)
+    got, (ref, _) = host(out).astype(np.float64).reshape(nz, ny, nx), convnet.forward(params, x)
+    ref = np.asarray(ref).reshape(nz, ny, nx)
+    box = np.zeros((nz, ny, nx), bool)
+    box[2:9, 1:8, 0:7] = True
+    assert np.array_equal(np.isposinf(ref), box) and np.array_equal(np.isposinf(got), box)
+    assert_close(got[~box], ref[~box], 3e-2, "finite outputs")
+
+    w0[:, 0] = -1.0
+    x[0, 5, 4, 3] = 0.0
+    x[0, 5, 4, nx - 1] = np.inf      # a face cell: off-lattice cells at x = nx reach it through dx = -1
+    ctx.guess_set_params(dev(flat_params(params), torch.float32))
+    g = torch.empty(15601, dtype=torch.float32, device="cuda")
+    target = torch.zeros(nx * ny * nz, dtype=torch.float32, device="cuda")
+    ctx.guess_grad(dev(x.reshape(3, -1), torch.float32), target, g)
+    got = host(g)[:16 * 3 * 27].reshape(16, 3, 27)
+    x[0, 5, 4, nx - 1] = 1e4         # cut off just as well: the same network, with a finite input
+    ctx.guess_grad(dev(x.reshape(3, -1), torch.float32), target, g)
+    ref = host(g)[:16 * 3 * 27].reshape(16, 3, 27)
+    dx_minus = [t for t in range(27) if t % 3 == 0]
+    assert np.array_equal(got[:, 0, dx_minus], ref[:, 0, dx_minus])
