@@ -131,6 +131,9 @@ qpat_status alloc_core(qpat_ctx* c) {
     QPAT_TRY(dalloc(c, &c->lp, 2 * N));
     QPAT_TRY(dalloc(c, &c->lr, 2 * N));
     QPAT_HIP(c, hipHostMalloc((void**)&c->scal_host, sizeof(PcgScal) * kMaxSys, hipHostMallocDefault));
+    QPAT_HIP(c, hipHostMalloc((void**)&c->live, sizeof(uint32_t) * kMaxSys, hipHostMallocCoherent | hipHostMallocMapped));
+    std::memset(c->live, 0, sizeof(uint32_t) * kMaxSys);
+    QPAT_HIP(c, hipHostGetDevicePointer((void**)&c->live_dev, c->live, 0));
     QPAT_HIP(c, hipHostMalloc((void**)&c->ls_host, sizeof(LsqrScal), hipHostMallocDefault));
     QPAT_HIP(c, hipHostMalloc((void**)&c->red_host, sizeof(double) * 64, hipHostMallocDefault));
     std::memset(c->ls_host, 0, sizeof(LsqrScal));
@@ -786,6 +789,7 @@ void qpat_destroy(qpat_ctx* c) {
     for (void* p : c->allocs) (void)hipFree(p);
     c->allocs.clear();
     if (c->scal_host) (void)hipHostFree(c->scal_host);
+    if (c->live) (void)hipHostFree(c->live);
     if (c->ls_host) (void)hipHostFree(c->ls_host);
     if (c->red_host) (void)hipHostFree(c->red_host);
     delete c;

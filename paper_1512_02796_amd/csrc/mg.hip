@@ -27,6 +27,7 @@
 // residual at the end. Everything is FP64.
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -1912,7 +1913,8 @@ __global__ __launch_bounds__(kMgT) void k_mgp_bstats(PcgMg a, const double* __re
     }
 }
 
-__global__ __launch_bounds__(kMgT) void k_mgp_init(PcgMg a, int nb, double inv_delta) {
+// live: where this is the start's last kernel, its answer for the host
+__global__ __launch_bounds__(kMgT) void k_mgp_init(PcgMg a, int nb, double inv_delta, Live live) {
     __shared__ double sm[(kMgT / 64) * 2];
     const int lane = blockIdx.y;
     if (a.ring > 0 && lane == 0 && threadIdx.x == 0) *a.slot = 0;   // a run's first iteration: slot 0
@@ -1930,6 +1932,7 @@ __global__ __launch_bounds__(kMgT) void k_mgp_init(PcgMg a, int nb, double inv_d
         s.iters = 0;
         s.done = s2 == 0.0 ? 1 : 0;       // b = 0: x = 0
         s.active = s2 == 0.0 ? 0 : 1;
+        live.put(lane, s2 != 0.0);
     }
 }
 
@@ -2026,7 +2029,7 @@ __global__ __launch_bounds__(kMgT) void k_mgp_true(PcgMg a, const double* __rest
     }
 }
 
-__global__ __launch_bounds__(kMgT) void k_mgp_true_fin(PcgMg a, int nb, int reopen) {
+__global__ __launch_bounds__(kMgT) void k_mgp_true_fin(PcgMg a, int nb, int reopen, Live live) {
     __shared__ double sm[kMgT / 64];
     const int lane = blockIdx.y;
     double v[1];
@@ -2038,7 +2041,9 @@ __global__ __launch_bounds__(kMgT) void k_mgp_true_fin(PcgMg a, int nb, int reop
         if (s.iters == 0) s.rr0 = rr;
         const bool ok = rr <= a.rtol2 * s.bnorm2;
         s.done = ok ? 1 : 0;
-        s.active = (!ok && reopen && s.iters < a.maxit) ? 1 : 0;
+        const bool on = !ok && reopen && s.iters < a.maxit;
+        s.active = on ? 1 : 0;
+        live.put(lane, on);
         s.rz = 0.0;   // a reopened run restarts its Krylov space from the true residual
     }
 }
@@ -3692,9 +3697,12 @@ void launch_resid_restrict(const MgState& M, int l, hipStream_t st, const double
 // it and the prolongation recomputes it. Level 0 takes 2 kMgNu - 1 ping-pong
 // sweeps (an odd number), so z ends in level 0's t.
 // first_done: the PCG update already wrote the finest level's first sweep
+// look: asked once the finest level's way down is launched (so that the device has
+// work while the host waits for the answer); false ends the cycle there. Returns
+// whether it was completed.
 template <int B>
-void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev = nullptr, const double* b0 = nullptr,
-            bool resid_done = false, bool first_done = false) {
+bool vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev = nullptr, const double* b0 = nullptr,
+            bool resid_done = false, bool first_done = false, const std::function<bool()>& look = {}) {
     const int nl = static_cast<int>(M.lv.size());
     const bool v1 = v32_path<B>(M, tg);   // level 1's vectors in FP32
     const bool f0 = f32v0_path<B>(M, tg);  // level 0's vectors in FP32 (one right-hand side)
@@ -3706,6 +3714,7 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
     }
     auto sm = [&](int l) { return level_args(M, l); };
     for (int l = 0; l < nl - 1; ++l) {
+        if (l == 1 && look && !look()) return false;
         const MgLevel& L = M.lv[l];
         const MgLevel& C = M.lv[l + 1];
         const SmArgs a = sm(l);
@@ -3748,6 +3757,7 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
             hipLaunchKernelGGL((k_mg_restrict<B, false>), sgrid<B>(C.N, M.nsys), dim3(kMgT), 0, st, sm(l + 1), L.nx, L.ny,
                                L.nz, L.r, C.b, xl[l + 1], static_cast<const float*>(nullptr));
     }
+    if (nl == 2 && look && !look()) return false;
     const MgLevel& K = M.lv[nl - 1];
     hipLaunchKernelGGL(k_mg_dense<B>,
                        dim3((unsigned)((K.N + kMgT / 64 - 1) / (kMgT / 64)), (unsigned)Pk<B>::BV, (unsigned)M.nsys),
@@ -3795,6 +3805,7 @@ void vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
             std::swap(xl[l], tl[l]);
         }
     }
+    return true;
 }
 
 // blocks of the V-cycle's last finest-level sweep, which leave r.z
@@ -3975,18 +3986,21 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         QPAT_HIP(c, hipGetLastError());
         return QPAT_OK;
     };
+    const Live live = live_begin(c);
     if (tg.on && !a.deflate && !has_x0) {   // one pass over b
         const dim3 gs = vgrid(c->N * Pk<B>::BV / 4 + 1, kMgBlocks);
         hipLaunchKernelGGL(k_mgp_start0<B>, gs, dim3(kMgT), 0, sm, a, c->b64);
-        hipLaunchKernelGGL(k_mgp_init, lanes, dim3(kMgT), 0, sm, a, (int)gs.x, c->delta > 0 ? 1.0 / c->delta : 0.0);
+        hipLaunchKernelGGL(k_mgp_init, lanes, dim3(kMgT), 0, sm, a, (int)gs.x, c->delta > 0 ? 1.0 / c->delta : 0.0,
+                           live);
     } else {
         hipLaunchKernelGGL(k_mgp_bstats<B>, g, dim3(kMgT), 0, sm, a, c->b64);
-        hipLaunchKernelGGL(k_mgp_init, lanes, dim3(kMgT), 0, sm, a, (int)g.x, c->delta > 0 ? 1.0 / c->delta : 0.0);
+        hipLaunchKernelGGL(k_mgp_init, lanes, dim3(kMgT), 0, sm, a, (int)g.x, c->delta > 0 ? 1.0 / c->delta : 0.0,
+                           has_x0 ? Live{} : live);
         hipLaunchKernelGGL(k_mgp_start<B>, g, dim3(kMgT), 0, sm, a, c->b64, has_x0 ? 1 : 0);
     }
     if (has_x0) {   // r = b - A x0; lanes that x0 already solves stop here
         true_residual<B>(M, a, tg, c->b64, sm);
-        hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, tg.on ? tg.blocks : (int)g.x, 1);
+        hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, tg.on ? tg.blocks : (int)g.x, 1, live);
     }
     QPAT_HIP(c, hipGetLastError());
     auto fetch = [&]() -> qpat_status {
@@ -4001,10 +4015,15 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
     };
     std::vector<int> reopened(S, 0);   // per lane: restarts after a failed true-residual check
     bool fetched = false;              // sc_host holds the lanes' last state
-    // A solve's first V-cycle and chunk go out unseen: a lane with nothing to
-    // do is inactive on the device already, and what the chunk lengths need of
-    // the start (rr0) comes back with the first check. Each host check is a
-    // copy, a wait and an idle device while the next chunk is launched.
+    bool idle = false;                 // every right-hand side is 0
+    // A solve's first V-cycle and chunk go out without a copy of the scalars: a
+    // lane with nothing to do is inactive on the device already, and what the
+    // chunk lengths need of the start (rr0) comes back with the first check. Each
+    // such check is a copy, a wait and an idle device while the next chunk is
+    // launched. Only whether any lane iterates at all is asked, behind the first
+    // kernels of the V-cycle: right-hand sides of zero (J 0) or a start that
+    // solves them end there (M_delta^{-1} 0 on 128^3 voxels 97 us, 670 with the
+    // first chunk; on 16^3 82, 200; a pair's two solves are no slower for it).
     for (int restart = 0; restart < 4; ++restart) {
         if (restart > 0) {
             QPAT_TRY(fetch());
@@ -4019,7 +4038,15 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         if (restart > 0 && tg.on) true_residual<B>(M, a, tg, c->b64, sm);
         // first direction of a run: z = V(r) (+ Z y), p = z - c
         region_solve<B>(M, a, sm);
-        vcycle<B>(M, sm, tg);
+        if (restart == 0) {
+            if (!vcycle<B>(M, sm, tg, nullptr, nullptr, false, false, [&] { return any_live(c, S); })) {
+                QPAT_TRY(ring_flush());   // x = 0 where the start left it unwritten
+                fetched = idle = !has_x0; // b = 0: nothing to learn from the scalars
+                break;
+            }
+        } else {
+            vcycle<B>(M, sm, tg);
+        }
         hipLaunchKernelGGL(k_mgp_scalars, lanes, dim3(kMgT), 0, sm, a,
                            last_blocks<B>(M, tg), 3);
         QPAT_HIP(c, hipGetLastError());
@@ -4140,7 +4167,8 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         // confirm on the true residual; a failed check restarts from the true residual
         QPAT_TRY(ring_flush());
         true_residual<B>(M, a, tg, c->b64, sm, !tg.on);
-        hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, tg.on ? tg.blocks : (int)g.x, restart < 3 ? 1 : 0);
+        hipLaunchKernelGGL(k_mgp_true_fin, lanes, dim3(kMgT), 0, sm, a, tg.on ? tg.blocks : (int)g.x, restart < 3 ? 1 : 0,
+                           Live{});
         QPAT_HIP(c, hipGetLastError());
     }
     if (!fetched) QPAT_TRY(fetch());
@@ -4148,6 +4176,10 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
         const MgScal& s = M.sc_host[i];
         if (op == Op::Prior)   // the output kernel of the prior solve adds mean(b)/delta
             QPAT_HIP(c, hipMemcpyAsync(&c->scal[i].mean, &M.sc[i].mean, sizeof(double), hipMemcpyDeviceToDevice, sm));
+        if (idle) {
+            st->add(0, 0.0, 0, true);
+            continue;
+        }
         const double rel = s.bnorm2 > 0 ? std::sqrt(s.rr / s.bnorm2) : 0.0;
         st->add(s.iters, rel, reopened[i], s.done != 0);
     }

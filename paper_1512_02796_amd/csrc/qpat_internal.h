@@ -208,6 +208,11 @@ struct qpat_ctx {
     double* partials = nullptr;    // [4][kMaxSys][max blocks]
     int32_t pcg_blocks = 0;        // blocks per system
     qpat::PcgScal* scal_host = nullptr;  // pinned mirror
+    // per right-hand side of a solve that starts, written to host memory by the
+    // start's last kernel: the solve's tag, + 1 if it iterates
+    uint32_t* live = nullptr;
+    uint32_t* live_dev = nullptr;  // the same memory, as the device sees it
+    uint32_t live_tag = 0;         // of the last solve (even)
 
     // Jacobian accumulators
     double* acc1 = nullptr;        // [N]
@@ -338,6 +343,18 @@ qpat_status exp_params(qpat_ctx* c, double kappa0, double mu0, const double* bet
 qpat_status check_positive(qpat_ctx* c, const double* a, const double* b, int64_t n, bool* ok);
 
 // ---- pcg.hip
+// Whether any right-hand side of a solve that starts iterates, through host
+// memory: no copy and no stream synchronisation, so that a solve can look, for a
+// few microseconds, before it launches what would do nothing.
+struct Live {
+    uint32_t* flags = nullptr;   // (device) null: not asked
+    uint32_t tag = 0;            // differs from solve to solve: an older solve's late store is no answer
+    __device__ __forceinline__ void put(int i, bool active) const {
+        if (flags) __hip_atomic_store(flags + i, tag + (active ? 1u : 0u), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+};
+Live live_begin(qpat_ctx* c);          // for the start's last kernel
+bool any_live(qpat_ctx* c, int n);     // its answer for n right-hand sides
 // Which operator a solve uses.
 enum class Op { K, Prior };
 

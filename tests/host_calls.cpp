@@ -125,6 +125,11 @@ hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) {
+    *d = h;
+    return hipSuccess;
+}
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 const char* hipGetErrorString(hipError_t) { return "error"; }
@@ -176,6 +181,8 @@ qpat_ctx* box(int nx, int ny, int nz, int n_ill) {
     (void)dalloc(c, &c->scal, 1);
     (void)dalloc(c, &c->shared, 1);
     (void)dalloc(c, &c->scal_host, 1);
+    (void)dalloc(c, &c->live, 1);
+    c->live_dev = c->live;
     (void)dalloc(c, &c->ls, 1);
     (void)dalloc(c, &c->ls_host, 1);
     return c;
@@ -400,6 +407,32 @@ int failed_sources_state() {
     }
     return 0;
 }
+
+// A solve whose right-hand sides are all zero, or whose start solves them, launches no iteration; one that the device
+// says nothing about does.
+int idle_solves() {
+    for (const bool idle : {true, false})
+        for (const bool multigrid : {true, false})
+            for (const bool x0 : {false, true})
+                for (const int B : {4, 16}) {
+                    qpat_ctx* c = box(17, 18, 19, B);
+                    c->opts.pcg_precond = multigrid ? 1 : 0;
+                    EXPECT(mg_setup(c, Op::K) == QPAT_OK && mg_ready(c, Op::K) == multigrid);
+                    c->K_sell = true;
+                    g_launched.clear();
+                    g_on_launch = [&](const std::string& name, void**) {
+                        if (idle && (name.find("k_red_true") != std::string::npos ||
+                                     name.find(x0 ? "k_mgp_true_fin" : "k_mgp_init") != std::string::npos))
+                            for (int i = 0; i < B; ++i) c->live[i] = c->live_tag;
+                    };
+                    SolveStats st;
+                    EXPECT((multigrid ? mg_solve(c, Op::K, B, &st, x0) : pcg_solve(c, Op::K, B, &st, x0)) == QPAT_OK);
+                    EXPECT(st.n_solves == B);
+                    EXPECT((launches("k_mgp_scalars") == 0 && launches("k_red_alpha") == 0) == idle);
+                    EXPECT(!(multigrid && B == 16 && !x0) || launches("k_mgp_ring_flush") >= 1);   // x = 0 is written
+                }
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -414,6 +447,7 @@ int main(int argc, char** argv) {
         {"solve_alloc_failures", solve_alloc_failures},
         {"product_alloc_failures", product_alloc_failures},
         {"failed_sources_state", failed_sources_state},
+        {"idle_solves", idle_solves},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();

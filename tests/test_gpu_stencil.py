@@ -480,3 +480,35 @@ def test_sell_products_on_shuffled_meshes(mesh, block, n_ill, precision):
     ctx.vjp(dev(t), jt)
     assert_close(host(js).reshape(n_ill, N), lin.jvp(s), tol, "J s")
     assert_close(host(jt), lin.vjp(t), tol, "J^T t")
+
+
+@pytest.mark.parametrize("n_ill,kw,shuffled", [(16, {}, False), (5, {}, False), (4, {}, False), (16, {"precision": 1}, False),
+                                               (3, {"max_rhs_block": 1}, False), (4, {"pcg_precond": 0, "prior_precond": 0}, False),
+                                               (8, {"pcg_precond": 0, "precision": 1}, False), (6, {}, True),
+                                               (6, {"use_graphs": 0}, True)])
+def test_solves_with_nothing_to_do(n_ill, kw, shuffled):
+    """J 0, J^T 0 and M_delta^{-1} 0 are zero and a start that solves the system comes back bit for bit, in no
+    iterations, on every path of the solves; a product after them is what it was before (bit for bit)."""
+    coords, tets, bfaces, kappa, mu, src = box_problem(17, 15, 9, n_ill, 90 + n_ill)
+    N = coords.shape[0]
+    rng = np.random.default_rng(n_ill)
+    if shuffled:
+        new = rng.permutation(N).astype(np.int32)
+        back = np.argsort(new)
+        coords, kappa, mu, tets, bfaces = coords[back], kappa[back], mu[back], new[tets], new[bfaces]
+    ctx, phi, _ = solve(coords, tets, bfaces, kappa, mu, src, pcg_rtol=1e-12, prior_rtol=1e-9, **kw)
+    zeros = lambda n: torch.zeros(n, dtype=torch.float64, device="cuda")
+    s, before, after = dev(rng.standard_normal(2 * N)), zeros(n_ill * N), zeros(n_ill * N)
+    ctx.jvp(s, before)
+    js, jt, r = (torch.full((n,), 3.0, dtype=torch.float64, device="cuda") for n in (n_ill * N, 2 * N, 2 * N))
+    assert ctx.jvp(zeros(2 * N), js)["iters_max"] == 0 and not js.any()
+    assert ctx.vjp(zeros(n_ill * N), jt)["iters_max"] == 0 and not jt.any()
+    ctx.prior_setup(dev(0.1 * rng.standard_normal(N)), dev(0.1 * rng.standard_normal(N)))
+    assert ctx.prior_solve(zeros(2 * N), r)["iters_max"] == 0 and not r.any()
+    ctx.jvp(s, after)
+    assert torch.equal(before, after)
+    x0, out = dev(phi.reshape(-1)), zeros(n_ill * N)
+    ctx.set_opts(pcg_rtol=1e-11)
+    info = ctx.forward_x0(dev(kappa), dev(mu), x0, out)
+    assert info["iters_max"] == 0 and info["relres_max"] <= 1e-11, info
+    assert torch.equal(out, x0)
