@@ -1203,9 +1203,42 @@ qpat_status make_st(qpat_ctx* c, Op op, const PcgArgs<T>& a, StArgs<T>* out) {
     return QPAT_OK;
 }
 
+// The blocks of a run: no more than the direction + product keeps resident (one
+// more is a second turn of the whole device), split over the systems, a multiple
+// of 8 (XCD mapping), each with the same number of whole passes. A Jacobian pair
+// on 65^3 nodes with 16 right-hand sides in FP32, 7 blocks a CU where 6 are
+// resident -> 6: 55.2 -> 45.2 ms in the lattice's order, 69.8 -> 59.1 renumbered.
+template <typename T, int B, bool DEFL>
+void set_blocks(qpat_ctx* c, PcgArgs<T>& a) {
+    const void* kfn = reinterpret_cast<const void*>(&k_dir_spmv<T, B, DEFL, false>);
+    char key[96];
+    snprintf(key, sizeof key, "ell/%p", kfn);
+    int occ = 0, cus = 256;
+    auto it = c->st_occ.find(key);
+    if (it != c->st_occ.end()) {
+        occ = it->second;
+    } else {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kfn, kThreads, 0) != hipSuccess) occ = 4;
+        c->st_occ[key] = occ;
+    }
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) cus = 256;
+    const int64_t rows_per_pass = kThreads / B;
+    const int64_t want = (a.N + rows_per_pass - 1) / rows_per_pass;
+    const int64_t cap = std::max<int64_t>((int64_t)std::max(occ, 1) * cus / a.nsys, 8);
+    const int64_t passes = (want + cap - 1) / cap;
+    int64_t gs = (want + passes - 1) / passes;
+    gs = ((gs + 7) / 8) * 8;
+    gs = std::min<int64_t>(gs, kMaxBlocks);   // size of the partial-sum buffer
+    int64_t rpb = (a.N + gs - 1) / gs;
+    rpb = (rpb + rows_per_pass - 1) / rows_per_pass * rows_per_pass;
+    a.gs = static_cast<int32_t>(gs);
+    a.rpb = static_cast<int32_t>(rpb);
+}
+
 template <typename T, int B, bool DEFL>
 struct Runner {
     static qpat_status run(qpat_ctx* c, Op op, PcgArgs<T>& a, double rtol, SolveStats* st, bool has_x0) {
+        set_blocks<T, B, DEFL>(c, a);
         const int S = a.nsys * B;
         const dim3 grid(a.gs * a.nsys), blk(kThreads);
         StArgs<T> g{};
@@ -1397,22 +1430,6 @@ PcgArgs<T> make_args(qpat_ctx* c, Op op, int B) {
     a.s = c->sell;
     a.N = c->N;
     a.nsys = op == Op::Prior ? 2 : 1;
-    // about as many blocks as the direction + product keeps resident (more only
-    // lengthen the reductions of their partial sums), split over the systems, a
-    // multiple of 8 (XCD mapping), each with the same number of whole passes
-    const int64_t rows_per_pass = kThreads / B;
-    int64_t want = (c->N + rows_per_pass - 1) / rows_per_pass;
-    int cus = 256;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) cus = 256;
-    const int64_t cap = std::max<int64_t>((std::is_same<T, double>::value ? 5 : 7) * cus / a.nsys, 8);
-    const int64_t passes = (want + cap - 1) / cap;
-    int64_t gs = (want + passes - 1) / passes;
-    gs = ((gs + 7) / 8) * 8;
-    gs = std::min<int64_t>(gs, kMaxBlocks);   // size of the partial-sum buffer
-    int64_t rpb = (c->N + gs - 1) / gs;
-    rpb = (rpb + rows_per_pass - 1) / rows_per_pass * rows_per_pass;
-    a.gs = static_cast<int32_t>(gs);
-    a.rpb = static_cast<int32_t>(rpb);
     const bool is64 = std::is_same<T, double>::value;
     if (op == Op::K) {
         a.vals = is64 ? reinterpret_cast<const T*>(c->K64) : reinterpret_cast<const T*>(c->K32);
