@@ -23,6 +23,7 @@ std::map<const void*, std::string>& kernel_names() {
     return m;
 }
 std::vector<std::string> g_launched;
+dim3 g_grid;                        // of the launch at hand
 std::function<void(const std::string&, void**)> g_on_launch;
 struct Config {
     dim3 grid, block;
@@ -74,8 +75,9 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* l, hipStream_t* s
     *s = g_config.stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, hipStream_t) {
     const std::string& name = kernel_names()[f];
+    g_grid = grid;
     g_launched.push_back(name);
     if (g_on_launch) g_on_launch(name, args);
     return hipSuccess;
@@ -433,6 +435,25 @@ int idle_solves() {
                 }
     return 0;
 }
+
+// The sliced-ELL product runs no more blocks than the device keeps resident (2 on each of 256 units here).
+int resident_blocks() {
+    for (const int precision : {0, 1})
+        for (const int B : {1, 8, 16}) {
+            qpat_ctx* c = box(65, 65, 65, B);
+            c->opts.pcg_precond = c->opts.operator_format = 0;
+            c->opts.precision = precision;
+            c->K_sell = true;
+            unsigned most = 0;
+            g_on_launch = [&](const std::string& name, void**) {
+                if (name.find("k_dir_spmv") != std::string::npos) most = std::max(most, g_grid.x);
+            };
+            SolveStats st;
+            EXPECT(pcg_solve(c, Op::K, B, &st) == QPAT_OK);
+            EXPECT(most > 256 && most <= 512);
+        }
+    return 0;
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -448,6 +469,7 @@ int main(int argc, char** argv) {
         {"product_alloc_failures", product_alloc_failures},
         {"failed_sources_state", failed_sources_state},
         {"idle_solves", idle_solves},
+        {"resident_blocks", resident_blocks},
     };
     for (const auto& k : cases)
         if (argc == 2 && std::string(argv[1]) == k.first) return k.second();

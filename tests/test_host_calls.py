@@ -27,7 +27,7 @@ def program(tmp_path_factory):
 @pytest.mark.parametrize("case", ["guess_sides", "guess_alloc_failures", "voxel_limit_per_call",
                                   "voxel_form_after_format_0", "failed_forward_state", "failed_prior_state",
                                   "hierarchy_alloc_failures", "solve_alloc_failures", "product_alloc_failures",
-                                  "failed_sources_state", "idle_solves"])
+                                  "failed_sources_state", "idle_solves", "resident_blocks"])
 def test_host_call(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
