@@ -653,8 +653,6 @@ __global__ __launch_bounds__(kMgT) void k_mg_diag(LvArgs L, double* __restrict__
     }
 }
 
-__device__ __forceinline__ double pw(int d) { return d == 0 ? 1.0 : 0.5; }
-
 // Prolongation weight of fine node i (coords fx, fy, fz) towards coarse node
 // J0(i) + corner c, J0(i) = (fx/2, fy/2, fz/2), c = cz 4 + cy 2 + cx. W: the
 // operator-dependent weights of the system, corner-major ([8][N]: the loads of
@@ -912,7 +910,6 @@ __global__ __launch_bounds__(kMgT) void k_mg_smooth(SmArgs a, const double* __re
     constexpr int V = Pk<B>::V;
     __shared__ double sm[kSumLds];
     const int v = threadIdx.x % Pk<B>::BV;
-    const int32_t M1 = a.L.m + 1;
     for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
         const double w = a.w[sys * a.nlev + a.lev];
         const double* U = rows_of<KIND>(a.L, sys);
@@ -955,7 +952,6 @@ __global__ __launch_bounds__(kMgT) void k_mg_resid(SmArgs a, const double* __res
     using T = TB<B>;
     constexpr int V = Pk<B>::V;
     const int v = threadIdx.x % Pk<B>::BV;
-    const int32_t M1 = a.L.m + 1;
     for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
         if (!pair_active<B>(a.sc, sys, v)) continue;
         const double* U = rows_of<KIND>(a.L, sys);
@@ -1332,7 +1328,6 @@ __global__ __launch_bounds__(kMgT) void k_mgp_spmv(PcgMg a) {
     constexpr int V = Pk<B>::V;
     __shared__ double sm[kSumLds];
     const int v = threadIdx.x % Pk<B>::BV;
-    const int32_t M1 = a.L.m + 1;
     for (int sys = blockIdx.y; sys < a.nsys; sys += gridDim.y) {
         const double* U = rows_of<KIND>(a.L, sys);
         const int64_t o = sys * a.L.N * B + v * V;

@@ -79,10 +79,6 @@ struct StArgs {
     int32_t tiles_x, tiles_y, zc, items;
 };
 
-__device__ __forceinline__ double ld_acq(const double* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // XCD-aware block -> row-range map: consecutive hardware blocks go to
 // different XCDs, so give each XCD a contiguous band of rows.
 __device__ __forceinline__ void block_rows(int32_t gs, int32_t rpb, int64_t N, int32_t& sys, int64_t& r0,
@@ -1040,9 +1036,11 @@ const void* stencil_kernel() {
 // right-hand sides 2643 -> 2452 us, 25^3 with 8 4036 -> 3961, 29^3 with 8
 // 5873 -> 5900, 33^3 with 8 7843 -> 8654, 65^3 with 16 75 -> 116 ms; with 2
 // 25^3 3385 -> 3496; in FP32 25^3 with 16 5249 -> 5088, 33^3 8926 -> 9659.
-template <typename T>
-inline bool fused_dir(int64_t N, int B) {
-    return B >= 4 && N * B * (int64_t)sizeof(T) <= (int64_t(1) << 20);
+template <int B, bool DEFL>
+constexpr bool kMayFuse = B >= 4 && !DEFL;
+template <typename T, int B, bool DEFL>
+inline bool fused_dir(int64_t N) {
+    return kMayFuse<B, DEFL> && N * B * (int64_t)sizeof(T) <= (int64_t(1) << 20);
 }
 
 // one PCG iteration: direction+SpMV, alpha, update, beta
@@ -1058,9 +1056,10 @@ inline void launch_iteration(const PcgArgs<T>& a, const StArgs<T>& g, dim3 grid,
     else if (g.on)
         hipLaunchKernelGGL((k_dir_stencil<T, B, DEFL, TL::NPF, TL::NU, 0>), grid, dim3(kStThreads), TL::LDS, st, a,
                            g);
-    else if (fused_dir<T>(a.N, B))
-        hipLaunchKernelGGL((k_dir_spmv<T, B, DEFL, true>), grid, blk, 0, st, a);
-    else {
+    else if (fused_dir<T, B, DEFL>(a.N)) {
+        if constexpr (kMayFuse<B, DEFL>)
+            hipLaunchKernelGGL((k_dir_spmv<T, B, DEFL, true>), grid, blk, 0, st, a);
+    } else {
         hipLaunchKernelGGL((k_dir<T, B, DEFL>), grid, blk, 0, st, a);
         hipLaunchKernelGGL((k_dir_spmv<T, B, DEFL, false>), grid, blk, 0, st, a);
     }
