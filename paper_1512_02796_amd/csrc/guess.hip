@@ -9,8 +9,8 @@
 // starts from phi0 stops on the same ||b - K x|| <= rtol ||b|| as a zero start.
 //
 // Convolutions are implicit GEMMs on the 16x16x16 BF16 MFMA over 16 output
-// channels x 16 lattice points; the K dimension is one tap x 16 input channels (or four taps x 4 channels for the 3-channel input
-// layer, padded to 4). Weight gradients are the same product with the voxel
+// channels x 16 lattice points; the K dimension is one tap x 16 input channels
+// (or four taps x 4 channels for the 3-channel input layer, padded to 4). Weight gradients are the same product with the voxel
 // index as the K dimension, split over wavefronts and reduced in fixed order.
 #include <cmath>
 
@@ -310,7 +310,7 @@ __global__ void k_wgrad_reduce(const float* __restrict__ part2, int cin, int cou
     if (co < cout && ci < cin && tap < 27) grad[(co * cin + ci) * 27 + tap] = s;
 }
 
-// BF16 weights for the MFMA B operand, [m][n = output channel][k]:
+// BF16 weights for the MFMA A operand, [m][n = output channel][k]:
 // forward (trans = 0): n = co, k = ci (CIN 16) or k = 4 tl + ci, tap = 4m + tl (CIN 4)
 // backward data (trans = 1): the adjoint convolution, n = ci, k = co, tap mirrored
 __global__ void k_pack(const float* __restrict__ w, int cin, int cout, int nch, int trans, uint16_t* __restrict__ Wp) {
@@ -440,10 +440,14 @@ __global__ void k_zero_f(int n, float* p) {
     if (i < n) p[i] = 0.f;
 }
 
-constexpr int kWgradBlocks = 512;   // two resident blocks a CU
-// the convolutions keep their weights in registers, so a launch is one resident
-// set of 4 blocks a CU (128 registers) that walks the items: inference at 97^3
-// 128 us, against 138 - 151 us with 1536 - 3776 blocks and 135 us with 768
+// One resident set of blocks on 256 CUs, for both. A gradient's weight kernels
+// hold 108 accumulators (two blocks a CU); with 256, 512, 768 and 1024 blocks the
+// gradient takes 268, 248, 278, 278 us on 65^3 nodes and 1162, 960, 1039, 997 on
+// 129^3 (a net of 17^3 nodes: 137, 150, 174, 182, its partials' sums being most of it).
+constexpr int kWgradBlocks = 512;
+// The convolutions keep their weights in registers (128: four blocks a CU) and
+// walk the items. Inference with 512, 768, 1024, 1536 and 2048 blocks: 76, 70,
+// 70, 76, 76 us on 65^3 nodes, 318, 270, 268, 277, 270 on 129^3.
 constexpr int kConvBlocks = 1024;
 
 int nch_of(int layer) { return layer == 0 ? 7 : 27; }
@@ -457,8 +461,8 @@ struct GuessNet {
     float* grads = nullptr;
     float* m1 = nullptr;
     float* m2 = nullptr;
-    uint16_t* Wf[kLayers] = {};  // forward B operands
-    uint16_t* Wb[kLayers] = {};  // backward-data B operands
+    uint16_t* Wf[kLayers] = {};  // forward A operands
+    uint16_t* Wb[kLayers] = {};  // backward-data A operands
     // on the padded lattice, zero outside the node lattice
     uint16_t* X0 = nullptr;      // [P][4]
     uint16_t* Y[3] = {};         // hidden activations [P][16]

@@ -847,8 +847,8 @@ static VoxGeo vox_geo(const qpat_ctx* c) {
     return g;
 }
 
-// k_gadj_vox: 8 equal parts of the voxels (one per XCD), B lanes per voxel
-inline dim3 vox_grid(int64_t Nv, int B) {   // k_gadj_vox: a lane for two right-hand sides
+// k_gadj_vox: 8 equal parts of the voxels (one per XCD), a lane for two right-hand sides of a voxel
+inline dim3 vox_grid(int64_t Nv, int B) {
     const int64_t per_xcd = (Nv + 7) / 8, lanes = B >= 2 ? B / 2 : 1;
     return dim3(static_cast<unsigned>(8 * ((per_xcd * lanes + kThreads - 1) / kThreads)));
 }

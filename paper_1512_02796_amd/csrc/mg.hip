@@ -24,7 +24,12 @@
 // b <- b - mean(b), z <- V(r) - mean(V(r)), and the mean of the solution is
 // mean(b)/delta. The stopping rule is the same as Jacobi-PCG's:
 // ||b - A x||_2 <= rtol ||b||_2 on the FP64 residual, confirmed on the true
-// residual at the end. Everything is FP64.
+// residual at the end. The PCG's iterate, residual, product and dot products and
+// the set-up are FP64, and its direction but for mixed precision. The V-cycle
+// keeps parts of its own work in FP32: M_delta's finest vectors, rows and
+// transfer weights, and with 16 right-hand sides on the tiled levels of K the
+// finest residual it restricts, its output z, level 1's vectors and the 27-point
+// rows.
 #include <cmath>
 #include <cstring>
 #include <functional>
@@ -80,8 +85,8 @@ struct TileGeo {
     Rst rst[kMgMaxLevels];
     // the fused prolongation + last sweep (even z-chunks)
     int32_t ps_zc = 0, ps_items = 0, ps_blocks = 0;
-    // the cost model's z-chunk lengths (tiles, prolongation + sweep FP64, FP32) and whether
-    // the ones in use were picked by timing them (autotune)
+    // the cost model's z-chunk lengths (tiles, prolongation + sweep) and whether the ones in
+    // use were picked by timing them (autotune)
     int32_t zc_model = 0, ps_zc_model = 0;
     bool tuned = false;
     // the tiled 27-point kernels of the coarse levels (16 right-hand sides)
