@@ -59,9 +59,10 @@ typedef struct {
                                and the PCG vectors are FP32, with FP64 dot products, FP64
                                true-residual recomputation (reliable updates) and an FP64
                                iterate. In both modes the multigrid V-cycle keeps parts of its
-                               own work in FP32 (the finest residual it restricts and, on the
-                               tiled path, the last sweep's rows and its output z). M_delta
-                               solves and LSQR are FP64 in both modes.                      */
+                               own work in FP32 (K: on the tiled path the finest residual it
+                               restricts, with 16 right-hand sides its output z and its first
+                               coarse level; M_delta: the finest level's vectors and rows).
+                               The PCG of the M_delta solves and LSQR are FP64 in both modes. */
     int32_t max_rhs_block;  /* right-hand sides per block PCG (1, 2, 4, 8 or 16). 1 solves the
                                illuminations one after another ("plain").                    */
     double  pcg_rtol;       /* K solves stop when ||b - K x||_2 <= pcg_rtol ||b||_2 (true
