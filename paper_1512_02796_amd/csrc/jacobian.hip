@@ -877,18 +877,18 @@ static qpat_status rel_maxdiff(qpat_ctx* c, int64_t n, const double* a, const do
 // agree to 1e-12 relative, else the element form stays in use.
 static qpat_status vox_check_rows(qpat_ctx* c) {
     if (c->vox_rows != 0 || c->vox < 0) return QPAT_OK;
-    if (c->opts.operator_format != 1) return QPAT_OK;   // an option, which may change: no verdict
+    if (c->opts.operator_format != 1) return QPAT_OK;   // an option, which may change: left open
     const ScopedArrays scratch(c);
-    const auto verdict = [c](bool same) {   // none where the check fails for want of memory
+    const auto settle = [c](bool same) {   // not reached where the check fails for want of memory
         c->vox_rows = same ? 1 : -1;
         return QPAT_OK;
     };
-    if (!c->lat.on || c->lat.m != 7) return verdict(false);
+    if (!c->lat.on || c->lat.m != 7) return settle(false);
     for (int m = 1; m < 8; ++m)   // upper offset with axis mask m in slot m (the Kuhn pattern's order)
-        if (c->lat.code[13 + (m & 1) + 3 * ((m >> 1) & 1) + 9 * (m >> 2)] != m) return verdict(false);
+        if (c->lat.code[13 + (m & 1) + 3 * ((m >> 1) & 1) + 9 * (m >> 2)] != m) return settle(false);
     const int64_t N = c->N, nx = c->lat.nx, ny = c->lat.ny, nz = c->lat.nz;
     const int64_t Nv = (nx - 1) * (ny - 1) * (nz - 1);
-    if (Nv < 1 || 6 * Nv != c->E) return verdict(false);
+    if (Nv < 1 || 6 * Nv != c->E) return settle(false);
     const VoxGeo vg = vox_geo(c);
     const dim3 blk(kThreads);
     double *uu = nullptr, *ue = nullptr, *uv = nullptr;
@@ -903,7 +903,7 @@ static qpat_status vox_check_rows(qpat_ctx* c) {
     hipLaunchKernelGGL(k_dk_voxel, gv, blk, 0, c->stream, N, c->lat, vg, uu, uv);
     double rel_dk = 0.0;
     QPAT_TRY(rel_maxdiff(c, 8 * N, uv, ue, &rel_dk));
-    return verdict(rel_dk <= 1e-12);
+    return settle(rel_dk <= 1e-12);
 }
 
 // the adjoint kernel's 32-bit byte offsets: phi [N][columns], blocks [N][16], sums
@@ -918,13 +918,13 @@ static qpat_status vox_check(qpat_ctx* c) {
     QPAT_TRY(vox_check_rows(c));
     if (c->vox_rows == 0) return QPAT_OK;
     const ScopedArrays scratch(c);
-    const auto verdict = [c](bool same) {
+    const auto settle = [c](bool same) {
         c->vox = same ? 1 : -1;
         return QPAT_OK;
     };
-    if (c->vox_rows != 1) return verdict(false);
+    if (c->vox_rows != 1) return settle(false);
     const int64_t N = c->N, Nv = c->E / 6;
-    if (!vox_fits(c, 16)) return verdict(false);
+    if (!vox_fits(c, 16)) return settle(false);
     const VoxGeo vg = vox_geo(c);
     const dim3 blk(kThreads);
     constexpr int BC = 16;   // right-hand sides of the check
@@ -949,7 +949,7 @@ static qpat_status vox_check(qpat_ctx* c) {
     double rel1 = 0.0, rel2 = 0.0;
     QPAT_TRY(rel_maxdiff(c, N, a + 2 * N, a, &rel1));
     QPAT_TRY(rel_maxdiff(c, N, a + 3 * N, a + N, &rel2));
-    return verdict(rel1 <= 1e-12 && rel2 <= 1e-12);
+    return settle(rel1 <= 1e-12 && rel2 <= 1e-12);
 }
 
 qpat_status forward_out(qpat_ctx* c, double* phi_out, double* h_out) {

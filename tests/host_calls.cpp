@@ -256,7 +256,7 @@ int voxel_limit_per_call() {
     return 0;
 }
 
-// A product taken while the sliced-ELL form was asked for leaves no verdict on the voxel form behind.
+// A product taken while the sliced-ELL form was asked for leaves the question of the voxel form open.
 int voxel_form_after_format_0() {
     qpat_ctx* c = box(9, 10, 11, 16);
     c->opts.operator_format = 0;
@@ -371,7 +371,7 @@ int solve_alloc_failures() {
     return 0;
 }
 
-// The same for the arrays of the Jacobian's products and the check of the voxel form, which leaves no verdict when it
+// The same for the arrays of the Jacobian's products and the check of the voxel form, which settles nothing when it
 // could not be made and gives back its own arrays.
 int product_alloc_failures() {
     size_t whole = 0;
