@@ -1274,12 +1274,26 @@ struct Runner {
         std::vector<int> stalls(S, 0);
         std::vector<double> rr_prev(S);
         std::vector<int> iters_before(S, 0);
-        // nothing to do: right-hand sides of zero, a start that solves them already
-        // (a chunk of 16 iterations that return at once costs 0.1 ms)
-        const bool idle = !any_live(c, S);
-        if (idle) QPAT_TRY(fetch());
-        // the first chunk goes out without the scalars on the host
-        for (bool first = true; !idle; first = false) {
+        // Replays of captured graphs where allowed (kernel arguments are identical from
+        // one iteration to the next: all state is on the device)
+        auto iterate = [&](int n) -> qpat_status {
+            if (c->opts.use_graphs) {
+                hipGraphExec_t gx = nullptr;
+                QPAT_TRY((chunk_graph<T, B, DEFL>(c, a, g, n, grid, blk, &gx)));
+                QPAT_HIP(c, hipGraphLaunch(gx, sm));
+            } else {
+                for (int it = 0; it < n; ++it) launch_iteration<T, B, DEFL>(a, g, grid, blk, sm, nullptr);
+            }
+            return QPAT_OK;
+        };
+        // The first chunk goes out without the scalars on the host. Only whether any
+        // right-hand side iterates at all is asked, behind its first two iterations (work
+        // for the device while the host waits and launches the rest): zeros, or a start
+        // that solves them, end there (J 0 on 33^3 nodes 107 us, 212 with the whole chunk;
+        // asked before the first iteration 88, but a solve of a 5^3 lattice then waits 22 us).
+        constexpr int kAhead = 2;
+        bool idle = false;
+        for (bool first = true;; first = false) {
             if (!first) {
                 bool any_active = false;
                 for (int i = 0; i < S; ++i) {
@@ -1294,16 +1308,16 @@ struct Runner {
                 c->ev_pool.resize((size_t)5 * chunk);
                 for (size_t e = old; e < c->ev_pool.size(); ++e) QPAT_HIP(c, hipEventCreate(&c->ev_pool[e]));
             }
-            if (!prof && c->opts.use_graphs) {
-                // replay a captured graph of `chunk` iterations (kernel arguments are
-                // identical from one iteration to the next: all state is on the device)
-                hipGraphExec_t gx = nullptr;
-                QPAT_TRY((chunk_graph<T, B, DEFL>(c, a, g, chunk, grid, blk, &gx)));
-                QPAT_HIP(c, hipGraphLaunch(gx, sm));
-            } else {
-                for (int it = 0; it < chunk; ++it)
-                    launch_iteration<T, B, DEFL>(a, g, grid, blk, sm, prof ? &c->ev_pool[5 * it] : nullptr);
+            if (first && !prof) QPAT_TRY(iterate(kAhead));
+            if (first && !any_live(c, S)) {
+                idle = true;
+                QPAT_TRY(fetch());
+                break;
             }
+            if (prof)
+                for (int it = 0; it < chunk; ++it) launch_iteration<T, B, DEFL>(a, g, grid, blk, sm, &c->ev_pool[5 * it]);
+            else
+                QPAT_TRY(iterate(first ? chunk - kAhead : chunk));
             QPAT_HIP(c, hipGetLastError());
             QPAT_TRY(fetch());
             for (int i = 0; first && i < S; ++i) rr_prev[i] = hs[i].rlast2;   // ||r||^2 at the start
