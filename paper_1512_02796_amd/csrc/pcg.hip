@@ -1287,11 +1287,15 @@ struct Runner {
             return QPAT_OK;
         };
         // The first chunk goes out without the scalars on the host. Only whether any
-        // right-hand side iterates at all is asked, behind its first two iterations (work
+        // right-hand side iterates at all is asked, behind some of its iterations (work
         // for the device while the host waits and launches the rest): zeros, or a start
-        // that solves them, end there (J 0 on 33^3 nodes 107 us, 212 with the whole chunk;
-        // asked before the first iteration 88, but a solve of a 5^3 lattice then waits 22 us).
-        constexpr int kAhead = 2;
+        // that solves them, end there. Eight cover both, two leave 10 - 20 us of a solve
+        // uncovered (25^3 shuffled nodes with 8 right-hand sides, a pair without the
+        // question 3880 us, behind eight iterations 3869, two 3909, none 3897; 9^3 with 2
+        // 1255, 1239, 1258, 1290), but idle ones take 1.3 us a launch: a start, which
+        // may well solve the system, is asked about early (converged on 25^3: 351 us
+        // with the whole chunk, 260 behind two).
+        const int ahead = has_x0 ? 2 : 8;
         bool idle = false;
         for (bool first = true;; first = false) {
             if (!first) {
@@ -1308,7 +1312,7 @@ struct Runner {
                 c->ev_pool.resize((size_t)5 * chunk);
                 for (size_t e = old; e < c->ev_pool.size(); ++e) QPAT_HIP(c, hipEventCreate(&c->ev_pool[e]));
             }
-            if (first && !prof) QPAT_TRY(iterate(kAhead));
+            if (first && !prof) QPAT_TRY(iterate(ahead));
             if (first && !any_live(c, S)) {
                 idle = true;
                 QPAT_TRY(fetch());
@@ -1317,7 +1321,7 @@ struct Runner {
             if (prof)
                 for (int it = 0; it < chunk; ++it) launch_iteration<T, B, DEFL>(a, g, grid, blk, sm, &c->ev_pool[5 * it]);
             else
-                QPAT_TRY(iterate(first ? chunk - kAhead : chunk));
+                QPAT_TRY(iterate(first ? chunk - ahead : chunk));
             QPAT_HIP(c, hipGetLastError());
             QPAT_TRY(fetch());
             for (int i = 0; first && i < S; ++i) rr_prev[i] = hs[i].rlast2;   // ||r||^2 at the start
