@@ -25,6 +25,7 @@ qpat_status fail(qpat_ctx* c, qpat_status st, const char* fmt, ...) {
 
 qpat_status hip_check(qpat_ctx* c, hipError_t e, const char* what) {
     if (e == hipSuccess) return QPAT_OK;
+    (void)hipGetLastError();   // reported here: not the next call's
     return fail(c, e == hipErrorOutOfMemory ? QPAT_ERR_OOM : QPAT_ERR_DEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 

@@ -283,6 +283,7 @@ qpat_status dalloc(qpat_ctx* c, T** p, size_t n) {
     void* q = nullptr;
     hipError_t e = hipMalloc(&q, n * sizeof(T) > 0 ? n * sizeof(T) : 16);
     if (e != hipSuccess) {
+        (void)hipGetLastError();   // reported here: not the next call's
         *p = nullptr;
         return fail(c, QPAT_ERR_OOM, "hipMalloc(%zu bytes) failed: %s", n * sizeof(T), hipGetErrorString(e));
     }

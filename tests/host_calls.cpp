@@ -18,6 +18,7 @@ namespace {
 constexpr size_t kHeld = 1 << 16;   // bytes behind every allocation, whatever its size
 int g_fail_at = -1;                 // allocations that still succeed (-1: all)
 bool g_failed = false;              // one did not, since fail_at
+hipError_t g_last = hipSuccess;     // as the runtime keeps it until it is asked for
 std::map<const void*, std::string>& kernel_names() {
     static std::map<const void*, std::string> m;
     return m;
@@ -35,7 +36,7 @@ hipError_t alloc(void** p) {
     if (g_fail_at == 0) {
         *p = nullptr;
         g_failed = true;
-        return hipErrorOutOfMemory;
+        return g_last = hipErrorOutOfMemory;
     }
     if (g_fail_at > 0) --g_fail_at;
     *p = std::calloc(1, kHeld);
@@ -133,7 +134,7 @@ hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned) {
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) { return std::exchange(g_last, hipSuccess); }
 const char* hipGetErrorString(hipError_t) { return "error"; }
 }
 
