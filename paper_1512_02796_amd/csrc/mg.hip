@@ -3697,9 +3697,12 @@ void launch_resid_restrict(const MgState& M, int l, hipStream_t st, const double
 // it and the prolongation recomputes it. Level 0 takes 2 kMgNu - 1 ping-pong
 // sweeps (an odd number), so z ends in level 0's t.
 // first_done: the PCG update already wrote the finest level's first sweep
-// look: asked once the finest level's way down (with two levels, the coarse solve as
-// well) is launched, so that the device has work while the host waits for the
-// answer; false ends the cycle there. Returns whether it was completed.
+// look: asked once the way down and the coarsest solve are launched, so that the
+// device has work while the host waits for the answer and launches the rest (asked
+// behind level 0 alone, a pair on 41 x 34 x 29 nodes with 16 right-hand sides took
+// 2577 - 2585 us against 2567 without the question or with it here; an idle way
+// down costs a zero right-hand side some 15 us); false ends the cycle there.
+// Returns whether it was completed.
 template <int B>
 bool vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev = nullptr, const double* b0 = nullptr,
             bool resid_done = false, bool first_done = false, const std::function<bool()>& look = {}) {
@@ -3714,7 +3717,6 @@ bool vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
     }
     auto sm = [&](int l) { return level_args(M, l); };
     for (int l = 0; l < nl - 1; ++l) {
-        if (l == 1 && look && !look()) return false;
         const MgLevel& L = M.lv[l];
         const MgLevel& C = M.lv[l + 1];
         const SmArgs a = sm(l);
@@ -3761,7 +3763,7 @@ bool vcycle(const MgState& M, hipStream_t st, const TileGeo& tg, hipEvent_t* ev 
     hipLaunchKernelGGL(k_mg_dense<B>,
                        dim3((unsigned)((K.N + kMgT / 64 - 1) / (kMgT / 64)), (unsigned)Pk<B>::BV, (unsigned)M.nsys),
                        dim3(kMgT), K.N * sizeof(TB<B>), st, K.N, M.nsys, M.ainv, K.b, xl[nl - 1], M.sc);
-    if (nl == 2 && look && !look()) return false;
+    if (look && !look()) return false;
     for (int l = nl - 2; l >= 0; --l) {
         const MgLevel& L = M.lv[l];
         const MgLevel& C = M.lv[l + 1];
@@ -4020,10 +4022,10 @@ qpat_status solve_B(qpat_ctx* c, Op op, SolveStats* st, bool has_x0) {
     // lane with nothing to do is inactive on the device already, and what the
     // chunk lengths need of the start (rr0) comes back with the first check. Each
     // such check is a copy, a wait and an idle device while the next chunk is
-    // launched. Only whether any lane iterates at all is asked, behind the first
-    // kernels of the V-cycle: right-hand sides of zero (J 0) or a start that
-    // solves them end there (M_delta^{-1} 0 on 128^3 voxels 98 us, 670 with the
-    // first chunk; on 16^3 70, 200; a pair's two solves are no slower for it).
+    // launched. Only whether any lane iterates at all is asked, behind the
+    // V-cycle's way down: right-hand sides of zero (J 0) or a start that solves
+    // them end there (M_delta^{-1} 0 on 128^3 voxels 115 us, 670 with the first
+    // chunk; on 16^3 82, 200; a pair's two solves are no slower for it).
     for (int restart = 0; restart < 4; ++restart) {
         if (restart > 0) {
             QPAT_TRY(fetch());

@@ -343,7 +343,7 @@ struct Live {
     uint32_t* flags = nullptr;   // (device) null: not asked
     uint32_t tag = 0;            // differs from solve to solve: an older solve's late store is no answer
     __device__ __forceinline__ void put(int i, bool active) const {
-        if (flags) __hip_atomic_store(flags + i, tag + (active ? 1u : 0u), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (flags) __hip_atomic_store(flags + i, tag + (active ? 1u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 };
 Live live_begin(qpat_ctx* c);          // for the start's last kernel
